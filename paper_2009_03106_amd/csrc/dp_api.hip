@@ -89,8 +89,8 @@ size_t sqnorm_ws_bytes(int64_t B, int64_t T, int64_t d_in, int64_t d_out, dp_dty
             const GramColsPlan c = plan_gram_cols((int)B, (int)T, (int)d_in, (int)d_out, (int)dtype);
             if (c.use) return c.ws_floats * sizeof(float);
         }
-        GramPlan g = (is16(dtype) || is8(dtype)) ? plan_gram_bf16((int)T, (int)d_in, (int)d_out) : plan_gram_f32((int)T);
-        return (size_t)B * g.npairs * sizeof(float);
+        const int sums = (is16(dtype) || is8(dtype)) ? plan_gram_bf16((int)T, (int)d_in, (int)d_out).npairs : gram_f32_sums((int)T);
+        return (size_t)B * sums * sizeof(float);
     }
     TnPlan p = is8(dtype)  ? plan_direct_f8_dma((int)B, (int)T, (int)d_in, (int)d_out)
              : is16(dtype) ? plan_direct_bf16((int)B, (int)T, (int)d_in, (int)d_out)
@@ -131,28 +131,42 @@ size_t round16(size_t n) { return (n + 15) & ~size_t(15); }
 // a layer whose direct norm the shared copy-pipeline launch of dp_layers_sqnorm can take (16-bit, direct path, T >= 64,
 // aligned widths), and the scratch such a layer needs in the several-layers call: the larger of its own call's and
 // the shared launch's (one sum per example and 128 x 128 tile)
+// sums per example of a layer's direct norm in a shared launch
+int direct_sums(int64_t B, int64_t T, int64_t d_in, int64_t d_out, dp_dtype dtype) {
+    if (is16(dtype)) return direct_joint_tiles((int)d_in, (int)d_out);
+    const TnPlan p = plan_direct_f32((int)B, (int)T, (int)d_in, (int)d_out);
+    return p.tiles_m * p.tiles_n;
+}
 bool direct_joinable(int64_t B, int64_t T, int64_t d_in, int64_t d_out, dp_dtype dtype, dp_path path) {
     if (is8(dtype) || T <= 1 || d_in == 0 || d_out == 0 || B >= (int64_t(1) << 20)) return false;
     if (gram_batchable(T, d_in, d_out, dtype, path) || gram_cols_class(B, T, d_in, d_out, dtype, path) != 0) return false;
     if (resolve_path(path, dtype, T, d_in, d_out) != DP_PATH_DIRECT) return false;
     if (!is16(dtype)) {
-        // float32: the layers whose direct norm runs on the copy-pipeline kernel (128 x 128 tiles as well)
+        // float32: the layers whose direct norm runs on the copy-pipeline kernel as well
         if (B * T >= (int64_t(1) << 31)) return false;
         const TnPlan p = plan_direct_f32((int)B, (int)T, (int)d_in, (int)d_out);
         if (!p.dma) return false;
     } else if (!dma_direct_joint_ok((int)B, (int)T, (int)d_in, (int)d_out)) return false;
-    return B * direct_joint_tiles((int)d_in, (int)d_out) < (int64_t(1) << 24);       // 16 layers' items stay below the launch's 2^28
+    return B * direct_sums(B, T, d_in, d_out, dtype) < (int64_t(1) << 24);       // 16 layers' items stay below the launch's 2^28
+}
+// a float32 layer whose Gram norm can share a launch of the several-layers call: its launch class (0: none)
+int gram_f32_join_class(int64_t B, int64_t T, int64_t d_in, int64_t d_out, dp_dtype dtype, dp_path path) {
+    if (dtype != DP_F32 || T <= 1 || d_in == 0 || d_out == 0 || B >= (int64_t(1) << 20)) return 0;
+    if (resolve_path(path, dtype, T, d_in, d_out) != DP_PATH_GRAM || gram_cols_class(B, T, d_in, d_out, dtype, path) != 0) return 0;
+    if (B * gram_f32_sums((int)T) >= (int64_t(1) << 24)) return 0;              // 16 layers' items stay below 2^31
+    return gram_f32_class((int)B, (int)T, (int)d_in, (int)d_out);
 }
 size_t single_layer_need(int64_t B, const dp_layer_desc& y, dp_dtype dtype, dp_path path) {
     size_t n = dp_workspace_bytes(DP_OP_SQNORM, B, y.T, y.d_in, y.d_out, dtype, path);
     if (direct_joinable(B, y.T, y.d_in, y.d_out, dtype, path))
-        n = std::max(n, (size_t)B * (size_t)direct_joint_tiles((int)y.d_in, (int)y.d_out) * sizeof(float));
+        n = std::max(n, (size_t)B * (size_t)direct_sums(B, y.T, y.d_in, y.d_out, dtype) * sizeof(float));
     return round16(n);
 }
 
 // Which joint clipped-sum launch of dp_layers_clipped_grad(_noise) can take a layer (by shape and type): 0 none,
 // 1 the 256 x 256-tile launch, 3 the 128 x 128-tile launch for aligned 16-bit layers of a few hundred columns, 4 the
-// same for such layers whose T is not a multiple of the 32-row stage, 5 the float32 launch
+// same for such layers whose T is not a multiple of the 32-row stage, 5 and 6 the float32 launches (tiles up to
+// 128 x 128, and 256 x 256)
 int clipped_join_class(int64_t B, int64_t T, int64_t d_in, int64_t d_out, dp_dtype dtype) {
     if (B == 0 || T == 0 || d_in == 0 || d_out == 0) return 0;
     if (is8(dtype)) return (dma8_clipped_ok((int)T, (int)d_in, (int)d_out) && dma8_joint_ok((int)T, (int)d_in, (int)d_out)) ? 1 : 0;
@@ -160,7 +174,8 @@ int clipped_join_class(int64_t B, int64_t T, int64_t d_in, int64_t d_out, dp_dty
         // float32: the layers of the copy-pipeline kernel (long contractions, widths multiples of 4) share launches too
         if (B * T >= (int64_t(1) << 31)) return 0;
         const TnPlan p = plan_clipped_f32((int)B, (int)T, (int)d_in, (int)d_out);
-        return (p.dma && !clipped_f32_is_short(p)) ? 5 : 0;
+        if (!p.dma || ((d_in * d_out) & 3) != 0) return 0;              // the shared fold takes four entries at a time
+        return p.tile_m == f32_split_tile_m(F32_BIG) ? 6 : 5;
     }
     if (plan_clipped_bf16((int)B, (int)T, (int)d_in, (int)d_out).dma && dma_joint_ok((int)T, (int)d_in, (int)d_out)) return 1;
     if (B * T < (int64_t(1) << 31) && dma_joint_mid_ok((int)T, (int)d_in, (int)d_out)) return 3;
@@ -168,7 +183,7 @@ int clipped_join_class(int64_t B, int64_t T, int64_t d_in, int64_t d_out, dp_dty
     return 0;
 }
 size_t joint_ws_bytes(const JointShape* sh, int n, int64_t B, dp_dtype dtype, int geo) {
-    if (geo == 5) return joint_f32_workspace_floats(sh, n, (int)B) * sizeof(float);
+    if (geo >= 5) return joint_f32_workspace_floats(sh, n, (int)B, geo == 6) * sizeof(float);
     return (is8(dtype) ? joint8_workspace_floats(sh, n, (int)B) : joint_workspace_floats(sh, n, (int)B, geo)) * sizeof(float);
 }
 
@@ -317,7 +332,7 @@ dp_status layer_sqnorm_clip(const void* A, const void* G, int64_t B, int64_t T, 
         e = launch_gram_cols(plan_gram_cols((int)B, (int)T, (int)d_in, (int)d_out, (int)dtype), A, G, (int)B, (int)T, (int)d_in,
                              (int)d_out, accumulate != 0, sqnorm, partial, stream, (int)dtype, co);
     } else if (p == DP_PATH_GRAM && !is16(dtype)) {
-        e = launch_gram_f32(plan_gram_f32((int)T), static_cast<const float*>(A), static_cast<const float*>(G), (int)B, (int)T,
+        e = launch_gram_f32(plan_gram_f32((int)B, (int)T), static_cast<const float*>(A), static_cast<const float*>(G), (int)B, (int)T,
                             (int)d_in, (int)d_out, accumulate != 0, sqnorm, partial, stream, co);
     } else if (p == DP_PATH_GRAM) {
         GramPlan g = plan_gram_bf16((int)T, (int)d_in, (int)d_out);
@@ -833,11 +848,13 @@ dp_status dp_layers_sqnorm_clip(const dp_layer_desc* layers, int64_t n_layers, i
     for (int64_t l = 0; l < n_layers; ++l)
         if (direct_joinable(B, layers[l].T, layers[l].d_in, layers[l].d_out, dtype, path)) ++n_dj;
     const bool join_direct = defer_on && n_dj >= 2;
-    if (join_direct) {
+    // (the float32 Gram norms do the same, a class of layers after the other; heaviest first inside a launch)
+    std::vector<char> joined((size_t)n_layers, 0);
+    auto join = [&](const std::vector<int64_t>& which, auto sums_of, auto launch) -> hipError_t {
         JointShape sh[kJointLayers];
         JointOperands op[kJointLayers];
         float* part[kJointLayers];
-        int tiles[kJointLayers];
+        int sums[kJointLayers];                              // per example
         int ng = 0;
         size_t group_bytes = 0;
         auto flush_group = [&]() -> hipError_t {
@@ -848,35 +865,61 @@ dp_status dp_layers_sqnorm_clip(const dp_layer_desc* layers, int64_t n_layers, i
             }
             for (int k = 0; k < ng; ++k) {
                 part[k] = reinterpret_cast<float*>(static_cast<char*>(workspace) + ws_off);
-                ws_off += round16((size_t)B * tiles[k] * sizeof(float));
+                ws_off += round16((size_t)B * sums[k] * sizeof(float));
             }
-            const hipError_t e = is16(dtype) ? launch_direct_bf16_dma_joint(sh, op, part, ng, (int)B, stream, dtype == DP_F16)
-                                             : launch_direct_f32_dma_joint(sh, op, part, ng, (int)B, stream);
-            for (int k = 0; k < ng; ++k) { queue.partial[queue.count] = part[k]; queue.n[queue.count] = tiles[k]; ++queue.count; }
+            const hipError_t e = launch(sh, op, part, ng);
+            for (int k = 0; k < ng; ++k) { queue.partial[queue.count] = part[k]; queue.n[queue.count] = sums[k]; ++queue.count; }
             ng = 0; group_bytes = 0;
             return e;
         };
-        for (int64_t l = 0; l < n_layers; ++l) {
+        for (int64_t l : which) {
             const dp_layer_desc& y = layers[l];
-            if (!direct_joinable(B, y.T, y.d_in, y.d_out, dtype, path)) continue;
-            const int t = direct_joint_tiles((int)y.d_in, (int)y.d_out);
+            const int t = sums_of(y);
             // (a layer's sums alone always fit: the scratch is at least the largest single layer's need)
-            if (ng > 0 && group_bytes + round16((size_t)B * t * sizeof(float)) > workspace_bytes && flush_group() != hipSuccess) return DP_ERR_HIP;
+            if (ng > 0 && group_bytes + round16((size_t)B * t * sizeof(float)) > workspace_bytes) {
+                const hipError_t e = flush_group();
+                if (e != hipSuccess) return e;
+            }
             sh[ng] = JointShape{(int)y.T, (int)y.d_in, (int)y.d_out};
             op[ng] = JointOperands{static_cast<const uint16_t*>(y.A), static_cast<const uint16_t*>(y.G), nullptr, nullptr, 0};
-            tiles[ng] = t;
-            group_bytes += round16((size_t)B * tiles[ng] * sizeof(float));
+            sums[ng] = t;
+            group_bytes += round16((size_t)B * sums[ng] * sizeof(float));
             ++ng;
-            if (ng == kJointLayers && flush_group() != hipSuccess) return DP_ERR_HIP;
+            joined[(size_t)l] = 1;
+            if (ng == kJointLayers) {
+                const hipError_t e = flush_group();
+                if (e != hipSuccess) return e;
+            }
         }
-        if (flush_group() != hipSuccess) return DP_ERR_HIP;
+        return flush_group();
+    };
+    if (join_direct) {
+        std::vector<int64_t> which;
+        for (int64_t l = 0; l < n_layers; ++l)
+            if (direct_joinable(B, layers[l].T, layers[l].d_in, layers[l].d_out, dtype, path)) which.push_back(l);
+        const hipError_t e = join(which, [&](const dp_layer_desc& y) { return direct_sums(B, y.T, y.d_in, y.d_out, dtype); },
+            [&](const JointShape* sh, const JointOperands* op, float* const* part, int n) {
+                return is16(dtype) ? launch_direct_bf16_dma_joint(sh, op, part, n, (int)B, stream, dtype == DP_F16)
+                                   : launch_direct_f32_split_joint(sh, op, part, n, (int)B, stream); });
+        if (e != hipSuccess) return DP_ERR_HIP;
+    }
+    for (int cls = 1; defer_on && dtype == DP_F32 && cls <= 4; ++cls) {
+        std::vector<int64_t> which;
+        for (int64_t l = 0; l < n_layers; ++l)
+            if (gram_f32_join_class(B, layers[l].T, layers[l].d_in, layers[l].d_out, dtype, path) == cls) which.push_back(l);
+        if (which.size() < 2) continue;
+        std::stable_sort(which.begin(), which.end(), [&](int64_t p, int64_t q) { return layers[p].d_in + layers[p].d_out > layers[q].d_in + layers[q].d_out; });
+        const hipError_t e = join(which, [&](const dp_layer_desc& y) { return plan_gram_f32((int)B, (int)y.T).npairs; },
+            [&](const JointShape* sh, const JointOperands* op, float* const* part, int n) {
+                return launch_gram_f32_layers(sh, op, part, n, (int)B, stream); });
+        if (e != hipSuccess) return DP_ERR_HIP;
     }
     for (int64_t l = 0; l < n_layers; ++l) {
         const dp_layer_desc& y = layers[l];
         if (y.T == 0 || (y.T == 1 && !is8(dtype)) || y.d_in == 0 || y.d_out == 0) continue;     // empty layers add nothing
         if (gram_batchable(y.T, y.d_in, y.d_out, dtype, path)) continue;
         if (gram_cols_class(B, y.T, y.d_in, y.d_out, dtype, path) != 0) continue;
-        if (join_direct && direct_joinable(B, y.T, y.d_in, y.d_out, dtype, path)) continue;
+        if (joined[(size_t)l]) continue;
         if (!defer_on) {
             const dp_status s1 = layer_sqnorm_clip(y.A, y.G, B, y.T, y.d_in, y.d_out, dtype, path, acc, sqnorm, workspace, workspace_bytes,
                                                    hip_stream, (clip_with_single && l == last_single) ? &clip_out : nullptr);
@@ -1074,7 +1117,7 @@ size_t dp_layers_clipped_workspace_bytes(const dp_layer_desc* layers, int64_t n_
         const size_t n = dp_workspace_bytes(DP_OP_CLIPPED_GRAD, B, y.T, y.d_in, y.d_out, dtype, DP_PATH_AUTO);
         if (n > need) need = n;
     }
-    for (int geo : {1, 3, 4, 5}) {                              // the two classes of joint launches, each in groups of its own
+    for (int geo : {1, 3, 4, 5, 6}) {                              // the two classes of joint launches, each in groups of its own
         JointShape sh[kJointLayers];
         int nj = 0;
         auto joint_need = [&]() {
@@ -1133,7 +1176,7 @@ dp_status dp_layers_clipped_grad_noise(const dp_layer_desc* layers, int64_t n_la
     // A second class of joint launches (128 x 128 tiles) takes the aligned 16-bit layers of a few hundred columns.
     std::vector<std::vector<int64_t>> joint_groups;
     std::vector<int> joint_geo;
-    for (int geo : {1, 3, 4, 5}) {
+    for (int geo : {1, 3, 4, 5, 6}) {
         std::vector<int64_t> cur;
         const size_t first_group = joint_groups.size();
         for (int64_t l = 0; l < n_layers; ++l) {
@@ -1171,9 +1214,9 @@ dp_status dp_layers_clipped_grad_noise(const dp_layer_desc* layers, int64_t n_la
                                   y.noise_offset};
             done[(size_t)g[k]] = 1;
         }
-        const hipError_t ej = joint_geo[gi] == 5
-            ? launch_clipped_f32_dma_joint(sh, op, (int)g.size(), (int)B, accumulate != 0, stddev, seed, static_cast<float*>(workspace),
-                                           static_cast<hipStream_t>(hip_stream))
+        const hipError_t ej = joint_geo[gi] >= 5
+            ? launch_clipped_f32_split_joint(sh, op, (int)g.size(), (int)B, accumulate != 0, stddev, seed, static_cast<float*>(workspace),
+                                           static_cast<hipStream_t>(hip_stream), joint_geo[gi] == 6)
             : is8(dtype)
             ? launch_clipped_f8_dma_joint(sh, op, (int)g.size(), (int)B, accumulate != 0, stddev, seed, static_cast<float*>(workspace),
                                           static_cast<hipStream_t>(hip_stream), fmt_of(dtype))

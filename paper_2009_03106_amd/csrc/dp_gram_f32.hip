@@ -1,133 +1,241 @@
 // Gram path of the per-example squared norm for float32 inputs:
 //     ||A_i^T G_i||_F^2 = sum_{t,s} (A_i A_i^T)_{ts} (G_i G_i^T)_{ts}.
-// Same decomposition as the 16-bit Gram kernels: one workgroup per example and
-// pair of row tiles (t-tile <= s-tile, 64 rows each), the tile of A_i A_i^T
-// (contraction over d_in) and then the tile of G_i G_i^T (contraction over
-// d_out) kept in MFMA accumulators of identical layout, multiplied lane by lane
-// and reduced; off-diagonal pairs count twice.  The matrix instruction is the
-// fp32 one (v_mfma_f32_32x32x2_f32: one k per lane and instruction, lanes 0-31
-// take k, lanes 32-63 take k + 1), so a lane reads its operands straight from the
-// row-major LDS tiles; the rows are padded to 33 floats, which puts the 32 rows
-// that one read touches into 32 different banks.
+// Same decomposition as the 16-bit Gram kernels: one workgroup per example and pair of row tiles (t-tile <= s-tile),
+// the tile of A_i A_i^T (contraction over d_in) and then the tile of G_i G_i^T (contraction over d_out) kept in MFMA
+// accumulators of identical layout, multiplied lane by lane and reduced; off-diagonal pairs count twice, and so does the
+// upper right quarter of a diagonal tile, whose mirror image is not computed.
+// The products run on the bf16 MFMA with every operand split into three bf16 numbers (dp_split.h): the rate of the fp32
+// MFMA (157 TFLOP/s nominal) bounded them, six bf16 products have 2.7 times that.  Each element is split once, on its
+// way into LDS: stages of 16 columns, two in LDS, the loads of two stages at a time (whole 128-byte lines of the rows)
+// wait in registers; a thread's four columns are half an MFMA operand of 8, 8 bytes per part.
+#include <algorithm>
 #include "dp_common.h"
 #include "dp_internal.h"
+#include "dp_split.h"
 
 namespace dpk {
 
 namespace {
 
-constexpr int FT = 64;        // rows of T per tile
-constexpr int FK = 32;        // contraction elements per LDS stage
-constexpr int FP = FK + 1;    // padded row length in LDS
+struct GramF32Layer {
+    const float* A;
+    const float* G;
+    float* partial;      // [B][npairs]
+    int T, d_in, d_out, npairs, n_items;
+    int first_item;      // among the items of one XCD
+};
+struct GramF32Args {
+    GramF32Layer layer[kJointLayers];
+    int n_layers;
+};
+
+constexpr int GK = 16;        // contraction elements per stage: one MFMA deep
+
+// MI: 32-row blocks per wave and side; the tile has 64 MI rows
+template <int MI> struct GramTile {
+    static constexpr int R = 64 * MI;
+    static constexpr int PLANE = R * 16 + 64;              // bytes of [8 columns of a part][row]; the 64 bytes keep the two halves of a write in different banks
+    static constexpr int SIDE = 6 * PLANE;                 // [part][k / 8]
+    static constexpr int STAGE = 2 * SIDE;                 // rows of the t-tile, rows of the s-tile
+};
+
+// The wave's tile of X_t X_s^T once more with the float32 instruction, in the order of k, straight from memory: for
+// sums that the three bf16 parts cannot carry (see dp_split.h); ordinary data never come here.
+template <int MI>
+__device__ __forceinline__ void gram_f32_exact(const float* Xi, int T, int D, int t0, int s0, f32x16 (&acc)[MI][MI]) {
+    const int lrow = threadIdx.x & 31, lhalf = (threadIdx.x & 63) >> 5;
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < MI; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+    for (int k = 0; k < D; k += 2) {
+        const bool in = k + lhalf < D;
+        const int c = in ? k + lhalf : 0;
+        float ft[MI], fs[MI];
+#pragma unroll
+        for (int i = 0; i < MI; ++i) {
+            const int rt = t0 + 32 * i + lrow, rs = s0 + 32 * i + lrow;
+            const float xt = Xi[(size_t)min(rt, T - 1) * D + c], xs = Xi[(size_t)min(rs, T - 1) * D + c];
+            ft[i] = in && rt < T ? xt : 0.f;
+            fs[i] = in && rs < T ? xs : 0.f;
+        }
+#pragma unroll
+        for (int i = 0; i < MI; ++i)
+#pragma unroll
+            for (int j = 0; j < MI; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(ft[i], fs[j], acc[i][j], 0, 0, 0);
+    }
+}
+
+// One Gram product tile: acc = X[t-tile rows] . X[s-tile rows]^T over the D columns of X_i[T, D].
+// VEC: D % 4 == 0 (every 16-byte piece lies inside a row or outside it) and D < 2^22 (a tile's rows lie within 2^31 bytes).
+// Every wave leaves with its LDS reads done.
+template <int MI, bool VEC, bool DIAG>
+__device__ __forceinline__ void gram_f32_product(const float* __restrict__ Xi, int T, int D, int t0, int s0,
+                                                 unsigned char* lds, f32x16 (&acc)[MI][MI]) {
+    using GT = GramTile<MI>;
+    constexpr int SIDES = DIAG ? 1 : 2;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave >> 1, wn = wave & 1;
+    const int lrow = lane & 31, lhalf = lane >> 5;
+    // global -> LDS: four threads per row, MI rows of either side and two stages (a 128-byte line of the row) at a time
+    const int lr = tid >> 2, lc = (tid & 3) * 4;
+    const int t_rows = min(T - t0, GT::R), s_rows = min(T - s0, GT::R);
+    // VEC: buffer loads, a row past T or a column past D lies outside the buffer and comes back as zero
+    const auto buf_t = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(Xi + (size_t)t0 * D), (short)0, VEC ? t_rows * D * 4 : 0, 0x00020000);
+    const auto buf_s = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(Xi + (size_t)s0 * D), (short)0, VEC ? s_rows * D * 4 : 0, 0x00020000);
+    const uint32_t wr = (uint32_t)((lc >> 3) * GT::PLANE + lr * 16 + (lc & 4) * 2);
+    f32x4 x[2][SIDES][MI];
+    int next_k = lc;
+    auto fetch = [&]() {
+#pragma unroll
+        for (int h = 0; h < SIDES; ++h)
+#pragma unroll
+            for (int v = 0; v < MI; ++v)
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    const int row = lr + 64 * v, k = next_k + u * GK;
+                    if (VEC) {
+                        const uint32_t off = k < D ? (uint32_t)(row * D + k) * 4u : 0x7ffffff0u;
+                        x[u][h][v] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(h == 0 ? buf_t : buf_s, off, 0, 0));
+                    } else {
+                        const bool in = row < (h == 0 ? t_rows : s_rows);
+                        const float* p = Xi + (size_t)((h == 0 ? t0 : s0) + (in ? row : 0)) * D;
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) {
+                            const float q = p[k + j < D ? k + j : 0];
+                            x[u][h][v][j] = in && k + j < D ? q : 0.f;
+                        }
+                    }
+                }
+        next_k += 2 * GK;
+    };
+    // the split of one of the thread's SIDES * MI pieces of stage half u
+    auto split_step = [&](int u, int piece, int buf) {
+        const int h = piece / MI, v = piece % MI;
+        uint32_t part[3][2];
+#pragma unroll
+        for (int q = 0; q < 2; ++q) split2(x[u][h][v][2 * q], x[u][h][v][2 * q + 1], part[0][q], part[1][q], part[2][q]);
+#pragma unroll
+        for (int p = 0; p < 3; ++p)
+            *reinterpret_cast<uint2*>(lds + buf * GT::STAGE + h * GT::SIDE + p * 2 * GT::PLANE + wr + v * 64 * 16) =
+                make_uint2(part[p][0], part[p][1]);
+    };
+    const uint32_t rdT = (uint32_t)(lhalf * GT::PLANE + (wm * MI * 32 + lrow) * 16);
+    const uint32_t rdS = (uint32_t)((DIAG ? 0 : GT::SIDE) + lhalf * GT::PLANE + (wn * MI * 32 + lrow) * 16);
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < MI; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+    constexpr int TILES = MI * MI, PIECES = SIDES * MI, STEPS = (PIECES + TILES - 1) / TILES;
+    fetch();
+#pragma unroll
+    for (int q = 0; q < PIECES; ++q) split_step(0, q, 0);
+    __builtin_amdgcn_s_waitcnt(0xC07F);
+    __builtin_amdgcn_s_barrier();
+    // Past the last column the copies bring zeros: the loop takes two stages a turn and has no branches.  One 32 x 32 tile
+    // of the wave after the other: its six MFMAs, in their shadow a share of the next stage's split and the addition of
+    // the tile before.  The idle wave of a diagonal pair multiplies as well and drops its sums below (a branch around
+    // its MFMAs would end the interleaving for all).
+    f32x16 pend = {};                                      // the sums of the tile before, not yet added
+    for (int k0 = 0; k0 < D; k0 += 2 * GK) {
+#pragma unroll
+        for (int buf = 0; buf < 2; ++buf) {
+            bf16x8 ft[MI][3], fs[MI][3];
+            const unsigned char* sb = lds + buf * GT::STAGE;
+#pragma unroll
+            for (int i = 0; i < MI; ++i)
+#pragma unroll
+                for (int p = 0; p < 3; ++p) {
+                    ft[i][p] = *reinterpret_cast<const bf16x8*>(sb + rdT + p * 2 * GT::PLANE + i * 512);
+                    fs[i][p] = *reinterpret_cast<const bf16x8*>(sb + rdS + p * 2 * GT::PLANE + i * 512);
+                }
+#pragma unroll
+            for (int t = 0; t < TILES; ++t) {
+                const int before = (t + TILES - 1) % TILES;
+                acc[before / MI][before % MI] += pend;
+                pend = split_mfma(ft[t / MI], fs[t % MI]);
+#pragma unroll
+                for (int q = 0; q < STEPS; ++q)
+                    if (t * STEPS + q < PIECES) split_step(buf ^ 1, t * STEPS + q, buf ^ 1);
+                if (t == TILES - 1 && buf == 0) fetch();
+#pragma unroll
+                for (int q = 0; q < 6; ++q) {
+                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x002, 7, 0);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            __builtin_amdgcn_s_waitcnt(0xC07F);            // lgkmcnt(0): this wave's parts of the next stage are in LDS
+            __builtin_amdgcn_s_barrier();
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+    acc[MI - 1][MI - 1] += pend;
+    SplitCheck check;
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < MI; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) check.add(acc[i][j][r]);
+    if (__any(check.suspect())) gram_f32_exact<MI>(Xi, T, D, t0 + wm * MI * 32, s0 + wn * MI * 32, acc);
+}
+
+template <int MI, bool VEC, bool DIAG>
+__device__ __forceinline__ void gram_f32_pair(const GramF32Layer& a, int ex, int tt, int ss, unsigned char* lds, float* out) {
+    constexpr int R = GramTile<MI>::R;
+    f32x16 accP[MI][MI], accQ[MI][MI];
+    gram_f32_product<MI, VEC, DIAG>(a.A + (size_t)ex * a.T * a.d_in, a.T, a.d_in, tt * R, ss * R, lds, accP);
+    gram_f32_product<MI, VEC, DIAG>(a.G + (size_t)ex * a.T * a.d_out, a.T, a.d_out, tt * R, ss * R, lds, accQ);
+    // rows beyond T were stored as zeros, so their entries of both tiles are zero
+    float s = 0.f;
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < MI; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) s += accP[i][j][r] * accQ[i][j][r];
+    if (DIAG && (threadIdx.x >> 6) == 1) s += s;            // wave 2 holds the mirror image of wave 1's quarter
+    if (DIAG && (threadIdx.x >> 6) == 2) s = 0.f;
+    s = block_sum_256(s, reinterpret_cast<float*>(lds));
+    if (threadIdx.x == 0) *out = DIAG ? s : 2.0f * s;
+}
+
+// Items (layer, example, tile pair), the layers in the order given.  Workgroup b runs on XCD b % 8: every XCD takes a
+// contiguous eighth of every layer's items, example by example, so that an example's pairs read its rows through one L2
+// and the XCDs have equal work (an eighth of the whole list gave those with the widest layer 1.25 times the mean: four
+// layers of 768 .. 3072 columns, B = 64, T = 512: 1.71 ms, 1.39 ms so).
+template <int MI, bool VEC>
+__global__ __launch_bounds__(kThreads, MI == 2 ? 2 : 4) void k_gram_f32(GramF32Args g) {
+    __shared__ __attribute__((aligned(1024))) unsigned char lds[2 * GramTile<MI>::STAGE];
+    const int L = blockIdx.x >> 3;
+    int l = 0;
+    while (l + 1 < g.n_layers && L >= g.layer[l + 1].first_item) ++l;
+    const GramF32Layer a = g.layer[l];
+    const int item = (int)(blockIdx.x & 7) * ((a.n_items + 7) >> 3) + L - a.first_item;
+    if (item >= a.n_items) return;
+    const int ex = item / a.npairs, pair0 = item - ex * a.npairs;
+    int pair = pair0;
+    // pair -> (tt, ss), tt <= ss, rows of the upper triangle in order
+    const int nt = (a.T + GramTile<MI>::R - 1) / GramTile<MI>::R;
+    int tt = 0;
+    while (pair >= nt - tt) { pair -= nt - tt; ++tt; }
+    const int ss = tt + pair;
+    float* out = a.partial + (size_t)ex * a.npairs + pair0;
+    if (tt == ss) gram_f32_pair<MI, VEC, true>(a, ex, tt, ss, lds, out);
+    else          gram_f32_pair<MI, VEC, false>(a, ex, tt, ss, lds, out);
+}
 
 struct GramArgsF {
     const float* A;
     const float* G;
     float* partial;      // [B][npairs]
     int T, d_in, d_out;
-    int nt, npairs;
 };
-
-// One Gram product tile: acc += X[t-tile rows] . X[s-tile rows]^T over the D columns of X_i[T, D].
-// VEC: D % 4 == 0 (every 16-byte piece lies inside a row or outside it).
-template <bool VEC>
-__device__ __forceinline__ void gram_product_f32(const float* __restrict__ Xi, int T, int D, int t0, int s0, bool diag,
-                                                 float (*sT)[FP], float (*sS)[FP], f32x16& acc) {
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = wave >> 1, wn = wave & 1;
-    const int lrow = lane & 31, lhalf = lane >> 5;
-    // global -> LDS: a thread moves two 4-column pieces of either tile per stage (rows lr and lr + 32)
-    const int lr = tid >> 3, lc = (tid & 7) * 4;
-    float xt[2][4], xs[2][4];
-    bool in_t[2], in_s[2];
-    // loads are issued from clamped (valid) addresses and zeroed when they are committed, one stage of MFMAs
-    // later, so that nothing waits for them in between
-    auto fetch = [&](int k0) {
-#pragma unroll
-        for (int v = 0; v < 2; ++v) {
-            const int rt = t0 + lr + 32 * v, rs = s0 + lr + 32 * v;
-            in_t[v] = rt < T; in_s[v] = rs < T;
-            const float* pt = Xi + (size_t)(in_t[v] ? rt : T - 1) * D;
-            const float* ps = Xi + (size_t)(in_s[v] ? rs : T - 1) * D;
-            if (VEC) {
-                const int c = (k0 + lc < D) ? k0 + lc : 0;
-                const float4 q = *reinterpret_cast<const float4*>(pt + c);
-                xt[v][0] = q.x; xt[v][1] = q.y; xt[v][2] = q.z; xt[v][3] = q.w;
-                if (!diag) {
-                    const float4 r = *reinterpret_cast<const float4*>(ps + c);
-                    xs[v][0] = r.x; xs[v][1] = r.y; xs[v][2] = r.z; xs[v][3] = r.w;
-                }
-            } else {
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int c = (k0 + lc + j < D) ? k0 + lc + j : 0;
-                    xt[v][j] = pt[c];
-                    if (!diag) xs[v][j] = ps[c];
-                }
-            }
-        }
-    };
-    auto commit = [&](int k0) {
-#pragma unroll
-        for (int v = 0; v < 2; ++v)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const bool col_ok = k0 + lc + j < D;
-                sT[lr + 32 * v][lc + j] = (in_t[v] && col_ok) ? xt[v][j] : 0.f;
-                if (!diag) sS[lr + 32 * v][lc + j] = (in_s[v] && col_ok) ? xs[v][j] : 0.f;
-            }
-    };
-    float (*sB)[FP] = diag ? sT : sS;
-    if (D > 0) fetch(0);
-    for (int k0 = 0; k0 < D; k0 += FK) {
-        commit(k0);
-        __syncthreads();
-        if (k0 + FK < D) fetch(k0 + FK);
-        // the operands of 8 MFMAs are read together, so that their LDS latency is paid once per group
-#pragma unroll
-        for (int k8 = 0; k8 < FK / 2; k8 += 8) {
-            float fa[8], fb[8];
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                fa[j] = sT[wm * 32 + lrow][(k8 + j) * 2 + lhalf];
-                fb[j] = sB[wn * 32 + lrow][(k8 + j) * 2 + lhalf];
-            }
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int j = 0; j < 8; ++j) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[j], fb[j], acc, 0, 0, 0);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        __syncthreads();
-    }
-}
-
-template <bool VEC>
-__global__ __launch_bounds__(kThreads) void k_gram_f32(GramArgsF a) {
-    __shared__ float sT[FT][FP];
-    __shared__ float sS[FT][FP];
-    __shared__ float red[4];
-
-    const int ex = blockIdx.x / a.npairs;
-    int pair = blockIdx.x - ex * a.npairs;
-    // pair -> (tt, ss), tt <= ss, rows of the upper triangle in order
-    int tt = 0;
-    while (pair >= a.nt - tt) { pair -= a.nt - tt; ++tt; }
-    const int ss = tt + pair;
-    const bool diag = (tt == ss);
-
-    f32x16 accP, accQ;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) { accP[r] = 0.f; accQ[r] = 0.f; }
-    gram_product_f32<VEC>(a.A + (size_t)ex * a.T * a.d_in, a.T, a.d_in, tt * FT, ss * FT, diag, sT, sS, accP);
-    gram_product_f32<VEC>(a.G + (size_t)ex * a.T * a.d_out, a.T, a.d_out, tt * FT, ss * FT, diag, sT, sS, accQ);
-
-    // rows beyond T were stored as zeros, so their entries of both tiles are zero
-    float s = 0.f;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) s += accP[r] * accQ[r];
-    s = block_sum_256(s, red);
-    if (threadIdx.x == 0) a.partial[blockIdx.x] = diag ? s : 2.0f * s;
-}
 
 // Short sequences (T <= 32: the late convolutions of an image model, 16 positions of 2304 to 4608 inputs): the kernel
 // above would give the one useful 32 x 32 tile to one wave, a chain of d / 2 dependent 64-cycle MFMAs (75 to 135 us
@@ -224,28 +332,72 @@ __global__ __launch_bounds__(kThreads) void k_gram_f32_small(GramArgsF a) {
 
 }  // namespace
 
-GramPlan plan_gram_f32(int T) {
+// Tiles of 64 or 128 rows.  In workgroups' time of the 128-row tile (two fit a compute unit, four of the 64-row one), an item
+// of 64-row tiles takes 0.425 of it where the chip is full and 0.6 where it is not; 64-row tiles waste less of a sequence
+// that is no multiple of 128 (B = 9, T = 192, 844 x 1664: 0.14 ms on them, 0.18 ms on 128-row tiles), 128-row tiles read
+// their fragments half as often (B = 64, T = 512).  At most the pairs of 64-row tiles: gram_f32_sums.
+GramPlan plan_gram_f32(int B, int T) {
+    const auto pairs = [&](int tile) { const int64_t nt = (T + tile - 1) / tile; return nt * (nt + 1) / 2; };
+    const double cost128 = std::max(0.5, (double)B * pairs(128) / 256), cost64 = std::max(0.3, 0.425 * B * pairs(64) / 256);
     GramPlan p;
-    p.tile = FT;
-    p.nt = (T + FT - 1) / FT;
-    p.npairs = p.nt * (p.nt + 1) / 2;
+    p.tile = T > 64 && cost128 <= cost64 ? 128 : 64;
+    p.nt = (T + p.tile - 1) / p.tile;
+    p.npairs = (int)pairs(p.tile);
     return p;
+}
+
+int gram_f32_sums(int T) { const int nt = (T + 63) / 64; return nt * (nt + 1) / 2; }
+
+int gram_f32_class(int B, int T, int d_in, int d_out) {
+    if (T <= 32) return 0;
+    return (plan_gram_f32(B, T).tile == 128 ? 2 : 1) + (((d_in | d_out) & 3) == 0 && (d_in | d_out) < (1 << 22) ? 2 : 0);
+}
+
+hipError_t launch_gram_f32_layers(const JointShape* sh, const JointOperands* op, float* const* partial, int n_layers, int B,
+                                  hipStream_t st) {
+    if (n_layers < 1 || n_layers > kJointLayers) return hipErrorInvalidValue;
+    const int cls = gram_f32_class(B, sh[0].T, sh[0].M, sh[0].N);
+    if (cls == 0) return hipErrorInvalidValue;
+    GramF32Args g;
+    int64_t first = 0;
+    for (int l = 0; l < n_layers; ++l) {
+        if (gram_f32_class(B, sh[l].T, sh[l].M, sh[l].N) != cls) return hipErrorInvalidValue;
+        GramF32Layer& y = g.layer[l];
+        y.A = reinterpret_cast<const float*>(op[l].A); y.G = reinterpret_cast<const float*>(op[l].G); y.partial = partial[l];
+        y.T = sh[l].T; y.d_in = sh[l].M; y.d_out = sh[l].N;
+        y.npairs = plan_gram_f32(B, sh[l].T).npairs;
+        y.first_item = (int)first;
+        const int64_t n = (int64_t)y.npairs * B;
+        if (n >= (int64_t(1) << 31) - 8) return hipErrorInvalidValue;
+        y.n_items = (int)n;
+        first += (n + 7) / 8;
+        if (first >= (int64_t(1) << 28)) return hipErrorInvalidValue;
+    }
+    for (int l = n_layers; l < kJointLayers; ++l) g.layer[l] = g.layer[0];
+    g.n_layers = n_layers;
+    const unsigned grid = 8u * (unsigned)first;
+    if      (cls == 1) k_gram_f32<1, false><<<grid, kThreads, 0, st>>>(g);
+    else if (cls == 2) k_gram_f32<2, false><<<grid, kThreads, 0, st>>>(g);
+    else if (cls == 3) k_gram_f32<1, true><<<grid, kThreads, 0, st>>>(g);
+    else               k_gram_f32<2, true><<<grid, kThreads, 0, st>>>(g);
+    return hipGetLastError();
 }
 
 hipError_t launch_gram_f32(const GramPlan& p, const float* A, const float* G, int B, int T, int d_in, int d_out,
                            bool accumulate, float* sqnorm, float* partial, hipStream_t st, const ClipOut* co) {
-    GramArgsF a;
-    a.A = A; a.G = G; a.partial = partial;
-    a.T = T; a.d_in = d_in; a.d_out = d_out;
-    a.nt = p.nt; a.npairs = p.npairs;
-    const int64_t grid = (int64_t)B * p.npairs;
-    if (grid >= (int64_t(1) << 31)) return hipErrorInvalidValue;
+    hipError_t e;
     if (T <= 32) {              // one tile pair per example (p.npairs == 1): the four waves split the contraction
+        GramArgsF a;
+        a.A = A; a.G = G; a.partial = partial;
+        a.T = T; a.d_in = d_in; a.d_out = d_out;
         if (((d_in | d_out) & 3) == 0) k_gram_f32_small<true><<<(unsigned)B, kThreads, 0, st>>>(a);
         else                           k_gram_f32_small<false><<<(unsigned)B, kThreads, 0, st>>>(a);
-    } else if (((d_in | d_out) & 3) == 0) k_gram_f32<true><<<(unsigned)grid, kThreads, 0, st>>>(a);
-    else                                  k_gram_f32<false><<<(unsigned)grid, kThreads, 0, st>>>(a);
-    const hipError_t e = hipGetLastError();
+        e = hipGetLastError();
+    } else {
+        const JointShape sh{T, d_in, d_out};
+        const JointOperands op{reinterpret_cast<const uint16_t*>(A), reinterpret_cast<const uint16_t*>(G), nullptr, nullptr, 0};
+        e = launch_gram_f32_layers(&sh, &op, &partial, 1, B, st);
+    }
     if (e != hipSuccess) return e;
     return launch_finalize_partials(partial, B, p.npairs, accumulate, sqnorm, st, co);
 }

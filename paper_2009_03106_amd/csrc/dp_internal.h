@@ -87,7 +87,7 @@ struct TnPlan {
     int epu;                // segmented: examples per K slice
     bool big;               // 16-bit clipped sum only: 256 x 256 tiles, one workgroup per compute unit
     bool zero_head = false; // the kernel needs a line of zeros: the first kZeroHeadFloats floats of the workspace are set aside for it
-    bool dma;               // copy-pipeline kernel (direct-to-LDS copies); tile_m x tile_n names its geometry (16-bit inputs) or is 128 x 128 (float32)
+    bool dma;               // copy-pipeline kernel (direct-to-LDS copies; float32: the split kernel); tile_m x tile_n names its geometry
 };
 constexpr int kZeroHeadFloats = 64;   // 256 bytes
 // direct norm in chunks of positions (few long examples of a small layer): sets p.splits (chunks per example) and
@@ -110,12 +110,14 @@ bool dma_clipped_ok(int B, int T, int M, int N);
 // flat: the rows of A lie in memory as they are (not the implicit unfolding of an image)
 TnPlan plan_clipped_bf16_dma(int B, int T, int M, int N, bool flat = false);
 TnPlan plan_direct_f32(int B, int T, int M, int N);
-// float32 copy-pipeline kernel (dp_tn_f32_dma.hip): 128 x 128 tiles, 16-row stages; the plans above choose it (dma = true)
-// for long contractions of shapes it fits
-bool f32_dma_ok(int64_t K, int M, int N);
-int f32_dma_tile();
-int f32_dma_stage_rows();
-hipError_t launch_tn_f32_dma(int mode, const TnPlan& p, const float* A, const float* G, const float* clip, int B, int T,
+// float32 products on the bf16 matrix instruction (dp_tn_f32_split.hip), 16-row stages; the plans above choose it
+// (dma = true, tile_m x tile_n names the geometry) for contractions that are long enough and shapes that fill its tiles
+enum F32Geo { F32_NONE = 0, F32_MID, F32_NARROW, F32_FLAT, F32_BIG };
+int f32_split_geo(int64_t K, int M, int N, bool direct);
+int f32_split_tile_m(int geo);
+int f32_split_tile_n(int geo);
+int f32_split_stage_rows();
+hipError_t launch_tn_f32_split(int mode, const TnPlan& p, const float* A, const float* G, const float* clip, int B, int T,
                              int M, int N, float* out, int64_t slice, bool accumulate, hipStream_t st);
 
 // The 16-bit launchers below take bf16 bits, or fp16 bits when f16 is set.
@@ -177,12 +179,12 @@ bool dma_joint_ok(int T, int M, int N);
 bool dma_joint_mid_ok(int T, int M, int N);      // the second class: 128 x 128 tiles, geo = 3 below
 bool dma_joint_ragged_ok(int T, int M, int N);   // the same tiles, T not a multiple of the stage: geo = 4
 size_t joint_workspace_floats(const JointShape* sh, int n_layers, int B, int geo = 1);
-// the same for float32 inputs (dp_tn_f32_dma.hip; 128 x 128 tiles, any T); A, G of JointOperands are float pointers
-size_t joint_f32_workspace_floats(const JointShape* sh, int n_layers, int B);
-hipError_t launch_direct_f32_dma_joint(const JointShape* sh, const JointOperands* op, float* const* partial, int n_layers,
+// the same for float32 inputs (dp_tn_f32_split.hip; 128 x 128 tiles, any T); A, G of JointOperands are float pointers
+size_t joint_f32_workspace_floats(const JointShape* sh, int n_layers, int B, bool big);
+hipError_t launch_direct_f32_split_joint(const JointShape* sh, const JointOperands* op, float* const* partial, int n_layers,
                                        int B, hipStream_t st);
-hipError_t launch_clipped_f32_dma_joint(const JointShape* sh, const JointOperands* op, int n_layers, int B, bool accumulate,
-                                        float stddev, uint64_t seed, float* ws, hipStream_t st);
+hipError_t launch_clipped_f32_split_joint(const JointShape* sh, const JointOperands* op, int n_layers, int B, bool accumulate,
+                                        float stddev, uint64_t seed, float* ws, hipStream_t st, bool big);
 // the same for 8-bit inputs (dp_tn_f8_dma.hip; 256 x 256 tiles, T a multiple of 64); A, G of JointOperands are byte pointers
 bool dma8_joint_ok(int T, int M, int N);
 size_t joint8_workspace_floats(const JointShape* sh, int n_layers, int B);
@@ -258,8 +260,14 @@ hipError_t launch_gram_bf16_dma_layers(const GramLayerDesc* layers, int n_layers
                                        float* partial, hipStream_t st, int fmt, float C = 0.f, float* clip = nullptr);
 hipError_t launch_gram_bf16_dma(const GramPlan& p, const void* A, const void* G, int B, int T, int d_in, int d_out,
                                 bool accumulate, float* sqnorm, float* partial, hipStream_t st, int fmt, const ClipOut* co = nullptr);
-// float32 inputs (dp_gram_f32.hip): 64-row tiles
-GramPlan plan_gram_f32(int T);
+// float32 inputs (dp_gram_f32.hip)
+GramPlan plan_gram_f32(int B, int T);
+int gram_f32_sums(int T);              // the most sums per example that the plan of any batch has (scratch is sized by it)
+// launch class of a layer: 0 for T <= 32 (a kernel of its own); layers of one class > 0 can share a launch, partial[l]: the
+// layer's [B][npairs] sums, to be added by the caller (A, G of the operands are float pointers)
+int gram_f32_class(int B, int T, int d_in, int d_out);
+hipError_t launch_gram_f32_layers(const JointShape* sh, const JointOperands* op, float* const* partial, int n_layers, int B,
+                                  hipStream_t st);
 hipError_t launch_gram_f32(const GramPlan& p, const float* A, const float* G, int B, int T, int d_in, int d_out,
                            bool accumulate, float* sqnorm, float* partial, hipStream_t st, const ClipOut* co = nullptr);
 hipError_t launch_gram_bf16(const GramPlan& p, const uint16_t* A, const uint16_t* G, int B, int T, int d_in, int d_out,

@@ -324,32 +324,37 @@ TnPlan plan_clipped_f32(int B, int T, int M, int N) {
     const int64_t K = (int64_t)B * T;
     TnPlan p;
     p.segmented = false; p.epu = 0; p.big = false; p.dma = false;
-    if (K <= kShortK) {
+    // From 256 rows on, outputs of at least 64 tiles of 128 x 128 fill the chip without K slices: 512 rows of 4608 x 512
+    // take 42 us on 32 x 32 tiles of the fp32 instruction.
+    const int geo = K < (int64_t(1) << 31) ? f32_split_geo(K, M, N, false) : F32_NONE;
+    const bool wide = geo != F32_NONE && (int64_t)ceil_div(M, 128) * ceil_div(N, 128) >= 64;
+    if (K <= kShortK && !wide) {
         p.tile_m = STM; p.tile_n = STN;
         p.tiles_m = ceil_div(M, STM); p.tiles_n = ceil_div(N, STN);
         p.splits = 1; p.kchunk = (int)K;
         return p;
     }
-    if (f32_dma_ok(K, M, N) && K < (int64_t(1) << 31)) {
-        // 128 x 128 tiles on the copy pipeline: two workgroups per compute unit, slices of at least 16 stages
-        const int t = f32_dma_tile(), dk = f32_dma_stage_rows();
+    if (geo != F32_NONE) {
+        // 4-wave geometries: two workgroups per compute unit, 256 x 256: one; slices of at least 4 stages
+        const int dk = f32_split_stage_rows();
+        const int64_t slots = geo == F32_BIG ? 256 : 512;
         p.dma = true;
-        p.tile_m = p.tile_n = t;
-        p.tiles_m = ceil_div(M, t); p.tiles_n = ceil_div(N, t);
+        p.tile_m = f32_split_tile_m(geo); p.tile_n = f32_split_tile_n(geo);
+        p.tiles_m = ceil_div(M, p.tile_m); p.tiles_n = ceil_div(N, p.tile_n);
         const int64_t tiles = (int64_t)p.tiles_m * p.tiles_n;
-        // K slices: the (tile, slice) items run 512 at a time (two workgroups per compute unit); an item costs its
-        // stages plus about 16 stage times of start-up, store and fold.  Take the slice count with the smallest
-        // rounds x (stages per slice + 16): a count that just spills into one more round (540 items) costs a whole
-        // extra round, many short slices cost their overheads.
+        // K slices: the (tile, slice) items run `slots` at a time; an item costs its stages plus about 16 stage times of
+        // start-up and store, and the fold reads all slices, 4 MB in about a stage time.  Take the slice count with the
+        // smallest rounds x (stages per slice + 16) + fold: a count that just spills into one more round (540 items)
+        // costs a whole extra round, many short slices cost their overheads.
         const int64_t stages = (K + dk - 1) / dk;
-        int64_t max_splits = stages / 16;
+        int64_t max_splits = stages / 4;
         if (max_splits < 1) max_splits = 1;
         if (max_splits > 256) max_splits = 256;
         int64_t best = 1, best_cost = -1;
         for (int64_t sp = 1; sp <= max_splits; ++sp) {
             const int64_t sps = (stages + sp - 1) / sp, real = (stages + sps - 1) / sps;
-            const int64_t rounds = (tiles * real + 511) / 512;
-            const int64_t cost = rounds * (sps + 16);
+            const int64_t rounds = (tiles * real + slots - 1) / slots;
+            const int64_t cost = rounds * (sps + 16) + real * (int64_t)M * N / (1 << 20);
             if (best_cost < 0 || cost < best_cost) { best_cost = cost; best = sp; }
         }
         const int64_t kchunk = ((stages + best - 1) / best) * dk;
@@ -377,11 +382,11 @@ TnPlan plan_clipped_f32(int B, int T, int M, int N) {
 TnPlan plan_direct_f32(int B, int T, int M, int N) {
     TnPlan p;
     p.segmented = false; p.epu = 0; p.big = false; p.dma = false;
-    if (f32_dma_ok(T, M, N)) {
-        const int t = f32_dma_tile();
+    const int geo = f32_split_geo(T, M, N, true);
+    if (geo != F32_NONE) {
         p.dma = true;
-        p.tile_m = p.tile_n = t;
-        p.tiles_m = ceil_div(M, t); p.tiles_n = ceil_div(N, t);
+        p.tile_m = f32_split_tile_m(geo); p.tile_n = f32_split_tile_n(geo);
+        p.tiles_m = ceil_div(M, p.tile_m); p.tiles_n = ceil_div(N, p.tile_n);
         p.splits = 1; p.kchunk = 0;
         return p;
     }
@@ -403,7 +408,7 @@ hipError_t launch_clipped_f32(const TnPlan& p, const float* A, const float* G, c
     if (p.splits == 1) { a.out = grad; a.slice = 0; a.accumulate = accumulate ? 1 : 0; }
     else { a.out = ws; a.slice = splitk_slice_elems(n); a.accumulate = 0; }
     if (p.dma) {
-        hipError_t e = launch_tn_f32_dma(0, p, A, G, clip, B, T, M, N, a.out, a.slice, a.accumulate != 0, st);
+        hipError_t e = launch_tn_f32_split(0, p, A, G, clip, B, T, M, N, a.out, a.slice, a.accumulate != 0, st);
         if (e != hipSuccess || p.splits == 1) return e;
         return launch_splitk_reduce(ws, n, p.splits, accumulate, grad, st, noise);
     }
@@ -463,7 +468,7 @@ hipError_t launch_direct_f32(const TnPlan& p, const float* A, const float* G, in
         const int64_t per = ((int64_t(1) << 30) / tiles);
         for (int64_t b0 = 0; b0 < B; b0 += per) {
             const int nb = (int)((B - b0 < per) ? (B - b0) : per);
-            hipError_t e = launch_tn_f32_dma(1, p, A + (size_t)b0 * T * M, G + (size_t)b0 * T * N, nullptr, nb, T, M, N,
+            hipError_t e = launch_tn_f32_split(1, p, A + (size_t)b0 * T * M, G + (size_t)b0 * T * N, nullptr, nb, T, M, N,
                                              partial + (size_t)b0 * tiles, 0, false, st);
             if (e != hipSuccess) return e;
         }

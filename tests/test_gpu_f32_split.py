@@ -1,0 +1,103 @@
+"""The float32 kernels that run on the bf16 matrix instruction with every operand split into three bf16 numbers
+(long clipped sums, direct norms, Gram norms): tile edges, remainders, and the values the three parts cannot carry."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2009_03106_amd import dpclip as dp
+
+pytestmark = pytest.mark.gpu
+
+# A float32 sum of K terms in any order is within about K 2^-24 of the sum of absolute values; for terms of random sign
+# the 2-norm error is a few sqrt(K) 2^-24 / sqrt(K) = a few 2^-24 of the result's.  1e-6 is 17 units of 2^-24.
+REL = 1e-6
+
+
+def _data(B, T, d_in, d_out, seed, scale=1.0):
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    A = torch.randn((B, T, d_in), device="cuda", generator=gen)
+    G = torch.randn((B, T, d_out), device="cuda", generator=gen) * scale
+    clip = torch.rand(B, device="cuda", generator=gen) + 0.25
+    return A, G, clip
+
+
+def _sum64(A, G, clip):
+    a = (A * clip.view(-1, 1, 1)).double().reshape(-1, A.shape[-1])
+    return a.T @ G.double().reshape(-1, G.shape[-1])
+
+
+def _norm64(A, G):
+    return torch.stack([(a.double().T @ g.double()).pow(2).sum() for a, g in zip(A, G)])
+
+
+def _rel(x, ref):
+    return float((x.double() - ref).norm() / ref.norm())
+
+
+@pytest.mark.parametrize("B,T,d_in,d_out", [
+    (600, 1, 128, 128), (1031, 1, 252, 508), (3, 347, 256, 256), (5, 260, 100, 124), (260, 5, 512, 260),
+    (600, 1, 784, 512), (2, 512, 260, 512), (64, 9, 128, 1028), (521, 1, 200, 1024),
+    (300, 1, 1500, 1030), (4097, 1, 64, 120), (2053, 1, 577, 64), (3, 700, 101, 61), (33000, 1, 512, 251), (2, 333, 63, 127)])
+@pytest.mark.parametrize("accumulate", [False, True])
+def test_clipped_sum(B, T, d_in, d_out, accumulate):
+    A, G, clip = _data(B, T, d_in, d_out, 1)
+    start = torch.ones((d_in, d_out), device="cuda") if accumulate else None
+    g = dp.clipped_grad(A, G, clip, grad=start, accumulate=accumulate)
+    ref = _sum64(A, G, clip) + (1.0 if accumulate else 0.0)
+    assert _rel(g, ref) < REL
+
+
+@pytest.mark.parametrize("path,T,d_in,d_out", [
+    ("gram", 33, 36, 68), ("gram", 64, 17, 40), ("gram", 65, 64, 128), ("gram", 127, 30, 33), ("gram", 128, 48, 260),
+    ("gram", 129, 1, 16), ("gram", 300, 132, 20), ("direct", 128, 128, 64), ("direct", 260, 577, 61), ("direct", 131, 60, 125), ("direct", 256, 128, 128), ("direct", 300, 252, 100), ("direct", 1024, 384, 128)])
+def test_norms(path, T, d_in, d_out):
+    A, G, _ = _data(9, T, d_in, d_out, 2)
+    s = dp.layer_sqnorm(A, G, path=path)
+    ref = _norm64(A, G)
+    assert float(((s.double() - ref) / ref).abs().max()) < REL
+
+
+@pytest.mark.parametrize("B", [1, 7, 8, 19])
+@pytest.mark.parametrize("kind", ["gram", "direct"])
+def test_layers_of_one_launch(B, kind):
+    """Layers of different widths and lengths share a launch; examples that are no multiple of the eight XCDs."""
+    shapes = ([(200, 256, 512), (130, 768, 260), (64, 260, 320), (50, 512, 400), (70, 301, 402)] if kind == "gram"
+              else [(1024, 128, 128), (1024, 576, 64), (512, 256, 124), (300, 128, 256), (400, 64, 128)])
+    layers = [_data(B, T, a, b, 3 + i)[:2] for i, (T, a, b) in enumerate(shapes)]
+    s = dp.layers_sqnorm(layers)
+    ref = sum(_norm64(A, G) for A, G in layers)
+    assert float(((s.double() - ref) / ref).abs().max()) < REL
+    clip = torch.rand(B, device="cuda") + 0.25
+    for (A, G), g in zip(layers, dp.layers_clipped_grad(layers, clip)):
+        assert _rel(g, _sum64(A, G, clip)) < REL
+
+
+@pytest.mark.parametrize("scale", [1e-20, 1e-25, 1e-28, 1e-30, 1e-33, 1e-36])
+def test_small_gradients_keep_their_bits(scale):
+    A, G, clip = _data(4, 256, 128, 128, 4, scale)
+    assert _rel(dp.clipped_grad(A, G, clip), _sum64(A, G, clip)) < REL
+    if scale >= 1e-18:
+        s, ref = dp.layer_sqnorm(A, G, path="direct"), _norm64(A, G)
+        assert float(((s.double() - ref) / ref).abs().max()) < REL
+
+
+@pytest.mark.parametrize("value", [float("inf"), float("-inf"), float("nan"), 3.4e38])
+@pytest.mark.parametrize("d", [128, 256])
+def test_values_without_three_parts(value, d):
+    """Infinities, NaN and numbers that round to an infinite bf16 come out as float32 sums give them."""
+    A, G, clip = _data(4, 256, d, d, 5, 1e-3)
+    clip.fill_(0.5)
+    A[1, 17, 5] = value
+    got = dp.clipped_grad(A, G, clip).cpu().numpy()
+    a = (A * 0.5).cpu().numpy().astype(np.float64).reshape(-1, d)
+    with np.errstate(all="ignore"):
+        ref = a.T @ G.cpu().numpy().astype(np.float64).reshape(-1, d)
+    assert (np.isnan(got) == np.isnan(ref)).all()
+    assert (np.isinf(got) == np.isinf(ref)).all()
+    inf = np.isinf(ref)
+    assert (np.sign(got[inf]) == np.sign(ref[inf])).all()
+    ok = np.isfinite(ref)
+    assert np.abs(got[ok] - ref[ok]).max() <= 1e-5 * np.abs(ref[ok]).max()
+    for path in ("gram", "direct"):
+        s = dp.layer_sqnorm(A, G, path=path).cpu().numpy()
+        assert not np.isfinite(s[1]) and np.isfinite(s[[0, 2, 3]]).all()
