@@ -156,6 +156,13 @@ int gram_f32_join_class(int64_t B, int64_t T, int64_t d_in, int64_t d_out, dp_dt
     if (B * gram_f32_sums((int)T) >= (int64_t(1) << 24)) return 0;              // 16 layers' items stay below 2^31
     return gram_f32_class((int)B, (int)T, (int)d_in, (int)d_out);
 }
+// a 16-bit layer whose Gram norm runs on the any-shape kernel with 128-row tiles: such layers share launches too
+bool gram16_joinable(int64_t B, int64_t T, int64_t d_in, int64_t d_out, dp_dtype dtype, dp_path path) {
+    if (!is16(dtype) || T <= 64 || d_in == 0 || d_out == 0 || B >= (int64_t(1) << 20)) return false;
+    if (resolve_path(path, dtype, T, d_in, d_out) != DP_PATH_GRAM || gram_batchable(T, d_in, d_out, dtype, path) ||
+        gram_cols_class(B, T, d_in, d_out, dtype, path) != 0) return false;
+    return B * plan_gram_bf16((int)T, (int)d_in, (int)d_out).npairs < (int64_t(1) << 24);
+}
 size_t single_layer_need(int64_t B, const dp_layer_desc& y, dp_dtype dtype, dp_path path) {
     size_t n = dp_workspace_bytes(DP_OP_SQNORM, B, y.T, y.d_in, y.d_out, dtype, path);
     if (direct_joinable(B, y.T, y.d_in, y.d_out, dtype, path))
@@ -901,6 +908,17 @@ dp_status dp_layers_sqnorm_clip(const dp_layer_desc* layers, int64_t n_layers, i
             [&](const JointShape* sh, const JointOperands* op, float* const* part, int n) {
                 return is16(dtype) ? launch_direct_bf16_dma_joint(sh, op, part, n, (int)B, stream, dtype == DP_F16)
                                    : launch_direct_f32_split_joint(sh, op, part, n, (int)B, stream); });
+        if (e != hipSuccess) return DP_ERR_HIP;
+    }
+    if (defer_on && is16(dtype)) {
+        std::vector<int64_t> which;
+        for (int64_t l = 0; l < n_layers; ++l)
+            if (gram16_joinable(B, layers[l].T, layers[l].d_in, layers[l].d_out, dtype, path)) which.push_back(l);
+        std::stable_sort(which.begin(), which.end(), [&](int64_t p, int64_t q) { return layers[p].d_in + layers[p].d_out > layers[q].d_in + layers[q].d_out; });
+        const hipError_t e = which.size() < 2 ? hipSuccess
+            : join(which, [&](const dp_layer_desc& y) { return plan_gram_bf16((int)y.T, (int)y.d_in, (int)y.d_out).npairs; },
+            [&](const JointShape* sh, const JointOperands* op, float* const* part, int n) {
+                return launch_gram_bf16_layers(sh, op, part, n, (int)B, stream, dtype == DP_F16); });
         if (e != hipSuccess) return DP_ERR_HIP;
     }
     for (int cls = 1; defer_on && dtype == DP_F32 && cls <= 4; ++cls) {

@@ -270,6 +270,8 @@ hipError_t launch_gram_f32_layers(const JointShape* sh, const JointOperands* op,
                                   hipStream_t st);
 hipError_t launch_gram_f32(const GramPlan& p, const float* A, const float* G, int B, int T, int d_in, int d_out,
                            bool accumulate, float* sqnorm, float* partial, hipStream_t st, const ClipOut* co = nullptr);
+hipError_t launch_gram_bf16_layers(const JointShape* sh, const JointOperands* op, float* const* partial, int n_layers, int B,
+                                   hipStream_t st, bool f16);
 hipError_t launch_gram_bf16(const GramPlan& p, const uint16_t* A, const uint16_t* G, int B, int T, int d_in, int d_out,
                             bool accumulate, float* sqnorm, float* partial, hipStream_t st, bool f16, const ClipOut* co = nullptr);
 
