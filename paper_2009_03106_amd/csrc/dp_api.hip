@@ -170,6 +170,21 @@ size_t single_layer_need(int64_t B, const dp_layer_desc& y, dp_dtype dtype, dp_p
     return round16(n);
 }
 
+// which of the arrays p[k][0 .. n[k]) overlap another one: their writers must not share a launch
+std::vector<char> overlapping(const std::vector<const float*>& p, const std::vector<int64_t>& n) {
+    std::vector<size_t> order(p.size());
+    for (size_t k = 0; k < order.size(); ++k) order[k] = k;
+    std::sort(order.begin(), order.end(), [&](size_t a, size_t b) { return p[a] < p[b]; });
+    std::vector<char> bad(p.size(), 0);
+    size_t last = 0;                                     // the array that reaches furthest so far
+    for (size_t k = 1; k < order.size(); ++k) {
+        const size_t a = order[last], b = order[k];
+        if (p[a] + n[a] > p[b]) bad[a] = bad[b] = 1;
+        if (p[b] + n[b] > p[a] + n[a]) last = k;
+    }
+    return bad;
+}
+
 // Which joint clipped-sum launch of dp_layers_clipped_grad(_noise) can take a layer (by shape and type): 0 none,
 // 1 the 256 x 256-tile launch, 3 the 128 x 128-tile launch for aligned 16-bit layers of a few hundred columns, 4 the
 // same for such layers whose T is not a multiple of the 32-row stage, 5 and 6 the float32 launches (tiles up to
@@ -961,12 +976,45 @@ dp_status dp_layers_sqnorm_clip(const dp_layer_desc* layers, int64_t n_layers, i
         if (flush_queue(clip_with_single) != hipSuccess) return DP_ERR_HIP;
         if (clip_with_single && !queued && launch_clip_factors(sqnorm, (int)B, C, clip, stream) != hipSuccess) return DP_ERR_HIP;
     }
-    // bias terms of the layers above (dense ones included): their own pass over G
+    // bias terms of the layers above (dense ones included): their own pass over G, up to kBiasLayers of them in two launches
+    std::vector<int64_t> biased;
     for (int64_t l = 0; l < n_layers; ++l) {
         const dp_layer_desc& y = layers[l];
         if (!y.bias_rows || y.d_out == 0) continue;
         // taken by the Gram kernel (16-bit types: the 8-bit Gram kernel has no column sums)
         if (!is8(dtype) && y.T > 1 && y.d_in > 0 && gram_batchable(y.T, y.d_in, y.d_out, dtype, path)) continue;
+        biased.push_back(l);
+    }
+    std::vector<char> bias_done((size_t)n_layers, 0);
+    if (biased.size() >= 2 && !is8(dtype) && B <= 65535) {
+        std::vector<const float*> rows;
+        std::vector<int64_t> sizes;
+        for (int64_t l : biased) { rows.push_back(layers[l].bias_rows); sizes.push_back(B * layers[l].d_out); }
+        const std::vector<char> shared = overlapping(rows, sizes);
+        BiasLayerDesc group[kBiasLayers];
+        int64_t which[kBiasLayers];
+        int ng = 0;
+        for (size_t k = 0; k <= biased.size(); ++k) {
+            if (k < biased.size()) {
+                const dp_layer_desc& y = layers[biased[k]];
+                if (!shared[k] && y.T > 0 && y.G && aligned16(y.G)) {
+                    which[ng] = biased[k];
+                    group[ng++] = BiasLayerDesc{y.G, (int)y.T, (int)y.d_out, y.bias_rows};
+                }
+            }
+            if (ng == kBiasLayers || (k == biased.size() && ng >= 2)) {
+                const hipError_t e = launch_bias_sqnorm_layers(group, ng, (int)B, (int)dtype, acc != 0, sqnorm, stream);
+                if (e == hipSuccess) {
+                    for (int i = 0; i < ng; ++i) bias_done[(size_t)which[i]] = 1;
+                    acc = 1; launched = true;
+                } else if (e != hipErrorInvalidValue) return DP_ERR_HIP;     // (too large for one launch: one by one below)
+                ng = 0;
+            }
+        }
+    }
+    for (int64_t l : biased) {
+        if (bias_done[(size_t)l]) continue;
+        const dp_layer_desc& y = layers[l];
         const dp_status s1 = dp_bias_sqnorm(y.G, B, y.T, y.d_out, dtype, acc, sqnorm, y.bias_rows, hip_stream);
         if (s1 != DP_OK) return s1;
         acc = 1; launched = true;
@@ -1192,6 +1240,14 @@ dp_status dp_layers_clipped_grad_noise(const dp_layer_desc* layers, int64_t n_la
     // one launch whose items fill the chip a whole number of times, the K slices folded (and the noise added) inside
     // it.  With noise the kernel adds it four elements at a time, so the layer's offset and size must be multiples of 4.
     // A second class of joint launches (128 x 128 tiles) takes the aligned 16-bit layers of a few hundred columns.
+    // (layers whose gradients overlap, as tied weights accumulated into one array do, run one after the other)
+    std::vector<char> shared_grad((size_t)n_layers, 0);
+    if (n_layers >= 2) {
+        std::vector<const float*> grads;
+        std::vector<int64_t> sizes;
+        for (int64_t l = 0; l < n_layers; ++l) { grads.push_back(layers[l].grad); sizes.push_back(layers[l].d_in * layers[l].d_out); }
+        shared_grad = overlapping(grads, sizes);
+    }
     std::vector<std::vector<int64_t>> joint_groups;
     std::vector<int> joint_geo;
     for (int geo : {1, 3, 4, 5, 6}) {
@@ -1199,7 +1255,7 @@ dp_status dp_layers_clipped_grad_noise(const dp_layer_desc* layers, int64_t n_la
         const size_t first_group = joint_groups.size();
         for (int64_t l = 0; l < n_layers; ++l) {
             const dp_layer_desc& y = layers[l];
-            if (clipped_join_class(B, y.T, y.d_in, y.d_out, dtype) != geo) continue;
+            if (shared_grad[(size_t)l] || clipped_join_class(B, y.T, y.d_in, y.d_out, dtype) != geo) continue;
             if (stddev > 0.0f && !splitk_noise_ok(y.d_in * y.d_out, y.noise_offset)) continue;
             cur.push_back(l);
             if ((int)cur.size() == kJointLayers) { joint_groups.push_back(cur); joint_geo.push_back(geo); cur.clear(); }
@@ -1258,7 +1314,7 @@ dp_status dp_layers_clipped_grad_noise(const dp_layer_desc* layers, int64_t n_la
         for (int64_t l = 0; l < n_layers; ++l) {
             const dp_layer_desc& y = layers[l];
             if (y.T == 0 || y.d_in == 0 || y.d_out == 0) continue;
-            if (!clipped_f32_is_short(plan_clipped_f32((int)B, (int)y.T, (int)y.d_in, (int)y.d_out))) continue;
+            if (shared_grad[(size_t)l] || !clipped_f32_is_short(plan_clipped_f32((int)B, (int)y.T, (int)y.d_in, (int)y.d_out))) continue;
             which[nb] = l;
             batch[nb++] = ShortLayerDesc{static_cast<const float*>(y.A), static_cast<const float*>(y.G), y.clip ? y.clip : clip, y.grad,
                                          (int)y.T, (int)y.d_in, (int)y.d_out};
@@ -1272,15 +1328,42 @@ dp_status dp_layers_clipped_grad_noise(const dp_layer_desc* layers, int64_t n_la
                            : clipped_grad_noise(y.A, y.G, y.clip ? y.clip : clip, B, y.T, y.d_in, y.d_out, dtype, accumulate, y.grad, workspace,
                                                 workspace_bytes, hip_stream, stddev, seed, y.noise_offset);
         if (s1 != DP_OK) return s1;
-        if (y.grad_b && y.d_out > 0) {
-            // the layer's bias: sum_i nu_i bias_rows[i, :], with its own stretch of the noise stream
-            hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-            hipError_t e = hipSuccess;
-            if (B == 0) { if (!accumulate) e = launch_fill_zero(y.grad_b, y.d_out, stream); }
-            else e = launch_clipped_bias(y.bias_rows, y.clip ? y.clip : clip, (int)B, (int)y.d_out, accumulate != 0, y.grad_b, stream);
-            if (e == hipSuccess && stddev > 0.0f) e = launch_add_noise(y.grad_b, y.d_out, stddev, seed, y.bias_noise_offset, stream);
-            if (e != hipSuccess) return DP_ERR_HIP;
+    }
+    // the biases: sum_i nu_i bias_rows[i, :], each with its own stretch of the noise stream; up to kBiasLayers in a launch
+    hipStream_t stream = static_cast<hipStream_t>(hip_stream);
+    std::vector<int64_t> biased;
+    std::vector<const float*> out;
+    std::vector<int64_t> sizes;
+    for (int64_t l = 0; l < n_layers; ++l)
+        if (layers[l].grad_b && layers[l].d_out > 0) { biased.push_back(l); out.push_back(layers[l].grad_b); sizes.push_back(layers[l].d_out); }
+    std::vector<char> bias_done((size_t)n_layers, 0);
+    if (B > 0 && biased.size() >= 2) {
+        const std::vector<char> shared = overlapping(out, sizes);
+        ClippedBiasDesc group[kBiasLayers];
+        int64_t which[kBiasLayers];
+        int ng = 0;
+        for (size_t k = 0; k <= biased.size(); ++k) {
+            if (k < biased.size() && !shared[k]) {
+                const dp_layer_desc& y = layers[biased[k]];
+                which[ng] = biased[k];
+                group[ng++] = ClippedBiasDesc{y.bias_rows, y.clip ? y.clip : clip, (int)y.d_out, y.grad_b, y.bias_noise_offset};
+            }
+            if (ng == kBiasLayers || (k == biased.size() && ng >= 2)) {
+                const hipError_t e = launch_clipped_bias_layers(group, ng, (int)B, accumulate != 0, stddev, seed, stream);
+                if (e == hipSuccess) { for (int i = 0; i < ng; ++i) bias_done[(size_t)which[i]] = 1; }
+                else if (e != hipErrorInvalidValue) return DP_ERR_HIP;       // (too large for one launch: one by one below)
+                ng = 0;
+            }
         }
+    }
+    for (int64_t l : biased) {
+        if (bias_done[(size_t)l]) continue;
+        const dp_layer_desc& y = layers[l];
+        hipError_t e = hipSuccess;
+        if (B == 0) { if (!accumulate) e = launch_fill_zero(y.grad_b, y.d_out, stream); }
+        else e = launch_clipped_bias(y.bias_rows, y.clip ? y.clip : clip, (int)B, (int)y.d_out, accumulate != 0, y.grad_b, stream);
+        if (e == hipSuccess && stddev > 0.0f) e = launch_add_noise(y.grad_b, y.d_out, stddev, seed, y.bias_noise_offset, stream);
+        if (e != hipSuccess) return DP_ERR_HIP;
     }
     return DP_OK;
 }

@@ -6,6 +6,7 @@
 // All of it is bandwidth-bound; every sum runs in a fixed order (no atomics).
 #include "dp_common.h"
 #include "dp_internal.h"
+#include "dp_noise.h"
 #include <type_traits>
 
 namespace dpk {
@@ -26,16 +27,15 @@ template <int DT> __device__ __forceinline__ float f8_byte(uint32_t word, int wh
          : which == 2 ? __builtin_amdgcn_cvt_f32_fp8((int)word, 2) : __builtin_amdgcn_cvt_f32_fp8((int)word, 3);
 }
 template <int DT, bool PROD, int DTH = DT>
-__global__ __launch_bounds__(kThreads) void k_bias_rows(const void* __restrict__ G, const void* __restrict__ Hb, int T, int D, int ctl,
-                                                        float* __restrict__ u, float* __restrict__ u2) {
+__device__ __forceinline__ void bias_rows_block(const void* __restrict__ G, const void* __restrict__ Hb, int T, int D, int ctl,
+                                                float* __restrict__ u, float* __restrict__ u2, int bx, int ex) {
     constexpr int ES = ElemBytes<DT>::value;          // bytes per element
     static_assert(ElemBytes<DTH>::value == ES, "G and Hb of one width");
     constexpr int VEC = 16 / ES;
     __shared__ float part[kThreads][PROD ? 2 * VEC : VEC];
     const int tid = threadIdx.x, ct = 1 << ctl, rg = kThreads >> ctl;
     const int ctid = tid & (ct - 1), rgid = tid >> ctl;
-    const int ex = blockIdx.y;
-    const int col0 = (blockIdx.x * ct + ctid) * VEC;
+    const int col0 = (bx * ct + ctid) * VEC;
     float acc[VEC], acc2[VEC];                        // acc2 (PROD only): plain sums
 #pragma unroll
     for (int v = 0; v < VEC; ++v) { acc[v] = 0.f; acc2[v] = 0.f; }
@@ -118,6 +118,12 @@ __global__ __launch_bounds__(kThreads) void k_bias_rows(const void* __restrict__
     }
 }
 
+template <int DT, bool PROD, int DTH = DT>
+__global__ __launch_bounds__(kThreads) void k_bias_rows(const void* __restrict__ G, const void* __restrict__ Hb, int T, int D, int ctl,
+                                                        float* __restrict__ u, float* __restrict__ u2) {
+    bias_rows_block<DT, PROD, DTH>(G, Hb, T, D, ctl, u, u2, blockIdx.x, blockIdx.y);
+}
+
 // Any D: one thread per column, rows in ascending order.
 template <int DT> __device__ __forceinline__ float load_elem(const void* p, size_t k) {
     if (DT >= 3) return f8_byte<DT>(static_cast<const unsigned char*>(p)[k], 0);
@@ -125,10 +131,9 @@ template <int DT> __device__ __forceinline__ float load_elem(const void* p, size
     return static_cast<const float*>(p)[k];
 }
 template <int DT, bool PROD, int DTH = DT>
-__global__ __launch_bounds__(kThreads) void k_bias_rows_scalar(const void* __restrict__ G, const void* __restrict__ Hb, int T, int D,
-                                                               float* __restrict__ u, float* __restrict__ u2) {
-    const int q = blockIdx.x * kThreads + threadIdx.x;
-    const int ex = blockIdx.y;
+__device__ __forceinline__ void bias_rows_scalar_block(const void* __restrict__ G, const void* __restrict__ Hb, int T, int D,
+                                                       float* __restrict__ u, float* __restrict__ u2, int bx, int ex) {
+    const int q = bx * kThreads + threadIdx.x;
     if (q >= D) return;
     float acc = 0.f, acc2 = 0.f;
     const size_t base = (size_t)ex * T * D + q;
@@ -144,6 +149,24 @@ __global__ __launch_bounds__(kThreads) void k_bias_rows_scalar(const void* __res
     }
     u[(size_t)ex * D + q] = acc;
     if (PROD) u2[(size_t)ex * D + q] = acc2;
+}
+template <int DT, bool PROD, int DTH = DT>
+__global__ __launch_bounds__(kThreads) void k_bias_rows_scalar(const void* __restrict__ G, const void* __restrict__ Hb, int T, int D,
+                                                               float* __restrict__ u, float* __restrict__ u2) {
+    bias_rows_scalar_block<DT, PROD, DTH>(G, Hb, T, D, u, u2, blockIdx.x, blockIdx.y);
+}
+
+// The bias rows of several layers in one launch, each with its own launch's split (ctl; < 0: one thread per column): a
+// layer of 32 examples is a few hundred workgroups of 5 to 6 us, five of them and their norms were ten launches.
+struct BiasRowsLayers { const void* G[kBiasLayers]; float* u[kBiasLayers]; int T[kBiasLayers], D[kBiasLayers], ctl[kBiasLayers],
+                        chunks[kBiasLayers], first_block[kBiasLayers]; int n_layers; };
+template <int DT>
+__global__ __launch_bounds__(kThreads) void k_bias_rows_layers(BiasRowsLayers a) {
+    int l = 0;
+    while (l + 1 < a.n_layers && (int)blockIdx.x >= a.first_block[l + 1]) ++l;
+    const int b = blockIdx.x - a.first_block[l], ex = b / a.chunks[l], bx = b - ex * a.chunks[l];
+    if (a.ctl[l] >= 0) bias_rows_block<DT, false>(a.G[l], nullptr, a.T[l], a.D[l], a.ctl[l], a.u[l], nullptr, bx, ex);
+    else               bias_rows_scalar_block<DT, false>(a.G[l], nullptr, a.T[l], a.D[l], a.u[l], nullptr, bx, ex);
 }
 
 // s_i (+)= sum_q u[i, q]^2 (+ sum_q u2[i, q]^2 when u2 is given: LayerNorm's scale and shift rows in one launch):
@@ -182,6 +205,21 @@ __global__ __launch_bounds__(kThreads) void k_rows_sqnorm(const float* __restric
     }
 }
 
+// the same for several layers' rows, added in the order given: the bits of one launch per layer
+struct RowsLayers { const float* u[kBiasLayers]; int D[kBiasLayers]; int n_layers; };
+__global__ __launch_bounds__(kThreads) void k_rows_sqnorm_layers(RowsLayers a, int B, int accumulate, float* __restrict__ sqnorm) {
+    const int lane = threadIdx.x & (kWave - 1);
+    const int ex = blockIdx.x * (kThreads / kWave) + (threadIdx.x >> 6);
+    if (ex >= B) return;
+    float s = 0.f;
+    if (accumulate) s = sqnorm[ex];
+    for (int l = 0; l < a.n_layers; ++l) {
+        const float v = row_sq(a.u[l] + (size_t)ex * a.D[l], a.D[l], lane);
+        s = l == 0 && !accumulate ? v : s + v;
+    }
+    if (lane == 0) sqnorm[ex] = s;
+}
+
 // grad_b[q] (+)= sum_i nu_i u[i, q].  A workgroup owns 32 columns; its NG row groups add examples g, g + NG, ... in
 // ascending order (four loads in flight each), and the NG partial sums are added in the order g = 0 .. NG - 1: a
 // fixed order, so the result is reproducible.  (One thread per column walking all B examples one dependent load
@@ -189,11 +227,11 @@ __global__ __launch_bounds__(kThreads) void k_rows_sqnorm(const float* __restric
 // 2048 examples on: the grid is only d_out / 32 workgroups, so a long batch needs the loads of many threads in
 // flight per workgroup (B = 65536, d_out = 512: 0.70 ms with 8 groups).
 template <int NG>
-__global__ __launch_bounds__(NG * 32) void k_clipped_bias(const float* __restrict__ u, const float* __restrict__ clip, int B, int D,
-                                                          int accumulate, float* __restrict__ grad_b) {
+__device__ __forceinline__ void clipped_bias_block(const float* __restrict__ u, const float* __restrict__ clip, int B, int D,
+                                                   int accumulate, float* __restrict__ grad_b, int bx, const NoiseArgs& nz) {
     __shared__ float part[NG][32];
     const int g = threadIdx.x >> 5, cl = threadIdx.x & 31;
-    const int q = blockIdx.x * 32 + cl;
+    const int q = bx * 32 + cl;
     float acc = 0.f;
     if (q < D) {
         int i = g;
@@ -209,20 +247,48 @@ __global__ __launch_bounds__(NG * 32) void k_clipped_bias(const float* __restric
     if (g == 0 && q < D) {
 #pragma unroll
         for (int k = 1; k < NG; ++k) acc += part[k][cl];
-        grad_b[q] = accumulate ? grad_b[q] + acc : acc;
+        float v = accumulate ? grad_b[q] + acc : acc;
+        if (nz.stddev != 0.0f) {
+            // entry q of the layer's stretch of the noise stream: slot (offset + q) % 4 of Philox block (offset + q) / 4
+            const uint64_t j = nz.offset + (uint64_t)q;
+            const U4 w = philox4x32_10((uint32_t)(j >> 2), (uint32_t)(j >> 34), 0u, 0u, nz.k0, nz.k1);
+            float z0, z1;
+            if (j & 2) box_muller(w.z, w.w, z0, z1); else box_muller(w.x, w.y, z0, z1);
+            v += nz.stddev * ((j & 1) ? z1 : z0);
+        }
+        grad_b[q] = v;
     }
 }
+template <int NG>
+__global__ __launch_bounds__(NG * 32) void k_clipped_bias(const float* __restrict__ u, const float* __restrict__ clip, int B, int D,
+                                                          int accumulate, float* __restrict__ grad_b) {
+    clipped_bias_block<NG>(u, clip, B, D, accumulate, grad_b, blockIdx.x, NoiseArgs{0.0f, 0u, 0u, 0u});
+}
+// several layers' bias gradients and their noise in one launch
+struct ClippedBiasLayers { const float* u[kBiasLayers]; const float* clip[kBiasLayers]; float* grad_b[kBiasLayers];
+                           uint64_t noise_offset[kBiasLayers]; int D[kBiasLayers], first_block[kBiasLayers]; int n_layers; };
+template <int NG>
+__global__ __launch_bounds__(NG * 32) void k_clipped_bias_layers(ClippedBiasLayers a, int B, int accumulate, NoiseArgs nz) {
+    int l = 0;
+    while (l + 1 < a.n_layers && (int)blockIdx.x >= a.first_block[l + 1]) ++l;
+    nz.offset = a.noise_offset[l];
+    clipped_bias_block<NG>(a.u[l], a.clip[l], B, a.D[l], accumulate, a.grad_b[l], blockIdx.x - a.first_block[l], nz);
+}
 
+// log2 of the column threads of k_bias_rows: next power of two, at most 64, but narrower column chunks (down to 16 threads =
+// 256-byte row pieces) while the grid is too small to keep enough loads in flight for HBM
+int column_threads_log2(int nvec, int B) {
+    int ctl = 0;
+    while (ctl < 6 && (1 << ctl) < nvec) ++ctl;
+    while (ctl > 4 && (int64_t)((nvec + (1 << ctl) - 1) >> ctl) * B < 1024) --ctl;
+    return ctl;
+}
 template <int DT, int DTH = DT> void launch_bias_rows_dt(const void* G, const void* Hb, int B, int T, int D, float* u, float* u2, hipStream_t st) {
     constexpr int vec = 16 / ElemBytes<DT>::value;
     const bool prod = Hb != nullptr;
     if (D % vec == 0) {
         const int nvec = D / vec;
-        int ctl = 0;
-        while (ctl < 6 && (1 << ctl) < nvec) ++ctl;      // column threads: next power of two, at most 64 ...
-        // ... but narrower column chunks (down to 16 threads = 256-byte row pieces) while the grid is too small
-        // to keep enough loads in flight for HBM
-        while (ctl > 4 && (int64_t)((nvec + (1 << ctl) - 1) >> ctl) * B < 1024) --ctl;
+        const int ctl = column_threads_log2(nvec, B);
         const dim3 grid((unsigned)((nvec + (1 << ctl) - 1) >> ctl), (unsigned)B);
         if (prod) k_bias_rows<DT, true, DTH><<<grid, kThreads, 0, st>>>(G, Hb, T, D, ctl, u, u2);
         else      k_bias_rows<DT, false><<<grid, kThreads, 0, st>>>(G, Hb, T, D, ctl, u, u2);
@@ -308,6 +374,55 @@ hipError_t launch_rows_sqnorm(const float* u, int B, int D, bool accumulate, flo
 hipError_t launch_clipped_bias(const float* u, const float* clip, int B, int D, bool accumulate, float* grad_b, hipStream_t st) {
     if (B >= 2048) k_clipped_bias<32><<<(unsigned)((D + 31) / 32), 1024, 0, st>>>(u, clip, B, D, accumulate ? 1 : 0, grad_b);
     else           k_clipped_bias<8><<<(unsigned)((D + 31) / 32), kThreads, 0, st>>>(u, clip, B, D, accumulate ? 1 : 0, grad_b);
+    return hipGetLastError();
+}
+
+hipError_t launch_bias_sqnorm_layers(const BiasLayerDesc* layers, int n_layers, int B, int dt, bool accumulate, float* sqnorm, hipStream_t st) {
+    if (n_layers < 1 || n_layers > kBiasLayers || B < 1 || B > 65535 || dt < 0 || dt > 2) return hipErrorInvalidValue;
+    BiasRowsLayers a;
+    RowsLayers r;
+    int64_t blocks = 0;
+    const int vec = dt == 0 ? 4 : 8;
+    for (int l = 0; l < kBiasLayers; ++l) {
+        const BiasLayerDesc& y = layers[l < n_layers ? l : 0];
+        const bool wide = y.D % vec == 0;
+        a.G[l] = y.G; a.u[l] = y.u; a.T[l] = y.T; a.D[l] = y.D;
+        a.ctl[l] = wide ? column_threads_log2(y.D / vec, B) : -1;
+        a.chunks[l] = wide ? (y.D / vec + (1 << a.ctl[l]) - 1) >> a.ctl[l] : ceil_div(y.D, kThreads);
+        a.first_block[l] = (int)blocks;
+        if (l < n_layers) blocks += (int64_t)a.chunks[l] * B;
+        if (blocks >= (int64_t(1) << 24)) return hipErrorInvalidValue;
+        r.u[l] = y.u; r.D[l] = y.D;
+    }
+    a.n_layers = r.n_layers = n_layers;
+    if (dt == 0)      k_bias_rows_layers<0><<<(unsigned)blocks, kThreads, 0, st>>>(a);
+    else if (dt == 1) k_bias_rows_layers<1><<<(unsigned)blocks, kThreads, 0, st>>>(a);
+    else              k_bias_rows_layers<2><<<(unsigned)blocks, kThreads, 0, st>>>(a);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    const int per_block = kThreads / kWave;
+    k_rows_sqnorm_layers<<<(unsigned)((B + per_block - 1) / per_block), kThreads, 0, st>>>(r, B, accumulate ? 1 : 0, sqnorm);
+    return hipGetLastError();
+}
+
+hipError_t launch_clipped_bias_layers(const ClippedBiasDesc* layers, int n_layers, int B, bool accumulate, float stddev, uint64_t seed, hipStream_t st) {
+    if (n_layers < 1 || n_layers > kBiasLayers || B < 1) return hipErrorInvalidValue;
+    ClippedBiasLayers a;
+    int64_t blocks = 0;
+    for (int l = 0; l < kBiasLayers; ++l) {
+        const ClippedBiasDesc& y = layers[l < n_layers ? l : 0];
+        a.u[l] = y.u; a.clip[l] = y.clip; a.grad_b[l] = y.grad_b; a.noise_offset[l] = y.noise_offset; a.D[l] = y.D;
+        a.first_block[l] = (int)blocks;
+        if (l < n_layers) blocks += ceil_div(y.D, 32);       // widths are below 2^24: fewer than 2^23 workgroups
+    }
+    a.n_layers = n_layers;
+    const NoiseArgs nz{stddev, (uint32_t)seed, (uint32_t)(seed >> 32), 0};
+    if (B >= 2048) {
+        if (blocks >= (int64_t(1) << 22)) return hipErrorInvalidValue;
+        k_clipped_bias_layers<32><<<(unsigned)blocks, 1024, 0, st>>>(a, B, accumulate ? 1 : 0, nz);
+    } else {
+        k_clipped_bias_layers<8><<<(unsigned)blocks, kThreads, 0, st>>>(a, B, accumulate ? 1 : 0, nz);
+    }
     return hipGetLastError();
 }
 

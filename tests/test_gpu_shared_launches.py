@@ -1,0 +1,79 @@
+"""Layers that share launches: 16-bit Gram norms of ragged shapes, bias rows and bias gradients, and the layers that must
+not share one (gradients of one array)."""
+import pytest
+import torch
+
+from paper_2009_03106_amd import dpclip as dp
+
+pytestmark = pytest.mark.gpu
+
+
+def _layers(B, shapes, dtype, seed=0):
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    return [(torch.randn((B, T, a), device="cuda", generator=gen).to(dtype), (torch.randn((B, T, b), device="cuda", generator=gen)).to(dtype))
+            for T, a, b in shapes]
+
+
+def _norm64(A, G):
+    return torch.stack([(a.double().T @ g.double()).pow(2).sum() for a, g in zip(A, G)])
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
+@pytest.mark.parametrize("B", [1, 9, 32])
+def test_ragged_gram_norms_of_one_launch(dtype, B):
+    layers = _layers(B, [(250, 200, 600), (65, 199, 201), (128, 100, 444), (129, 300, 333)], dtype)
+    s = dp.layers_sqnorm(layers, path="gram")
+    ref = sum(_norm64(A, G) for A, G in layers)
+    # float32 sums of exact products, all of them squares' sums of up to 2^15 terms: K 2^-24 at the worst, 1e-5 covers it
+    assert float(((s.double() - ref) / ref).abs().max()) < 1e-5
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16, torch.float16])
+@pytest.mark.parametrize("B,n", [(1, 2), (5, 3), (32, 17), (2050, 2)])
+@pytest.mark.parametrize("noise", [0.0, 0.7])
+def test_biases_of_one_launch_equal_one_by_one(dtype, B, n, noise):
+    """Widths of 16-byte rows and ragged ones; the shared launches add in the order of the single ones: same bits."""
+    shapes = [(1 + 3 * (l % 5), 8, (40, 33, 520, 2, 128)[l % 5]) for l in range(n)]
+    layers = _layers(B, shapes, dtype, 1)
+    grads = [torch.zeros((a, b), device="cuda") for _, a, b in shapes]
+    rows = [torch.zeros((B, b), device="cuda") for _, _, b in shapes]
+    gbs = [torch.ones(b, device="cuda") for _, _, b in shapes]
+    offs = [4 * 10 ** 6 + 1001 * l for l in range(n)]
+    descs = dp.layer_descs(layers, grads, bias_rows=rows, grad_bs=gbs, bias_noise_offsets=offs)
+    s = dp.layers_sqnorm(layers, descs=descs)
+    clip = torch.rand(B, device="cuda") + 0.25
+    dp.layers_clipped_grad(layers, clip, grads, descs=descs, noise_std=noise, seed=11)
+    ref_s = dp.layers_sqnorm(layers)
+    for (A, G), r, g, off in zip(layers, rows, gbs, offs):
+        one = torch.empty_like(r)
+        dp.bias_sqnorm(G, ref_s, one, accumulate=True)
+        assert torch.equal(one, r)
+        gb = torch.empty_like(g)
+        dp.clipped_bias_grad(one, clip, gb)
+        if noise:
+            dp.add_noise(gb, noise, 11, off)
+        assert torch.equal(gb, g)
+    # the weights' norms are added before the biases' in both
+    assert torch.allclose(s, ref_s, rtol=1e-6, atol=0)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_tied_weights_accumulate_into_one_array(dtype):
+    shapes = [(64, 128, 128), (64, 128, 128), (64, 256, 128)]
+    layers = _layers(8, shapes, dtype, 2)
+    tied = torch.zeros((128, 128), device="cuda")
+    grads = [tied, tied, torch.zeros((256, 128), device="cuda")]
+    bias = torch.zeros(128, device="cuda")
+    rows = [torch.zeros((8, 128), device="cuda") for _ in shapes]
+    clip = torch.rand(8, device="cuda") + 0.25
+    descs = dp.layer_descs(layers, grads, bias_rows=rows, grad_bs=[bias] * 3)
+    dp.layers_sqnorm(layers, descs=descs)
+    dp.layers_clipped_grad(layers, clip, grads, accumulate=True, descs=descs)
+    w = clip.double().view(-1, 1, 1)
+    sums = [(A.double() * w).reshape(-1, A.shape[-1]).T @ G.double().reshape(-1, G.shape[-1]) for A, G in layers]
+    ref, ref_b = sums[0] + sums[1], sum((G.double() * w).sum((0, 1)) for _, G in layers)
+    # bfloat16 rows may be rounded once more by the factor: 2^-9 each
+    tol = 1e-6 if dtype == torch.float32 else 4e-3
+    assert float((tied.double() - ref).norm() / ref.norm()) < tol
+    assert float((grads[2].double() - sums[2]).norm() / sums[2].norm()) < tol
+    assert float((bias.double() - ref_b).norm() / ref_b.norm()) < 1e-5
