@@ -292,15 +292,15 @@ struct F32JointArgs {
 template <int MODE, bool BIG>
 __global__ __launch_bounds__(BIG ? GeoBig::THREADS : GeoMid::THREADS, 2) void k_tn_f32_split_joint(F32JointArgs j) {
     __shared__ u32x4 lds[2 * (BIG ? GeoBig::STAGE_UNITS : GeoMid::STAGE_UNITS)];
-    // Direct norms: the layers' items differ in length, so every XCD takes its eighth of every layer's items
-    // (first_item: among the items of one XCD).  Clipped sums have items of about one length: an eighth of the list.
-    const int xcd = blockIdx.x & 7, L = MODE == 1 ? (int)(blockIdx.x >> 3) : xcd * j.per_xcd + (int)(blockIdx.x >> 3);
+    // The layers' items differ in length, so every XCD takes its eighth of every layer's items (first_item: among the
+    // items of one XCD): 18 convolutions' sums 0.28 ms, with eighths of the whole list 0.34 ms.  On 256 x 256 tiles they have about one length: an eighth of the list.
+    const int xcd = blockIdx.x & 7, L = BIG ? xcd * j.per_xcd + (int)(blockIdx.x >> 3) : (int)(blockIdx.x >> 3);
     if (L >= j.n_items) return;
     int l = 0;
     while (l + 1 < j.n_layers && L >= j.layer[l + 1].first_item) ++l;
     const F32JointLayer& y = j.layer[l];
     int item = L - y.first_item;
-    if (MODE == 1) item += xcd * (((int64_t)y.tiles_m * y.tiles_n * y.splits + 7) / 8);
+    if (!BIG) item += xcd * (((int64_t)y.tiles_m * y.tiles_n * y.splits + 7) / 8);
     F32SplitArgs a;
     a.A = y.A; a.G = y.G; a.clip = y.clip;
     a.out = y.out; a.slice = (((int64_t)y.M * y.N) + 3) & ~(int64_t)3;          // splitk_slice_elems
@@ -378,7 +378,7 @@ hipError_t launch_clipped_f32_split_joint(const JointShape* sh, const JointOpera
         y.K = B * sh[l].T; y.T = sh[l].T; y.M = sh[l].M; y.N = sh[l].N;
         y.tiles_m = p.tiles_m[l]; y.tiles_n = p.tiles_n[l]; y.splits = p.splits[l]; y.kchunk = p.kchunk[l]; y.geo = p.geo[l];
         y.first_item = (int)first;
-        first += (int64_t)p.tiles_m[l] * p.tiles_n[l] * p.splits[l];
+        first += big ? (int64_t)p.tiles_m[l] * p.tiles_n[l] * p.splits[l] : ceil_div((int64_t)p.tiles_m[l] * p.tiles_n[l] * p.splits[l], 8);
         if (!whole) {
             f.ws[nf] = slices; f.grad[nf] = op[l].grad; f.n[nf] = (int64_t)sh[l].M * sh[l].N;
             f.splits[nf] = p.splits[l]; f.noise_offset[nf] = op[l].noise_offset;
@@ -387,7 +387,7 @@ hipError_t launch_clipped_f32_split_joint(const JointShape* sh, const JointOpera
         slices += (size_t)p.splits[l] * (size_t)splitk_slice_elems((int64_t)sh[l].M * sh[l].N);
     }
     for (int l = n_layers; l < kJointLayers; ++l) j.layer[l] = j.layer[0];
-    j.n_layers = n_layers; j.n_items = (int)p.items; j.per_xcd = ceil_div(p.items, 8);
+    j.n_layers = n_layers; j.n_items = big ? (int)p.items : (int)first; j.per_xcd = big ? ceil_div(p.items, 8) : (int)first;
     if (big) k_tn_f32_split_joint<0, true><<<8u * (unsigned)j.per_xcd, GeoBig::THREADS, 0, st>>>(j);
     else     k_tn_f32_split_joint<0, false><<<8u * (unsigned)j.per_xcd, GeoMid::THREADS, 0, st>>>(j);
     const hipError_t e = hipGetLastError();
