@@ -871,7 +871,8 @@ dp_status dp_layers_sqnorm_clip(const dp_layer_desc* layers, int64_t n_layers, i
         if (direct_joinable(B, layers[l].T, layers[l].d_in, layers[l].d_out, dtype, path)) ++n_dj;
     const bool join_direct = defer_on && n_dj >= 2;
     // (the float32 Gram norms do the same, a class of layers after the other; heaviest first inside a launch)
-    std::vector<char> joined((size_t)n_layers, 0);
+    std::vector<char> joined;                                // allocated where a layer can be in it
+    if (defer_on) joined.resize((size_t)n_layers, 0);
     auto join = [&](const std::vector<int64_t>& which, auto sums_of, auto launch) -> hipError_t {
         JointShape sh[kJointLayers];
         JointOperands op[kJointLayers];
@@ -936,7 +937,7 @@ dp_status dp_layers_sqnorm_clip(const dp_layer_desc* layers, int64_t n_layers, i
                 return launch_gram_bf16_layers(sh, op, part, n, (int)B, stream, dtype == DP_F16); });
         if (e != hipSuccess) return DP_ERR_HIP;
     }
-    for (int cls = 1; defer_on && dtype == DP_F32 && cls <= 4; ++cls) {
+    for (int cls = 1; defer_on && dtype == DP_F32 && cls <= 6; ++cls) {
         std::vector<int64_t> which;
         for (int64_t l = 0; l < n_layers; ++l)
             if (gram_f32_join_class(B, layers[l].T, layers[l].d_in, layers[l].d_out, dtype, path) == cls) which.push_back(l);
@@ -952,7 +953,7 @@ dp_status dp_layers_sqnorm_clip(const dp_layer_desc* layers, int64_t n_layers, i
         if (y.T == 0 || (y.T == 1 && !is8(dtype)) || y.d_in == 0 || y.d_out == 0) continue;     // empty layers add nothing
         if (gram_batchable(y.T, y.d_in, y.d_out, dtype, path)) continue;
         if (gram_cols_class(B, y.T, y.d_in, y.d_out, dtype, path) != 0) continue;
-        if (joined[(size_t)l]) continue;
+        if (defer_on && joined[(size_t)l]) continue;
         if (!defer_on) {
             const dp_status s1 = layer_sqnorm_clip(y.A, y.G, B, y.T, y.d_in, y.d_out, dtype, path, acc, sqnorm, workspace, workspace_bytes,
                                                    hip_stream, (clip_with_single && l == last_single) ? &clip_out : nullptr);
@@ -985,7 +986,8 @@ dp_status dp_layers_sqnorm_clip(const dp_layer_desc* layers, int64_t n_layers, i
         if (!is8(dtype) && y.T > 1 && y.d_in > 0 && gram_batchable(y.T, y.d_in, y.d_out, dtype, path)) continue;
         biased.push_back(l);
     }
-    std::vector<char> bias_done((size_t)n_layers, 0);
+    std::vector<char> bias_done;
+    if (!biased.empty()) bias_done.resize((size_t)n_layers, 0);
     if (biased.size() >= 2 && !is8(dtype) && B <= 65535) {
         std::vector<const float*> rows;
         std::vector<int64_t> sizes;
@@ -1241,13 +1243,13 @@ dp_status dp_layers_clipped_grad_noise(const dp_layer_desc* layers, int64_t n_la
     // it.  With noise the kernel adds it four elements at a time, so the layer's offset and size must be multiples of 4.
     // A second class of joint launches (128 x 128 tiles) takes the aligned 16-bit layers of a few hundred columns.
     // (layers whose gradients overlap, as tied weights accumulated into one array do, run one after the other)
-    std::vector<char> shared_grad((size_t)n_layers, 0);
-    if (n_layers >= 2) {
-        std::vector<const float*> grads;
-        std::vector<int64_t> sizes;
-        for (int64_t l = 0; l < n_layers; ++l) { grads.push_back(layers[l].grad); sizes.push_back(layers[l].d_in * layers[l].d_out); }
-        shared_grad = overlapping(grads, sizes);
-    }
+    auto shared_grad = [&](int64_t l) {
+        const float* p = layers[l].grad;
+        const int64_t n = layers[l].d_in * layers[l].d_out;
+        for (int64_t k = 0; k < n_layers; ++k)
+            if (k != l && layers[k].grad < p + n && p < layers[k].grad + layers[k].d_in * layers[k].d_out) return true;
+        return false;
+    };
     std::vector<std::vector<int64_t>> joint_groups;
     std::vector<int> joint_geo;
     for (int geo : {1, 3, 4, 5, 6}) {
@@ -1255,7 +1257,7 @@ dp_status dp_layers_clipped_grad_noise(const dp_layer_desc* layers, int64_t n_la
         const size_t first_group = joint_groups.size();
         for (int64_t l = 0; l < n_layers; ++l) {
             const dp_layer_desc& y = layers[l];
-            if (shared_grad[(size_t)l] || clipped_join_class(B, y.T, y.d_in, y.d_out, dtype) != geo) continue;
+            if (clipped_join_class(B, y.T, y.d_in, y.d_out, dtype) != geo || shared_grad(l)) continue;
             if (stddev > 0.0f && !splitk_noise_ok(y.d_in * y.d_out, y.noise_offset)) continue;
             cur.push_back(l);
             if ((int)cur.size() == kJointLayers) { joint_groups.push_back(cur); joint_geo.push_back(geo); cur.clear(); }
@@ -1314,7 +1316,7 @@ dp_status dp_layers_clipped_grad_noise(const dp_layer_desc* layers, int64_t n_la
         for (int64_t l = 0; l < n_layers; ++l) {
             const dp_layer_desc& y = layers[l];
             if (y.T == 0 || y.d_in == 0 || y.d_out == 0) continue;
-            if (shared_grad[(size_t)l] || !clipped_f32_is_short(plan_clipped_f32((int)B, (int)y.T, (int)y.d_in, (int)y.d_out))) continue;
+            if (!clipped_f32_is_short(plan_clipped_f32((int)B, (int)y.T, (int)y.d_in, (int)y.d_out)) || shared_grad(l)) continue;
             which[nb] = l;
             batch[nb++] = ShortLayerDesc{static_cast<const float*>(y.A), static_cast<const float*>(y.G), y.clip ? y.clip : clip, y.grad,
                                          (int)y.T, (int)y.d_in, (int)y.d_out};
@@ -1336,7 +1338,8 @@ dp_status dp_layers_clipped_grad_noise(const dp_layer_desc* layers, int64_t n_la
     std::vector<int64_t> sizes;
     for (int64_t l = 0; l < n_layers; ++l)
         if (layers[l].grad_b && layers[l].d_out > 0) { biased.push_back(l); out.push_back(layers[l].grad_b); sizes.push_back(layers[l].d_out); }
-    std::vector<char> bias_done((size_t)n_layers, 0);
+    std::vector<char> bias_done;
+    if (!biased.empty()) bias_done.resize((size_t)n_layers, 0);
     if (B > 0 && biased.size() >= 2) {
         const std::vector<char> shared = overlapping(out, sizes);
         ClippedBiasDesc group[kBiasLayers];

@@ -69,9 +69,10 @@ __device__ __forceinline__ void gram_f32_exact(const float* Xi, int T, int D, in
 }
 
 // One Gram product tile: acc = X[t-tile rows] . X[s-tile rows]^T over the D columns of X_i[T, D].
-// VEC: D % 4 == 0 (every 16-byte piece lies inside a row or outside it) and D < 2^22 (a tile's rows lie within 2^31 bytes).
+// LOAD: how a thread's four columns come: 2 = one 16-byte buffer load (D % 4 == 0: every such piece lies inside a row or
+// outside it), 1 = four 4-byte buffer loads, 0 = four loads by address (D >= 2^22: a tile's rows span 2^31 bytes or more).
 // Every wave leaves with its LDS reads done.
-template <int MI, bool VEC, bool DIAG>
+template <int MI, int LOAD, bool DIAG>
 __device__ __forceinline__ void gram_f32_product(const float* __restrict__ Xi, int T, int D, int t0, int s0,
                                                  unsigned char* lds, f32x16 (&acc)[MI][MI]) {
     using GT = GramTile<MI>;
@@ -82,9 +83,9 @@ __device__ __forceinline__ void gram_f32_product(const float* __restrict__ Xi, i
     // global -> LDS: four threads per row, MI rows of either side and two stages (a 128-byte line of the row) at a time
     const int lr = tid >> 2, lc = (tid & 3) * 4;
     const int t_rows = min(T - t0, GT::R), s_rows = min(T - s0, GT::R);
-    // VEC: buffer loads, a row past T or a column past D lies outside the buffer and comes back as zero
-    const auto buf_t = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(Xi + (size_t)t0 * D), (short)0, VEC ? t_rows * D * 4 : 0, 0x00020000);
-    const auto buf_s = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(Xi + (size_t)s0 * D), (short)0, VEC ? s_rows * D * 4 : 0, 0x00020000);
+    // buffer loads: a row past T or a column past D lies outside the buffer and comes back as zero
+    const auto buf_t = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(Xi + (size_t)t0 * D), (short)0, LOAD ? t_rows * D * 4 : 0, 0x00020000);
+    const auto buf_s = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(Xi + (size_t)s0 * D), (short)0, LOAD ? s_rows * D * 4 : 0, 0x00020000);
     const uint32_t wr = (uint32_t)((lc >> 3) * GT::PLANE + lr * 16 + (lc & 4) * 2);
     f32x4 x[2][SIDES][MI];
     int next_k = lc;
@@ -96,9 +97,15 @@ __device__ __forceinline__ void gram_f32_product(const float* __restrict__ Xi, i
 #pragma unroll
                 for (int u = 0; u < 2; ++u) {
                     const int row = lr + 64 * v, k = next_k + u * GK;
-                    if (VEC) {
+                    if (LOAD == 2) {
                         const uint32_t off = k < D ? (uint32_t)(row * D + k) * 4u : 0x7ffffff0u;
                         x[u][h][v] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(h == 0 ? buf_t : buf_s, off, 0, 0));
+                    } else if (LOAD == 1) {
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) {
+                            const uint32_t off = k + j < D ? (uint32_t)(row * D + k + j) * 4u : 0x7ffffff0u;
+                            x[u][h][v][j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(h == 0 ? buf_t : buf_s, off, 0, 0));
+                        }
                     } else {
                         const bool in = row < (h == 0 ? t_rows : s_rows);
                         const float* p = Xi + (size_t)((h == 0 ? t0 : s0) + (in ? row : 0)) * D;
@@ -185,12 +192,12 @@ __device__ __forceinline__ void gram_f32_product(const float* __restrict__ Xi, i
     if (__any(check.suspect())) gram_f32_exact<MI>(Xi, T, D, t0 + wm * MI * 32, s0 + wn * MI * 32, acc);
 }
 
-template <int MI, bool VEC, bool DIAG>
+template <int MI, int LOAD, bool DIAG>
 __device__ __forceinline__ void gram_f32_pair(const GramF32Layer& a, int ex, int tt, int ss, unsigned char* lds, float* out) {
     constexpr int R = GramTile<MI>::R;
     f32x16 accP[MI][MI], accQ[MI][MI];
-    gram_f32_product<MI, VEC, DIAG>(a.A + (size_t)ex * a.T * a.d_in, a.T, a.d_in, tt * R, ss * R, lds, accP);
-    gram_f32_product<MI, VEC, DIAG>(a.G + (size_t)ex * a.T * a.d_out, a.T, a.d_out, tt * R, ss * R, lds, accQ);
+    gram_f32_product<MI, LOAD, DIAG>(a.A + (size_t)ex * a.T * a.d_in, a.T, a.d_in, tt * R, ss * R, lds, accP);
+    gram_f32_product<MI, LOAD, DIAG>(a.G + (size_t)ex * a.T * a.d_out, a.T, a.d_out, tt * R, ss * R, lds, accQ);
     // rows beyond T were stored as zeros, so their entries of both tiles are zero
     float s = 0.f;
 #pragma unroll
@@ -209,7 +216,7 @@ __device__ __forceinline__ void gram_f32_pair(const GramF32Layer& a, int ex, int
 // contiguous eighth of every layer's items, example by example, so that an example's pairs read its rows through one L2
 // and the XCDs have equal work (an eighth of the whole list gave those with the widest layer 1.25 times the mean: four
 // layers of 768 .. 3072 columns, B = 64, T = 512: 1.71 ms, 1.39 ms so).
-template <int MI, bool VEC>
+template <int MI, int LOAD>
 __global__ __launch_bounds__(kThreads, MI == 2 ? 2 : 4) void k_gram_f32(GramF32Args g) {
     __shared__ __attribute__((aligned(1024))) unsigned char lds[2 * GramTile<MI>::STAGE];
     const int L = blockIdx.x >> 3;
@@ -226,8 +233,8 @@ __global__ __launch_bounds__(kThreads, MI == 2 ? 2 : 4) void k_gram_f32(GramF32A
     while (pair >= nt - tt) { pair -= nt - tt; ++tt; }
     const int ss = tt + pair;
     float* out = a.partial + (size_t)ex * a.npairs + pair0;
-    if (tt == ss) gram_f32_pair<MI, VEC, true>(a, ex, tt, ss, lds, out);
-    else          gram_f32_pair<MI, VEC, false>(a, ex, tt, ss, lds, out);
+    if (tt == ss) gram_f32_pair<MI, LOAD, true>(a, ex, tt, ss, lds, out);
+    else          gram_f32_pair<MI, LOAD, false>(a, ex, tt, ss, lds, out);
 }
 
 struct GramArgsF {
@@ -348,9 +355,11 @@ GramPlan plan_gram_f32(int B, int T) {
 
 int gram_f32_sums(int T) { const int nt = (T + 63) / 64; return nt * (nt + 1) / 2; }
 
+// 1 + the way of loading, + 3 for tiles of 128 rows
 int gram_f32_class(int B, int T, int d_in, int d_out) {
     if (T <= 32) return 0;
-    return (plan_gram_f32(B, T).tile == 128 ? 2 : 1) + (((d_in | d_out) & 3) == 0 && (d_in | d_out) < (1 << 22) ? 2 : 0);
+    const int load = (d_in | d_out) >= (1 << 22) ? 0 : ((d_in | d_out) & 3) == 0 ? 2 : 1;
+    return 1 + load + (plan_gram_f32(B, T).tile == 128 ? 3 : 0);
 }
 
 hipError_t launch_gram_f32_layers(const JointShape* sh, const JointOperands* op, float* const* partial, int n_layers, int B,
@@ -376,10 +385,12 @@ hipError_t launch_gram_f32_layers(const JointShape* sh, const JointOperands* op,
     for (int l = n_layers; l < kJointLayers; ++l) g.layer[l] = g.layer[0];
     g.n_layers = n_layers;
     const unsigned grid = 8u * (unsigned)first;
-    if      (cls == 1) k_gram_f32<1, false><<<grid, kThreads, 0, st>>>(g);
-    else if (cls == 2) k_gram_f32<2, false><<<grid, kThreads, 0, st>>>(g);
-    else if (cls == 3) k_gram_f32<1, true><<<grid, kThreads, 0, st>>>(g);
-    else               k_gram_f32<2, true><<<grid, kThreads, 0, st>>>(g);
+    if      (cls == 1) k_gram_f32<1, 0><<<grid, kThreads, 0, st>>>(g);
+    else if (cls == 2) k_gram_f32<1, 1><<<grid, kThreads, 0, st>>>(g);
+    else if (cls == 3) k_gram_f32<1, 2><<<grid, kThreads, 0, st>>>(g);
+    else if (cls == 4) k_gram_f32<2, 0><<<grid, kThreads, 0, st>>>(g);
+    else if (cls == 5) k_gram_f32<2, 1><<<grid, kThreads, 0, st>>>(g);
+    else               k_gram_f32<2, 2><<<grid, kThreads, 0, st>>>(g);
     return hipGetLastError();
 }
 

@@ -49,7 +49,7 @@ def test_clipped_sum(B, T, d_in, d_out, accumulate):
 
 @pytest.mark.parametrize("path,T,d_in,d_out", [
     ("gram", 33, 36, 68), ("gram", 64, 17, 40), ("gram", 65, 64, 128), ("gram", 127, 30, 33), ("gram", 128, 48, 260),
-    ("gram", 129, 1, 16), ("gram", 300, 132, 20), ("direct", 128, 128, 64), ("direct", 260, 577, 61), ("direct", 131, 60, 125), ("direct", 256, 128, 128), ("direct", 300, 252, 100), ("direct", 1024, 384, 128)])
+    ("gram", 129, 1, 16), ("gram", 256, 48, 33), ("gram", 512, 18, 61), ("gram", 300, 132, 20), ("direct", 128, 128, 64), ("direct", 260, 577, 61), ("direct", 131, 60, 125), ("direct", 256, 128, 128), ("direct", 300, 252, 100), ("direct", 1024, 384, 128)])
 def test_norms(path, T, d_in, d_out):
     A, G, _ = _data(9, T, d_in, d_out, 2)
     s = dp.layer_sqnorm(A, G, path=path)
