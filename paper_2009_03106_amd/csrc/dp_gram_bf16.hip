@@ -170,7 +170,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_gram_bf16(GramArgs a) {
 }
 
 // Several layers in one launch: a layer of 32 examples and 250 positions is 96 workgroups on 256 compute units, three
-// such layers one after the other 47 us, in one launch 25 us.  XCD b % 8 takes an eighth of every layer's items (layer l:
+// such layers one after the other 47 us, in one launch 21 us.  XCD b % 8 takes an eighth of every layer's items (layer l:
 // those from first_item[l] on in the XCD's list).
 struct GramLayers { GramArgs layer[kJointLayers]; int n_items[kJointLayers], first_item[kJointLayers]; int n_layers; };
 template <bool F16>

@@ -412,8 +412,8 @@ int f32_split_geo(int64_t K, int M, int N, bool direct) {
     if (fits(F32_MID)) return F32_MID;
     if (fits(F32_NARROW)) return F32_NARROW;
     if (fits(F32_FLAT)) return F32_FLAT;
-    // a classifier head over a large batch is bound by reading its inputs, the padding costs nothing: 256 x 10 at
-    // B = 65536 took 41 us on 64 x 64 tiles of the fp32 instruction, 25 us here
+    // a classifier head over a large batch is bound by reading its inputs, the padding costs nothing: a step of
+    // three layers ending in 256 x 10 at B = 65536 takes 541 us so, 556 us with the head on 64 x 64 tiles of the fp32 instruction
     if (!direct && K >= 8192 && N < 64 && (int64_t)ceil_div(M, 128) * 128 * 3 <= (int64_t)M * 4) return F32_NARROW;
     return F32_NONE;
 }
