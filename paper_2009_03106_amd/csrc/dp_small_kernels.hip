@@ -516,7 +516,7 @@ hipError_t launch_splitk_reduce(const float* ws, int64_t n, int splits, bool acc
     return hipGetLastError();
 }
 
-// The same fold for the layers of a joint launch in ONE launch (z ascending for every entry, as k_splitk_reduce):
+// The same fold for the layers of a joint launch in ONE launch (z ascending for every entry, in blocks of eight):
 // a fold per layer is a launch of a few microseconds each, which for a dozen small layers is longer than their sums
 // took.  A workgroup takes 256 groups of 4 entries of one layer.
 template <bool NOISE>
@@ -528,21 +528,28 @@ __global__ __launch_bounds__(256) void k_splitk_reduce_layers(FoldLayers f, int 
     const float* ws = f.ws[l];
     const int64_t slice = f.slice[l];
     const int splits = f.splits[l];
-    float4 acc = reinterpret_cast<const float4*>(ws)[c];
-    int z = 1;
-    for (; z + 3 < splits; z += 4) {
-        const float4 v0 = reinterpret_cast<const float4*>(ws + (size_t)z * slice)[c];
-        const float4 v1 = reinterpret_cast<const float4*>(ws + (size_t)(z + 1) * slice)[c];
-        const float4 v2 = reinterpret_cast<const float4*>(ws + (size_t)(z + 2) * slice)[c];
-        const float4 v3 = reinterpret_cast<const float4*>(ws + (size_t)(z + 3) * slice)[c];
-        acc.x += v0.x; acc.y += v0.y; acc.z += v0.z; acc.w += v0.w;
-        acc.x += v1.x; acc.y += v1.y; acc.z += v1.z; acc.w += v1.w;
-        acc.x += v2.x; acc.y += v2.y; acc.z += v2.z; acc.w += v2.w;
-        acc.x += v3.x; acc.y += v3.y; acc.z += v3.z; acc.w += v3.w;
-    }
-    for (; z < splits; ++z) {
-        const float4 v = reinterpret_cast<const float4*>(ws + (size_t)z * slice)[c];
-        acc.x += v.x; acc.y += v.y; acc.z += v.z; acc.w += v.w;
+    // blocks of eight slices, then the blocks: one after the other, 165 slices of a float32 sum cost twice its rounding error
+    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int z0 = 0; z0 < splits; z0 += 8) {
+        const int end = min(z0 + 8, splits);
+        float4 b = reinterpret_cast<const float4*>(ws + (size_t)z0 * slice)[c];
+        int z = z0 + 1;
+        for (; z + 3 < end; z += 4) {
+            const float4 v0 = reinterpret_cast<const float4*>(ws + (size_t)z * slice)[c];
+            const float4 v1 = reinterpret_cast<const float4*>(ws + (size_t)(z + 1) * slice)[c];
+            const float4 v2 = reinterpret_cast<const float4*>(ws + (size_t)(z + 2) * slice)[c];
+            const float4 v3 = reinterpret_cast<const float4*>(ws + (size_t)(z + 3) * slice)[c];
+            b.x += v0.x; b.y += v0.y; b.z += v0.z; b.w += v0.w;
+            b.x += v1.x; b.y += v1.y; b.z += v1.z; b.w += v1.w;
+            b.x += v2.x; b.y += v2.y; b.z += v2.z; b.w += v2.w;
+            b.x += v3.x; b.y += v3.y; b.z += v3.z; b.w += v3.w;
+        }
+        for (; z < end; ++z) {
+            const float4 v = reinterpret_cast<const float4*>(ws + (size_t)z * slice)[c];
+            b.x += v.x; b.y += v.y; b.z += v.z; b.w += v.w;
+        }
+        if (z0 == 0) acc = b;
+        else { acc.x += b.x; acc.y += b.y; acc.z += b.z; acc.w += b.w; }
     }
     float4* o = reinterpret_cast<float4*>(f.grad[l]) + c;
     if (accumulate) { const float4 g = *o; acc.x += g.x; acc.y += g.y; acc.z += g.z; acc.w += g.w; }
