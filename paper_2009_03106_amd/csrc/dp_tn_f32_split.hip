@@ -110,6 +110,9 @@ __device__ __forceinline__ void tn_f32_split_tile(const F32SplitArgs& a, const i
     if (MODE == 0) { fex = (k_begin + 8 * kgA + (lane & 7)) / a.T; fpos = (k_begin + 8 * kgA + (lane & 7)) - fex * a.T; }
     const int adv_ex = DKF / a.T, adv_pos = DKF - adv_ex * a.T;
     int next_a = k_begin + 8 * kgA, next_g = k_begin + 8 * kgG;
+    // The MFMA rounds its sums down, which in long sums of random sign adds up (K = 65536: 5.6e-7 of the result): every other
+    // stage is formed with the sign of A turned and subtracted, so that the two errors cancel.
+    float sign_a = 1.0f;                                 // of the next stage to fetch
     auto fetch = [&](bool of_a) {                        // one operand of the next stage; A first
         const int next_row = of_a ? next_a : next_g;
         const int rows = __builtin_amdgcn_readfirstlane(max(0, min(8, k_end - next_row)));
@@ -120,7 +123,8 @@ __device__ __forceinline__ void tn_f32_split_tile(const F32SplitArgs& a, const i
 #pragma unroll
             for (int j = 0; j < 8; ++j, off += rowA) ra[j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(buf, off, 0, 0));
             if (MODE == 0) {
-                rc = a.clip[min(fex, last_ex)];
+                rc = a.clip[min(fex, last_ex)] * sign_a;
+                sign_a = -sign_a;
                 fex += adv_ex; fpos += adv_pos;
                 if (fpos >= a.T) { fpos -= a.T; ++fex; }
             }
@@ -194,6 +198,7 @@ __device__ __forceinline__ void tn_f32_split_tile(const F32SplitArgs& a, const i
     }
     for (int st = 0; st < n_stages; ++st) {
         const int buf = st & 1;
+        const float sign = MODE == 0 ? (buf ? -1.0f : 1.0f) : 1.0f;
         bf16x8 fg[NI][3], fa[2][3];
         auto read_a = [&](int i) {
 #pragma unroll
@@ -208,7 +213,7 @@ __device__ __forceinline__ void tn_f32_split_tile(const F32SplitArgs& a, const i
         for (int t = 0; t < TILES; ++t) {
             const int i = t / NI, j = t % NI, before = (t + TILES - 1) % TILES;
             if (j == 0 && i + 1 < MI) read_a(i + 1);
-            acc[before / NI][before % NI] += pend;
+            acc[before / NI][before % NI] += pend * (MODE == 0 && t == 0 ? -sign : sign);
             pend = split_mfma(fa[i & 1], fg[j]);
 #pragma unroll
             for (int q = 0; q < STEPS; ++q) split_step(t * STEPS + q, buf ^ 1);
@@ -231,7 +236,7 @@ __device__ __forceinline__ void tn_f32_split_tile(const F32SplitArgs& a, const i
             }
         }
     }
-    acc[MI - 1][NI - 1] += pend;
+    acc[MI - 1][NI - 1] += pend * (MODE == 0 && !(n_stages & 1) ? -1.0f : 1.0f);
     if constexpr (TWO) {
 #pragma unroll
         for (int i = 0; i < MI; ++i)
