@@ -185,9 +185,8 @@ __device__ __forceinline__ void tn_f32_split_tile(const F32SplitArgs& a, const i
     constexpr int TILES = MI * NI, STEPS = 8 / TILES;
     static_assert(TILES * STEPS == 8, "");
     f32x16 pend = {};                                    // the sums of the tile before, not yet added
-    // The 4-wave geometries have registers for sums in two levels, blocks of 8 stages and their sum: over hundreds of
-    // stages that halves the rounding error (64 -> 432, B = 42257: 5.2e-7 of the result without, against 2.4e-7 of the
-    // fp32 instruction over its shorter slices).
+    // The 4-wave geometries have registers for sums in two levels, blocks of 8 stages and their sum: a little of the
+    // rounding error of long sums (64 -> 432, B = 42257: 5.2e-7 of the result to 4.9e-7; the turned signs take the rest).
     constexpr bool TWO = MODE == 0 && MI * NI <= 4;
     f32x16 total[TWO ? MI : 1][TWO ? NI : 1];
     if constexpr (TWO) {
