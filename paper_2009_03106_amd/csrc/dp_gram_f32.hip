@@ -39,8 +39,8 @@ template <int MI> struct GramTile {
     static constexpr int STAGE = 2 * SIDE;                 // rows of the t-tile, rows of the s-tile
 };
 
-// The wave's tile of X_t X_s^T once more with the float32 instruction, in the order of k, straight from memory: for
-// sums that the three bf16 parts cannot carry (see dp_split.h); ordinary data never come here.
+// The wave's tile of X_t X_s^T once more with the float32 instruction, in the order of k, straight from memory and slow:
+// for sums of 2^80 and more, infinities and NaN (see dp_split.h).
 template <int MI>
 __device__ __forceinline__ void gram_f32_exact(const float* Xi, int T, int D, int t0, int s0, f32x16 (&acc)[MI][MI]) {
     const int lrow = threadIdx.x & 31, lhalf = (threadIdx.x & 63) >> 5;
@@ -123,7 +123,8 @@ __device__ __forceinline__ void gram_f32_product(const float* __restrict__ Xi, i
         const int h = piece / MI, v = piece % MI;
         uint32_t part[3][2];
 #pragma unroll
-        for (int q = 0; q < 2; ++q) split2(x[u][h][v][2 * q], x[u][h][v][2 * q + 1], part[0][q], part[1][q], part[2][q]);
+        for (int q = 0; q < 2; ++q)
+            split2(x[u][h][v][2 * q] * kSplitScale, x[u][h][v][2 * q + 1] * kSplitScale, part[0][q], part[1][q], part[2][q]);
 #pragma unroll
         for (int p = 0; p < 3; ++p)
             *reinterpret_cast<uint2*>(lds + buf * GT::STAGE + h * GT::SIDE + p * 2 * GT::PLANE + wr + v * 64 * 16) =
@@ -163,7 +164,7 @@ __device__ __forceinline__ void gram_f32_product(const float* __restrict__ Xi, i
 #pragma unroll
             for (int t = 0; t < TILES; ++t) {
                 const int before = (t + TILES - 1) % TILES;
-                acc[before / MI][before % MI] += pend;
+                acc[before / MI][before % MI] += pend * kSplitUnscale;
                 pend = split_mfma(ft[t / MI], fs[t % MI]);
 #pragma unroll
                 for (int q = 0; q < STEPS; ++q)
@@ -181,7 +182,7 @@ __device__ __forceinline__ void gram_f32_product(const float* __restrict__ Xi, i
             __builtin_amdgcn_sched_barrier(0);
         }
     }
-    acc[MI - 1][MI - 1] += pend;
+    acc[MI - 1][MI - 1] += pend * kSplitUnscale;
     SplitCheck check;
 #pragma unroll
     for (int i = 0; i < MI; ++i)

@@ -7,8 +7,8 @@
 //     without bank conflicts.  4-byte loads also take any width and alignment.
 //   * 16-row stages, two in LDS; the loads of the stage after next wait in registers, one barrier per stage.
 //   * The clip factors of a stage's rows are the same for a whole wave: scalar loads, multiplied into the A values
-//     before the split (the same a * c rounded once to float32 as in the row-scaling kernels).  Rows past the end of
-//     the K slice read a clamped valid row and get the factor 0.
+//     before the split (the same a * c rounded once to float32 as in the row-scaling kernels; the split's scale is in
+//     the factor).  Rows past the end of the K slice come back from the buffer loads as zeros.
 // Two uses, as in the 16-bit file: clipped sum (Eq. weighted_loss) over K slices, and direct squared norm (Algorithm
 // 3 / 4 without their output tensor): the slice is one example and the finished tile is squared and summed.
 #include <algorithm>
@@ -49,8 +49,8 @@ struct F32SplitArgs {
     int accumulate;
 };
 
-// The wave's sums once more with the float32 instruction, in the order of k: for sums that the three bf16 parts cannot
-// carry (see dp_split.h).  Straight from memory and slow; ordinary data never come here.
+// The wave's sums once more with the float32 instruction, in the order of k: for sums of 2^80 and more, infinities and
+// NaN (see dp_split.h).  Straight from memory and slow.
 template <int MODE, class GEO>
 __device__ __forceinline__ void tn_f32_exact(const F32SplitArgs& a, int k_begin, int k_end, int mw, int nw, f32x16 (&acc)[GEO::MI][GEO::NI]) {
     const int lrow = threadIdx.x & 31, lhalf = (threadIdx.x & 63) >> 5;
@@ -123,7 +123,7 @@ __device__ __forceinline__ void tn_f32_split_tile(const F32SplitArgs& a, const i
 #pragma unroll
             for (int j = 0; j < 8; ++j, off += rowA) ra[j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(buf, off, 0, 0));
             if (MODE == 0) {
-                rc = a.clip[min(fex, last_ex)] * sign_a;
+                rc = a.clip[min(fex, last_ex)] * (sign_a * kSplitScale);
                 sign_a = -sign_a;
                 fex += adv_ex; fpos += adv_pos;
                 if (fpos >= a.T) { fpos -= a.T; ++fex; }
@@ -147,8 +147,8 @@ __device__ __forceinline__ void tn_f32_split_tile(const F32SplitArgs& a, const i
             if (MODE == 0) {
                 x0 *= __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(rc), 2 * q));
                 x1 *= __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(rc), 2 * q + 1));
-            }
-        } else { x0 = rg[2 * q]; x1 = rg[2 * q + 1]; }
+            } else { x0 *= kSplitScale; x1 *= kSplitScale; }
+        } else { x0 = rg[2 * q] * kSplitScale; x1 = rg[2 * q + 1] * kSplitScale; }
         uint32_t p1, p2, p3;
         split2(x0, x1, p1, p2, p3);
         parts[0][q] = p1; parts[1][q] = p2; parts[2][q] = p3;
@@ -197,7 +197,7 @@ __device__ __forceinline__ void tn_f32_split_tile(const F32SplitArgs& a, const i
     }
     for (int st = 0; st < n_stages; ++st) {
         const int buf = st & 1;
-        const float sign = MODE == 0 ? (buf ? -1.0f : 1.0f) : 1.0f;
+        const float sign = MODE == 0 && buf ? -kSplitUnscale : kSplitUnscale;
         bf16x8 fg[NI][3], fa[2][3];
         auto read_a = [&](int i) {
 #pragma unroll
@@ -235,7 +235,7 @@ __device__ __forceinline__ void tn_f32_split_tile(const F32SplitArgs& a, const i
             }
         }
     }
-    acc[MI - 1][NI - 1] += pend * (MODE == 0 && !(n_stages & 1) ? -1.0f : 1.0f);
+    acc[MI - 1][NI - 1] += pend * (MODE == 0 && !(n_stages & 1) ? -kSplitUnscale : kSplitUnscale);
     if constexpr (TWO) {
 #pragma unroll
         for (int i = 0; i < MI; ++i)

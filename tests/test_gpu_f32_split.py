@@ -81,6 +81,56 @@ def test_small_gradients_keep_their_bits(scale):
         assert float(((s.double() - ref) / ref).abs().max()) < REL
 
 
+@pytest.mark.parametrize("a_scale,g_scale", [(1e10, 1e-36), (1e10, 1e-37), (1e12, 1e-38), (1e20, 1e-40), (1e30, 1e-41), (1e30, 1e-43)])
+@pytest.mark.parametrize("small_a", [False, True])
+@pytest.mark.parametrize("B,T,d", [(4, 256, 128), (65536, 1, 256)])
+def test_small_operands_with_large_partners(B, T, d, small_a, a_scale, g_scale):
+    """Operands whose low parts fall below the smallest bf16, subnormal ones among them, in sums that are not small."""
+    A, G, clip = _data(B, T, d, d, 6)
+    A, G = (A * g_scale, G * a_scale) if small_a else (A * a_scale, G * g_scale)
+    clip.copy_(torch.exp2(torch.randint(-1, 2, (B,), device="cuda").float()))     # subnormal a * c: rounded by no one
+    if small_a:
+        clip.clamp_(min=1.0)
+    assert _rel(dp.clipped_grad(A, G, clip), _sum64(A, G, clip)) < REL
+    if T > 1 and a_scale >= 1e20:                             # (squares of the sums that float32 holds)
+        s, ref = dp.layer_sqnorm(A, G, path="direct"), _norm64(A, G)
+        assert float(((s.double() - ref) / ref).abs().max()) < REL
+
+
+@pytest.mark.parametrize("g_scale", [1e-10, 1e-14, 1e-17])
+@pytest.mark.parametrize("path", ["gram", "direct"])
+def test_norms_of_small_gradients(path, g_scale):
+    A, G, _ = _data(4, 256, 128, 128, 7, g_scale)
+    s, ref = dp.layer_sqnorm(A, G, path=path), _norm64(A, G)
+    # (below 1e-38 / 2^-24 a norm is a subnormal or near it: 1e-17 gives 1e-30)
+    assert float(((s.double() - ref) / ref).abs().max()) < REL
+
+
+@pytest.mark.parametrize("path,T,d_in,d_out", [("gram", 512, 768, 768), ("direct", 1024, 576, 128)])
+def test_small_rows_take_no_longer(path, T, d_in, d_out):
+    """A position whose gradient is almost zero (a prediction that is almost perfect), a column of gradients of almost
+    zero (a class that never occurs): ordinary data, in the ordinary time."""
+    A, G, _ = _data(32, T, d_in, d_out, 8, 1e-3)
+    small = G.clone()
+    small[:, 5::64] *= 1e-16
+    small[:, :, 7] *= 1e-33
+
+    def ms(g):
+        best = 1e9
+        for _ in range(5):
+            e = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+            e[0].record()
+            s = dp.layer_sqnorm(A, g, path=path)
+            e[1].record()
+            e[1].synchronize()
+            best = min(best, e[0].elapsed_time(e[1]))
+        return best, s
+    (usual, _), (time, s) = ms(G), ms(small)
+    ref = _norm64(A, small)
+    assert float(((s.double() - ref) / ref).abs().max()) < REL
+    assert time < 1.5 * usual, (time, usual)
+
+
 @pytest.mark.parametrize("value", [float("inf"), float("-inf"), float("nan"), 3.4e38])
 @pytest.mark.parametrize("d", [128, 256])
 def test_values_without_three_parts(value, d):
