@@ -61,14 +61,20 @@ __device__ __forceinline__ void tn_f32_exact(const F32SplitArgs& a, int k_begin,
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
     for (int k = k_begin; k < k_end; k += 2) {
-        const int row = min(k + lhalf, k_end - 1);
-        float c = k + lhalf < k_end ? 1.0f : 0.0f;
-        if (MODE == 0 && c != 0.f) c = a.clip[row / a.T];
+        const bool in = k + lhalf < k_end;                   // an odd last row: the other half of the lanes gives zeros
+        const int row = in ? k + lhalf : k_end - 1;
+        const float c = MODE == 0 ? a.clip[row / a.T] : 1.0f;
         float fa[GEO::MI], fg[GEO::NI];
 #pragma unroll
-        for (int i = 0; i < GEO::MI; ++i) fa[i] = a.A[(size_t)row * a.M + min(mw + i * 32 + lrow, a.M - 1)] * c;
+        for (int i = 0; i < GEO::MI; ++i) {
+            const float x = a.A[(size_t)row * a.M + min(mw + i * 32 + lrow, a.M - 1)] * c;
+            fa[i] = in ? x : 0.f;
+        }
 #pragma unroll
-        for (int j = 0; j < GEO::NI; ++j) fg[j] = a.G[(size_t)row * a.N + min(nw + j * 32 + lrow, a.N - 1)];
+        for (int j = 0; j < GEO::NI; ++j) {
+            const float x = a.G[(size_t)row * a.N + min(nw + j * 32 + lrow, a.N - 1)];
+            fg[j] = in ? x : 0.f;
+        }
 #pragma unroll
         for (int i = 0; i < GEO::MI; ++i)
 #pragma unroll

@@ -131,6 +131,27 @@ def test_small_rows_take_no_longer(path, T, d_in, d_out):
     assert time < 1.5 * usual, (time, usual)
 
 
+@pytest.mark.parametrize("value", [float("inf"), float("-inf")])
+@pytest.mark.parametrize("in_g", [False, True])
+@pytest.mark.parametrize("B,T,d_in,d_out", [(3, 257, 128, 128), (65, 131, 577, 61)])
+def test_infinity_in_the_last_of_an_odd_number_of_rows(B, T, d_in, d_out, in_g, value):
+    """The sums of its column are infinite, not NaN: the clip factor of an infinite norm is 0."""
+    A, G, clip = _data(B, T, d_in, d_out, 9)
+    clip.fill_(0.5)
+    A[A == 0] = 1.0
+    G[G == 0] = 1.0
+    (G if in_g else A)[-1, T - 1, 5] = value
+    s = dp.layer_sqnorm(A, G, path="direct")
+    assert torch.isfinite(s[:-1]).all() and torch.isposinf(s[-1])
+    got = dp.clipped_grad(A, G, clip)
+    line = got[:, 5] if in_g else got[5]
+    other = (A if in_g else G)[-1, T - 1]
+    assert torch.equal(line, torch.sign(other) * value)
+    rest = got.clone()
+    (rest[:, 5] if in_g else rest[5]).zero_()
+    assert torch.isfinite(rest).all()
+
+
 @pytest.mark.parametrize("value", [float("inf"), float("-inf"), float("nan"), 3.4e38])
 @pytest.mark.parametrize("d", [128, 256])
 def test_values_without_three_parts(value, d):
