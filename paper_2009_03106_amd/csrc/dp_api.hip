@@ -204,9 +204,9 @@ int clipped_join_class(int64_t B, int64_t T, int64_t d_in, int64_t d_out, dp_dty
     if (B * T < (int64_t(1) << 31) && dma_joint_ragged_ok((int)T, (int)d_in, (int)d_out)) return 4;
     return 0;
 }
-size_t joint_ws_bytes(const JointShape* sh, int n, int64_t B, dp_dtype dtype, int geo) {
-    if (geo >= 5) return joint_f32_workspace_floats(sh, n, (int)B, geo == 6) * sizeof(float);
-    return (is8(dtype) ? joint8_workspace_floats(sh, n, (int)B) : joint_workspace_floats(sh, n, (int)B, geo)) * sizeof(float);
+size_t joint_ws_bytes(const JointShape* sh, int n, int64_t B, dp_dtype dtype, int geo, size_t max_floats = kAnySlices) {
+    if (geo >= 5) return joint_f32_workspace_floats(sh, n, (int)B, geo == 6, max_floats) * sizeof(float);
+    return (is8(dtype) ? joint8_workspace_floats(sh, n, (int)B, max_floats) : joint_workspace_floats(sh, n, (int)B, geo, max_floats)) * sizeof(float);
 }
 
 constexpr size_t kConvZeroBytes = 256;                // head of the conv workspace: a line of zeros for the padding
@@ -1242,7 +1242,10 @@ dp_status dp_layers_clipped_grad_noise(const dp_layer_desc* layers, int64_t n_la
     // one launch whose items fill the chip a whole number of times, the K slices folded (and the noise added) inside
     // it.  With noise the kernel adds it four elements at a time, so the layer's offset and size must be multiples of 4.
     // A second class of joint launches (128 x 128 tiles) takes the aligned 16-bit layers of a few hundred columns.
-    // (layers whose gradients overlap, as tied weights accumulated into one array do, run one after the other)
+    // (layers whose gradients overlap, as tied weights accumulated into one array do, run one after the other: like those
+    // whose noise the fold cannot add, they are left out of the group that the workspace query planned for them.  The
+    // layers that remain may then take more slices than the query gave them, so where that is more than the query's
+    // answer, they are held to it.  Their longest slices fit: the query's group had as many of each layer, or more.)
     auto shared_grad = [&](int64_t l) {
         const float* p = layers[l].grad;
         const int64_t n = layers[l].d_in * layers[l].d_out;
@@ -1252,20 +1255,15 @@ dp_status dp_layers_clipped_grad_noise(const dp_layer_desc* layers, int64_t n_la
     };
     std::vector<std::vector<int64_t>> joint_groups;
     std::vector<int> joint_geo;
+    std::vector<size_t> joint_floats;                        // the most that a group's slices may take
     for (int geo : {1, 3, 4, 5, 6}) {
         std::vector<int64_t> cur;
-        const size_t first_group = joint_groups.size();
-        for (int64_t l = 0; l < n_layers; ++l) {
-            const dp_layer_desc& y = layers[l];
-            if (clipped_join_class(B, y.T, y.d_in, y.d_out, dtype) != geo || shared_grad(l)) continue;
-            if (stddev > 0.0f && !splitk_noise_ok(y.d_in * y.d_out, y.noise_offset)) continue;
-            cur.push_back(l);
-            if ((int)cur.size() == kJointLayers) { joint_groups.push_back(cur); joint_geo.push_back(geo); cur.clear(); }
-        }
-        if (cur.size() >= 2) { joint_groups.push_back(cur); joint_geo.push_back(geo); }
-        // the largest layers first: the tiles that are folded when the launch ends are then the smallest layer's
-        for (size_t gi = first_group; gi < joint_groups.size(); ++gi) {
-            auto& g = joint_groups[gi];
+        int in_query = 0;                                    // layers of the query's group so far
+        auto end_group = [&]() {
+            if (cur.size() < 2) { cur.clear(); in_query = 0; return; }
+            joint_groups.push_back(cur); joint_geo.push_back(geo);
+            auto& g = joint_groups.back();
+            // the largest layers first: the tiles that are folded when the launch ends are then the smallest layer's
             std::stable_sort(g.begin(), g.end(), [&](int64_t a, int64_t b) {
                 return layers[a].d_in * layers[a].d_out * layers[a].T > layers[b].d_in * layers[b].d_out * layers[b].T; });
             JointShape sh[kJointLayers];
@@ -1273,8 +1271,23 @@ dp_status dp_layers_clipped_grad_noise(const dp_layer_desc* layers, int64_t n_la
                 const dp_layer_desc& y = layers[g[k]];
                 sh[k] = JointShape{(int)y.T, (int)y.d_in, (int)y.d_out};
             }
-            need = std::max(need, joint_ws_bytes(sh, (int)g.size(), B, dtype, geo));
+            size_t most = kAnySlices, own = joint_ws_bytes(sh, (int)g.size(), B, dtype, geo);
+            if ((int)g.size() < in_query) {
+                const size_t query = dp_layers_clipped_workspace_bytes(layers, n_layers, B, dtype);
+                if (own > query) { most = query / sizeof(float); own = joint_ws_bytes(sh, (int)g.size(), B, dtype, geo, most); }
+            }
+            joint_floats.push_back(most);
+            need = std::max(need, own);
+            cur.clear(); in_query = 0;
+        };
+        for (int64_t l = 0; l < n_layers; ++l) {
+            const dp_layer_desc& y = layers[l];
+            if (clipped_join_class(B, y.T, y.d_in, y.d_out, dtype) != geo) continue;
+            ++in_query;
+            if (!shared_grad(l) && !(stddev > 0.0f && !splitk_noise_ok(y.d_in * y.d_out, y.noise_offset))) cur.push_back(l);
+            if (in_query == kJointLayers) end_group();
         }
+        end_group();
     }
     if (need > 0 && (!workspace || workspace_bytes < need || !aligned16(workspace))) return DP_ERR_WORKSPACE;
     // float32 layers with a short contraction (a model of small dense layers) share launches, 8 layers each
@@ -1292,12 +1305,12 @@ dp_status dp_layers_clipped_grad_noise(const dp_layer_desc* layers, int64_t n_la
         }
         const hipError_t ej = joint_geo[gi] >= 5
             ? launch_clipped_f32_split_joint(sh, op, (int)g.size(), (int)B, accumulate != 0, stddev, seed, static_cast<float*>(workspace),
-                                           static_cast<hipStream_t>(hip_stream), joint_geo[gi] == 6)
+                                           static_cast<hipStream_t>(hip_stream), joint_geo[gi] == 6, joint_floats[gi])
             : is8(dtype)
             ? launch_clipped_f8_dma_joint(sh, op, (int)g.size(), (int)B, accumulate != 0, stddev, seed, static_cast<float*>(workspace),
-                                          static_cast<hipStream_t>(hip_stream), fmt_of(dtype))
+                                          static_cast<hipStream_t>(hip_stream), fmt_of(dtype), joint_floats[gi])
             : launch_clipped_bf16_dma_joint(sh, op, (int)g.size(), (int)B, accumulate != 0, stddev, seed, static_cast<float*>(workspace),
-                                            static_cast<hipStream_t>(hip_stream), dtype == DP_F16, joint_geo[gi]);
+                                            static_cast<hipStream_t>(hip_stream), dtype == DP_F16, joint_geo[gi], joint_floats[gi]);
         if (ej != hipSuccess) return DP_ERR_HIP;
     }
     if (dtype == DP_F32 && B > 0 && !(stddev > 0.0f)) {

@@ -154,9 +154,11 @@ struct JointOperands { const uint16_t* A; const uint16_t* G; const float* clip; 
 // to minimise   rounds of 256 workgroups  x  (stages of the longest slice + what an item costs besides its stages):
 // slices long enough that their start-up, their store and their fold stay small, and a number of items that fills
 // the chip's 256 compute units a whole number of times.  dk: rows per stage; tile: the square output tile; slots:
-// workgroups resident at a time (256 x workgroups per compute unit).
+// workgroups resident at a time (256 x workgroups per compute unit); max_floats: the most that the slices may take (the
+// longest slices, S = 1, are taken even above it).
 struct JointPlan { int n_layers; int tiles_m[kJointLayers], tiles_n[kJointLayers], splits[kJointLayers], sps[kJointLayers]; int64_t items; };
-inline JointPlan plan_joint(const JointShape* sh, int n_layers, int B, int dk, int tile, int slots = 256) {
+constexpr size_t kAnySlices = ~size_t(0);
+inline JointPlan plan_joint(const JointShape* sh, int n_layers, int B, int dk, int tile, int slots = 256, size_t max_floats = kAnySlices) {
     constexpr int64_t kItemOverhead = 16;            // prologue + slice store + the slice's share of the fold, in stage times
     JointPlan best{};
     int64_t best_cost = -1, stages_max = 1;
@@ -167,6 +169,7 @@ inline JointPlan plan_joint(const JointShape* sh, int n_layers, int B, int dk, i
         JointPlan p{};
         p.n_layers = n_layers;
         int64_t longest = 0;
+        size_t floats = 0;
         for (int l = 0; l < n_layers; ++l) {
             const int64_t spe = ceil_div(sh[l].T, dk), stages = (int64_t)B * spe;
             const int64_t want = len < 63 * spe ? len : 63 * spe;   // a slice touches at most 64 examples (one clip factor per lane)
@@ -177,7 +180,9 @@ inline JointPlan plan_joint(const JointShape* sh, int n_layers, int B, int dk, i
             p.splits[l] = (int)splits; p.sps[l] = (int)sps;
             p.items += (int64_t)p.tiles_m[l] * p.tiles_n[l] * splits;
             longest = longest > sps ? longest : sps;
+            floats += (size_t)splits * (size_t)splitk_slice_elems((int64_t)sh[l].M * sh[l].N);
         }
+        if (floats > max_floats && S > 1) break;                    // (more slices take more)
         const int64_t cost = ((p.items + slots - 1) / slots) * (longest + kItemOverhead);
         if (best_cost < 0 || cost < best_cost) { best_cost = cost; best = p; }
     }
@@ -186,21 +191,21 @@ inline JointPlan plan_joint(const JointShape* sh, int n_layers, int B, int dk, i
 bool dma_joint_ok(int T, int M, int N);
 bool dma_joint_mid_ok(int T, int M, int N);      // the second class: 128 x 128 tiles, geo = 3 below
 bool dma_joint_ragged_ok(int T, int M, int N);   // the same tiles, T not a multiple of the stage: geo = 4
-size_t joint_workspace_floats(const JointShape* sh, int n_layers, int B, int geo = 1);
+size_t joint_workspace_floats(const JointShape* sh, int n_layers, int B, int geo, size_t max_floats);
 // the same for float32 inputs (dp_tn_f32_split.hip; 128 x 128 tiles, any T); A, G of JointOperands are float pointers
-size_t joint_f32_workspace_floats(const JointShape* sh, int n_layers, int B, bool big);
+size_t joint_f32_workspace_floats(const JointShape* sh, int n_layers, int B, bool big, size_t max_floats);
 hipError_t launch_direct_f32_split_joint(const JointShape* sh, const JointOperands* op, float* const* partial, int n_layers,
                                        int B, hipStream_t st);
 hipError_t launch_clipped_f32_split_joint(const JointShape* sh, const JointOperands* op, int n_layers, int B, bool accumulate,
-                                        float stddev, uint64_t seed, float* ws, hipStream_t st, bool big);
+                                        float stddev, uint64_t seed, float* ws, hipStream_t st, bool big, size_t max_floats);
 // the same for 8-bit inputs (dp_tn_f8_dma.hip; 256 x 256 tiles, T a multiple of 64); A, G of JointOperands are byte pointers
 bool dma8_joint_ok(int T, int M, int N);
-size_t joint8_workspace_floats(const JointShape* sh, int n_layers, int B);
+size_t joint8_workspace_floats(const JointShape* sh, int n_layers, int B, size_t max_floats);
 hipError_t launch_clipped_f8_dma_joint(const JointShape* sh, const JointOperands* op, int n_layers, int B, bool accumulate,
-                                       float stddev, uint64_t seed, float* ws, hipStream_t st, int fmt);
+                                       float stddev, uint64_t seed, float* ws, hipStream_t st, int fmt, size_t max_floats);
 // noise: stddev == 0 for none, else every layer's d_in * d_out and noise_offset are multiples of 4
 hipError_t launch_clipped_bf16_dma_joint(const JointShape* sh, const JointOperands* op, int n_layers, int B, bool accumulate,
-                                         float stddev, uint64_t seed, float* ws, hipStream_t st, bool f16, int geo = 1);
+                                         float stddev, uint64_t seed, float* ws, hipStream_t st, bool f16, int geo, size_t max_floats);
 // several layers' direct norms in one launch (128 x 128 tiles; T >= 64, widths multiples of 8); partial[l]: the layer's
 // [B][direct_joint_tiles(M, N)] sums of squares per (example, tile), to be added by the caller
 bool dma_direct_joint_ok(int B, int T, int M, int N);

@@ -663,19 +663,19 @@ inline int joint_group_geo(const JointShape* sh, int n_layers, int B, int geo) {
 }
 
 // floats of workspace: every layer's slices, one layer after the other
-size_t joint_workspace_floats(const JointShape* sh, int n_layers, int B, int geo) {
+size_t joint_workspace_floats(const JointShape* sh, int n_layers, int B, int geo, size_t max_floats) {
     geo = joint_group_geo(sh, n_layers, B, geo);
-    const JointPlan p = plan_joint(sh, n_layers, B, DK, joint_tile(geo), joint_slots(geo));
+    const JointPlan p = plan_joint(sh, n_layers, B, DK, joint_tile(geo), joint_slots(geo), max_floats);
     size_t slices = 0;
     for (int l = 0; l < n_layers; ++l) slices += (size_t)p.splits[l] * (size_t)splitk_slice_elems((int64_t)sh[l].M * sh[l].N);
     return slices;
 }
 
 hipError_t launch_clipped_bf16_dma_joint(const JointShape* sh, const JointOperands* op, int n_layers, int B, bool accumulate,
-                                         float stddev, uint64_t seed, float* ws, hipStream_t st, bool f16, int geo) {
+                                         float stddev, uint64_t seed, float* ws, hipStream_t st, bool f16, int geo, size_t max_floats) {
     if (n_layers < 1 || n_layers > kJointMax || (geo != 1 && geo != 3 && geo != 4)) return hipErrorInvalidValue;
     geo = joint_group_geo(sh, n_layers, B, geo);
-    const JointPlan p = plan_joint(sh, n_layers, B, DK, joint_tile(geo), joint_slots(geo));
+    const JointPlan p = plan_joint(sh, n_layers, B, DK, joint_tile(geo), joint_slots(geo), max_floats);
     if (p.items >= (int64_t(1) << 28)) return hipErrorInvalidValue;
     JointArgs j;
     float* slices = ws;

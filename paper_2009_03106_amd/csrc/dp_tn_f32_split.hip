@@ -352,7 +352,7 @@ __global__ __launch_bounds__(BIG ? GeoBig::THREADS : GeoMid::THREADS, 2) void k_
 // minimise  rounds of 512 (256 x 256 tiles: 256) workgroups x (stages of the longest slice + what an item costs besides its stages) + the fold's
 // reading of the slices (4 MB in about a stage time).
 struct F32JointPlan { int splits[kJointLayers], kchunk[kJointLayers], geo[kJointLayers], tiles_m[kJointLayers], tiles_n[kJointLayers]; int64_t items; };
-F32JointPlan plan_joint_f32(const JointShape* sh, int n_layers, int B, bool big) {
+F32JointPlan plan_joint_f32(const JointShape* sh, int n_layers, int B, bool big, size_t max_floats) {
     constexpr int64_t kItemOverhead = 16;
     const int64_t kSlots = big ? 256 : 512;
     F32JointPlan best{};
@@ -363,6 +363,7 @@ F32JointPlan plan_joint_f32(const JointShape* sh, int n_layers, int B, bool big)
         if (len < 4 && S > 1) break;
         F32JointPlan p{};
         int64_t longest = 0, fold = 0;                       // fold: entries of all slices
+        size_t floats = 0;
         for (int l = 0; l < n_layers; ++l) {
             const int64_t stages = ceil_div((int64_t)B * sh[l].T, DKF);
             p.geo[l] = big ? F32_BIG : f32_split_geo((int64_t)B * sh[l].T, sh[l].M, sh[l].N, false);
@@ -375,7 +376,9 @@ F32JointPlan plan_joint_f32(const JointShape* sh, int n_layers, int B, bool big)
             p.items += (int64_t)p.tiles_m[l] * p.tiles_n[l] * splits;
             longest = std::max(longest, own == len ? sps : sps * 2 / 3);
             fold += (int64_t)sh[l].M * sh[l].N * splits;
+            floats += (size_t)splits * (size_t)splitk_slice_elems((int64_t)sh[l].M * sh[l].N);
         }
+        if (floats > max_floats && S > 1) break;             // (as plan_joint)
         const int64_t cost = ((p.items + kSlots - 1) / kSlots) * (longest + kItemOverhead) + fold / (1 << 20);
         if (best_cost < 0 || cost < best_cost) { best_cost = cost; best = p; }
     }
@@ -384,8 +387,8 @@ F32JointPlan plan_joint_f32(const JointShape* sh, int n_layers, int B, bool big)
 
 }  // namespace
 
-size_t joint_f32_workspace_floats(const JointShape* sh, int n_layers, int B, bool big) {
-    const F32JointPlan p = plan_joint_f32(sh, n_layers, B, big);
+size_t joint_f32_workspace_floats(const JointShape* sh, int n_layers, int B, bool big, size_t max_floats) {
+    const F32JointPlan p = plan_joint_f32(sh, n_layers, B, big, max_floats);
     size_t slices = 0;
     for (int l = 0; l < n_layers; ++l) slices += (size_t)p.splits[l] * (size_t)splitk_slice_elems((int64_t)sh[l].M * sh[l].N);
     return slices;
@@ -394,9 +397,9 @@ size_t joint_f32_workspace_floats(const JointShape* sh, int n_layers, int B, boo
 // noise: stddev == 0 for none, else every layer's d_in * d_out and noise_offset are multiples of 4.  A, G of the
 // operands are float pointers here.
 hipError_t launch_clipped_f32_split_joint(const JointShape* sh, const JointOperands* op, int n_layers, int B, bool accumulate,
-                                        float stddev, uint64_t seed, float* ws, hipStream_t st, bool big) {
+                                        float stddev, uint64_t seed, float* ws, hipStream_t st, bool big, size_t max_floats) {
     if (n_layers < 1 || n_layers > kJointLayers) return hipErrorInvalidValue;
-    const F32JointPlan p = plan_joint_f32(sh, n_layers, B, big);
+    const F32JointPlan p = plan_joint_f32(sh, n_layers, B, big, max_floats);
     if (p.items >= (int64_t(1) << 28)) return hipErrorInvalidValue;
     F32JointArgs j;
     FoldLayers f;

@@ -494,17 +494,17 @@ hipError_t launch_clipped_f8_dma(const TnPlan& p, const void* A, const void* G, 
 // ---- joint launch of several layers' clipped sums
 bool dma8_joint_ok(int T, int M, int N) { return T > 0 && (T % DK8) == 0 && dma8_geometry(T, M, N) == 1; }
 
-size_t joint8_workspace_floats(const JointShape* sh, int n_layers, int B) {
-    const JointPlan p = plan_joint(sh, n_layers, B, DK8, Geo8L::TM);
+size_t joint8_workspace_floats(const JointShape* sh, int n_layers, int B, size_t max_floats) {
+    const JointPlan p = plan_joint(sh, n_layers, B, DK8, Geo8L::TM, 256, max_floats);
     size_t slices = 0;
     for (int l = 0; l < n_layers; ++l) slices += (size_t)p.splits[l] * (size_t)splitk_slice_elems((int64_t)sh[l].M * sh[l].N);
     return slices;
 }
 
 hipError_t launch_clipped_f8_dma_joint(const JointShape* sh, const JointOperands* op, int n_layers, int B, bool accumulate,
-                                       float stddev, uint64_t seed, float* ws, hipStream_t st, int fmt) {
+                                       float stddev, uint64_t seed, float* ws, hipStream_t st, int fmt, size_t max_floats) {
     if (n_layers < 1 || n_layers > kJointLayers) return hipErrorInvalidValue;
-    const JointPlan p = plan_joint(sh, n_layers, B, DK8, Geo8L::TM);
+    const JointPlan p = plan_joint(sh, n_layers, B, DK8, Geo8L::TM, 256, max_floats);
     if (p.items >= (int64_t(1) << 28)) return hipErrorInvalidValue;
     Joint8Args j;
     float* slices = ws;

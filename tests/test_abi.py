@@ -3,9 +3,11 @@ entry points (path choice, workspace sizes, status strings) behave as documented
 No kernel is launched here."""
 import ctypes
 import os
+import random
 import re
 
 import pytest
+import torch
 
 from oracle import dp_oracle as orc
 from paper_2009_03106_amd import dpclip, workloads as wl
@@ -208,6 +210,32 @@ def test_layer_descriptor_layout_and_argument_checks(lib):
     assert cg(descs(grad_b=fake(12), bias_rows=fake(14), bias_noise_offset=2 ** 64 - 8), 2, B, fake(13), dt, 0, 1.0, 0, None, 0, None) == dpclip.DP_ERR_INVALID_ARG
     assert cg(descs(noise_offset=2 ** 64 - 8), 2, B, fake(13), dt, 0, 1.0, 0, None, 0, None) == dpclip.DP_ERR_INVALID_ARG
     assert cg(descs(grad=[fake(5), None]), 2, B, fake(13), dt, 0, 0.0, 0, None, 0, None) == dpclip.DP_ERR_INVALID_ARG
+
+
+@pytest.mark.skipif(torch.cuda.is_available(), reason="goes on to launch kernels on made-up pointers")
+@pytest.mark.parametrize("dtype", [dpclip.DP_F32, dpclip.DP_BF16, dpclip.DP_F8_E4M3])
+@pytest.mark.parametrize("left_out", ["tied", "offset"])
+def test_queried_workspace_is_enough_for_layers_that_cannot_share_a_launch(lib, dtype, left_out):
+    """Host logic only: gradients that overlap, or whose noise starts at an odd place of the stream, leave their layers out of
+    the shared launches; the layers that remain must do with the scratch that the query gave for all of them.  Without a
+    GPU the call ends at its first launch, behind that check."""
+    rng = random.Random(7)
+    fake = lambda k: 0x10000000 + 0x10000000 * k
+    for _ in range(300):
+        n = rng.choice((3, 4, 5, 6, 8, 19))
+        B = rng.choice((8, 32, 64, 256, 1000))
+        T = rng.choice((1, 16, 64, 128, 192, 512))
+        shapes = [(T if rng.random() < 0.7 else 64 * rng.randint(1, 8), 64 * rng.randint(1, 16), 64 * rng.randint(1, 16)) for _ in range(n)]
+        shapes[1] = shapes[0]
+        arr = (dpclip.LayerDesc * n)()
+        for l, (t, a, b) in enumerate(shapes):
+            grad = 0 if left_out == "tied" and l == 1 else l
+            off = 2 * l + 1 if left_out == "offset" and l < n - 2 else 4 * l      # (offsets are only looked at modulo 4)
+            arr[l] = dpclip.LayerDesc(A=fake(1), G=fake(2), T=t, d_in=a, d_out=b, grad=fake(3 + grad), noise_offset=off)
+        need = dpclip.layers_clipped_workspace_bytes(arr, B, dtype)
+        for std in (0.0, 1.0):
+            st = lib.dp_layers_clipped_grad_noise(arr, n, B, fake(0), dtype, 0, std, 0, fake(90), need, None)
+            assert st != dpclip.DP_ERR_WORKSPACE, (dtype, B, shapes, std)
 
 
 def test_noise_layout_gives_every_gradient_its_own_stretch():

@@ -77,3 +77,36 @@ def test_tied_weights_accumulate_into_one_array(dtype):
     assert float((tied.double() - ref).norm() / ref.norm()) < tol
     assert float((grads[2].double() - sums[2]).norm() / sums[2].norm()) < tol
     assert float((bias.double() - ref_b).norm() / ref_b.norm()) < 1e-5
+
+
+@pytest.mark.parametrize("dtype,shapes,B", [
+    (torch.float32, [(128, 256, 128)] * 2 + [(128, 512, 768), (128, 768, 512)], 64),
+    (torch.bfloat16, [(128, 256, 256)] * 2 + [(128, 256, 512), (128, 512, 256)], 64),
+    (torch.bfloat16, [(64, 576, 64)] * 2 + [(64, 576, 128)] * 3, 32)])
+@pytest.mark.parametrize("left_out", ["tied", "offset"])
+def test_layers_beside_some_that_cannot_share(dtype, shapes, B, left_out):
+    """The remaining layers of a group do with the scratch that the query gave for the whole one."""
+    layers = _layers(B, shapes, dtype, 3)
+    grads = [torch.zeros((a, b), device="cuda") for _, a, b in shapes]
+    offs, at = [], 0
+    for l, (_, a, b) in enumerate(shapes):
+        offs.append(at + (1 if left_out == "offset" and l < 2 else 0))
+        at += a * b + 4
+    std = 1.0 if left_out == "offset" else 0.0
+    if left_out == "tied":
+        grads[1] = grads[0]
+    clip = torch.rand(B, device="cuda") + 0.25
+    descs = dp.layer_descs(layers, grads, noise_offsets=offs)
+    dp.layers_clipped_grad(layers, clip, grads, accumulate=True, descs=descs, noise_std=std, seed=5)
+    w = clip.double().view(-1, 1, 1)
+    sums = [(A.double() * w).reshape(-1, A.shape[-1]).T @ G.double().reshape(-1, G.shape[-1]) for A, G in layers]
+    if left_out == "tied":
+        sums[0] = sums[1] = sums[0] + sums[1]
+    # bfloat16 rows may be rounded once more by the factor: 2^-9 each
+    tol = 1e-6 if dtype == torch.float32 else 4e-3
+    for g, r, off in zip(grads, sums, offs):
+        if std:
+            z = torch.zeros_like(g)
+            dp.add_noise(z, std, 5, off)
+            r = r + z
+        assert float((g.double() - r).norm() / r.norm()) < tol
