@@ -59,7 +59,8 @@ struct FoldLayers {
     const float* ws[kJointLayers]; float* grad[kJointLayers]; int64_t n[kJointLayers], slice[kJointLayers];
     uint64_t noise_offset[kJointLayers]; int splits[kJointLayers]; unsigned first_block[kJointLayers]; int n_layers;
 };
-hipError_t launch_splitk_reduce_layers(FoldLayers& f, bool accumulate, hipStream_t st, float stddev, uint64_t seed);
+// blocks: the slices of eight first, then those sums (float32 layers)
+hipError_t launch_splitk_reduce_layers(FoldLayers& f, bool accumulate, hipStream_t st, float stddev, uint64_t seed, bool blocks);
 hipError_t launch_fill_zero(float* p, int64_t n, hipStream_t st);
 // kZeroHeadFloats floats of zeros that live in the device image of the current GPU (nothing to fill, no launch), or
 // nullptr when they cannot be looked up now (first use on this GPU while `st` is being captured): the caller then

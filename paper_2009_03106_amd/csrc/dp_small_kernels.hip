@@ -516,10 +516,13 @@ hipError_t launch_splitk_reduce(const float* ws, int64_t n, int splits, bool acc
     return hipGetLastError();
 }
 
-// The same fold for the layers of a joint launch in ONE launch (z ascending for every entry, in blocks of eight):
+// The same fold for the layers of a joint launch in ONE launch (z ascending for every entry, as k_splitk_reduce):
 // a fold per layer is a launch of a few microseconds each, which for a dozen small layers is longer than their sums
 // took.  A workgroup takes 256 groups of 4 entries of one layer.
-template <bool NOISE>
+// BLOCKS (float32 layers, which can have hundreds of slices): the sums of eight slices, then the sum of those, fewer
+// roundings in a row (65536 rows: 1.8e-7 of the result without, 1.3e-7 with).  Each thread walks its slices by itself and
+// waits once per eight; the 16-bit layers have few slices and keep the plain order.
+template <bool NOISE, bool BLOCKS>
 __global__ __launch_bounds__(256) void k_splitk_reduce_layers(FoldLayers f, int accumulate, NoiseArgs nz) {
     int l = 0;
     while (l + 1 < f.n_layers && blockIdx.x >= f.first_block[l + 1]) ++l;
@@ -528,28 +531,36 @@ __global__ __launch_bounds__(256) void k_splitk_reduce_layers(FoldLayers f, int 
     const float* ws = f.ws[l];
     const int64_t slice = f.slice[l];
     const int splits = f.splits[l];
-    // blocks of eight slices, then the blocks: fewer roundings in a row where a layer has many slices
-    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int z0 = 0; z0 < splits; z0 += 8) {
-        const int end = min(z0 + 8, splits);
-        float4 b = reinterpret_cast<const float4*>(ws + (size_t)z0 * slice)[c];
-        int z = z0 + 1;
-        for (; z + 3 < end; z += 4) {
+    float4 acc;
+    if constexpr (BLOCKS) {
+        acc = make_float4(0.f, 0.f, 0.f, 0.f);
+        for (int z0 = 0; z0 < splits; z0 += 8) {
+            float4 v[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) v[k] = reinterpret_cast<const float4*>(ws + (size_t)min(z0 + k, splits - 1) * slice)[c];
+#pragma unroll
+            for (int k = 1; k < 8; ++k)
+                if (z0 + k < splits) { v[0].x += v[k].x; v[0].y += v[k].y; v[0].z += v[k].z; v[0].w += v[k].w; }
+            if (z0 == 0) acc = v[0];
+            else { acc.x += v[0].x; acc.y += v[0].y; acc.z += v[0].z; acc.w += v[0].w; }
+        }
+    } else {
+        acc = reinterpret_cast<const float4*>(ws)[c];
+        int z = 1;
+        for (; z + 3 < splits; z += 4) {
             const float4 v0 = reinterpret_cast<const float4*>(ws + (size_t)z * slice)[c];
             const float4 v1 = reinterpret_cast<const float4*>(ws + (size_t)(z + 1) * slice)[c];
             const float4 v2 = reinterpret_cast<const float4*>(ws + (size_t)(z + 2) * slice)[c];
             const float4 v3 = reinterpret_cast<const float4*>(ws + (size_t)(z + 3) * slice)[c];
-            b.x += v0.x; b.y += v0.y; b.z += v0.z; b.w += v0.w;
-            b.x += v1.x; b.y += v1.y; b.z += v1.z; b.w += v1.w;
-            b.x += v2.x; b.y += v2.y; b.z += v2.z; b.w += v2.w;
-            b.x += v3.x; b.y += v3.y; b.z += v3.z; b.w += v3.w;
+            acc.x += v0.x; acc.y += v0.y; acc.z += v0.z; acc.w += v0.w;
+            acc.x += v1.x; acc.y += v1.y; acc.z += v1.z; acc.w += v1.w;
+            acc.x += v2.x; acc.y += v2.y; acc.z += v2.z; acc.w += v2.w;
+            acc.x += v3.x; acc.y += v3.y; acc.z += v3.z; acc.w += v3.w;
         }
-        for (; z < end; ++z) {
+        for (; z < splits; ++z) {
             const float4 v = reinterpret_cast<const float4*>(ws + (size_t)z * slice)[c];
-            b.x += v.x; b.y += v.y; b.z += v.z; b.w += v.w;
+            acc.x += v.x; acc.y += v.y; acc.z += v.z; acc.w += v.w;
         }
-        if (z0 == 0) acc = b;
-        else { acc.x += b.x; acc.y += b.y; acc.z += b.z; acc.w += b.w; }
     }
     float4* o = reinterpret_cast<float4*>(f.grad[l]) + c;
     if (accumulate) { const float4 g = *o; acc.x += g.x; acc.y += g.y; acc.z += g.z; acc.w += g.w; }
@@ -558,20 +569,22 @@ __global__ __launch_bounds__(256) void k_splitk_reduce_layers(FoldLayers f, int 
 }
 
 // every layer: n a multiple of 4, slices spaced splitk_slice_elems(n) apart; with noise, noise_offset a multiple of 4
-hipError_t launch_splitk_reduce_layers(FoldLayers& f, bool accumulate, hipStream_t st, float stddev, uint64_t seed) {
+hipError_t launch_splitk_reduce_layers(FoldLayers& f, bool accumulate, hipStream_t st, float stddev, uint64_t seed, bool blocks) {
     if (f.n_layers < 1 || f.n_layers > kJointLayers) return hipErrorInvalidValue;
-    int64_t blocks = 0;
+    int64_t groups = 0;
     for (int l = 0; l < f.n_layers; ++l) {
         if ((f.n[l] & 3) != 0 || (stddev != 0.0f && (f.noise_offset[l] & 3) != 0)) return hipErrorInvalidValue;
-        f.first_block[l] = (unsigned)blocks;
+        f.first_block[l] = (unsigned)groups;
         f.slice[l] = splitk_slice_elems(f.n[l]);
-        blocks += ((f.n[l] >> 2) + 255) / 256;
-        if (blocks >= (int64_t(1) << 31)) return hipErrorInvalidValue;
+        groups += ((f.n[l] >> 2) + 255) / 256;
+        if (groups >= (int64_t(1) << 31)) return hipErrorInvalidValue;
     }
-    for (int l = f.n_layers; l < kJointLayers; ++l) { f.first_block[l] = (unsigned)blocks; f.slice[l] = 0; }
+    for (int l = f.n_layers; l < kJointLayers; ++l) { f.first_block[l] = (unsigned)groups; f.slice[l] = 0; }
     const NoiseArgs nz{stddev, (uint32_t)seed, (uint32_t)(seed >> 32), 0};
-    if (stddev != 0.0f) k_splitk_reduce_layers<true><<<(unsigned)blocks, 256, 0, st>>>(f, accumulate ? 1 : 0, nz);
-    else                k_splitk_reduce_layers<false><<<(unsigned)blocks, 256, 0, st>>>(f, accumulate ? 1 : 0, nz);
+    const unsigned grid = (unsigned)groups;
+    const int add = accumulate ? 1 : 0;
+    if (blocks) { if (stddev != 0.0f) k_splitk_reduce_layers<true, true><<<grid, 256, 0, st>>>(f, add, nz); else k_splitk_reduce_layers<false, true><<<grid, 256, 0, st>>>(f, add, nz); }
+    else        { if (stddev != 0.0f) k_splitk_reduce_layers<true, false><<<grid, 256, 0, st>>>(f, add, nz); else k_splitk_reduce_layers<false, false><<<grid, 256, 0, st>>>(f, add, nz); }
     return hipGetLastError();
 }
 

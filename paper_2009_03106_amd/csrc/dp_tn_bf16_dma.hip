@@ -722,7 +722,7 @@ hipError_t launch_clipped_bf16_dma_joint(const JointShape* sh, const JointOperan
     if (nf == 0) return hipSuccess;
     f.n_layers = nf;
     for (int l = nf; l < kJointLayers; ++l) { f.ws[l] = f.ws[0]; f.grad[l] = f.grad[0]; f.n[l] = 0; f.splits[l] = 0; f.noise_offset[l] = 0; }
-    return launch_splitk_reduce_layers(f, accumulate, st, stddev, seed);
+    return launch_splitk_reduce_layers(f, accumulate, st, stddev, seed, false);
 }
 
 // implicit unfolding: whole 16-byte pieces must stay inside one pixel's channels, image offsets must fit 32 bits

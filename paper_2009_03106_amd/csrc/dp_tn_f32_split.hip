@@ -432,7 +432,7 @@ hipError_t launch_clipped_f32_split_joint(const JointShape* sh, const JointOpera
     if (e != hipSuccess || nf == 0) return e;
     f.n_layers = nf;
     for (int l = nf; l < kJointLayers; ++l) { f.ws[l] = f.ws[0]; f.grad[l] = f.grad[0]; f.n[l] = 0; f.splits[l] = 0; f.noise_offset[l] = 0; }
-    return launch_splitk_reduce_layers(f, accumulate, st, stddev, seed);
+    return launch_splitk_reduce_layers(f, accumulate, st, stddev, seed, true);
 }
 
 // The geometry of a layer: the largest tiles of which at most a quarter is padding.  256 x 256 tiles (clipped sums

@@ -545,7 +545,7 @@ hipError_t launch_clipped_f8_dma_joint(const JointShape* sh, const JointOperands
     if (nf == 0) return hipSuccess;
     f.n_layers = nf;
     for (int l = nf; l < kJointLayers; ++l) { f.ws[l] = f.ws[0]; f.grad[l] = f.grad[0]; f.n[l] = 0; f.splits[l] = 0; f.noise_offset[l] = 0; }
-    return launch_splitk_reduce_layers(f, accumulate, st, stddev, seed);
+    return launch_splitk_reduce_layers(f, accumulate, st, stddev, seed, false);
 }
 
 TnPlan plan_direct_f8_dma(int B, int T, int M, int N) {
