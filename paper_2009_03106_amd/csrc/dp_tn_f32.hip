@@ -343,18 +343,20 @@ TnPlan plan_clipped_f32(int B, int T, int M, int N) {
         p.tiles_m = ceil_div(M, p.tile_m); p.tiles_n = ceil_div(N, p.tile_n);
         const int64_t tiles = (int64_t)p.tiles_m * p.tiles_n;
         // K slices: the (tile, slice) items run `slots` at a time; an item costs its stages plus about 16 stage times of
-        // start-up and store, and the fold reads all slices, 4 MB in about a stage time.  Take the slice count with the
+        // start-up and store, and the fold reads all slices, 4 MB in about a stage time, and walks them one after the
+        // other, 32 (k_splitk_reduce_wide) or 4 (k_splitk_reduce) in a stage time.  Take the slice count with the
         // smallest rounds x (stages per slice + 16) + fold: a count that just spills into one more round (540 items)
         // costs a whole extra round, many short slices cost their overheads.
         const int64_t stages = (K + dk - 1) / dk;
         int64_t max_splits = stages / 4;
         if (max_splits < 1) max_splits = 1;
         if (max_splits > 256) max_splits = 256;
+        const int64_t walked = splitk_reduce_is_wide((int64_t)M * N) ? 32 : 4;
         int64_t best = 1, best_cost = -1;
         for (int64_t sp = 1; sp <= max_splits; ++sp) {
             const int64_t sps = (stages + sp - 1) / sp, real = (stages + sps - 1) / sps;
             const int64_t rounds = (tiles * real + slots - 1) / slots;
-            const int64_t cost = rounds * (sps + 16) + real * (int64_t)M * N / (1 << 20);
+            const int64_t cost = rounds * (sps + 16) + real * (int64_t)M * N / (1 << 20) + real / walked;
             if (best_cost < 0 || cost < best_cost) { best_cost = cost; best = sp; }
         }
         const int64_t kchunk = ((stages + best - 1) / best) * dk;

@@ -350,7 +350,7 @@ __global__ __launch_bounds__(BIG ? GeoBig::THREADS : GeoMid::THREADS, 2) void k_
 
 // One slice length (in 16-row stages) for all layers of a joint launch, each layer rounding it to equal slices:
 // minimise  rounds of 512 (256 x 256 tiles: 256) workgroups x (stages of the longest slice + what an item costs besides its stages) + the fold's
-// reading of the slices (4 MB in about a stage time).
+// reading of the slices (4 MB in about a stage time) and its walk through the layer with the most of them (8 in a stage time).
 struct F32JointPlan { int splits[kJointLayers], kchunk[kJointLayers], geo[kJointLayers], tiles_m[kJointLayers], tiles_n[kJointLayers]; int64_t items; };
 F32JointPlan plan_joint_f32(const JointShape* sh, int n_layers, int B, bool big, size_t max_floats) {
     constexpr int64_t kItemOverhead = 16;
@@ -362,7 +362,7 @@ F32JointPlan plan_joint_f32(const JointShape* sh, int n_layers, int B, bool big,
         const int64_t len = (stages_max + S - 1) / S;
         if (len < 4 && S > 1) break;
         F32JointPlan p{};
-        int64_t longest = 0, fold = 0;                       // fold: entries of all slices
+        int64_t longest = 0, fold = 0, most = 0;             // fold: entries of all slices
         size_t floats = 0;
         for (int l = 0; l < n_layers; ++l) {
             const int64_t stages = ceil_div((int64_t)B * sh[l].T, DKF);
@@ -376,10 +376,11 @@ F32JointPlan plan_joint_f32(const JointShape* sh, int n_layers, int B, bool big,
             p.items += (int64_t)p.tiles_m[l] * p.tiles_n[l] * splits;
             longest = std::max(longest, own == len ? sps : sps * 2 / 3);
             fold += (int64_t)sh[l].M * sh[l].N * splits;
+            most = std::max(most, splits);
             floats += (size_t)splits * (size_t)splitk_slice_elems((int64_t)sh[l].M * sh[l].N);
         }
         if (floats > max_floats && S > 1) break;             // (as plan_joint)
-        const int64_t cost = ((p.items + kSlots - 1) / kSlots) * (longest + kItemOverhead) + fold / (1 << 20);
+        const int64_t cost = ((p.items + kSlots - 1) / kSlots) * (longest + kItemOverhead) + fold / (1 << 20) + most / 8;
         if (best_cost < 0 || cost < best_cost) { best_cost = cost; best = p; }
     }
     return best;

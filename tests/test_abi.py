@@ -238,6 +238,23 @@ def test_queried_workspace_is_enough_for_layers_that_cannot_share_a_launch(lib, 
             assert st != dpclip.DP_ERR_WORKSPACE, (dtype, B, shapes, std)
 
 
+@pytest.mark.parametrize("n_layers", [1, 2, 4])
+@pytest.mark.parametrize("d_in,d_out", [(63, 127), (577, 61), (96, 64), (128, 128), (64, 256), (1030, 1200)])
+def test_float32_sums_are_not_cut_into_more_slices_than_the_fold_can_walk(lib, n_layers, d_in, d_out):
+    """Host logic only: a fold walks a layer's slices one after the other, 4 (odd sizes), 8 (several layers) or 32 in the
+    time of one 16-row stage; that is no longer than a slice of the sum takes, its start-up of 16 stages included."""
+    arr = (dpclip.LayerDesc * n_layers)(*[dpclip.LayerDesc(None, None, 1, d_in, d_out) for _ in range(n_layers)])
+    odd = d_in * d_out % 4 != 0
+    for K in (600, 1500, 3000, 6000, 12500, 25000, 50000, 100000):
+        if n_layers == 1 or odd:
+            need = dpclip.workspace_bytes(dpclip.DP_OP_CLIPPED_GRAD, K, 1, d_in, d_out, dpclip.DP_F32)
+            slices, walked = need / (4 * ((d_in * d_out + 3) // 4 * 4)), 4 if odd or d_in * d_out > 2 ** 20 else 32
+        else:
+            slices, walked = dpclip.layers_clipped_workspace_bytes(arr, K, dpclip.DP_F32) / (4 * n_layers * d_in * d_out), 8
+        if slices > 1:
+            assert slices / walked <= K / 16 / slices + 17, (K, slices)
+
+
 def test_noise_layout_gives_every_gradient_its_own_stretch():
     """Host logic only: the default positions in the noise stream (weights back to back, then the biases) are pairwise
     disjoint, also next to weight offsets given by the caller; overlapping offsets are refused.  Independent noise
