@@ -195,18 +195,49 @@ int clipped_join_class(int64_t B, int64_t T, int64_t d_in, int64_t d_out, dp_dty
     if (!is16(dtype)) {
         // float32: the layers of the copy-pipeline kernel (long contractions, widths multiples of 4) share launches too
         if (B * T >= (int64_t(1) << 31)) return 0;
-        const TnPlan p = plan_clipped_f32((int)B, (int)T, (int)d_in, (int)d_out);
-        if (!p.dma || ((d_in * d_out) & 3) != 0) return 0;              // the shared fold takes four entries at a time
-        return p.tile_m == f32_split_tile_m(F32_BIG) ? 6 : 5;
+        const int geo = clipped_f32_route(B * T, (int)d_in, (int)d_out).geo;
+        if (geo == F32_NONE || ((d_in * d_out) & 3) != 0) return 0;     // the shared fold takes four entries at a time
+        return geo == F32_BIG ? 6 : 5;
     }
     if (plan_clipped_bf16((int)B, (int)T, (int)d_in, (int)d_out).dma && dma_joint_ok((int)T, (int)d_in, (int)d_out)) return 1;
     if (B * T < (int64_t(1) << 31) && dma_joint_mid_ok((int)T, (int)d_in, (int)d_out)) return 3;
     if (B * T < (int64_t(1) << 31) && dma_joint_ragged_ok((int)T, (int)d_in, (int)d_out)) return 4;
     return 0;
 }
-size_t joint_ws_bytes(const JointShape* sh, int n, int64_t B, dp_dtype dtype, int geo, size_t max_floats = kAnySlices) {
-    if (geo >= 5) return joint_f32_workspace_floats(sh, n, (int)B, geo == 6, max_floats) * sizeof(float);
+// plan: the float32 launch's, left for it
+size_t joint_ws_bytes(const JointShape* sh, int n, int64_t B, dp_dtype dtype, int geo, size_t max_floats = kAnySlices, F32JointPlan* plan = nullptr) {
+    if (geo >= 5) {
+        const F32JointPlan p = plan_joint_f32(sh, n, (int)B, geo == 6, max_floats);
+        if (plan) *plan = p;
+        return p.floats * sizeof(float);
+    }
     return (is8(dtype) ? joint8_workspace_floats(sh, n, (int)B, max_floats) : joint_workspace_floats(sh, n, (int)B, geo, max_floats)) * sizeof(float);
+}
+std::vector<int> clipped_join_classes(const dp_layer_desc* layers, int64_t n_layers, int64_t B, dp_dtype dtype) {
+    std::vector<int> cls((size_t)n_layers);
+    for (int64_t l = 0; l < n_layers; ++l) cls[(size_t)l] = clipped_join_class(B, layers[l].T, layers[l].d_in, layers[l].d_out, dtype);
+    return cls;
+}
+// which layers' gradients overlap another's (empty: none do)
+std::vector<char> shared_gradients(const dp_layer_desc* layers, int64_t n_layers) {
+    const float* reach = nullptr;
+    bool apart = true;                                   // one after the other in memory, as a flat gradient has them
+    for (int64_t l = 0; l < n_layers; ++l) {
+        const int64_t n = layers[l].d_in * layers[l].d_out;
+        if (n == 0) continue;
+        if (layers[l].grad < reach) { apart = false; break; }
+        reach = layers[l].grad + n;
+    }
+    std::vector<char> shared;
+    if (apart) return shared;
+    std::vector<const float*> p;
+    std::vector<int64_t> n, which;
+    for (int64_t l = 0; l < n_layers; ++l)
+        if (layers[l].d_in * layers[l].d_out > 0) { p.push_back(layers[l].grad); n.push_back(layers[l].d_in * layers[l].d_out); which.push_back(l); }
+    const std::vector<char> bad = overlapping(p, n);
+    shared.resize((size_t)n_layers, 0);
+    for (size_t k = 0; k < which.size(); ++k) shared[(size_t)which[k]] = bad[k];
+    return shared;
 }
 
 constexpr size_t kConvZeroBytes = 256;                // head of the conv workspace: a line of zeros for the padding
@@ -1185,7 +1216,8 @@ size_t dp_layers_clipped_workspace_bytes(const dp_layer_desc* layers, int64_t n_
         const size_t n = dp_workspace_bytes(DP_OP_CLIPPED_GRAD, B, y.T, y.d_in, y.d_out, dtype, DP_PATH_AUTO);
         if (n > need) need = n;
     }
-    for (int geo : {1, 3, 4, 5, 6}) {                              // the two classes of joint launches, each in groups of its own
+    const std::vector<int> cls = clipped_join_classes(layers, n_layers, B, dtype);
+    for (int geo : {1, 3, 4, 5, 6}) {                              // the classes of joint launches, each in groups of its own
         JointShape sh[kJointLayers];
         int nj = 0;
         auto joint_need = [&]() {
@@ -1194,7 +1226,7 @@ size_t dp_layers_clipped_workspace_bytes(const dp_layer_desc* layers, int64_t n_
         };
         for (int64_t l = 0; l < n_layers; ++l) {
             const dp_layer_desc& y = layers[l];
-            if (clipped_join_class(B, y.T, y.d_in, y.d_out, dtype) != geo) continue;
+            if (cls[(size_t)l] != geo) continue;
             sh[nj++] = JointShape{(int)y.T, (int)y.d_in, (int)y.d_out};
             if (nj == kJointLayers) joint_need();
         }
@@ -1246,23 +1278,19 @@ dp_status dp_layers_clipped_grad_noise(const dp_layer_desc* layers, int64_t n_la
     // whose noise the fold cannot add, they are left out of the group that the workspace query planned for them.  The
     // layers that remain may then take more slices than the query gave them, so where that is more than the query's
     // answer, they are held to it.  Their longest slices fit: the query's group had as many of each layer, or more.)
-    auto shared_grad = [&](int64_t l) {
-        const float* p = layers[l].grad;
-        const int64_t n = layers[l].d_in * layers[l].d_out;
-        for (int64_t k = 0; k < n_layers; ++k)
-            if (k != l && layers[k].grad < p + n && p < layers[k].grad + layers[k].d_in * layers[k].d_out) return true;
-        return false;
-    };
-    std::vector<std::vector<int64_t>> joint_groups;
-    std::vector<int> joint_geo;
-    std::vector<size_t> joint_floats;                        // the most that a group's slices may take
+    const std::vector<char> shared = shared_gradients(layers, n_layers);
+    auto shared_grad = [&](int64_t l) { return !shared.empty() && shared[(size_t)l]; };
+    const std::vector<int> cls = clipped_join_classes(layers, n_layers, B, dtype);
+    struct JointGroup { std::vector<int64_t> layer; int geo; size_t max_floats; F32JointPlan plan; };   // max_floats: the most that its slices may take
+    std::vector<JointGroup> joint_groups;
     for (int geo : {1, 3, 4, 5, 6}) {
         std::vector<int64_t> cur;
         int in_query = 0;                                    // layers of the query's group so far
         auto end_group = [&]() {
             if (cur.size() < 2) { cur.clear(); in_query = 0; return; }
-            joint_groups.push_back(cur); joint_geo.push_back(geo);
-            auto& g = joint_groups.back();
+            joint_groups.push_back(JointGroup{cur, geo, kAnySlices, {}});
+            JointGroup& group = joint_groups.back();
+            auto& g = group.layer;
             // the largest layers first: the tiles that are folded when the launch ends are then the smallest layer's
             std::stable_sort(g.begin(), g.end(), [&](int64_t a, int64_t b) {
                 return layers[a].d_in * layers[a].d_out * layers[a].T > layers[b].d_in * layers[b].d_out * layers[b].T; });
@@ -1271,18 +1299,20 @@ dp_status dp_layers_clipped_grad_noise(const dp_layer_desc* layers, int64_t n_la
                 const dp_layer_desc& y = layers[g[k]];
                 sh[k] = JointShape{(int)y.T, (int)y.d_in, (int)y.d_out};
             }
-            size_t most = kAnySlices, own = joint_ws_bytes(sh, (int)g.size(), B, dtype, geo);
+            size_t own = joint_ws_bytes(sh, (int)g.size(), B, dtype, geo, kAnySlices, &group.plan);
             if ((int)g.size() < in_query) {
                 const size_t query = dp_layers_clipped_workspace_bytes(layers, n_layers, B, dtype);
-                if (own > query) { most = query / sizeof(float); own = joint_ws_bytes(sh, (int)g.size(), B, dtype, geo, most); }
+                if (own > query) {
+                    group.max_floats = query / sizeof(float);
+                    own = joint_ws_bytes(sh, (int)g.size(), B, dtype, geo, group.max_floats, &group.plan);
+                }
             }
-            joint_floats.push_back(most);
             need = std::max(need, own);
             cur.clear(); in_query = 0;
         };
         for (int64_t l = 0; l < n_layers; ++l) {
             const dp_layer_desc& y = layers[l];
-            if (clipped_join_class(B, y.T, y.d_in, y.d_out, dtype) != geo) continue;
+            if (cls[(size_t)l] != geo) continue;
             ++in_query;
             if (!shared_grad(l) && !(stddev > 0.0f && !splitk_noise_ok(y.d_in * y.d_out, y.noise_offset))) cur.push_back(l);
             if (in_query == kJointLayers) end_group();
@@ -1293,7 +1323,8 @@ dp_status dp_layers_clipped_grad_noise(const dp_layer_desc* layers, int64_t n_la
     // float32 layers with a short contraction (a model of small dense layers) share launches, 8 layers each
     std::vector<char> done((size_t)n_layers, 0);
     for (size_t gi = 0; gi < joint_groups.size(); ++gi) {
-        const auto& g = joint_groups[gi];
+        const JointGroup& group = joint_groups[gi];
+        const auto& g = group.layer;
         JointShape sh[kJointLayers];
         JointOperands op[kJointLayers];
         for (size_t k = 0; k < g.size(); ++k) {
@@ -1303,14 +1334,14 @@ dp_status dp_layers_clipped_grad_noise(const dp_layer_desc* layers, int64_t n_la
                                   y.noise_offset};
             done[(size_t)g[k]] = 1;
         }
-        const hipError_t ej = joint_geo[gi] >= 5
+        const hipError_t ej = group.geo >= 5
             ? launch_clipped_f32_split_joint(sh, op, (int)g.size(), (int)B, accumulate != 0, stddev, seed, static_cast<float*>(workspace),
-                                           static_cast<hipStream_t>(hip_stream), joint_geo[gi] == 6, joint_floats[gi])
+                                           static_cast<hipStream_t>(hip_stream), group.geo == 6, group.plan)
             : is8(dtype)
             ? launch_clipped_f8_dma_joint(sh, op, (int)g.size(), (int)B, accumulate != 0, stddev, seed, static_cast<float*>(workspace),
-                                          static_cast<hipStream_t>(hip_stream), fmt_of(dtype), joint_floats[gi])
+                                          static_cast<hipStream_t>(hip_stream), fmt_of(dtype), group.max_floats)
             : launch_clipped_bf16_dma_joint(sh, op, (int)g.size(), (int)B, accumulate != 0, stddev, seed, static_cast<float*>(workspace),
-                                            static_cast<hipStream_t>(hip_stream), dtype == DP_F16, joint_geo[gi], joint_floats[gi]);
+                                            static_cast<hipStream_t>(hip_stream), dtype == DP_F16, group.geo, group.max_floats);
         if (ej != hipSuccess) return DP_ERR_HIP;
     }
     if (dtype == DP_F32 && B > 0 && !(stddev > 0.0f)) {
@@ -1329,7 +1360,7 @@ dp_status dp_layers_clipped_grad_noise(const dp_layer_desc* layers, int64_t n_la
         for (int64_t l = 0; l < n_layers; ++l) {
             const dp_layer_desc& y = layers[l];
             if (y.T == 0 || y.d_in == 0 || y.d_out == 0) continue;
-            if (!clipped_f32_is_short(plan_clipped_f32((int)B, (int)y.T, (int)y.d_in, (int)y.d_out)) || shared_grad(l)) continue;
+            if (!clipped_f32_route(B * y.T, (int)y.d_in, (int)y.d_out).is_short || shared_grad(l)) continue;
             which[nb] = l;
             batch[nb++] = ShortLayerDesc{static_cast<const float*>(y.A), static_cast<const float*>(y.G), y.clip ? y.clip : clip, y.grad,
                                          (int)y.T, (int)y.d_in, (int)y.d_out};

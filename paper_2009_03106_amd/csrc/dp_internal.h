@@ -107,6 +107,10 @@ void plan_direct_chunks(TnPlan& p, int B, int T, int M, int N, int esize, int st
 hipError_t launch_direct_chunks_finish(const float* shares, int64_t slice, int S, int n, int B, float* sums, hipStream_t st);
 TnPlan plan_clipped_bf16(int B, int T, int M, int N);
 TnPlan plan_clipped_f32(int B, int T, int M, int N);
+// how that plan takes a sum of K rows: the short-contraction kernel, else the split kernel with this geometry, or
+// F32_NONE: the kernel of the fp32 instruction
+struct ClippedF32Route { bool is_short; int geo; };
+ClippedF32Route clipped_f32_route(int64_t K, int M, int N);
 TnPlan plan_direct_bf16(int B, int T, int M, int N);
 // stride-1 convolution given by its channels-last input image (implicit unfolding in the copy-pipeline kernel)
 struct ConvGeom { int H, W, C, KH, KW, pad; };
@@ -195,11 +199,13 @@ bool dma_joint_mid_ok(int T, int M, int N);      // the second class: 128 x 128 
 bool dma_joint_ragged_ok(int T, int M, int N);   // the same tiles, T not a multiple of the stage: geo = 4
 size_t joint_workspace_floats(const JointShape* sh, int n_layers, int B, int geo, size_t max_floats);
 // the same for float32 inputs (dp_tn_f32_split.hip; 128 x 128 tiles, any T); A, G of JointOperands are float pointers
-size_t joint_f32_workspace_floats(const JointShape* sh, int n_layers, int B, bool big, size_t max_floats);
+// big: every layer on 256 x 256 tiles.  The plan of a call is made once and handed to the launch.
+struct F32JointPlan { int splits[kJointLayers], kchunk[kJointLayers], geo[kJointLayers], tiles_m[kJointLayers], tiles_n[kJointLayers]; int64_t items; size_t floats; };
+F32JointPlan plan_joint_f32(const JointShape* sh, int n_layers, int B, bool big, size_t max_floats);
 hipError_t launch_direct_f32_split_joint(const JointShape* sh, const JointOperands* op, float* const* partial, int n_layers,
                                        int B, hipStream_t st);
 hipError_t launch_clipped_f32_split_joint(const JointShape* sh, const JointOperands* op, int n_layers, int B, bool accumulate,
-                                        float stddev, uint64_t seed, float* ws, hipStream_t st, bool big, size_t max_floats);
+                                        float stddev, uint64_t seed, float* ws, hipStream_t st, bool big, const F32JointPlan& p);
 // the same for 8-bit inputs (dp_tn_f8_dma.hip; 256 x 256 tiles, T a multiple of 64); A, G of JointOperands are byte pointers
 bool dma8_joint_ok(int T, int M, int N);
 size_t joint8_workspace_floats(const JointShape* sh, int n_layers, int B, size_t max_floats);
@@ -232,7 +238,6 @@ hipError_t launch_direct_f8_dma(const TnPlan& p, const void* A, const void* G, i
                                 bool accumulate, float* sqnorm, float* partial, hipStream_t st, int fmt, const ClipOut* co = nullptr);
 // float32 layers with a short contraction (B T <= 512: plan_clipped_f32 gives them one 32 x 32-tile kernel without K
 // slices), up to 8 in one launch; per layer the same arithmetic as launch_clipped_f32
-bool clipped_f32_is_short(const TnPlan& p);
 struct ShortLayerDesc { const float* A; const float* G; const float* clip; float* grad; int T, M, N; };
 hipError_t launch_clipped_f32_short_layers(const ShortLayerDesc* layers, int n_layers, int B, bool accumulate, hipStream_t st);
 hipError_t launch_clipped_f32(const TnPlan& p, const float* A, const float* G, const float* clip,

@@ -320,15 +320,22 @@ template <int MODE> void launch_f32(bool deep, bool veca, bool vecg, dim3 grid, 
 
 }  // namespace
 
-TnPlan plan_clipped_f32(int B, int T, int M, int N) {
-    const int64_t K = (int64_t)B * T;
-    TnPlan p;
-    p.segmented = false; p.epu = 0; p.big = false; p.dma = false;
+ClippedF32Route clipped_f32_route(int64_t K, int M, int N) {
     // From 256 rows on, outputs of at least 64 tiles of 128 x 128 fill the chip without K slices: 512 rows of 4608 x 512
     // take 42 us on 32 x 32 tiles of the fp32 instruction.
     const int geo = K < (int64_t(1) << 31) ? f32_split_geo(K, M, N, false) : F32_NONE;
     const bool wide = geo != F32_NONE && (int64_t)ceil_div(M, 128) * ceil_div(N, 128) >= 64;
-    if (K <= kShortK && !wide) {
+    if (K <= kShortK && !wide) return ClippedF32Route{true, F32_NONE};
+    return ClippedF32Route{false, geo};
+}
+
+TnPlan plan_clipped_f32(int B, int T, int M, int N) {
+    const int64_t K = (int64_t)B * T;
+    TnPlan p;
+    p.segmented = false; p.epu = 0; p.big = false; p.dma = false;
+    const ClippedF32Route route = clipped_f32_route(K, M, N);
+    const int geo = route.geo;
+    if (route.is_short) {
         p.tile_m = STM; p.tile_n = STN;
         p.tiles_m = ceil_div(M, STM); p.tiles_n = ceil_div(N, STN);
         p.splits = 1; p.kchunk = (int)K;
@@ -337,7 +344,7 @@ TnPlan plan_clipped_f32(int B, int T, int M, int N) {
     if (geo != F32_NONE) {
         // 4-wave geometries: two workgroups per compute unit, 256 x 256: one; slices of at least 4 stages
         const int dk = f32_split_stage_rows();
-        const int64_t slots = geo == F32_BIG ? 256 : 512;
+        const int slots_log2 = geo == F32_BIG ? 8 : 9;
         p.dma = true;
         p.tile_m = f32_split_tile_m(geo); p.tile_n = f32_split_tile_n(geo);
         p.tiles_m = ceil_div(M, p.tile_m); p.tiles_n = ceil_div(N, p.tile_n);
@@ -347,19 +354,22 @@ TnPlan plan_clipped_f32(int B, int T, int M, int N) {
         // other, 32 (k_splitk_reduce_wide) or 4 (k_splitk_reduce) in a stage time.  Take the slice count with the
         // smallest rounds x (stages per slice + 16) + fold: a count that just spills into one more round (540 items)
         // costs a whole extra round, many short slices cost their overheads.
-        const int64_t stages = (K + dk - 1) / dk;
-        int64_t max_splits = stages / 4;
+        const uint32_t stages = (uint32_t)((K + dk - 1) / dk);
+        uint32_t max_splits = stages / 4;
         if (max_splits < 1) max_splits = 1;
         if (max_splits > 256) max_splits = 256;
-        const int64_t walked = splitk_reduce_is_wide((int64_t)M * N) ? 32 : 4;
-        int64_t best = 1, best_cost = -1;
-        for (int64_t sp = 1; sp <= max_splits; ++sp) {
-            const int64_t sps = (stages + sp - 1) / sp, real = (stages + sps - 1) / sps;
-            const int64_t rounds = (tiles * real + slots - 1) / slots;
-            const int64_t cost = rounds * (sps + 16) + real * (int64_t)M * N / (1 << 20) + real / walked;
+        const uint32_t walked = splitk_reduce_is_wide((int64_t)M * N) ? 32 : 4;
+        uint32_t best = 1;
+        int64_t best_cost = -1;
+        for (uint32_t sp = 1; sp <= max_splits;) {
+            const uint32_t sps = (stages + sp - 1) / sp, real = (stages + sps - 1) / sps;
+            const int64_t rounds = (tiles * real + (1 << slots_log2) - 1) >> slots_log2;
+            const int64_t cost = rounds * (sps + 16) + ((real * (int64_t)M * N) >> 20) + real / walked;
             if (best_cost < 0 || cost < best_cost) { best_cost = cost; best = sp; }
+            if (sps == 1) break;
+            sp = (stages + sps - 2) / (sps - 1);             // the next count whose slices are shorter
         }
-        const int64_t kchunk = ((stages + best - 1) / best) * dk;
+        const int64_t kchunk = (int64_t)((stages + best - 1) / best) * dk;
         p.kchunk = (int)kchunk;
         p.splits = (int)((K + kchunk - 1) / kchunk);
         return p;
@@ -427,7 +437,6 @@ hipError_t launch_clipped_f32(const TnPlan& p, const float* A, const float* G, c
     return launch_splitk_reduce(ws, n, p.splits, accumulate, grad, st, noise);
 }
 
-bool clipped_f32_is_short(const TnPlan& p) { return p.tile_m == STM && p.splits == 1; }
 
 hipError_t launch_clipped_f32_short_layers(const ShortLayerDesc* layers, int n_layers, int B, bool accumulate, hipStream_t st) {
     if (n_layers < 1 || n_layers > kShortBatch) return hipErrorInvalidValue;

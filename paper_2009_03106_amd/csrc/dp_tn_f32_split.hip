@@ -348,59 +348,69 @@ __global__ __launch_bounds__(BIG ? GeoBig::THREADS : GeoMid::THREADS, 2) void k_
     else                             tn_f32_split_tile<MODE, GeoFlat>(a, item, lds);
 }
 
+}  // namespace
+
 // One slice length (in 16-row stages) for all layers of a joint launch, each layer rounding it to equal slices:
 // minimise  rounds of 512 (256 x 256 tiles: 256) workgroups x (stages of the longest slice + what an item costs besides its stages) + the fold's
 // reading of the slices (4 MB in about a stage time) and its walk through the layer with the most of them (8 in a stage time).
-struct F32JointPlan { int splits[kJointLayers], kchunk[kJointLayers], geo[kJointLayers], tiles_m[kJointLayers], tiles_n[kJointLayers]; int64_t items; };
 F32JointPlan plan_joint_f32(const JointShape* sh, int n_layers, int B, bool big, size_t max_floats) {
     constexpr int64_t kItemOverhead = 16;
-    const int64_t kSlots = big ? 256 : 512;
-    F32JointPlan best{};
-    int64_t best_cost = -1, stages_max = 1;
-    for (int l = 0; l < n_layers; ++l) stages_max = std::max<int64_t>(stages_max, ceil_div((int64_t)B * sh[l].T, DKF));
-    for (int64_t S = 1; S <= 512 && S <= stages_max; ++S) {
-        const int64_t len = (stages_max + S - 1) / S;
+    const int slots_log2 = big ? 8 : 9;
+    F32JointPlan p{};
+    // layers with the same number of stages and slice length take the same number of slices: they are counted together
+    struct { uint32_t stages; bool half; int64_t tiles, entries, slice; } same[kJointLayers];
+    int n_same = 0, which[kJointLayers];
+    uint32_t stages_max = 1;
+    for (int l = 0; l < n_layers; ++l) {
+        const int64_t K = (int64_t)B * sh[l].T, entries = (int64_t)sh[l].M * sh[l].N;
+        p.geo[l] = big ? F32_BIG : f32_split_geo(K, sh[l].M, sh[l].N, false);
+        p.tiles_m[l] = ceil_div(sh[l].M, f32_split_tile_m(p.geo[l])); p.tiles_n[l] = ceil_div(sh[l].N, f32_split_tile_n(p.geo[l]));
+        const uint32_t stages = (uint32_t)ceil_div(K, DKF);
+        const bool half = p.geo[l] == F32_NARROW || p.geo[l] == F32_FLAT;
+        stages_max = std::max(stages_max, stages);
+        int k = 0;
+        while (k < n_same && (same[k].stages != stages || same[k].half != half)) ++k;
+        if (k == n_same) { same[k].stages = stages; same[k].half = half; same[k].tiles = same[k].entries = same[k].slice = 0; ++n_same; }
+        same[k].tiles += (int64_t)p.tiles_m[l] * p.tiles_n[l]; same[k].entries += entries; same[k].slice += splitk_slice_elems(entries);
+        which[l] = k;
+    }
+    int64_t best_cost = -1;
+    uint32_t splits[kJointLayers], sps[kJointLayers], best_splits[kJointLayers], best_sps[kJointLayers];
+    for (uint32_t S = 1; S <= 512 && S <= stages_max;) {
+        const uint32_t len = (stages_max + S - 1) / S;
         if (len < 4 && S > 1) break;
-        F32JointPlan p{};
-        int64_t longest = 0, fold = 0, most = 0;             // fold: entries of all slices
+        int64_t items = 0, fold = 0;                         // fold: entries of all slices
+        uint32_t longest = 0, most = 0;
         size_t floats = 0;
-        for (int l = 0; l < n_layers; ++l) {
-            const int64_t stages = ceil_div((int64_t)B * sh[l].T, DKF);
-            p.geo[l] = big ? F32_BIG : f32_split_geo((int64_t)B * sh[l].T, sh[l].M, sh[l].N, false);
-            const int64_t own = p.geo[l] == F32_NARROW || p.geo[l] == F32_FLAT ? len + len / 2 : len;      // half a tile: shorter stages
-            int64_t splits = (stages + own - 1) / own;
-            const int64_t sps = (stages + splits - 1) / splits;
-            splits = (stages + sps - 1) / sps;
-            p.tiles_m[l] = ceil_div(sh[l].M, f32_split_tile_m(p.geo[l])); p.tiles_n[l] = ceil_div(sh[l].N, f32_split_tile_n(p.geo[l]));
-            p.splits[l] = (int)splits; p.kchunk[l] = (int)(sps * DKF);
-            p.items += (int64_t)p.tiles_m[l] * p.tiles_n[l] * splits;
-            longest = std::max(longest, own == len ? sps : sps * 2 / 3);
-            fold += (int64_t)sh[l].M * sh[l].N * splits;
-            most = std::max(most, splits);
-            floats += (size_t)splits * (size_t)splitk_slice_elems((int64_t)sh[l].M * sh[l].N);
+        for (int k = 0; k < n_same; ++k) {
+            const uint32_t own = same[k].half ? len + len / 2 : len;          // half a tile: shorter stages
+            const uint32_t want = (same[k].stages + own - 1) / own;
+            sps[k] = (same[k].stages + want - 1) / want;
+            splits[k] = (same[k].stages + sps[k] - 1) / sps[k];
+            items += same[k].tiles * splits[k];
+            fold += same[k].entries * splits[k];
+            floats += (size_t)same[k].slice * splits[k];
+            longest = std::max(longest, own == len ? sps[k] : sps[k] * 2 / 3);
+            most = std::max(most, splits[k]);
         }
         if (floats > max_floats && S > 1) break;             // (as plan_joint)
-        const int64_t cost = ((p.items + kSlots - 1) / kSlots) * (longest + kItemOverhead) + fold / (1 << 20) + most / 8;
-        if (best_cost < 0 || cost < best_cost) { best_cost = cost; best = p; }
+        const int64_t cost = ((items + (1 << slots_log2) - 1) >> slots_log2) * (longest + kItemOverhead) + (fold >> 20) + most / 8;
+        if (best_cost < 0 || cost < best_cost) {
+            best_cost = cost; p.items = items; p.floats = floats;
+            for (int k = 0; k < n_same; ++k) { best_splits[k] = splits[k]; best_sps[k] = sps[k]; }
+        }
+        if (len == 1) break;
+        S = (stages_max + len - 2) / (len - 1);              // the next count whose slices are shorter
     }
-    return best;
-}
-
-}  // namespace
-
-size_t joint_f32_workspace_floats(const JointShape* sh, int n_layers, int B, bool big, size_t max_floats) {
-    const F32JointPlan p = plan_joint_f32(sh, n_layers, B, big, max_floats);
-    size_t slices = 0;
-    for (int l = 0; l < n_layers; ++l) slices += (size_t)p.splits[l] * (size_t)splitk_slice_elems((int64_t)sh[l].M * sh[l].N);
-    return slices;
+    for (int l = 0; l < n_layers; ++l) { p.splits[l] = (int)best_splits[which[l]]; p.kchunk[l] = (int)best_sps[which[l]] * DKF; }
+    return p;
 }
 
 // noise: stddev == 0 for none, else every layer's d_in * d_out and noise_offset are multiples of 4.  A, G of the
 // operands are float pointers here.
 hipError_t launch_clipped_f32_split_joint(const JointShape* sh, const JointOperands* op, int n_layers, int B, bool accumulate,
-                                        float stddev, uint64_t seed, float* ws, hipStream_t st, bool big, size_t max_floats) {
+                                        float stddev, uint64_t seed, float* ws, hipStream_t st, bool big, const F32JointPlan& p) {
     if (n_layers < 1 || n_layers > kJointLayers) return hipErrorInvalidValue;
-    const F32JointPlan p = plan_joint_f32(sh, n_layers, B, big, max_floats);
     if (p.items >= (int64_t(1) << 28)) return hipErrorInvalidValue;
     F32JointArgs j;
     FoldLayers f;
