@@ -153,9 +153,11 @@ __global__ __launch_bounds__(kThreads) void k_tn_f32(TnArgsF a) {
             }
         }
     } else {
-        float s = 0.f;
+        float s = 0.f;                  // columns outside the matrix are left out: an infinity times their zeros is NaN there
+        const bool inn = n0 + wn * 32 + lrow < a.N;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) s += acc[r] * acc[r];
+        for (int r = 0; r < 16; ++r)
+            s += inn && m0 + wm * 32 + 8 * (r >> 2) + 4 * lhalf + (r & 3) < a.M ? acc[r] * acc[r] : 0.f;
         s = block_sum_256(s, red);
         if (tid == 0) a.out[(size_t)z * (a.tiles_m * a.tiles_n) + tile] = s;
     }

@@ -133,7 +133,7 @@ def test_small_rows_take_no_longer(path, T, d_in, d_out):
 
 @pytest.mark.parametrize("value", [float("inf"), float("-inf")])
 @pytest.mark.parametrize("in_g", [False, True])
-@pytest.mark.parametrize("B,T,d_in,d_out", [(3, 257, 128, 128), (65, 131, 577, 61)])
+@pytest.mark.parametrize("B,T,d_in,d_out", [(3, 257, 128, 128), (65, 131, 577, 61), (3, 101, 70, 33)])
 def test_infinity_in_the_last_of_an_odd_number_of_rows(B, T, d_in, d_out, in_g, value):
     """The sums of its column are infinite, not NaN: the clip factor of an infinite norm is 0."""
     A, G, clip = _data(B, T, d_in, d_out, 9)
