@@ -128,24 +128,21 @@ int gram_cols_class(int64_t B, int64_t T, int64_t d_in, int64_t d_out, dp_dtype 
 
 size_t round16(size_t n) { return (n + 15) & ~size_t(15); }
 
-// a layer whose direct norm the shared copy-pipeline launch of dp_layers_sqnorm can take (16-bit, direct path, T >= 64,
-// aligned widths), and the scratch such a layer needs in the several-layers call: the larger of its own call's and
-// the shared launch's (one sum per example and 128 x 128 tile)
-// sums per example of a layer's direct norm in a shared launch
+// sums per example of a layer's direct norm in a shared launch: one per 128 x 128 tile, float32: per tile of its geometry
 int direct_sums(int64_t B, int64_t T, int64_t d_in, int64_t d_out, dp_dtype dtype) {
     if (is16(dtype)) return direct_joint_tiles((int)d_in, (int)d_out);
-    const TnPlan p = plan_direct_f32((int)B, (int)T, (int)d_in, (int)d_out);
-    return p.tiles_m * p.tiles_n;
+    const int geo = f32_split_geo(T, (int)d_in, (int)d_out, true);
+    return ceil_div(d_in, f32_split_tile_m(geo)) * ceil_div(d_out, f32_split_tile_n(geo));
 }
+// a layer whose direct norm the shared launch of dp_layers_sqnorm can take (16-bit: T >= 64 and aligned widths)
 bool direct_joinable(int64_t B, int64_t T, int64_t d_in, int64_t d_out, dp_dtype dtype, dp_path path) {
     if (is8(dtype) || T <= 1 || d_in == 0 || d_out == 0 || B >= (int64_t(1) << 20)) return false;
     if (gram_batchable(T, d_in, d_out, dtype, path) || gram_cols_class(B, T, d_in, d_out, dtype, path) != 0) return false;
     if (resolve_path(path, dtype, T, d_in, d_out) != DP_PATH_DIRECT) return false;
     if (!is16(dtype)) {
-        // float32: the layers whose direct norm runs on the copy-pipeline kernel as well
+        // float32: the layers whose direct norm the split kernel can form (choose_direct_f32_joint leaves some of them out)
         if (B * T >= (int64_t(1) << 31)) return false;
-        const TnPlan p = plan_direct_f32((int)B, (int)T, (int)d_in, (int)d_out);
-        if (!p.dma) return false;
+        if (f32_split_geo(T, (int)d_in, (int)d_out, true) == F32_NONE) return false;
     } else if (!dma_direct_joint_ok((int)B, (int)T, (int)d_in, (int)d_out)) return false;
     return B * direct_sums(B, T, d_in, d_out, dtype) < (int64_t(1) << 24);       // 16 layers' items stay below the launch's 2^28
 }
@@ -163,6 +160,7 @@ bool gram16_joinable(int64_t B, int64_t T, int64_t d_in, int64_t d_out, dp_dtype
         gram_cols_class(B, T, d_in, d_out, dtype, path) != 0) return false;
     return B * plan_gram_bf16((int)T, (int)d_in, (int)d_out).npairs < (int64_t(1) << 24);
 }
+// the scratch of a layer in the several-layers call: the larger of its own call's and a shared launch's
 size_t single_layer_need(int64_t B, const dp_layer_desc& y, dp_dtype dtype, dp_path path) {
     size_t n = dp_workspace_bytes(DP_OP_SQNORM, B, y.T, y.d_in, y.d_out, dtype, path);
     if (direct_joinable(B, y.T, y.d_in, y.d_out, dtype, path))
@@ -897,10 +895,19 @@ dp_status dp_layers_sqnorm_clip(const dp_layer_desc* layers, int64_t n_layers, i
     };
     // Two or more of them with aligned widths on the direct path: their norms share copy-pipeline launches of up to
     // kJointLayers layers (a launch each is a few hundred workgroups and a tail), the sums join the queue.
-    int64_t n_dj = 0;
-    for (int64_t l = 0; l < n_layers; ++l)
-        if (direct_joinable(B, layers[l].T, layers[l].d_in, layers[l].d_out, dtype, path)) ++n_dj;
-    const bool join_direct = defer_on && n_dj >= 2;
+    std::vector<int64_t> dj;
+    for (int64_t l = 0; defer_on && l < n_layers; ++l)
+        if (direct_joinable(B, layers[l].T, layers[l].d_in, layers[l].d_out, dtype, path)) dj.push_back(l);
+    if (dtype == DP_F32 && dj.size() >= 2) {
+        std::vector<JointShape> sh;
+        for (int64_t l : dj) sh.push_back(JointShape{(int)layers[l].T, (int)layers[l].d_in, (int)layers[l].d_out});
+        std::vector<char> take(dj.size());
+        choose_direct_f32_joint(sh.data(), (int)sh.size(), (int)B, take.data());
+        size_t n = 0;
+        for (size_t k = 0; k < dj.size(); ++k) if (take[k]) dj[n++] = dj[k];
+        dj.resize(n);
+    }
+    const bool join_direct = dj.size() >= 2;
     // (the float32 Gram norms do the same, a class of layers after the other; heaviest first inside a launch)
     std::vector<char> joined;                                // allocated where a layer can be in it
     if (defer_on) joined.resize((size_t)n_layers, 0);
@@ -948,10 +955,7 @@ dp_status dp_layers_sqnorm_clip(const dp_layer_desc* layers, int64_t n_layers, i
         return flush_group();
     };
     if (join_direct) {
-        std::vector<int64_t> which;
-        for (int64_t l = 0; l < n_layers; ++l)
-            if (direct_joinable(B, layers[l].T, layers[l].d_in, layers[l].d_out, dtype, path)) which.push_back(l);
-        const hipError_t e = join(which, [&](const dp_layer_desc& y) { return direct_sums(B, y.T, y.d_in, y.d_out, dtype); },
+        const hipError_t e = join(dj, [&](const dp_layer_desc& y) { return direct_sums(B, y.T, y.d_in, y.d_out, dtype); },
             [&](const JointShape* sh, const JointOperands* op, float* const* part, int n) {
                 return is16(dtype) ? launch_direct_bf16_dma_joint(sh, op, part, n, (int)B, stream, dtype == DP_F16)
                                    : launch_direct_f32_split_joint(sh, op, part, n, (int)B, stream); });

@@ -202,6 +202,8 @@ size_t joint_workspace_floats(const JointShape* sh, int n_layers, int B, int geo
 // big: every layer on 256 x 256 tiles.  The plan of a call is made once and handed to the launch.
 struct F32JointPlan { int splits[kJointLayers], kchunk[kJointLayers], geo[kJointLayers], tiles_m[kJointLayers], tiles_n[kJointLayers]; int64_t items; size_t floats; };
 F32JointPlan plan_joint_f32(const JointShape* sh, int n_layers, int B, bool big, size_t max_floats);
+// which layers of a several-layers call share that launch
+void choose_direct_f32_joint(const JointShape* sh, int n_layers, int B, char* take);
 hipError_t launch_direct_f32_split_joint(const JointShape* sh, const JointOperands* op, float* const* partial, int n_layers,
                                        int B, hipStream_t st);
 hipError_t launch_clipped_f32_split_joint(const JointShape* sh, const JointOperands* op, int n_layers, int B, bool accumulate,

@@ -4,6 +4,8 @@
 // in memory: LDS holds [k][col] and consecutive lanes read consecutive floats.
 // Same two uses as the bf16 file: clipped sum (rows of A scaled by their
 // example's clip factor, exactly, in fp32) and direct squared norm.
+#include <algorithm>
+#include <vector>
 #include "dp_common.h"
 #include "dp_internal.h"
 
@@ -393,22 +395,89 @@ TnPlan plan_clipped_f32(int B, int T, int M, int N) {
     return p;
 }
 
-TnPlan plan_direct_f32(int B, int T, int M, int N) {
+// Which kernel forms a direct norm.  The split kernel (dp_tn_f32_split.hip) walks an example in one workgroup per tile; the
+// fp32 kernel above has smaller tiles, a shorter way from stage to stage, and cuts the positions of few long examples
+// into chunks: B = 1 .. 16, T = 12544, 64 x 128 takes 29 .. 57 us there and 550 us on the split kernel, B = 512 takes 1.2 ms
+// and 1.05 ms.  The two are compared by their times in us, fitted to measurements of 13 shapes of 60 .. 1152 columns,
+// T = 128 .. 12544, B = 1 .. 512 (880 points: what is chosen takes 0.3 % longer than the faster one in the mean):
+//   split   a row of the longest example takes 0.044 us, 0.049 us where the launch has an item for every compute unit, and
+//           more in proportion from two per compute unit on; an item of 128 x 128 counts as one and a half
+//   fp32    rounds of 256 items, 0.022 us a row and 1.7 us an item, rows of unaligned widths up to 1.6 times as long;
+//           in chunks 18 us and the products' time
+// Aligned shapes of 128 x 128 tiles go to the split kernel from T = 256 on.
+namespace {
+bool direct_f32_always_split(int T, int M, int N) {
+    const int64_t pm = (int64_t)ceil_div(M, 128) * 128, pn = (int64_t)ceil_div(N, 128) * 128;
+    return T >= 256 && ((M | N) & 3) == 0 && pm * pn * 3 <= (int64_t)M * N * 4;
+}
+// rows that a layer's items walk
+double direct_f32_split_rows(int B, int T, int M, int N) {
+    const int geo = f32_split_geo(T, M, N, true);
+    const double items = (double)B * ceil_div(M, f32_split_tile_m(geo)) * ceil_div(N, f32_split_tile_n(geo));
+    return items * T * (geo == F32_MID ? 1.5 : 1.0);
+}
+double direct_f32_split_us(double longest, double rows) {
+    const double items = rows / longest;
+    const double row = items <= 256 ? 0.0435 + 0.005 * items / 256 : items <= 512 ? 0.0485 + 0.0275 * (items - 256) / 256 : 0.076 * items / 512;
+    return 6.7 + longest * row;
+}
+TnPlan plan_direct_f32_fp32(int B, int T, int M, int N) {
     TnPlan p;
     p.segmented = false; p.epu = 0; p.big = false; p.dma = false;
-    const int geo = f32_split_geo(T, M, N, true);
-    if (geo != F32_NONE) {
-        p.dma = true;
-        p.tile_m = f32_split_tile_m(geo); p.tile_n = f32_split_tile_n(geo);
-        p.tiles_m = ceil_div(M, p.tile_m); p.tiles_n = ceil_div(N, p.tile_n);
-        p.splits = 1; p.kchunk = 0;
-        return p;
-    }
     p.tile_m = FBM; p.tile_n = FBN;
     p.tiles_m = ceil_div(M, FBM); p.tiles_n = ceil_div(N, FBN);
     p.splits = 1; p.kchunk = 0;
     plan_direct_chunks(p, B, T, M, N, 4, 64);
     return p;
+}
+double direct_f32_fp32_us(int B, int T, int M, int N) {
+    const TnPlan p = plan_direct_f32_fp32(B, T, M, N);
+    const int odd = ((M & 3) != 0) + ((N & 3) != 0);
+    if (p.splits > 1) return 18.0 + (double)B * T * M * N / (odd == 0 ? 4.2e7 : odd == 1 ? 3.1e7 : 2.5e7);
+    const double row = odd == 0 ? 0.0222 : odd == 1 ? 0.030 : 0.0365;
+    return 5.5 + ceil_div((int64_t)B * p.tiles_m * p.tiles_n, 256) * (1.7 + row * T);
+}
+}  // namespace
+
+// Several layers in one launch (every layer has a geometry of the split kernel): take[l] = 0 for the layers that are left
+// to launches of their own.  Those are the longest ones, as many as makes the whole fastest: the launch takes as long
+// as its longest example, and saves the others a launch each.
+void choose_direct_f32_joint(const JointShape* sh, int n_layers, int B, char* take) {
+    std::vector<int> order;
+    double rows = 0.0, fixed = 0.0;                          // fixed: the longest of the layers that stay in any case
+    for (int l = 0; l < n_layers; ++l) {
+        take[l] = 1;
+        rows += direct_f32_split_rows(B, sh[l].T, sh[l].M, sh[l].N);
+        if (direct_f32_always_split(sh[l].T, sh[l].M, sh[l].N)) fixed = std::max(fixed, (double)sh[l].T);
+        else order.push_back(l);
+    }
+    std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return sh[a].T > sh[b].T; });
+    size_t best = 0;
+    double best_us = -1.0, alone = 0.0;
+    for (size_t k = 0; k <= order.size(); ++k) {             // the k longest on their own
+        const double longest = std::max(fixed, k < order.size() ? (double)sh[order[k]].T : 0.0);
+        const double us = alone + (longest > 0.0 ? direct_f32_split_us(longest, rows) : 0.0);
+        if (best_us < 0.0 || us < best_us) { best_us = us; best = k; }
+        if (k == order.size()) break;
+        const JointShape& s = sh[order[k]];
+        alone += direct_f32_fp32_us(B, s.T, s.M, s.N);
+        rows -= direct_f32_split_rows(B, s.T, s.M, s.N);
+    }
+    for (size_t k = 0; k < best; ++k) take[order[k]] = 0;
+}
+
+TnPlan plan_direct_f32(int B, int T, int M, int N) {
+    const int geo = f32_split_geo(T, M, N, true);
+    if (geo != F32_NONE && (direct_f32_always_split(T, M, N) ||
+                            direct_f32_split_us(T, direct_f32_split_rows(B, T, M, N)) <= direct_f32_fp32_us(B, T, M, N))) {
+        TnPlan p;
+        p.segmented = false; p.epu = 0; p.big = false; p.dma = true;
+        p.tile_m = f32_split_tile_m(geo); p.tile_n = f32_split_tile_n(geo);
+        p.tiles_m = ceil_div(M, p.tile_m); p.tiles_n = ceil_div(N, p.tile_n);
+        p.splits = 1; p.kchunk = 0;
+        return p;
+    }
+    return plan_direct_f32_fp32(B, T, M, N);
 }
 
 hipError_t launch_clipped_f32(const TnPlan& p, const float* A, const float* G, const float* clip,

@@ -490,8 +490,8 @@ hipError_t launch_tn_f32_split(int mode, const TnPlan& p, const float* A, const 
     return hipGetLastError();
 }
 
-// Several layers' direct norms in one launch; partial[l]: the layer's [B][tiles of plan_direct_f32] sums of squares, to be
-// added by the caller.  Every layer: plan_direct_f32 chooses this kernel.
+// Several layers' direct norms in one launch; partial[l]: the layer's [B][tiles of f32_split_geo] sums of squares, to be
+// added by the caller.  Every layer: f32_split_geo has a geometry for it.
 hipError_t launch_direct_f32_split_joint(const JointShape* sh, const JointOperands* op, float* const* partial, int n_layers,
                                        int B, hipStream_t st) {
     if (n_layers < 1 || n_layers > kJointLayers) return hipErrorInvalidValue;
@@ -502,10 +502,9 @@ hipError_t launch_direct_f32_split_joint(const JointShape* sh, const JointOperan
         y.A = reinterpret_cast<const float*>(op[l].A); y.G = reinterpret_cast<const float*>(op[l].G); y.clip = nullptr;
         y.out = partial[l]; y.accumulate = 0;
         y.K = B * sh[l].T; y.T = sh[l].T; y.M = sh[l].M; y.N = sh[l].N;
-        const TnPlan p = plan_direct_f32(B, sh[l].T, sh[l].M, sh[l].N);
-        y.tiles_m = p.tiles_m; y.tiles_n = p.tiles_n;
         y.geo = f32_split_geo(sh[l].T, sh[l].M, sh[l].N, true);
         if (y.geo == F32_NONE) return hipErrorInvalidValue;
+        y.tiles_m = ceil_div(sh[l].M, f32_split_tile_m(y.geo)); y.tiles_n = ceil_div(sh[l].N, f32_split_tile_n(y.geo));
         y.splits = B; y.kchunk = sh[l].T;
         y.first_item = (int)first;
         first += ceil_div((int64_t)y.tiles_m * y.tiles_n * B, 8);

@@ -275,6 +275,17 @@ def test_float32_plans_cost_no_more_than_16_bit_ones(lib):
     assert f32 < 2 * b16, (f32, b16)
 
 
+def test_few_long_examples_are_cut_into_chunks(lib):
+    """Host logic only: the float32 direct norm of a few long examples of a narrow layer keeps the chunks' shares of A_i^T G_i
+    in its scratch; one workgroup per example and tile would walk thousands of rows on an empty chip."""
+    for B in (1, 4, 16):
+        for T, d_in, d_out in ((12544, 64, 128), (3136, 256, 64), (12544, 577, 61), (3136, 63, 127)):
+            need = dpclip.workspace_bytes(dpclip.DP_OP_SQNORM, B, T, d_in, d_out, dpclip.DP_F32, "direct")
+            assert need > 2 * B * d_in * d_out * 4, (B, T, d_in, d_out)
+    # enough examples to fill the chip: one float per (example, tile)
+    assert dpclip.workspace_bytes(dpclip.DP_OP_SQNORM, 512, 3136, 64, 128, dpclip.DP_F32, "direct") == 512 * 4
+
+
 def test_noise_layout_gives_every_gradient_its_own_stretch():
     """Host logic only: the default positions in the noise stream (weights back to back, then the biases) are pairwise
     disjoint, also next to weight offsets given by the caller; overlapping offsets are refused.  Independent noise

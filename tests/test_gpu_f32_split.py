@@ -57,6 +57,18 @@ def test_norms(path, T, d_in, d_out):
     assert float(((s.double() - ref) / ref).abs().max()) < REL
 
 
+@pytest.mark.parametrize("B,shapes", [
+    (1, [(12544, 64, 128)]), (17, [(3136, 63, 127)]), (300, [(1030, 64, 128)]), (40, [(1100, 577, 61)]), (130, [(196, 128, 128)]),
+    (3, [(12544, 64, 128), (3136, 128, 256), (784, 256, 512)]), (3, [(784, 64, 128), (128, 128, 64)]), (65, [(784, 576, 64), (196, 576, 64)]),
+    (2, [(1600, 96, 64)] * 2 + [(700, 250, 60)] * 3), (20, [(1024, 64, 128)] * 18)])
+def test_direct_norms_on_either_side_of_the_choice(B, shapes):
+    """Layers on the split kernel and on the fp32 one, alone and in a shared launch that leaves the long ones out."""
+    layers = [_data(B, T, a, b, 11 + i)[:2] for i, (T, a, b) in enumerate(shapes)]
+    s = dp.layers_sqnorm(layers, path="direct")
+    ref = sum(_norm64(A, G) for A, G in layers)
+    assert float(((s.double() - ref) / ref).abs().max()) < REL
+
+
 @pytest.mark.parametrize("B", [1, 7, 8, 19])
 @pytest.mark.parametrize("kind", ["gram", "direct"])
 def test_layers_of_one_launch(B, kind):
