@@ -2,9 +2,9 @@
 // operand split into three bf16 numbers (dp_split.h): the rate of the fp32 MFMA (157 TFLOP/s nominal) bounded these
 // sums, six bf16 products have 2.7 times that.
 //   * The workgroup splits each element once, on its way into LDS: a thread loads the 8 rows of K of one column
-//     (4-byte loads, 64 consecutive columns per wave), so that the packed halves are the MFMA operand as it stands,
-//     16 bytes that go to LDS with one write per part and are read back with one read per fragment, both
-//     without bank conflicts.  4-byte loads also take any width and alignment.
+//     (4-byte loads, 64 consecutive columns per wave; 4 rows of the operand of 64 columns), so that the packed halves are
+//     the MFMA operand as it stands, 16 bytes that go to LDS with one write per part and are read back with one read
+//     per fragment, both without bank conflicts.  4-byte loads also take any width and alignment.
 //   * 16-row stages, two in LDS; the loads of the stage after next wait in registers, one barrier per stage.
 //   * The clip factors of a stage's rows are the same for a whole wave: scalar loads, multiplied into the A values
 //     before the split (the same a * c rounded once to float32 as in the row-scaling kernels; the split's scale is in
@@ -27,8 +27,9 @@ template <int MI_, int NI_, int WM_, int WN_> struct GeoF {
     static constexpr int MI = MI_, NI = NI_, WM = WM_, WN = WN_;
     static constexpr int TM = WM * MI * 32, TN = WN * NI * 32, THREADS = 64 * WM * WN;
     static constexpr int STAGE_UNITS = 2 * 3 * (TM + TN);      // 16-byte units: [part][k / 8][column], A then G
-    // one column of A and of G per thread (a narrower operand is loaded twice, with the same values)
-    static_assert(TM * 2 <= THREADS && TN * 2 <= THREADS && TM % 64 == 0 && TN % 64 == 0, "");
+    // one column of A and of G per thread, 2 PA and 2 PG rows of it: two or four threads take a column
+    static constexpr int PA = 8 * TM / THREADS, PG = 8 * TN / THREADS;
+    static_assert((PA == 4 || PA == 2) && (PG == 4 || PG == 2) && TM % 64 == 0 && TN % 64 == 0, "");
 };
 using GeoBig = GeoF<4, 2, 2, 4>;        // 256 x 256, 8 waves
 using GeoMid = GeoF<2, 2, 2, 2>;        // 128 x 128, 4 waves, as the next two: layers of these three share a launch
@@ -86,7 +87,7 @@ __device__ __forceinline__ void tn_f32_exact(const F32SplitArgs& a, int k_begin,
 // item L of the launch: (slice, tile), slice-major
 template <int MODE, class GEO>
 __device__ __forceinline__ void tn_f32_split_tile(const F32SplitArgs& a, const int L, u32x4* lds) {
-    constexpr int MI = GEO::MI, NI = GEO::NI, TM = GEO::TM, TN = GEO::TN, SU = GEO::STAGE_UNITS;
+    constexpr int MI = GEO::MI, NI = GEO::NI, TM = GEO::TM, TN = GEO::TN, SU = GEO::STAGE_UNITS, PA = GEO::PA, PG = GEO::PG;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int tiles = a.tiles_m * a.tiles_n;
@@ -102,32 +103,32 @@ __device__ __forceinline__ void tn_f32_split_tile(const F32SplitArgs& a, const i
     const int n_stages = (k_end - k_begin + DKF - 1) / DKF;
     if (n_stages <= 0) return;
 
-    // ---- global -> registers -> LDS: thread t moves rows 8 kg .. 8 kg + 7 of the stage, one column of either operand.
-    //      kgA and kgG are the same for a whole wave.  Columns outside the matrix only feed outputs that are never stored.
-    const int kgA = __builtin_amdgcn_readfirstlane((tid / TM) & 1), kgG = __builtin_amdgcn_readfirstlane((tid / TN) & 1);
-    const uint32_t wrA = (uint32_t)(kgA * TM + tid % TM), wrG = (uint32_t)(6 * TM + kgG * TN + tid % TN);   // units of part 0
+    // ---- global -> registers -> LDS: a thread moves rows r0 .. r0 + 2 P - 1 of the stage, one column of either operand.
+    //      r0A and r0G are the same for a whole wave.  Columns outside the matrix only feed outputs that are never stored.
+    const int r0A = __builtin_amdgcn_readfirstlane(tid / TM) * (2 * PA), r0G = __builtin_amdgcn_readfirstlane(tid / TN) * (2 * PG);
+    const uint32_t wrA = (uint32_t)((r0A >> 3) * TM + tid % TM), wrG = (uint32_t)(6 * TM + (r0G >> 3) * TN + tid % TN);   // units of part 0
     // buffer loads: a row past the end of the slice lies outside the buffer and comes back as zero
     const uint32_t rowA = (uint32_t)a.M * 4u, rowG = (uint32_t)a.N * 4u;
     const uint32_t offA = (uint32_t)min(m0 + tid % TM, a.M - 1) * 4u, offG = (uint32_t)min(n0 + tid % TN, a.N - 1) * 4u;
-    float ra[8], rg[8], rc = 1.0f;
-    // lane l: the factor of row l % 8 of the wave's rows of the stage
+    float ra[2 * PA], rg[2 * PG], rc = 1.0f;
+    // lane l: the factor of row l % (2 PA) of the wave's rows of the stage
     int fex = 0, fpos = 0;                               // example and position inside it of that row, next stage
     const int last_ex = MODE == 0 ? (k_end - 1) / a.T : 0;
-    if (MODE == 0) { fex = (k_begin + 8 * kgA + (lane & 7)) / a.T; fpos = (k_begin + 8 * kgA + (lane & 7)) - fex * a.T; }
+    if (MODE == 0) { const int row = k_begin + r0A + (lane & (2 * PA - 1)); fex = row / a.T; fpos = row - fex * a.T; }
     const int adv_ex = DKF / a.T, adv_pos = DKF - adv_ex * a.T;
-    int next_a = k_begin + 8 * kgA, next_g = k_begin + 8 * kgG;
+    int next_a = k_begin + r0A, next_g = k_begin + r0G;
     // The MFMA rounds its sums down, which in long sums of random sign adds up (K = 65536: 5.6e-7 of the result): every other
     // stage is formed with the sign of A turned and subtracted, so that the two errors cancel.
     float sign_a = 1.0f;                                 // of the next stage to fetch
     auto fetch = [&](bool of_a) {                        // one operand of the next stage; A first
         const int next_row = of_a ? next_a : next_g;
-        const int rows = __builtin_amdgcn_readfirstlane(max(0, min(8, k_end - next_row)));
+        const int rows = __builtin_amdgcn_readfirstlane(max(0, min(of_a ? 2 * PA : 2 * PG, k_end - next_row)));
         uint32_t off = of_a ? offA : offG;
         asm volatile("" : "+v"(off));                    // 16 offsets kept from stage to stage would not fit the registers
         if (of_a) {
             const auto buf = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.A + (size_t)next_row * a.M), (short)0, (int)(rows * rowA), 0x00020000);
 #pragma unroll
-            for (int j = 0; j < 8; ++j, off += rowA) ra[j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(buf, off, 0, 0));
+            for (int j = 0; j < 2 * PA; ++j, off += rowA) ra[j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(buf, off, 0, 0));
             if (MODE == 0) {
                 rc = a.clip[min(fex, last_ex)] * (sign_a * kSplitScale);
                 sign_a = -sign_a;
@@ -139,16 +140,17 @@ __device__ __forceinline__ void tn_f32_split_tile(const F32SplitArgs& a, const i
         }
         const auto buf = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.G + (size_t)next_row * a.N), (short)0, (int)(rows * rowG), 0x00020000);
 #pragma unroll
-        for (int j = 0; j < 8; ++j, off += rowG) rg[j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(buf, off, 0, 0));
+        for (int j = 0; j < 2 * PG; ++j, off += rowG) rg[j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(buf, off, 0, 0));
         next_g += DKF;
     };
-    // the split in eight steps, rows 2 q and 2 q + 1: of A for pair 0 .. 3, of G for pair 4 .. 7; the last of either
-    // writes the operand's parts to LDS and requests its rows of the stage after
+    // the split in PA + PG steps, rows 2 q and 2 q + 1 of A, then of G; the last of either writes the operand's parts to
+    // LDS and requests its rows of the stage after
     u32x4 parts[3];
     auto split_step = [&](int pair, int buf) {
-        const int q = pair & 3;
+        const bool of_a = pair < PA;
+        const int q = of_a ? pair : pair - PA;
         float x0, x1;
-        if (pair < 4) {
+        if (of_a) {
             x0 = ra[2 * q]; x1 = ra[2 * q + 1];
             if (MODE == 0) {
                 x0 *= __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(rc), 2 * q));
@@ -158,10 +160,14 @@ __device__ __forceinline__ void tn_f32_split_tile(const F32SplitArgs& a, const i
         uint32_t p1, p2, p3;
         split2(x0, x1, p1, p2, p3);
         parts[0][q] = p1; parts[1][q] = p2; parts[2][q] = p3;
-        if (q == 3) {
+        if (q == (of_a ? PA : PG) - 1) {
 #pragma unroll
-            for (int p = 0; p < 3; ++p) lds[buf * SU + (pair < 4 ? p * 2 * TM + wrA : p * 2 * TN + wrG)] = parts[p];
-            fetch(pair < 4);
+            for (int p = 0; p < 3; ++p) {
+                u32x4* to = lds + (buf * SU + (of_a ? p * 2 * TM + wrA : p * 2 * TN + wrG));
+                if ((of_a ? PA : PG) == 4) *to = parts[p];
+                else reinterpret_cast<uint2*>(to)[((of_a ? r0A : r0G) >> 2) & 1] = make_uint2(parts[p][0], parts[p][1]);
+            }
+            fetch(of_a);
         }
     };
 
@@ -182,14 +188,14 @@ __device__ __forceinline__ void tn_f32_split_tile(const F32SplitArgs& a, const i
     fetch(true);
     fetch(false);
 #pragma unroll
-    for (int q = 0; q < 8; ++q) split_step(q, 0);
+    for (int q = 0; q < PA + PG; ++q) split_step(q, 0);
     __builtin_amdgcn_s_waitcnt(0xC07F);
     __builtin_amdgcn_s_barrier();
     // Past the end of the slice the copies bring zeros, which nobody reads: the loop has no branches.  One 32 x 32 tile
     // of the wave after the other: its six MFMAs, in their shadow a share of the next stage's split and the addition
     // of the tile before.  (With the split in front of all MFMAs the two add up: the waves of a workgroup are in step.)
-    constexpr int TILES = MI * NI, STEPS = 8 / TILES;
-    static_assert(TILES * STEPS == 8, "");
+    constexpr int TILES = MI * NI, STEPS = (PA + PG) / TILES;
+    static_assert(TILES * STEPS == PA + PG, "");
     f32x16 pend = {};                                    // the sums of the tile before, not yet added
     // The 4-wave geometries have registers for sums in two levels, blocks of 8 stages and their sum: a little of the
     // rounding error of long sums (64 -> 432, B = 42257: 5.2e-7 of the result to 4.9e-7; the turned signs take the rest).
