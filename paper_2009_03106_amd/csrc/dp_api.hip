@@ -193,7 +193,7 @@ int clipped_join_class(int64_t B, int64_t T, int64_t d_in, int64_t d_out, dp_dty
     if (!is16(dtype)) {
         // float32: the layers of the copy-pipeline kernel (long contractions, widths multiples of 4) share launches too
         if (B * T >= (int64_t(1) << 31)) return 0;
-        const int geo = clipped_f32_route(B * T, (int)d_in, (int)d_out).geo;
+        const int geo = clipped_f32_split_geo(B * T, (int)d_in, (int)d_out);
         if (geo == F32_NONE || ((d_in * d_out) & 3) != 0) return 0;     // the shared fold takes four entries at a time
         return geo == F32_BIG ? 6 : 5;
     }
@@ -213,7 +213,18 @@ size_t joint_ws_bytes(const JointShape* sh, int n, int64_t B, dp_dtype dtype, in
 }
 std::vector<int> clipped_join_classes(const dp_layer_desc* layers, int64_t n_layers, int64_t B, dp_dtype dtype) {
     std::vector<int> cls((size_t)n_layers);
-    for (int64_t l = 0; l < n_layers; ++l) cls[(size_t)l] = clipped_join_class(B, layers[l].T, layers[l].d_in, layers[l].d_out, dtype);
+    double small = 0.0;                                  // products of the float32 layers that a short-contraction launch could take
+    for (int64_t l = 0; l < n_layers; ++l) {
+        const dp_layer_desc& y = layers[l];
+        cls[(size_t)l] = clipped_join_class(B, y.T, y.d_in, y.d_out, dtype);
+        if (cls[(size_t)l] >= 5 && B * y.T <= kShortK) small += (double)B * y.T * y.d_in * y.d_out;
+    }
+    // those share the split launch only where they fill it: two of 2304 x 512 from 256 rows (6e8) take 21 us in a
+    // short-contraction launch and 32 us there, two of 844 x 1664 from 384 (1.1e9) 34 and 39, from 512 (1.4e9) 43 and 43,
+    // four of 2304 x 512 from 256 (1.2e9) 39 and 32
+    if (small > 0.0 && small < 1.2e9)
+        for (int64_t l = 0; l < n_layers; ++l)
+            if (cls[(size_t)l] >= 5 && B * layers[l].T <= kShortK) cls[(size_t)l] = 0;
     return cls;
 }
 // which layers' gradients overlap another's (empty: none do)
@@ -1285,12 +1296,23 @@ dp_status dp_layers_clipped_grad_noise(const dp_layer_desc* layers, int64_t n_la
     const std::vector<char> shared = shared_gradients(layers, n_layers);
     auto shared_grad = [&](int64_t l) { return !shared.empty() && shared[(size_t)l]; };
     const std::vector<int> cls = clipped_join_classes(layers, n_layers, B, dtype);
+    auto one_narrow_tile = [&](int64_t l) {              // that clipped_f32_route leaves to the fp32 kernel
+        const dp_layer_desc& y = layers[l];
+        const ClippedF32Route r = clipped_f32_route(B * y.T, (int)y.d_in, (int)y.d_out);
+        return !r.is_short && r.geo == F32_NONE && y.d_in <= 128 && y.d_out <= 128;
+    };
     struct JointGroup { std::vector<int64_t> layer; int geo; size_t max_floats; F32JointPlan plan; };   // max_floats: the most that its slices may take
     std::vector<JointGroup> joint_groups;
     for (int geo : {1, 3, 4, 5, 6}) {
         std::vector<int64_t> cur;
         int in_query = 0;                                    // layers of the query's group so far
         auto end_group = [&]() {
+            // (two float32 layers of one 64-column tile each are as fast alone up to 5e5 rows: 64 x 128 twice from 25000 26 us,
+            // in one launch 31, from 400000 173 and 154; three or more gain from one launch everywhere)
+            if (cur.size() == 2 && geo == 5 && one_narrow_tile(cur[0]) && one_narrow_tile(cur[1])) {
+                const int64_t rows = B * (layers[cur[0]].T + layers[cur[1]].T);
+                if (rows >= 28000 && rows <= 500000) cur.clear();
+            }
             if (cur.size() < 2) { cur.clear(); in_query = 0; return; }
             joint_groups.push_back(JointGroup{cur, geo, kAnySlices, {}});
             JointGroup& group = joint_groups.back();
@@ -1364,7 +1386,7 @@ dp_status dp_layers_clipped_grad_noise(const dp_layer_desc* layers, int64_t n_la
         for (int64_t l = 0; l < n_layers; ++l) {
             const dp_layer_desc& y = layers[l];
             if (y.T == 0 || y.d_in == 0 || y.d_out == 0) continue;
-            if (!clipped_f32_route(B * y.T, (int)y.d_in, (int)y.d_out).is_short || shared_grad(l)) continue;
+            if (done[(size_t)l] || !clipped_f32_route(B * y.T, (int)y.d_in, (int)y.d_out).is_short || shared_grad(l)) continue;
             which[nb] = l;
             batch[nb++] = ShortLayerDesc{static_cast<const float*>(y.A), static_cast<const float*>(y.G), y.clip ? y.clip : clip, y.grad,
                                          (int)y.T, (int)y.d_in, (int)y.d_out};

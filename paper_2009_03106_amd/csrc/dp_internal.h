@@ -107,6 +107,8 @@ void plan_direct_chunks(TnPlan& p, int B, int T, int M, int N, int esize, int st
 hipError_t launch_direct_chunks_finish(const float* shares, int64_t slice, int S, int n, int B, float* sums, hipStream_t st);
 TnPlan plan_clipped_bf16(int B, int T, int M, int N);
 TnPlan plan_clipped_f32(int B, int T, int M, int N);
+constexpr int kShortK = 512;            // the float32 short-contraction kernel takes up to this many rows
+int clipped_f32_split_geo(int64_t K, int M, int N);
 // how that plan takes a sum of K rows: the short-contraction kernel, else the split kernel with this geometry, or
 // F32_NONE: the kernel of the fp32 instruction
 struct ClippedF32Route { bool is_short; int geo; };

@@ -310,9 +310,6 @@ __global__ __launch_bounds__(kThreads) void k_tn_f32_short_layers(TnShortLayers 
     tn_f32_short_dispatch(a, (int)blockIdx.x - t.first_tile[li], sA, sG, part);
 }
 
-// the short-contraction kernel takes K up to this many rows
-constexpr int kShortK = 512;
-
 template <int MODE, int FBK> void launch_f32_k(bool veca, bool vecg, dim3 grid, const TnArgsF& a, hipStream_t st) {
     if (veca) { if (vecg) k_tn_f32<MODE, FBK, true, true><<<grid, kThreads, 0, st>>>(a); else k_tn_f32<MODE, FBK, true, false><<<grid, kThreads, 0, st>>>(a); }
     else      { if (vecg) k_tn_f32<MODE, FBK, false, true><<<grid, kThreads, 0, st>>>(a); else k_tn_f32<MODE, FBK, false, false><<<grid, kThreads, 0, st>>>(a); }
@@ -324,13 +321,35 @@ template <int MODE> void launch_f32(bool deep, bool veca, bool vecg, dim3 grid, 
 
 }  // namespace
 
+// The geometry on which a layer's sum can run on the split kernel.  Up to kShortK rows only outputs of at least 64 tiles
+// of 128 x 128, which fill the chip without K slices.
+int clipped_f32_split_geo(int64_t K, int M, int N) {
+    if (K >= (int64_t(1) << 31)) return F32_NONE;
+    if (K <= kShortK && (int64_t)ceil_div(M, 128) * ceil_div(N, 128) < 64) return F32_NONE;
+    return f32_split_geo(K, M, N, false);
+}
+
+// Where the split kernel is the faster one for a layer by itself, in products K M N (us, fp32 kernels / split):
+//   up to kShortK rows from 1e9:  844 x 1664 from 384 20 / 29, 768 x 2304 from 512 28 / 34; 4608 x 512 from 512 37 / 36,
+//                                 2000 x 2000 from 256 35 / 33
+//   sizes whose fold is scalar, whose loads the fp32 kernel makes one by one, from 1.5e8:  63 x 127 from 12500 33 / 34,
+//                                 from 25000 53 / 45
+//   aligned shapes of 128 x 128 tiles always: 128 x 128 from 520 29 / 15 (the kernel it replaced)
+//   one aligned tile of 64 columns never: 64 x 128 from 25000 14 / 18, from 100000 31 / 32, from 400000 90 / 97
+//   others from 6e8:              576 x 64 from 6000 14 / 19, from 25000 31 / 32, from 50000 52 / 48
 ClippedF32Route clipped_f32_route(int64_t K, int M, int N) {
-    // From 256 rows on, outputs of at least 64 tiles of 128 x 128 fill the chip without K slices: 512 rows of 4608 x 512
-    // take 42 us on 32 x 32 tiles of the fp32 instruction.
-    const int geo = K < (int64_t(1) << 31) ? f32_split_geo(K, M, N, false) : F32_NONE;
-    const bool wide = geo != F32_NONE && (int64_t)ceil_div(M, 128) * ceil_div(N, 128) >= 64;
-    if (K <= kShortK && !wide) return ClippedF32Route{true, F32_NONE};
-    return ClippedF32Route{false, geo};
+    const int geo = clipped_f32_split_geo(K, M, N);
+    const double products = (double)K * M * N;
+    if (K <= kShortK) return geo != F32_NONE && products >= 1e9 ? ClippedF32Route{false, geo} : ClippedF32Route{true, F32_NONE};
+    if (geo == F32_NONE) return ClippedF32Route{false, F32_NONE};
+    const bool aligned = ((M | N) & 3) == 0;
+    const int64_t pm = (int64_t)ceil_div(M, 128) * 128, pn = (int64_t)ceil_div(N, 128) * 128;
+    bool split;
+    if (aligned && pm * pn * 3 <= (int64_t)M * N * 4) split = true;
+    else if ((((int64_t)M * N) & 3) != 0) split = products >= 1.5e8;
+    else if (aligned && M <= f32_split_tile_m(geo) && N <= f32_split_tile_n(geo)) split = false;
+    else split = products >= 6e8;
+    return ClippedF32Route{false, split ? geo : F32_NONE};
 }
 
 TnPlan plan_clipped_f32(int B, int T, int M, int N) {

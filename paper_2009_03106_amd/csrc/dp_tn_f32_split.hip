@@ -369,7 +369,7 @@ F32JointPlan plan_joint_f32(const JointShape* sh, int n_layers, int B, bool big,
     uint32_t stages_max = 1;
     for (int l = 0; l < n_layers; ++l) {
         const int64_t K = (int64_t)B * sh[l].T, entries = (int64_t)sh[l].M * sh[l].N;
-        p.geo[l] = big ? F32_BIG : f32_split_geo(K, sh[l].M, sh[l].N, false);
+        p.geo[l] = big ? F32_BIG : clipped_f32_split_geo(K, sh[l].M, sh[l].N);
         p.tiles_m[l] = ceil_div(sh[l].M, f32_split_tile_m(p.geo[l])); p.tiles_n[l] = ceil_div(sh[l].N, f32_split_tile_n(p.geo[l]));
         const uint32_t stages = (uint32_t)ceil_div(K, DKF);
         const bool half = p.geo[l] == F32_NARROW || p.geo[l] == F32_FLAT;

@@ -69,6 +69,29 @@ def test_direct_norms_on_either_side_of_the_choice(B, shapes):
     assert float(((s.double() - ref) / ref).abs().max()) < REL
 
 
+@pytest.mark.parametrize("B,shapes", [
+    (384, [(1, 844, 1664)]), (512, [(1, 844, 1664)] * 2), (500, [(1, 4608, 512)]), (256, [(1, 2304, 512)] * 2 + [(1, 64, 30)]), (256, [(1, 2304, 512)] * 4),
+    (12500, [(1, 63, 127)]), (25000, [(1, 63, 127)]), (6000, [(1, 576, 64)]), (20000, [(1, 576, 64)]), (14100, [(1, 64, 128)] * 2),
+    (9000, [(1, 64, 128)] * 2), (9000, [(1, 64, 128), (1, 96, 64), (1, 128, 128)]), (400, [(2, 126, 62), (1, 600, 1030)]), (1031, [(1, 600, 1030)])])
+@pytest.mark.parametrize("noise", [0.0, 1.0])
+def test_clipped_sums_on_either_side_of_the_choice(B, shapes, noise):
+    """Layers on the split kernel and on the fp32 ones, alone and beside each other."""
+    layers = [_data(B, T, a, b, 31 + i)[:2] for i, (T, a, b) in enumerate(shapes)]
+    grads = [torch.ones((a, b), device="cuda") for _, a, b in shapes]
+    clip = torch.rand(B, device="cuda") + 0.25
+    descs = dp.layer_descs(layers, grads)
+    dp.layers_clipped_grad(layers, clip, grads, accumulate=True, descs=descs, noise_std=noise, seed=3)
+    off = 0
+    for (A, G), g in zip(layers, grads):
+        ref = _sum64(A, G, clip) + 1.0
+        if noise:
+            z = torch.zeros_like(g)
+            dp.add_noise(z, noise, 3, off)
+            ref = ref + z
+        off += g.numel()
+        assert _rel(g, ref) < REL
+
+
 @pytest.mark.parametrize("B", [1, 7, 8, 19])
 @pytest.mark.parametrize("kind", ["gram", "direct"])
 def test_layers_of_one_launch(B, kind):
