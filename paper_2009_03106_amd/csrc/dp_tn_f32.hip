@@ -416,10 +416,10 @@ TnPlan plan_clipped_f32(int B, int T, int M, int N) {
 
 // Which kernel forms a direct norm.  The split kernel (dp_tn_f32_split.hip) walks an example in one workgroup per tile; the
 // fp32 kernel above has smaller tiles, a shorter way from stage to stage, and cuts the positions of few long examples
-// into chunks: B = 1 .. 16, T = 12544, 64 x 128 takes 29 .. 57 us there and 550 us on the split kernel, B = 512 takes 1.2 ms
-// and 1.05 ms.  The two are compared by their times in us, fitted to measurements of 13 shapes of 60 .. 1152 columns,
+// into chunks: B = 1 .. 16, T = 12544, 64 x 128 takes 29 .. 57 us there and 510 us on the split kernel, B = 512 takes 1.2 ms
+// and 0.95 ms.  The two are compared by their times in us, fitted to measurements of 13 shapes of 60 .. 1152 columns,
 // T = 128 .. 12544, B = 1 .. 512 (880 points: what is chosen takes 0.3 % longer than the faster one in the mean):
-//   split   a row of the longest example takes 0.044 us, 0.049 us where the launch has an item for every compute unit, and
+//   split   a row of the longest example takes 0.041 us, 0.045 us where the launch has an item for every compute unit, and
 //           more in proportion from two per compute unit on; an item of 128 x 128 counts as one and a half
 //   fp32    rounds of 256 items, 0.022 us a row and 1.7 us an item, rows of unaligned widths up to 1.6 times as long;
 //           in chunks 18 us and the products' time
@@ -437,8 +437,8 @@ double direct_f32_split_rows(int B, int T, int M, int N) {
 }
 double direct_f32_split_us(double longest, double rows) {
     const double items = rows / longest;
-    const double row = items <= 256 ? 0.0435 + 0.005 * items / 256 : items <= 512 ? 0.0485 + 0.0275 * (items - 256) / 256 : 0.076 * items / 512;
-    return 6.7 + longest * row;
+    const double row = items <= 256 ? 0.041 + 0.004 * items / 256 : items <= 512 ? 0.045 + 0.028 * (items - 256) / 256 : 0.073 * items / 512;
+    return 6.2 + longest * row;
 }
 TnPlan plan_direct_f32_fp32(int B, int T, int M, int N) {
     TnPlan p;

@@ -120,15 +120,17 @@ __device__ __forceinline__ void tn_f32_split_tile(const F32SplitArgs& a, const i
     // The MFMA rounds its sums down, which in long sums of random sign adds up (K = 65536: 5.6e-7 of the result): every other
     // stage is formed with the sign of A turned and subtracted, so that the two errors cancel.
     float sign_a = 1.0f;                                 // of the next stage to fetch
-    auto fetch = [&](bool of_a) {                        // one operand of the next stage; A first
+    uint32_t at_a = 0, at_g = 0;
+    auto fetch = [&](bool of_a, int q) {                 // rows 2 q and 2 q + 1 of one operand of the next stage, in order of q
         const int next_row = of_a ? next_a : next_g;
         const int rows = __builtin_amdgcn_readfirstlane(max(0, min(of_a ? 2 * PA : 2 * PG, k_end - next_row)));
-        uint32_t off = of_a ? offA : offG;
-        asm volatile("" : "+v"(off));                    // 16 offsets kept from stage to stage would not fit the registers
         if (of_a) {
+            if (q == 0) at_a = offA;
+            asm volatile("" : "+v"(at_a));               // 16 offsets kept from stage to stage would not fit the registers
             const auto buf = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.A + (size_t)next_row * a.M), (short)0, (int)(rows * rowA), 0x00020000);
-#pragma unroll
-            for (int j = 0; j < 2 * PA; ++j, off += rowA) ra[j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(buf, off, 0, 0));
+            ra[2 * q] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(buf, at_a, 0, 0)); at_a += rowA;
+            ra[2 * q + 1] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(buf, at_a, 0, 0)); at_a += rowA;
+            if (q < PA - 1) return;
             if (MODE == 0) {
                 rc = a.clip[min(fex, last_ex)] * (sign_a * kSplitScale);
                 sign_a = -sign_a;
@@ -138,13 +140,15 @@ __device__ __forceinline__ void tn_f32_split_tile(const F32SplitArgs& a, const i
             next_a += DKF;
             return;
         }
+        if (q == 0) at_g = offG;
+        asm volatile("" : "+v"(at_g));
         const auto buf = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.G + (size_t)next_row * a.N), (short)0, (int)(rows * rowG), 0x00020000);
-#pragma unroll
-        for (int j = 0; j < 2 * PG; ++j, off += rowG) rg[j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(buf, off, 0, 0));
-        next_g += DKF;
+        rg[2 * q] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(buf, at_g, 0, 0)); at_g += rowG;
+        rg[2 * q + 1] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(buf, at_g, 0, 0)); at_g += rowG;
+        if (q == PG - 1) next_g += DKF;
     };
-    // the split in PA + PG steps, rows 2 q and 2 q + 1 of A, then of G; the last of either writes the operand's parts to
-    // LDS and requests its rows of the stage after
+    // the split in PA + PG steps, rows 2 q and 2 q + 1 of A, then of G; each requests its rows of the stage after, the last of
+    // either writes the operand's parts to LDS
     u32x4 parts[3];
     auto split_step = [&](int pair, int buf) {
         const bool of_a = pair < PA;
@@ -167,8 +171,8 @@ __device__ __forceinline__ void tn_f32_split_tile(const F32SplitArgs& a, const i
                 if ((of_a ? PA : PG) == 4) *to = parts[p];
                 else reinterpret_cast<uint2*>(to)[((of_a ? r0A : r0G) >> 2) & 1] = make_uint2(parts[p][0], parts[p][1]);
             }
-            fetch(of_a);
         }
+        fetch(of_a, q);                                  // in the place of the two that were split
     };
 
     // ---- LDS -> MFMA operands: lane (lrow, lhalf) takes column lrow of a 32-wide block and rows 8 lhalf .. 8 lhalf + 7
@@ -185,8 +189,10 @@ __device__ __forceinline__ void tn_f32_split_tile(const F32SplitArgs& a, const i
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
-    fetch(true);
-    fetch(false);
+#pragma unroll
+    for (int q = 0; q < PA; ++q) fetch(true, q);
+#pragma unroll
+    for (int q = 0; q < PG; ++q) fetch(false, q);
 #pragma unroll
     for (int q = 0; q < PA + PG; ++q) split_step(q, 0);
     __builtin_amdgcn_s_waitcnt(0xC07F);
