@@ -128,6 +128,9 @@ int gram_cols_class(int64_t B, int64_t T, int64_t d_in, int64_t d_out, dp_dtype 
 
 size_t round16(size_t n) { return (n + 15) & ~size_t(15); }
 
+// A launch holds fewer than 2^32 threads, 2^24 workgroups of 256: the layers of a shared norm launch have at most this
+// many items together (every layer's are rounded up to eight times a whole number).
+constexpr int64_t kJointItems = (int64_t(1) << 24) - 8 * kJointLayers;
 // sums per example of a layer's direct norm in a shared launch: one per 128 x 128 tile, float32: per tile of its geometry
 int direct_sums(int64_t B, int64_t T, int64_t d_in, int64_t d_out, dp_dtype dtype) {
     if (is16(dtype)) return direct_joint_tiles((int)d_in, (int)d_out);
@@ -144,13 +147,13 @@ bool direct_joinable(int64_t B, int64_t T, int64_t d_in, int64_t d_out, dp_dtype
         if (B * T >= (int64_t(1) << 31)) return false;
         if (f32_split_geo(T, (int)d_in, (int)d_out, true) == F32_NONE) return false;
     } else if (!dma_direct_joint_ok((int)B, (int)T, (int)d_in, (int)d_out)) return false;
-    return B * direct_sums(B, T, d_in, d_out, dtype) < (int64_t(1) << 24);       // 16 layers' items stay below the launch's 2^28
+    return B * direct_sums(B, T, d_in, d_out, dtype) <= kJointItems;
 }
 // a float32 layer whose Gram norm can share a launch of the several-layers call: its launch class (0: none)
 int gram_f32_join_class(int64_t B, int64_t T, int64_t d_in, int64_t d_out, dp_dtype dtype, dp_path path) {
     if (dtype != DP_F32 || T <= 1 || d_in == 0 || d_out == 0 || B >= (int64_t(1) << 20)) return 0;
     if (resolve_path(path, dtype, T, d_in, d_out) != DP_PATH_GRAM || gram_cols_class(B, T, d_in, d_out, dtype, path) != 0) return 0;
-    if (B * gram_f32_sums((int)T) >= (int64_t(1) << 24)) return 0;              // 16 layers' items stay below 2^31
+    if (B * gram_f32_sums((int)T) > kJointItems) return 0;
     return gram_f32_class((int)B, (int)T, (int)d_in, (int)d_out);
 }
 // a 16-bit layer whose Gram norm runs on the any-shape kernel with 128-row tiles: such layers share launches too
@@ -158,7 +161,7 @@ bool gram16_joinable(int64_t B, int64_t T, int64_t d_in, int64_t d_out, dp_dtype
     if (!is16(dtype) || T <= 64 || d_in == 0 || d_out == 0 || B >= (int64_t(1) << 20)) return false;
     if (resolve_path(path, dtype, T, d_in, d_out) != DP_PATH_GRAM || gram_batchable(T, d_in, d_out, dtype, path) ||
         gram_cols_class(B, T, d_in, d_out, dtype, path) != 0) return false;
-    return B * plan_gram_bf16((int)T, (int)d_in, (int)d_out).npairs < (int64_t(1) << 24);
+    return B * plan_gram_bf16((int)T, (int)d_in, (int)d_out).npairs <= kJointItems;
 }
 // the scratch of a layer in the several-layers call: the larger of its own call's and a shared launch's
 size_t single_layer_need(int64_t B, const dp_layer_desc& y, dp_dtype dtype, dp_path path) {
@@ -929,6 +932,7 @@ dp_status dp_layers_sqnorm_clip(const dp_layer_desc* layers, int64_t n_layers, i
         int sums[kJointLayers];                              // per example
         int ng = 0;
         size_t group_bytes = 0;
+        int64_t group_items = 0;
         auto flush_group = [&]() -> hipError_t {
             if (ng == 0) return hipSuccess;
             if (queue.count + ng > FinalizeQueue::kMax || ws_off + group_bytes > workspace_bytes) {
@@ -941,14 +945,14 @@ dp_status dp_layers_sqnorm_clip(const dp_layer_desc* layers, int64_t n_layers, i
             }
             const hipError_t e = launch(sh, op, part, ng);
             for (int k = 0; k < ng; ++k) { queue.partial[queue.count] = part[k]; queue.n[queue.count] = sums[k]; ++queue.count; }
-            ng = 0; group_bytes = 0;
+            ng = 0; group_bytes = 0; group_items = 0;
             return e;
         };
         for (int64_t l : which) {
             const dp_layer_desc& y = layers[l];
             const int t = sums_of(y);
             // (a layer's sums alone always fit: the scratch is at least the largest single layer's need)
-            if (ng > 0 && group_bytes + round16((size_t)B * t * sizeof(float)) > workspace_bytes) {
+            if (ng > 0 && (group_bytes + round16((size_t)B * t * sizeof(float)) > workspace_bytes || group_items + B * t > kJointItems)) {
                 const hipError_t e = flush_group();
                 if (e != hipSuccess) return e;
             }
@@ -956,6 +960,7 @@ dp_status dp_layers_sqnorm_clip(const dp_layer_desc* layers, int64_t n_layers, i
             op[ng] = JointOperands{static_cast<const uint16_t*>(y.A), static_cast<const uint16_t*>(y.G), nullptr, nullptr, 0};
             sums[ng] = t;
             group_bytes += round16((size_t)B * sums[ng] * sizeof(float));
+            group_items += B * t;
             ++ng;
             joined[(size_t)l] = 1;
             if (ng == kJointLayers) {

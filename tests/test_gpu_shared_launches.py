@@ -110,3 +110,15 @@ def test_layers_beside_some_that_cannot_share(dtype, shapes, B, left_out):
             dp.add_noise(z, std, 5, off)
             r = r + z
         assert float((g.double() - r).norm() / r.norm()) < tol
+
+
+@pytest.mark.parametrize("dtype,B,n", [(torch.bfloat16, 4100, 2), (torch.float32, 2031, 4)])
+def test_more_items_than_a_launch_holds(dtype, B, n):
+    """2080 tile pairs per example: the layers together have more workgroups than one launch can."""
+    gen = torch.Generator(device="cuda").manual_seed(4)
+    A = torch.randn((B, 8192, 3), device="cuda", generator=gen).to(dtype)
+    G = torch.randn((B, 8192, 2), device="cuda", generator=gen).to(dtype)
+    s = dp.layers_sqnorm([(A, G)] * n, path="gram")
+    one = dp.layer_sqnorm(A, G, path="direct")
+    # float32 sums of 2^26 terms of random sign, in two ways
+    assert torch.allclose(s, n * one, rtol=1e-4, atol=0)
