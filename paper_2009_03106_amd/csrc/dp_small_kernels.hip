@@ -527,8 +527,8 @@ hipError_t launch_splitk_reduce(const float* ws, int64_t n, int splits, bool acc
 // a fold per layer is a launch of a few microseconds each, which for a dozen small layers is longer than their sums
 // took.  A workgroup takes 256 groups of 4 entries of one layer.
 // BLOCKS (float32 layers, which can have hundreds of slices): the sums of eight slices, then the sum of those, fewer
-// roundings in a row (65536 rows: 1.8e-7 of the result without, 1.3e-7 with).  Each thread walks its slices by itself and
-// waits once per eight; the 16-bit layers have few slices and keep the plain order.
+// roundings in a row (65536 rows: 1.8e-7 of the result without, 1.3e-7 with), eight slices requested at a time; the
+// 16-bit layers have few slices and keep the plain order.
 template <bool NOISE, bool BLOCKS>
 __global__ __launch_bounds__(256) void k_splitk_reduce_layers(FoldLayers f, int accumulate, NoiseArgs nz) {
     int l = 0;
@@ -540,16 +540,26 @@ __global__ __launch_bounds__(256) void k_splitk_reduce_layers(FoldLayers f, int 
     const int splits = f.splits[l];
     float4 acc;
     if constexpr (BLOCKS) {
-        acc = make_float4(0.f, 0.f, 0.f, 0.f);
-        for (int z0 = 0; z0 < splits; z0 += 8) {
+        auto at = [&](int z) { return reinterpret_cast<const float4*>(ws + (size_t)z * slice)[c]; };
+        auto add = [](float4& x, const float4& y) { x.x += y.x; x.y += y.y; x.z += y.z; x.w += y.w; };
+        int z = 0;
+        for (; z + 8 <= splits; z += 8) {
             float4 v[8];
 #pragma unroll
-            for (int k = 0; k < 8; ++k) v[k] = reinterpret_cast<const float4*>(ws + (size_t)min(z0 + k, splits - 1) * slice)[c];
+            for (int k = 0; k < 8; ++k) v[k] = at(z + k);
 #pragma unroll
-            for (int k = 1; k < 8; ++k)
-                if (z0 + k < splits) { v[0].x += v[k].x; v[0].y += v[k].y; v[0].z += v[k].z; v[0].w += v[k].w; }
-            if (z0 == 0) acc = v[0];
-            else { acc.x += v[0].x; acc.y += v[0].y; acc.z += v[0].z; acc.w += v[0].w; }
+            for (int k = 1; k < 8; ++k) add(v[0], v[k]);
+            if (z == 0) acc = v[0]; else add(acc, v[0]);
+        }
+        if (z < splits) {                                    // fewer than eight
+            const bool first = z == 0;
+            float4 b = at(z++);
+            for (; z + 3 < splits; z += 4) {
+                const float4 v0 = at(z), v1 = at(z + 1), v2 = at(z + 2), v3 = at(z + 3);
+                add(b, v0); add(b, v1); add(b, v2); add(b, v3);
+            }
+            for (; z < splits; ++z) add(b, at(z));
+            if (first) acc = b; else add(acc, b);
         }
     } else {
         acc = reinterpret_cast<const float4*>(ws)[c];

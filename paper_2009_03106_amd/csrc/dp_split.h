@@ -10,7 +10,9 @@
 // are multiplied by 2^24 (kSplitScale) before they are split and the sums by 2^-48 (kSplitUnscale): every part is then zero or
 // at least 2^-125, and the split is exact down to the smallest float32 subnormal.  The price is the top of the range:
 // operands from 2^104 on and sums from 2^80 on are infinite or NaN here, as infinities and NaN are themselves.  The
-// kernels look for that in their finished sums (SplitCheck) and form them again with the float32 instruction.
+// kernels look for that in their finished sums (SplitCheck) and form them again with the float32 instruction, straight from
+// memory: with every sum of a launch formed again 32 examples of 512 x (768, 768) take 0.43 ms for the Gram norms instead of
+// 0.12 and 1.5 ms for the clipped sum instead of 0.12.
 #pragma once
 #include "dp_common.h"
 

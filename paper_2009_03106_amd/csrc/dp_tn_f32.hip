@@ -332,11 +332,11 @@ int clipped_f32_split_geo(int64_t K, int M, int N) {
 // Where the split kernel is the faster one for a layer by itself, in products K M N (us, fp32 kernels / split):
 //   up to kShortK rows from 1e9:  844 x 1664 from 384 20 / 29, 768 x 2304 from 512 28 / 34; 4608 x 512 from 512 37 / 36,
 //                                 2000 x 2000 from 256 35 / 33
-//   sizes whose fold is scalar, whose loads the fp32 kernel makes one by one, from 1.5e8:  63 x 127 from 12500 33 / 34,
-//                                 from 25000 53 / 45
+//   sizes that are no multiple of 4 (the fp32 kernel loads their rows word by word) from 1.5e8:  63 x 127 from 6000
+//                                 22 / 24, from 25000 53 / 43
 //   aligned shapes of 128 x 128 tiles always: 128 x 128 from 520 29 / 15 (the kernel it replaced)
-//   one aligned tile of 64 columns never: 64 x 128 from 25000 14 / 18, from 100000 31 / 32, from 400000 90 / 97
-//   others from 6e8:              576 x 64 from 6000 14 / 19, from 25000 31 / 32, from 50000 52 / 48
+//   one aligned tile of 64 columns never: 64 x 128 from 25000 14 / 18, from 100000 31 / 32, from 400000 88 / 94
+//   others from 3.7e8:            576 x 64 from 6000 14 / 19, 64 x 256 from 12500 14 / 17, 250 x 60 from 25000 24 / 22
 ClippedF32Route clipped_f32_route(int64_t K, int M, int N) {
     const int geo = clipped_f32_split_geo(K, M, N);
     const double products = (double)K * M * N;
@@ -348,7 +348,7 @@ ClippedF32Route clipped_f32_route(int64_t K, int M, int N) {
     if (aligned && pm * pn * 3 <= (int64_t)M * N * 4) split = true;
     else if ((((int64_t)M * N) & 3) != 0) split = products >= 1.5e8;
     else if (aligned && M <= f32_split_tile_m(geo) && N <= f32_split_tile_n(geo)) split = false;
-    else split = products >= 6e8;
+    else split = products >= 3.7e8;
     return ClippedF32Route{false, split ? geo : F32_NONE};
 }
 
