@@ -1291,9 +1291,10 @@ dp_status dp_layers_clipped_grad_noise(const dp_layer_desc* layers, int64_t n_la
     for (int64_t l = 0; l < n_layers; ++l)
         if (B > 0 && !clip && !layers[l].clip) return DP_ERR_INVALID_ARG;          // neither the layer's own factors nor the call's
     // Aligned 16-bit and 8-bit layers with 256 x 256 tiles share launches, up to kJointLayers each (groups of at least two):
-    // one launch whose items fill the chip a whole number of times, the K slices folded (and the noise added) inside
-    // it.  With noise the kernel adds it four elements at a time, so the layer's offset and size must be multiples of 4.
-    // A second class of joint launches (128 x 128 tiles) takes the aligned 16-bit layers of a few hundred columns.
+    // one launch whose items fill the chip a whole number of times, the K slices folded (and the noise added) by a
+    // second one.  The noise is added four elements at a time, so the layer's offset and size must be multiples of 4.
+    // Further classes (clipped_join_class): 128 x 128 tiles for the aligned 16-bit layers of a few hundred columns, with
+    // whole and with ragged stages, and the float32 layers.
     // (layers whose gradients overlap, as tied weights accumulated into one array do, run one after the other: like those
     // whose noise the fold cannot add, they are left out of the group that the workspace query planned for them.  The
     // layers that remain may then take more slices than the query gave them, so where that is more than the query's

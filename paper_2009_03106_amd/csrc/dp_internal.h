@@ -200,7 +200,7 @@ bool dma_joint_ok(int T, int M, int N);
 bool dma_joint_mid_ok(int T, int M, int N);      // the second class: 128 x 128 tiles, geo = 3 below
 bool dma_joint_ragged_ok(int T, int M, int N);   // the same tiles, T not a multiple of the stage: geo = 4
 size_t joint_workspace_floats(const JointShape* sh, int n_layers, int B, int geo, size_t max_floats);
-// the same for float32 inputs (dp_tn_f32_split.hip; 128 x 128 tiles, any T); A, G of JointOperands are float pointers
+// the same for float32 inputs (dp_tn_f32_split.hip; every layer on its own geometry, any T); A, G of JointOperands are float pointers
 // big: every layer on 256 x 256 tiles.  The plan of a call is made once and handed to the launch.
 struct F32JointPlan { int splits[kJointLayers], kchunk[kJointLayers], geo[kJointLayers], tiles_m[kJointLayers], tiles_n[kJointLayers]; int64_t items; size_t floats; };
 F32JointPlan plan_joint_f32(const JointShape* sh, int n_layers, int B, bool big, size_t max_floats);

@@ -341,7 +341,8 @@ template <int MODE, bool BIG>
 __global__ __launch_bounds__(BIG ? GeoBig::THREADS : GeoMid::THREADS, 2) void k_tn_f32_split_joint(F32JointArgs j) {
     __shared__ u32x4 lds[2 * (BIG ? GeoBig::STAGE_UNITS : GeoMid::STAGE_UNITS)];
     // The layers' items differ in length, so every XCD takes its eighth of every layer's items (first_item: among the
-    // items of one XCD): 18 convolutions' sums 0.28 ms, with eighths of the whole list 0.34 ms.  On 256 x 256 tiles they have about one length: an eighth of the list.
+    // items of one XCD): with eighths of the whole list 18 convolutions' sums took 1.2 times as long.  On 256 x 256 tiles
+    // they have about one length: an eighth of the list.
     const int xcd = blockIdx.x & 7, L = BIG ? xcd * j.per_xcd + (int)(blockIdx.x >> 3) : (int)(blockIdx.x >> 3);
     if (L >= j.n_items) return;
     int l = 0;
@@ -461,8 +462,10 @@ hipError_t launch_clipped_f32_split_joint(const JointShape* sh, const JointOpera
 
 // The geometry of a layer: the largest tiles of which at most a quarter is padding.  256 x 256 tiles (clipped sums
 // only: half the L2 traffic per product of 128 x 128 tiles and a third less LDS traffic) where they are many
-// stages' work: B = 64, T = 512, 768 x 2304 / 768 / 3072 and 3072 x 768 take 2.14 ms on them and 2.8 ms on 128 x 128
-// tiles, 18 small convolutions of 16 .. 1024 positions 0.12 ms against 0.10 ms in one launch of the smaller tiles.
+// stages' work: B = 64, T = 512, 768 x 2304 / 768 / 3072 and 3072 x 768 take 2.36 .. 2.5 ms on them and 2.9 ms on 128 x
+// 128 tiles, 65536 rows of 784 x 512 and 512 x 256 0.43 .. 0.51 and 0.50 .. 0.60 ms; small convolutions of 16 .. 1024
+// positions are faster in one launch of the smaller tiles.  (Of the 256 registers that a lane of the 8 waves has, the
+// sums take 128; 122 values are kept in scratch memory, 228 bytes a lane, some of them across the stage loop.)
 int f32_split_geo(int64_t K, int M, int N, bool direct) {
     if (K < (direct ? 128 : 256)) return F32_NONE;
     auto fits = [&](int geo) {
