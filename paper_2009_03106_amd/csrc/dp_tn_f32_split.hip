@@ -369,7 +369,6 @@ __global__ __launch_bounds__(BIG ? GeoBig::THREADS : GeoMid::THREADS, 2) void k_
 // reading of the slices (4 MB in about a stage time) and its walk through the layer with the most of them (8 in a stage time).
 F32JointPlan plan_joint_f32(const JointShape* sh, int n_layers, int B, bool big, size_t max_floats) {
     constexpr int64_t kItemOverhead = 16;
-    const int slots_log2 = big ? 8 : 9;
     F32JointPlan p{};
     // layers with the same number of stages and slice length take the same number of slices: they are counted together
     struct { uint32_t stages; bool half; int64_t tiles, entries, slice; } same[kJointLayers];
@@ -408,7 +407,9 @@ F32JointPlan plan_joint_f32(const JointShape* sh, int n_layers, int B, bool big,
             most = std::max(most, splits[k]);
         }
         if (floats > max_floats && S > 1) break;             // (as plan_joint)
-        const int64_t cost = ((items + (1 << slots_log2) - 1) >> slots_log2) * (longest + kItemOverhead) + (fold >> 20) + most / 8;
+        // in eighths of a stage; a launch of one workgroup per compute unit or less takes 7 / 8 of one with two
+        const int64_t rounds = big ? ((items + 255) >> 8) * 8 : items <= 256 ? 7 : ((items + 511) >> 9) * 8;
+        const int64_t cost = rounds * (longest + kItemOverhead) + (fold >> 17) + most;
         if (best_cost < 0 || cost < best_cost) {
             best_cost = cost; p.items = items; p.floats = floats;
             for (int k = 0; k < n_same; ++k) { best_splits[k] = splits[k]; best_sps[k] = sps[k]; }
