@@ -194,7 +194,7 @@ int clipped_join_class(int64_t B, int64_t T, int64_t d_in, int64_t d_out, dp_dty
     if (B == 0 || T == 0 || d_in == 0 || d_out == 0) return 0;
     if (is8(dtype)) return (dma8_clipped_ok((int)T, (int)d_in, (int)d_out) && dma8_joint_ok((int)T, (int)d_in, (int)d_out)) ? 1 : 0;
     if (!is16(dtype)) {
-        // float32: the layers of the copy-pipeline kernel (long contractions, widths multiples of 4) share launches too
+        // float32: the layers that the split kernel can take (long contractions) share launches too
         if (B * T >= (int64_t(1) << 31)) return 0;
         const int geo = clipped_f32_split_geo(B * T, (int)d_in, (int)d_out);
         if (geo == F32_NONE || ((d_in * d_out) & 3) != 0) return 0;     // the shared fold takes four entries at a time
