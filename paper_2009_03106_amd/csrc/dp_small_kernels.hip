@@ -448,7 +448,7 @@ __global__ __launch_bounds__(256) void k_splitk_reduce(const float* __restrict__
     for (int64_t j = (n4 << 2) + (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < n; j += stride) {
         float acc = ws[j];
         int z = 1;
-        for (; z + 3 < splits; z += 4) {                     // four slices requested at a time, as above
+        for (; z + 3 < splits; z += 4) {                     // four slices requested at a time
             const float v0 = ws[(size_t)z * slice + j], v1 = ws[(size_t)(z + 1) * slice + j];
             const float v2 = ws[(size_t)(z + 2) * slice + j], v3 = ws[(size_t)(z + 3) * slice + j];
             acc += v0; acc += v1; acc += v2; acc += v3;
