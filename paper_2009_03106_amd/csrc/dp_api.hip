@@ -117,13 +117,11 @@ bool gram_batchable(int64_t T, int64_t d_in, int64_t d_out, dp_dtype dtype, dp_p
     return gram_dma_ok((int)T, (int)d_in, (int)d_out, fmt_of(dtype));
 }
 
-// a layer that the shared column-split Gram launches of dp_layers_sqnorm take (few positions, wide rows, small batch):
-// 0 = no, else the launch class (the plan's number of 32-row blocks)
-int gram_cols_class(int64_t B, int64_t T, int64_t d_in, int64_t d_out, dp_dtype dtype, dp_path path) {
-    if (is8(dtype) || T <= 1 || T > 64 || d_in == 0 || d_out == 0 || B >= (int64_t(1) << 20)) return 0;
-    if (resolve_path(path, dtype, T, d_in, d_out) != DP_PATH_GRAM) return 0;
-    const GramColsPlan c = plan_gram_cols((int)B, (int)T, (int)d_in, (int)d_out, (int)dtype);
-    return c.use ? c.nb : 0;
+// a layer that the shared column-split Gram launches of dp_layers_sqnorm take (few positions, wide rows, small batch)
+bool gram_cols_layer(int64_t B, int64_t T, int64_t d_in, int64_t d_out, dp_dtype dtype, dp_path path) {
+    if (is8(dtype) || T <= 1 || T > 64 || d_in == 0 || d_out == 0 || B >= (int64_t(1) << 20)) return false;
+    if (resolve_path(path, dtype, T, d_in, d_out) != DP_PATH_GRAM) return false;
+    return plan_gram_cols((int)B, (int)T, (int)d_in, (int)d_out, (int)dtype).use;
 }
 
 size_t round16(size_t n) { return (n + 15) & ~size_t(15); }
@@ -140,7 +138,7 @@ int direct_sums(int64_t B, int64_t T, int64_t d_in, int64_t d_out, dp_dtype dtyp
 // a layer whose direct norm the shared launch of dp_layers_sqnorm can take (16-bit: T >= 64 and aligned widths)
 bool direct_joinable(int64_t B, int64_t T, int64_t d_in, int64_t d_out, dp_dtype dtype, dp_path path) {
     if (is8(dtype) || T <= 1 || d_in == 0 || d_out == 0 || B >= (int64_t(1) << 20)) return false;
-    if (gram_batchable(T, d_in, d_out, dtype, path) || gram_cols_class(B, T, d_in, d_out, dtype, path) != 0) return false;
+    if (gram_batchable(T, d_in, d_out, dtype, path) || gram_cols_layer(B, T, d_in, d_out, dtype, path)) return false;
     if (resolve_path(path, dtype, T, d_in, d_out) != DP_PATH_DIRECT) return false;
     if (!is16(dtype)) {
         // float32: the layers whose direct norm the split kernel can form (choose_direct_f32_joint leaves some of them out)
@@ -152,7 +150,7 @@ bool direct_joinable(int64_t B, int64_t T, int64_t d_in, int64_t d_out, dp_dtype
 // a float32 layer whose Gram norm can share a launch of the several-layers call: its launch class (0: none)
 int gram_f32_join_class(int64_t B, int64_t T, int64_t d_in, int64_t d_out, dp_dtype dtype, dp_path path) {
     if (dtype != DP_F32 || T <= 1 || d_in == 0 || d_out == 0 || B >= (int64_t(1) << 20)) return 0;
-    if (resolve_path(path, dtype, T, d_in, d_out) != DP_PATH_GRAM || gram_cols_class(B, T, d_in, d_out, dtype, path) != 0) return 0;
+    if (resolve_path(path, dtype, T, d_in, d_out) != DP_PATH_GRAM || gram_cols_layer(B, T, d_in, d_out, dtype, path)) return 0;
     if (B * gram_f32_sums((int)T) > kJointItems) return 0;
     return gram_f32_class((int)B, (int)T, (int)d_in, (int)d_out);
 }
@@ -160,7 +158,7 @@ int gram_f32_join_class(int64_t B, int64_t T, int64_t d_in, int64_t d_out, dp_dt
 bool gram16_joinable(int64_t B, int64_t T, int64_t d_in, int64_t d_out, dp_dtype dtype, dp_path path) {
     if (!is16(dtype) || T <= 64 || d_in == 0 || d_out == 0 || B >= (int64_t(1) << 20)) return false;
     if (resolve_path(path, dtype, T, d_in, d_out) != DP_PATH_GRAM || gram_batchable(T, d_in, d_out, dtype, path) ||
-        gram_cols_class(B, T, d_in, d_out, dtype, path) != 0) return false;
+        gram_cols_layer(B, T, d_in, d_out, dtype, path)) return false;
     return B * plan_gram_bf16((int)T, (int)d_in, (int)d_out).npairs <= kJointItems;
 }
 // the scratch of a layer in the several-layers call: the larger of its own call's and a shared launch's
@@ -760,7 +758,7 @@ size_t layers_ws_bytes(const dp_layer_desc* layers, int64_t n_layers, int64_t B,
     for (int64_t l = 0; l < n_layers; ++l) {
         const dp_layer_desc& y = layers[l];
         if (B == 0 || y.T == 0 || y.d_in == 0 || y.d_out == 0) continue;
-        if (gram_cols_class(B, y.T, y.d_in, y.d_out, dtype, path) != 0) continue;      // below
+        if (gram_cols_layer(B, y.T, y.d_in, y.d_out, dtype, path)) continue;           // below
         if (gram_batchable(y.T, y.d_in, y.d_out, dtype, path)) {
             if (in_batch == kGramBatch) { in_batch = 0; batch = 0; }
             const GramPlan g = plan_gram_bf16((int)y.T, (int)y.d_in, (int)y.d_out);
@@ -777,15 +775,18 @@ size_t layers_ws_bytes(const dp_layer_desc* layers, int64_t n_layers, int64_t B,
     // the layers that run one by one keep their partial sums apart until one launch folds them (up to a limit: with
     // less scratch the fold comes earlier)
     if (!is8(dtype) && single_sum > single && single_sum <= (size_t(256) << 20)) single = single_sum;
-    // the shared column-split Gram launches, one class after the other, kGramColsLayers layers each
-    for (int cls = 1; cls <= 2; ++cls) {
+    // the column-split Gram layers: what those of one kind (T <= 32, T <= 64) take that are planned one by one, kGramColsLayers
+    // at a time.  The shared launches plan their layers together and do with this.
+    for (int nb = 1; nb <= 2; ++nb) {
         size_t group = 0;
         int in_group = 0;
         for (int64_t l = 0; l < n_layers; ++l) {
             const dp_layer_desc& y = layers[l];
-            if (B == 0 || gram_cols_class(B, y.T, y.d_in, y.d_out, dtype, path) != cls) continue;
+            if (B == 0 || !gram_cols_layer(B, y.T, y.d_in, y.d_out, dtype, path)) continue;
+            const GramColsPlan p = plan_gram_cols((int)B, (int)y.T, (int)y.d_in, (int)y.d_out, (int)dtype);
+            if (p.nb != nb) continue;
             if (in_group == kGramColsLayers) { in_group = 0; group = 0; }
-            group += plan_gram_cols((int)B, (int)y.T, (int)y.d_in, (int)y.d_out, (int)dtype).ws_floats * sizeof(float);
+            group += p.ws_floats * sizeof(float);
             ++in_group;
             if (group > batch_max) batch_max = group;
         }
@@ -829,7 +830,7 @@ dp_status dp_layers_sqnorm_clip(const dp_layer_desc* layers, int64_t n_layers, i
     // Which kernel completes the norms and can write the clip factors with them: the last shared Gram launch if
     // there is one; else, unless a bias pass follows, the last layer that runs on its own; else the last launch
     // of dense layers.  Otherwise (bias passes at the end, or nothing to launch) the clip kernel runs.
-    int64_t n_dense = 0, n_cols = 0, last_single = -1;
+    int64_t n_dense = 0, n_cols = 0, n_single = 0, last_single = -1;
     bool any_gram = false, any_bias_pass = false;
     for (int64_t l = 0; l < n_layers; ++l) {
         const dp_layer_desc& y = layers[l];
@@ -838,37 +839,69 @@ dp_status dp_layers_sqnorm_clip(const dp_layer_desc* layers, int64_t n_layers, i
         if (y.T == 0 || y.d_in == 0 || y.d_out == 0) continue;
         if (y.T == 1 && !is8(dtype)) ++n_dense;
         else if (gram_batchable(y.T, y.d_in, y.d_out, dtype, path)) any_gram = true;
-        else if (gram_cols_class(B, y.T, y.d_in, y.d_out, dtype, path) != 0) ++n_cols;
-        else last_single = l;
+        else if (gram_cols_layer(B, y.T, y.d_in, y.d_out, dtype, path)) ++n_cols;
+        else { last_single = l; ++n_single; }
     }
     const ClipOut clip_out{C, clip};
-    // layers of few positions and wide rows in a small batch: shared column-split Gram launches, first of all (they
-    // write the clip factors only when nothing else follows)
-    const bool clip_with_cols = clip && !any_gram && !any_bias_pass && last_single < 0 && n_dense == 0 && n_cols > 0;
-    {
-        int64_t cols_done = 0;
-        for (int cls = 1; cls <= 2; ++cls) {
-            GramLayerDesc group[kGramColsLayers];
-            int ng = 0;
-            auto flush_cols = [&]() -> hipError_t {
-                if (ng == 0) return hipSuccess;
-                cols_done += ng;
-                const hipError_t e = launch_gram_cols_layers(group, ng, (int)B, acc != 0, sqnorm, static_cast<float*>(workspace), stream,
-                                                             (int)dtype, (clip_with_cols && cols_done == n_cols) ? &clip_out : nullptr);
-                ng = 0; acc = 1; launched = true;
+    // Two or more layers outside the dense and the Gram launches: their partial sums are folded by one launch at the end
+    // (FinalizeQueue) instead of a launch of a few microseconds behind every layer.
+    const bool defer_on = n_single + n_cols >= 2 && !is8(dtype);
+    FinalizeQueue queue;
+    size_t ws_off = 0;
+    auto flush_queue = [&](bool with_clip) -> hipError_t {
+        if (queue.count == 0) return hipSuccess;
+        const hipError_t e = launch_finalize_queue(queue, (int)B, acc != 0, sqnorm, stream, with_clip ? &clip_out : nullptr);
+        queue.count = 0; ws_off = 0; acc = 1; launched = true;
+        return e;
+    };
+    // layers of few positions and wide rows in a small batch: shared column-split Gram launches, first of all.  Their sums
+    // join the queue; one such layer alone finishes its own norms (and the clip factors when nothing else follows).
+    const bool clip_with_cols = clip && !defer_on && !any_gram && !any_bias_pass && last_single < 0 && n_dense == 0 && n_cols > 0;
+    if (n_cols > 0) {
+        GramLayerDesc group[kGramColsLayers];
+        int ng = 0;
+        size_t least = 0;                                    // what the group's sums and one share per example and layer take
+        auto flush_cols = [&]() -> hipError_t {
+            if (ng == 0) return hipSuccess;
+            if (!defer_on) {
+                const GramLayerDesc& y = group[0];
+                const GramColsPlan p = plan_gram_cols((int)B, y.T, y.d_in, y.d_out, (int)dtype);
+                ng = 0;
+                const hipError_t e = launch_gram_cols(p, y.A, y.G, (int)B, y.T, y.d_in, y.d_out, acc != 0, sqnorm, static_cast<float*>(workspace),
+                                                      stream, (int)dtype, clip_with_cols ? &clip_out : nullptr);
+                acc = 1; launched = true;
                 return e;
-            };
-            for (int64_t l = 0; l < n_layers; ++l) {
-                const dp_layer_desc& y = layers[l];
-                if (gram_cols_class(B, y.T, y.d_in, y.d_out, dtype, path) != cls) continue;
-                group[ng++] = GramLayerDesc{y.A, y.G, (int)y.T, (int)y.d_in, (int)y.d_out, nullptr, nullptr};
-                if (ng == kGramColsLayers && flush_cols() != hipSuccess) return DP_ERR_HIP;
             }
-            if (flush_cols() != hipSuccess) return DP_ERR_HIP;
+            if (queue.count + ng > FinalizeQueue::kMax) { const hipError_t e = flush_queue(false); if (e != hipSuccess) return e; }
+            else if (ws_off + least > need) { const hipError_t e = flush_queue(false); if (e != hipSuccess) return e; }
+            float* sums[kGramColsLayers];
+            for (int k = 0; k < ng; ++k) {
+                const int n = gram_cols_sums(plan_gram_cols((int)B, group[k].T, group[k].d_in, group[k].d_out, (int)dtype));
+                sums[k] = reinterpret_cast<float*>(static_cast<char*>(workspace) + ws_off);
+                ws_off += round16((size_t)B * n * sizeof(float));
+                queue.partial[queue.count] = sums[k]; queue.n[queue.count] = n; ++queue.count;
+            }
+            // the shares behind them: they are added up by the time the next launch uses the place
+            const hipError_t e = launch_gram_cols_layers(group, sums, ng, (int)B, reinterpret_cast<float*>(static_cast<char*>(workspace) + ws_off),
+                                                         (need - ws_off) / sizeof(float), stream, (int)dtype);
+            ng = 0; least = 0;
+            return e;
+        };
+        for (int64_t l = 0; l < n_layers; ++l) {
+            const dp_layer_desc& y = layers[l];
+            if (!gram_cols_layer(B, y.T, y.d_in, y.d_out, dtype, path)) continue;
+            // (a layer alone fits: its own plan has at least two shares per example, 4 KB and more each)
+            const GramColsPlan p = plan_gram_cols((int)B, (int)y.T, (int)y.d_in, (int)y.d_out, (int)dtype);
+            const size_t own = round16((size_t)B * gram_cols_sums(p) * sizeof(float)) + p.ws_floats / (size_t)p.W * sizeof(float);
+            if (ng > 0 && least + own > need && flush_cols() != hipSuccess) return DP_ERR_HIP;
+            least += own;
+            group[ng++] = GramLayerDesc{y.A, y.G, (int)y.T, (int)y.d_in, (int)y.d_out, nullptr, nullptr};
+            if (ng == kGramColsLayers && flush_cols() != hipSuccess) return DP_ERR_HIP;
         }
+        if (flush_cols() != hipSuccess) return DP_ERR_HIP;
     }
-    const bool clip_with_single = clip && !any_gram && !any_bias_pass && last_single >= 0;
-    const bool clip_with_dense = clip && !any_gram && !any_bias_pass && last_single < 0 && n_dense > 0;
+    const bool clip_with_single = clip && !any_gram && !any_bias_pass && (last_single >= 0 || defer_on);
+    const bool clip_with_dense = clip && !any_gram && !any_bias_pass && last_single < 0 && !defer_on && n_dense > 0;
     // dense layers (T = 1, closed form): up to kDenseBatch per launch, in the order given
     DenseLayers dense;
     dense.n_layers = 0;
@@ -889,24 +922,7 @@ dp_status dp_layers_sqnorm_clip(const dp_layer_desc* layers, int64_t n_layers, i
         if (dense.n_layers == kDenseBatch && flush_dense() != hipSuccess) return DP_ERR_HIP;
     }
     if (flush_dense() != hipSuccess) return DP_ERR_HIP;
-    // layers outside the batched launches, in the order given.  Two or more of them: their partial sums are folded by
-    // one launch at the end (FinalizeQueue) instead of a launch of a few microseconds behind every layer.
-    int64_t n_single = 0;
-    for (int64_t l = 0; l < n_layers; ++l) {
-        const dp_layer_desc& y = layers[l];
-        if (y.T == 0 || (y.T == 1 && !is8(dtype)) || y.d_in == 0 || y.d_out == 0) continue;
-        if (gram_batchable(y.T, y.d_in, y.d_out, dtype, path) || gram_cols_class(B, y.T, y.d_in, y.d_out, dtype, path) != 0) continue;
-        ++n_single;
-    }
-    const bool defer_on = n_single >= 2 && !is8(dtype);
-    FinalizeQueue queue;
-    size_t ws_off = 0;
-    auto flush_queue = [&](bool with_clip) -> hipError_t {
-        if (queue.count == 0) return hipSuccess;
-        const hipError_t e = launch_finalize_queue(queue, (int)B, acc != 0, sqnorm, stream, with_clip ? &clip_out : nullptr);
-        queue.count = 0; ws_off = 0; acc = 1; launched = true;
-        return e;
-    };
+    // layers outside the batched launches, in the order given.
     // Two or more of them with aligned widths on the direct path: their norms share copy-pipeline launches of up to
     // kJointLayers layers (a launch each is a few hundred workgroups and a tail), the sums join the queue.
     std::vector<int64_t> dj;
@@ -1003,7 +1019,7 @@ dp_status dp_layers_sqnorm_clip(const dp_layer_desc* layers, int64_t n_layers, i
         const dp_layer_desc& y = layers[l];
         if (y.T == 0 || (y.T == 1 && !is8(dtype)) || y.d_in == 0 || y.d_out == 0) continue;     // empty layers add nothing
         if (gram_batchable(y.T, y.d_in, y.d_out, dtype, path)) continue;
-        if (gram_cols_class(B, y.T, y.d_in, y.d_out, dtype, path) != 0) continue;
+        if (gram_cols_layer(B, y.T, y.d_in, y.d_out, dtype, path)) continue;
         if (defer_on && joined[(size_t)l]) continue;
         if (!defer_on) {
             const dp_status s1 = layer_sqnorm_clip(y.A, y.G, B, y.T, y.d_in, y.d_out, dtype, path, acc, sqnorm, workspace, workspace_bytes,

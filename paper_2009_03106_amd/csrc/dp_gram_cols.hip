@@ -8,13 +8,17 @@
 // through LDS, and a second kernel adds the workgroups' shares of an example in a fixed order, multiplies the two
 // T x T products entry by entry and sums.
 //
-// No LDS staging of the inputs: both operands of a Gram product are rows of the same matrix, so a lane's 16-byte
-// piece of global memory serves the left and the right side of the MFMA alike.  16-bit inputs: the piece (8
-// consecutive columns of one row) is one operand of the 32 x 32 x 16 instruction (row = lane % 32, columns
-// 8 * (lane / 32) .. + 7 of a 16-column step).  float32: the piece (4 columns) feeds four 32 x 32 x 2 instructions,
-// entry j of lanes 0-31 and of lanes 32-63 being the two columns of the j-th; which columns meet in an instruction
-// does not matter to the sum, and both sides use the same register.  A wave issues the loads of 8 steps before the
-// first MFMA, so a range of 128 (64) columns is one memory round trip.
+// Both operands of a Gram product are rows of the same matrix, so a 16-byte piece of a row serves the left and the right
+// side of the MFMA alike.  16-bit inputs: the piece (8 consecutive columns of one row) is one operand of the 32 x 32 x 16
+// instruction (row = lane % 32, columns 8 * (lane / 32) .. + 7 of a 16-column step).  float32: the piece (4 columns) feeds
+// four 32 x 32 x 2 instructions, entry j of lanes 0-31 and of lanes 32-63 being the two columns of the j-th; which columns
+// meet in an instruction does not matter to the sum, and both sides use the same register.
+//
+// The pieces come through LDS: a copy instruction moves 8 rows x 128 bytes (global_load_lds_dwordx4), whole cache lines,
+// into the wave's own 16 KB, from where a lane reads its row.  (Loaded straight to registers a lane needs the 16 bytes of
+// its own row, an instruction touches 32 lines for 32 bytes each, and the launches moved 1.9 TB/s: 32 examples of 64
+// positions into 2304 x 256, three layers, and 1152 x 256 took 19.4 us.  Eight layers of an 18-layer image model, 56 MB,
+// take 14 us in one launch (4 TB/s) and 5 us for the sums; in two launches by registers, with a walk through the shares, 60 us.)
 #include "dp_common.h"
 #include "dp_internal.h"
 
@@ -22,35 +26,145 @@ namespace dpk {
 
 namespace {
 
-constexpr int kColsSteps = 8;        // 16-column steps whose loads are in flight together
+constexpr int kColsSteps = 8;        // 32-byte steps of a row that a wave takes at least, in flight together
+constexpr int kStageSteps = 4;       // steps of one copied stage: 128 bytes of every row
+constexpr int kWaveLds = 16384;      // bytes of a wave's stages: 2 of 64 rows or 4 of 32 rows
+#define LDS_PTR(T) __attribute__((address_space(3))) T*
 
 struct GramColsLayer {
     const void* A;
     const void* G;
+    float* sums;         // [B][tiles of the triangle]: the layer's sums (several layers only)
     size_t part_off;     // floats: where the layer's shares start in the scratch
     int T, d_in, d_out;
     int steps_a;         // steps (16 columns of 16-bit inputs, 8 of float32) of A; the steps of G follow them
     int steps;           // of A and G together
     int W;               // workgroups per example
     int per_wave;        // steps per wave
+    int nb;              // 32-row blocks of positions: 1 (T <= 32) or 2
     unsigned first_block;
+    unsigned first_finish;      // first workgroup of k_gram_cols_sums
 };
-// Several layers in one launch (the same number of 32-row blocks NB for all): a layer alone is a few hundred
-// workgroups that each make one memory round trip, so the launches of a model's layers mostly wait.
+// Several layers in one launch: a layer alone is a few hundred workgroups that each make one memory round trip, so the
+// launches of a model's layers mostly wait.
 struct GramColsArgs {
     GramColsLayer layer[kGramColsLayers];
-    float* part;         // per layer [B][W][2][NT][16][64]: the workgroups' shares of the two products, in accumulator layout
+    float* part;         // per layer [B][W][2][NT][4][64][4]: the workgroups' shares of the two products, in accumulator layout
     int n_layers;
 };
 
-// acc[tile] += X[rows of block b0] . X[rows of block b1]^T over the steps [kb, ke) of X_i[T, D]; tiles in the
-// order (0,0), (0,1), (1,1) for two 32-row blocks.  Rows >= T and columns >= D read as zero (loads go to clamped,
-// valid addresses).
-template <int NB, bool F16>
-__device__ __forceinline__ void gram_cols_run16(const uint16_t* __restrict__ X, int T, int D, int kb, int ke, int lane,
-                                                f32x16 (&acc)[NB * (NB + 1) / 2]) {
+// at most n of the wave's copies may still be in flight
+__device__ __forceinline__ void wait_copies(int n) {
+#define DP_WAIT(k) case k: asm volatile("s_waitcnt vmcnt(" #k ")" ::: "memory"); break;
+    switch (n) {
+        DP_WAIT(1) DP_WAIT(2) DP_WAIT(3) DP_WAIT(4) DP_WAIT(5) DP_WAIT(6) DP_WAIT(7) DP_WAIT(8) DP_WAIT(9) DP_WAIT(10) DP_WAIT(11) DP_WAIT(12)
+        default: asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    }
+#undef DP_WAIT
+}
+
+// acc[tile] += X[rows of block b0] . X[rows of block b1]^T for one step, a 16-byte piece per lane and block; tiles in the
+// order (0,0), (0,1), (1,1) for two 32-row blocks
+template <int NB, int DT>
+__device__ __forceinline__ void gram_cols_mfma(const uint4 (&f)[NB], f32x16 (&acc)[NB * (NB + 1) / 2]) {
+    if constexpr (DT == 0) {
+        const float a0[4] = {__uint_as_float(f[0].x), __uint_as_float(f[0].y), __uint_as_float(f[0].z), __uint_as_float(f[0].w)};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0[e], a0[e], acc[0], 0, 0, 0);
+        if constexpr (NB == 2) {
+            const float a1[4] = {__uint_as_float(f[1].x), __uint_as_float(f[1].y), __uint_as_float(f[1].z), __uint_as_float(f[1].w)};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0[e], a1[e], acc[1], 0, 0, 0);
+                acc[2] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1[e], a1[e], acc[2], 0, 0, 0);
+            }
+        }
+    } else {
+        constexpr bool F16 = DT == 2;
+        const bf16x8 f0 = __builtin_bit_cast(bf16x8, f[0]);
+        acc[0] = In16<F16>::mfma(f0, f0, acc[0]);
+        if constexpr (NB == 2) {
+            const bf16x8 f1 = __builtin_bit_cast(bf16x8, f[1]);
+            acc[1] = In16<F16>::mfma(f0, f1, acc[1]);
+            acc[2] = In16<F16>::mfma(f1, f1, acc[2]);
+        }
+    }
+}
+
+// The steps [kb, ke) of X (an example's T rows of `row_bytes` bytes, a multiple of 16), copied through the wave's 16 KB of
+// LDS at `lds`.  Rows >= T and pieces past the end of a row count as zero: they are copied from valid addresses, or not
+// at all, and zeroed when they are read.
+template <int NB, int DT>
+__device__ __forceinline__ void gram_cols_run(const unsigned char* __restrict__ X, int T, int row_bytes, int kb, int ke, int lane,
+                                              unsigned char* lds, f32x16 (&acc)[NB * (NB + 1) / 2]) {
+    constexpr int STAGE = NB * 32 * 128, NST = kWaveLds / STAGE;
+    constexpr int COPIES = NB * 4;                       // copy instructions of a whole stage, 8 rows each
+    const int n_stages = (ke - kb + kStageSteps - 1) / kStageSteps;
+    const int copies = min(COPIES, (T + 7) / 8);         // those with rows inside the example
+    const int limit = min(ke * 32, row_bytes);           // bytes of a row that this range has
+    // chunk c (16 bytes) of a stage row r lies at position c ^ ((r >> 1) & 7): 16 rows read at one c meet no bank twice
+    const unsigned char* src[COPIES];
+    int at[COPIES];
+#pragma unroll
+    for (int i = 0; i < COPIES; ++i) {
+        const int r = 8 * i + (lane >> 3);
+        src[i] = X + (size_t)min(r, T - 1) * row_bytes;
+        at[i] = kb * 32 + (((lane & 7) ^ ((r >> 1) & 7)) << 4);
+    }
+    const uint32_t base = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(LDS_PTR(unsigned char))lds);
+    auto issue = [&](int buf) {                          // the next stage (inline assembly: waited for with wait_copies)
+#pragma unroll
+        for (int i = 0; i < COPIES; ++i) {
+            if (i < copies) {
+                const uint64_t from = (uint64_t)(uintptr_t)(src[i] + (at[i] < limit ? at[i] : 0));
+                asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off" :: "s"(base + buf * STAGE + i * 1024), "v"(from) : "memory", "m0");
+            }
+            at[i] += 128;
+        }
+    };
     const int row = lane & 31, half = lane >> 5;
-    const uint16_t* p[NB];
+    bool in[NB];
+    uint32_t rd[NB];
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+        const int r = b * 32 + row;
+        in[b] = r < T;
+        rd[b] = (uint32_t)(r * 128 + ((half ^ ((r >> 1) & 7)) << 4));
+    }
+#pragma unroll
+    for (int p = 0; p < NST; ++p)
+        if (p < n_stages) issue(p);
+    for (int st = 0; st < n_stages; ++st) {
+        wait_copies(min(n_stages - 1 - st, NST - 1) * copies);
+        const unsigned char* sb = lds + (st % NST) * STAGE;
+        uint4 f[kStageSteps][NB];
+#pragma unroll
+        for (int u = 0; u < kStageSteps; ++u)
+#pragma unroll
+            for (int b = 0; b < NB; ++b) f[u][b] = *reinterpret_cast<const uint4*>(sb + (rd[b] ^ (u << 5)));
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");          // read: the buffer takes a later stage
+        if (st + NST < n_stages) issue(st % NST);
+        const int k = kb + st * kStageSteps;
+#pragma unroll
+        for (int u = 0; u < kStageSteps; ++u) {
+            if (k + u >= ke) break;                                  // uniform
+            uint4 g[NB];
+#pragma unroll
+            for (int b = 0; b < NB; ++b) {
+                const bool keep = in[b] && (k + u) * 32 + half * 16 < row_bytes;
+                g[b] = make_uint4(keep ? f[u][b].x : 0u, keep ? f[u][b].y : 0u, keep ? f[u][b].z : 0u, keep ? f[u][b].w : 0u);
+            }
+            gram_cols_mfma<NB, DT>(g, acc);
+        }
+    }
+}
+
+// float32 rows whose length is not a multiple of 4 start at any 4-byte address: four clamped 4-byte loads a piece
+template <int NB>
+__device__ __forceinline__ void gram_cols_run_odd(const float* __restrict__ X, int T, int D, int kb, int ke, int lane,
+                                                  f32x16 (&acc)[NB * (NB + 1) / 2]) {
+    const int row = lane & 31, half = lane >> 5;
+    const float* p[NB];
     bool in[NB];
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
@@ -62,105 +176,43 @@ __device__ __forceinline__ void gram_cols_run16(const uint16_t* __restrict__ X, 
         uint4 f[kColsSteps][NB];
 #pragma unroll
         for (int u = 0; u < kColsSteps; ++u) {
-            const int col = (k + u) * 16 + half * 8;
-            const bool ok = (k + u) < ke && col < D;                 // D is a multiple of 8: a piece is inside or outside
-            const int c = ok ? col : 0;
-#pragma unroll
-            for (int b = 0; b < NB; ++b) {
-                const uint4 v = *reinterpret_cast<const uint4*>(p[b] + c);
-                const bool keep = ok && in[b];
-                f[u][b] = make_uint4(keep ? v.x : 0u, keep ? v.y : 0u, keep ? v.z : 0u, keep ? v.w : 0u);
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < kColsSteps; ++u) {
-            if (k + u >= ke) break;                                  // uniform: the steps past the range hold zeros
-            const bf16x8 f0 = __builtin_bit_cast(bf16x8, f[u][0]);
-            acc[0] = In16<F16>::mfma(f0, f0, acc[0]);
-            if constexpr (NB == 2) {
-                const bf16x8 f1 = __builtin_bit_cast(bf16x8, f[u][1]);
-                acc[1] = In16<F16>::mfma(f0, f1, acc[1]);
-                acc[2] = In16<F16>::mfma(f1, f1, acc[2]);
-            }
-        }
-    }
-}
-
-// float32: a step is 8 columns, the lane's piece columns 4 * (lane / 32) .. + 3 of it; where D is not a multiple of 4
-// (rows then start at any 4-byte address) the piece is four clamped 4-byte loads
-template <int NB, bool VEC>
-__device__ __forceinline__ void gram_cols_run32(const float* __restrict__ X, int T, int D, int kb, int ke, int lane,
-                                                f32x16 (&acc)[NB * (NB + 1) / 2]) {
-    const int row = lane & 31, half = lane >> 5;
-    const float* p[NB];
-    bool in[NB];
-#pragma unroll
-    for (int b = 0; b < NB; ++b) {
-        const int r = b * 32 + row;
-        in[b] = r < T;
-        p[b] = X + (size_t)(r < T ? r : T - 1) * D;
-    }
-    for (int k = kb; k < ke; k += kColsSteps) {
-        float4 f[kColsSteps][NB];
-#pragma unroll
-        for (int u = 0; u < kColsSteps; ++u) {
             const int col = (k + u) * 8 + half * 4;
             const bool ok = (k + u) < ke && col < D;
             const int c = ok ? col : 0;
 #pragma unroll
             for (int b = 0; b < NB; ++b) {
                 const bool keep = ok && in[b];
-                if (VEC) {
-                    const float4 v = *reinterpret_cast<const float4*>(p[b] + c);
-                    f[u][b] = make_float4(keep ? v.x : 0.f, keep ? v.y : 0.f, keep ? v.z : 0.f, keep ? v.w : 0.f);
-                } else {
-                    const float x = p[b][c], y = p[b][min(c + 1, D - 1)], z = p[b][min(c + 2, D - 1)], w = p[b][min(c + 3, D - 1)];
-                    f[u][b] = make_float4(keep ? x : 0.f, (keep && c + 1 < D) ? y : 0.f, (keep && c + 2 < D) ? z : 0.f, (keep && c + 3 < D) ? w : 0.f);
-                }
+                const float x = p[b][c], y = p[b][min(c + 1, D - 1)], z = p[b][min(c + 2, D - 1)], w = p[b][min(c + 3, D - 1)];
+                f[u][b] = make_uint4(keep ? __float_as_uint(x) : 0u, (keep && c + 1 < D) ? __float_as_uint(y) : 0u,
+                                     (keep && c + 2 < D) ? __float_as_uint(z) : 0u, (keep && c + 3 < D) ? __float_as_uint(w) : 0u);
             }
         }
 #pragma unroll
         for (int u = 0; u < kColsSteps; ++u) {
             if (k + u >= ke) break;                                  // uniform: the steps past the range hold zeros
-            const float a0[4] = {f[u][0].x, f[u][0].y, f[u][0].z, f[u][0].w};
-#pragma unroll
-            for (int e = 0; e < 4; ++e) acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0[e], a0[e], acc[0], 0, 0, 0);
-            if constexpr (NB == 2) {
-                const float a1[4] = {f[u][1].x, f[u][1].y, f[u][1].z, f[u][1].w};
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0[e], a1[e], acc[1], 0, 0, 0);
-                    acc[2] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1[e], a1[e], acc[2], 0, 0, 0);
-                }
-            }
+            gram_cols_mfma<NB, 0>(f[u], acc);
         }
     }
 }
 
 // X_i of whichever type: DT 0 = float32, 1 = bf16, 2 = fp16 (the values of dp_dtype)
 template <int NB, int DT>
-__device__ __forceinline__ void gram_cols_run(const void* X, size_t ex, int T, int D, int kb, int ke, int lane,
-                                              f32x16 (&acc)[NB * (NB + 1) / 2]) {
+__device__ __forceinline__ void gram_cols_side(const void* X, size_t ex, int T, int D, int kb, int ke, int lane, unsigned char* lds,
+                                               f32x16 (&acc)[NB * (NB + 1) / 2]) {
+    constexpr int ES = DT == 0 ? 4 : 2;
     if constexpr (DT == 0) {
-        // (the choice sits outside the loops: a branch around every load would make each wait for the one before)
-        if ((D & 3) == 0) gram_cols_run32<NB, true>(static_cast<const float*>(X) + ex * T * D, T, D, kb, ke, lane, acc);
-        else              gram_cols_run32<NB, false>(static_cast<const float*>(X) + ex * T * D, T, D, kb, ke, lane, acc);
+        if ((D & 3) != 0) { gram_cols_run_odd<NB>(static_cast<const float*>(X) + ex * T * D, T, D, kb, ke, lane, acc); return; }
     }
-    else gram_cols_run16<NB, DT == 2>(static_cast<const uint16_t*>(X) + ex * T * D, T, D, kb, ke, lane, acc);
+    gram_cols_run<NB, DT>(static_cast<const unsigned char*>(X) + ex * T * D * ES, T, D * ES, kb, ke, lane, lds, acc);
 }
 
-// NB: 32-row blocks of positions (1: T <= 32, 2: T <= 64)
 template <int NB, int DT>
-__global__ __launch_bounds__(kThreads, 2) void k_gram_cols(GramColsArgs j) {
+__device__ __forceinline__ void gram_cols_block(const GramColsLayer& a, int item, float* part, unsigned char* lds) {
     constexpr int NT = NB * (NB + 1) / 2;            // tiles of the upper triangle
-    constexpr int SHARE = 2 * NT * 16 * 64;          // floats of one wave's share (both products)
-    __shared__ float red[2 * SHARE];
-    int li = 0;
-    while (li + 1 < j.n_layers && blockIdx.x >= j.layer[li + 1].first_block) ++li;
-    const GramColsLayer& a = j.layer[li];
-    const int item = blockIdx.x - a.first_block;
+    constexpr int SHARE = 2 * NT * 4 * 64;           // 16-byte units of one wave's share (both products)
+    static_assert(2 * SHARE * 16 <= 4 * kWaveLds, "the waves' shares meet where their stages were");
     const int ex = item / a.W, w = item - ex * a.W;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 
     f32x16 acc[2][NT];
 #pragma unroll
@@ -173,27 +225,33 @@ __global__ __launch_bounds__(kThreads, 2) void k_gram_cols(GramColsArgs j) {
     const int k0 = (w * 4 + wave) * a.per_wave;
     const int k1 = min(k0 + a.per_wave, a.steps);
     if (k0 < a.steps_a)
-        gram_cols_run<NB, DT>(a.A, (size_t)ex, a.T, a.d_in, k0, min(k1, a.steps_a), lane, acc[0]);
+        gram_cols_side<NB, DT>(a.A, (size_t)ex, a.T, a.d_in, k0, min(k1, a.steps_a), lane, lds + wave * kWaveLds, acc[0]);
     if (k1 > a.steps_a)
-        gram_cols_run<NB, DT>(a.G, (size_t)ex, a.T, a.d_out, max(k0, a.steps_a) - a.steps_a, k1 - a.steps_a, lane, acc[1]);
+        gram_cols_side<NB, DT>(a.G, (size_t)ex, a.T, a.d_out, max(k0, a.steps_a) - a.steps_a, k1 - a.steps_a, lane, lds + wave * kWaveLds, acc[1]);
 
     // waves 2, 3 -> LDS; waves 0, 1 add them; wave 1 -> LDS; wave 0 adds it and stores the workgroup's share
-    auto put = [&](float* slot) {
+    auto put = [&](float4* slot) {
 #pragma unroll
         for (int q = 0; q < 2; ++q)
 #pragma unroll
             for (int t = 0; t < NT; ++t)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) slot[((q * NT + t) * 16 + r) * 64 + lane] = acc[q][t][r];
+                for (int r = 0; r < 4; ++r)
+                    slot[((q * NT + t) * 4 + r) * 64 + lane] = make_float4(acc[q][t][4 * r], acc[q][t][4 * r + 1], acc[q][t][4 * r + 2], acc[q][t][4 * r + 3]);
     };
-    auto add = [&](const float* slot) {
+    auto add = [&](const float4* slot) {
 #pragma unroll
         for (int q = 0; q < 2; ++q)
 #pragma unroll
             for (int t = 0; t < NT; ++t)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) acc[q][t][r] += slot[((q * NT + t) * 16 + r) * 64 + lane];
+                for (int r = 0; r < 4; ++r) {
+                    const float4 v = slot[((q * NT + t) * 4 + r) * 64 + lane];
+                    acc[q][t][4 * r] += v.x; acc[q][t][4 * r + 1] += v.y; acc[q][t][4 * r + 2] += v.z; acc[q][t][4 * r + 3] += v.w;
+                }
     };
+    float4* red = reinterpret_cast<float4*>(lds);
+    __syncthreads();                                 // every wave is done with its stages
     if (wave >= 2) put(red + (wave - 2) * SHARE);
     __syncthreads();
     if (wave < 2) add(red + wave * SHARE);
@@ -202,13 +260,45 @@ __global__ __launch_bounds__(kThreads, 2) void k_gram_cols(GramColsArgs j) {
     __syncthreads();
     if (wave == 0) {
         add(red);
-        put(j.part + a.part_off + (size_t)item * SHARE);
+        put(reinterpret_cast<float4*>(part + a.part_off) + (size_t)item * SHARE);
     }
 }
 
-// sqnorm[ex] (+)= sum over the layers of the sum over the entries of (sum_w P_w) * (sum_w Q_w), the tile (0,1)
-// counted twice (it stands for its mirror image too); one workgroup of 1024 threads per example, the shares added in
-// the order of the workgroups, the layers in the order of the launch
+template <int DT>
+__global__ __launch_bounds__(kThreads, 2) void k_gram_cols(GramColsArgs j) {
+    __shared__ __attribute__((aligned(1024))) unsigned char lds[4 * kWaveLds];
+    int li = 0;
+    while (li + 1 < j.n_layers && blockIdx.x >= j.layer[li + 1].first_block) ++li;
+    const GramColsLayer& a = j.layer[li];
+    if (a.nb == 1) gram_cols_block<1, DT>(a, blockIdx.x - a.first_block, j.part, lds);
+    else           gram_cols_block<2, DT>(a, blockIdx.x - a.first_block, j.part, lds);
+}
+
+// Several layers: sums[ex][t] of a layer = the sum over the entries of triangle tile t of (sum_w P_w) * (sum_w Q_w), the
+// tile (0,1) counted twice (it stands for its mirror image too), the shares added in the order of the workgroups.  One
+// workgroup per (example, tile).  (A workgroup per example that walked all layers' shares read them at 20 GB/s each: 13 and
+// 19 us for 32 examples of four layers.)
+__global__ __launch_bounds__(kThreads) void k_gram_cols_sums(GramColsArgs j) {
+    __shared__ float red[4];
+    int li = 0;
+    while (li + 1 < j.n_layers && blockIdx.x >= j.layer[li + 1].first_finish) ++li;
+    const GramColsLayer& a = j.layer[li];
+    const int nt = a.nb == 1 ? 1 : 3, item = blockIdx.x - a.first_finish;
+    const int ex = item / nt, t = item - ex * nt;
+    const float4* base = reinterpret_cast<const float4*>(j.part + a.part_off) + ((size_t)ex * a.W * 2 * nt + t) * kThreads + threadIdx.x;
+    float4 p = make_float4(0.f, 0.f, 0.f, 0.f), q = p;
+    auto sum = [](float4& x, const float4& y) { x.x += y.x; x.y += y.y; x.z += y.z; x.w += y.w; };
+#pragma unroll 4
+    for (int w = 0; w < a.W; ++w) {
+        sum(p, base[(size_t)w * 2 * nt * kThreads]);
+        sum(q, base[((size_t)w * 2 + 1) * nt * kThreads]);
+    }
+    float s = (p.x * q.x + p.y * q.y) + (p.z * q.z + p.w * q.w);
+    s = block_sum_256(s, red);
+    if (threadIdx.x == 0) a.sums[item] = (nt == 3 && t == 1) ? 2.0f * s : s;
+}
+
+// One layer: sqnorm[ex] (+)= the same sums, added up; one workgroup of 1024 threads per example
 constexpr int kFinishThreads = 1024;
 template <int NB>
 __global__ __launch_bounds__(kFinishThreads) void k_gram_cols_finish(GramColsArgs j, int accumulate,
@@ -217,27 +307,22 @@ __global__ __launch_bounds__(kFinishThreads) void k_gram_cols_finish(GramColsArg
     constexpr int HALF = NT * 16 * 64;
     constexpr int PER = HALF / kFinishThreads;       // entries per thread: 1 or 3 (one of each tile)
     __shared__ float red[kFinishThreads / 64];
-    const int ex = blockIdx.x;
-    float s = 0.f;
-    for (int li = 0; li < j.n_layers; ++li) {
-        const int W = j.layer[li].W;
-        const float* base = j.part + j.layer[li].part_off + (size_t)ex * W * 2 * HALF + threadIdx.x;
-        float p[PER], q[PER];
+    const int ex = blockIdx.x, W = j.layer[0].W;
+    const float* base = j.part + j.layer[0].part_off + (size_t)ex * W * 2 * HALF + threadIdx.x;
+    float p[PER], q[PER];
 #pragma unroll
-        for (int i = 0; i < PER; ++i) { p[i] = 0.f; q[i] = 0.f; }
+    for (int i = 0; i < PER; ++i) { p[i] = 0.f; q[i] = 0.f; }
 #pragma unroll 4
-        for (int w = 0; w < W; ++w) {
+    for (int w = 0; w < W; ++w) {
 #pragma unroll
-            for (int i = 0; i < PER; ++i) {
-                p[i] += base[(size_t)w * 2 * HALF + i * kFinishThreads];
-                q[i] += base[(size_t)w * 2 * HALF + HALF + i * kFinishThreads];
-            }
+        for (int i = 0; i < PER; ++i) {
+            p[i] += base[(size_t)w * 2 * HALF + i * kFinishThreads];
+            q[i] += base[(size_t)w * 2 * HALF + HALF + i * kFinishThreads];
         }
-        float t = 0.f;
-#pragma unroll
-        for (int i = 0; i < PER; ++i) t += (NB == 2 && i == 1) ? 2.0f * (p[i] * q[i]) : p[i] * q[i];
-        s += t;
     }
+    float s = 0.f;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) s += (NB == 2 && i == 1) ? 2.0f * (p[i] * q[i]) : p[i] * q[i];
     s = wave_sum(s);
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
     __syncthreads();
@@ -274,56 +359,115 @@ GramColsPlan plan_gram_cols(int B, int T, int d_in, int d_out, int dt) {
     return p;
 }
 
+int gram_cols_sums(const GramColsPlan& p) { return p.nb == 1 ? 1 : 3; }
+
 namespace {
-template <int NB> hipError_t launch_cols_nb(const GramColsArgs& a, unsigned grid, int dt, hipStream_t st) {
-    if (dt == 0)      k_gram_cols<NB, 0><<<grid, kThreads, 0, st>>>(a);
-    else if (dt == 1) k_gram_cols<NB, 1><<<grid, kThreads, 0, st>>>(a);
-    else              k_gram_cols<NB, 2><<<grid, kThreads, 0, st>>>(a);
+// The layers of a shared launch fill the chip together, so each takes fewer workgroups than it would alone, all of about one
+// length: few shares to store and to add, and waves that stream (a wave of kColsSteps waits once for all it loads).  The
+// length, counted in steps of 32 rows, that makes  rounds of 512 workgroups x (length + what a workgroup costs besides)
+// least, of those whose shares take at most max_floats (at the longest, one workgroup per example, they do).
+void plan_cols_shared(const GramLayerDesc* layers, int n_layers, int B, int dt, size_t max_floats, GramColsPlan* p) {
+    constexpr int kOverhead = 24;
+    const int step = dt == 0 ? 8 : 16;
+    int steps[kGramColsLayers], longest = kColsSteps;
+    for (int l = 0; l < n_layers; ++l) {
+        p[l] = plan_gram_cols(B, layers[l].T, layers[l].d_in, layers[l].d_out, dt);
+        steps[l] = ceil_div(layers[l].d_in, step) + ceil_div(layers[l].d_out, step);
+        longest = longest > p[l].nb * ceil_div(steps[l], 4) ? longest : p[l].nb * ceil_div(steps[l], 4);
+    }
+    if (max_floats == kAnySlices) return;
+    auto take = [&](int l, int length, int& W) {              // whole stages per wave, so that the copies move whole lines
+        const int least = length / p[l].nb > kColsSteps ? length / p[l].nb : kColsSteps;
+        const int w = ceil_div(steps[l], 4 * least);
+        const int per_wave = (ceil_div(steps[l], 4 * w) + kStageSteps - 1) / kStageSteps * kStageSteps;
+        W = ceil_div(steps[l], 4 * per_wave);
+        return per_wave;
+    };
+    int64_t best_cost = -1;
+    int best = longest;
+    for (int length = kColsSteps; length < longest + 16; length += length < 64 ? 4 : 16) {
+        const int len = length < longest ? length : longest;
+        int64_t blocks = 0;
+        int most = 0;
+        size_t floats = 0;
+        for (int l = 0; l < n_layers; ++l) {
+            int W;
+            const int per_wave = take(l, len, W);
+            blocks += (int64_t)B * W;
+            floats += p[l].ws_floats / (size_t)p[l].W * (size_t)W;
+            most = most > p[l].nb * per_wave ? most : p[l].nb * per_wave;
+        }
+        if (floats > max_floats) continue;
+        const int64_t cost = ((blocks + 511) / 512) * (most + kOverhead);
+        if (best_cost < 0 || cost < best_cost) { best_cost = cost; best = len; }
+    }
+    for (int l = 0; l < n_layers; ++l) {
+        const size_t share = p[l].ws_floats / (size_t)p[l].W;
+        p[l].per_wave = take(l, best, p[l].W);
+        p[l].ws_floats = share * (size_t)p[l].W;
+    }
+}
+
+// fills the launch's arguments and makes the first launch; sums: nullptr, or each layer's own array; max_floats: kAnySlices for
+// the layers' own plans
+hipError_t launch_cols(const GramLayerDesc* layers, float* const* sums, int n_layers, int B, float* ws, size_t max_floats, hipStream_t st, int dt, GramColsArgs& a,
+                       unsigned& finish_blocks) {
+    if (n_layers < 1 || n_layers > kGramColsLayers || dt < 0 || dt > 2) return hipErrorInvalidValue;
+    a.part = ws; a.n_layers = n_layers;
+    const int step = dt == 0 ? 8 : 16;
+    int64_t blocks = 0, finish = 0;
+    size_t off = 0;
+    GramColsPlan plans[kGramColsLayers];
+    plan_cols_shared(layers, n_layers, B, dt, max_floats, plans);
+    for (int l = 0; l < n_layers; ++l) {
+        const GramLayerDesc& y = layers[l];
+        const GramColsPlan& p = plans[l];
+        if (!p.use) return hipErrorInvalidValue;
+        GramColsLayer& g = a.layer[l];
+        g.A = y.A; g.G = y.G;
+        g.sums = sums ? sums[l] : nullptr;
+        g.part_off = off;
+        g.T = y.T; g.d_in = y.d_in; g.d_out = y.d_out;
+        g.steps_a = ceil_div(y.d_in, step); g.steps = g.steps_a + ceil_div(y.d_out, step);
+        g.W = p.W; g.per_wave = p.per_wave; g.nb = p.nb;
+        g.first_block = (unsigned)blocks; g.first_finish = (unsigned)finish;
+        blocks += (int64_t)B * p.W;
+        finish += (int64_t)B * gram_cols_sums(p);
+        off += p.ws_floats;
+    }
+    for (int l = n_layers; l < kGramColsLayers; ++l) a.layer[l] = a.layer[0];
+    if (blocks >= (int64_t(1) << 24) || finish >= (int64_t(1) << 24)) return hipErrorInvalidValue;   // (B < 2^8 where W >= 2)
+    finish_blocks = (unsigned)finish;
+    if (dt == 0)      k_gram_cols<0><<<(unsigned)blocks, kThreads, 0, st>>>(a);
+    else if (dt == 1) k_gram_cols<1><<<(unsigned)blocks, kThreads, 0, st>>>(a);
+    else              k_gram_cols<2><<<(unsigned)blocks, kThreads, 0, st>>>(a);
     return hipGetLastError();
 }
 }  // namespace
 
-// layers: every one with plan_gram_cols(...).use and the same .nb; ws: the sum of their ws_floats; dt: 0 float32, 1 bf16, 2 fp16
-hipError_t launch_gram_cols_layers(const GramLayerDesc* layers, int n_layers, int B, bool accumulate, float* sqnorm, float* ws,
-                                   hipStream_t st, int dt, const ClipOut* co) {
-    if (n_layers < 1 || n_layers > kGramColsLayers || dt < 0 || dt > 2) return hipErrorInvalidValue;
+hipError_t launch_gram_cols_layers(const GramLayerDesc* layers, float* const* sums, int n_layers, int B, float* ws, size_t max_floats,
+                                   hipStream_t st, int dt) {
     GramColsArgs a;
-    a.part = ws; a.n_layers = n_layers;
-    const int step = dt == 0 ? 8 : 16;
-    int nb = 0;
-    int64_t blocks = 0;
-    size_t off = 0;
-    for (int l = 0; l < n_layers; ++l) {
-        const GramLayerDesc& y = layers[l];
-        const GramColsPlan p = plan_gram_cols(B, y.T, y.d_in, y.d_out, dt);
-        if (!p.use || (l > 0 && p.nb != nb)) return hipErrorInvalidValue;
-        nb = p.nb;
-        GramColsLayer& g = a.layer[l];
-        g.A = y.A; g.G = y.G;
-        g.part_off = off;
-        g.T = y.T; g.d_in = y.d_in; g.d_out = y.d_out;
-        g.steps_a = ceil_div(y.d_in, step); g.steps = g.steps_a + ceil_div(y.d_out, step);
-        g.W = p.W; g.per_wave = p.per_wave;
-        g.first_block = (unsigned)blocks;
-        blocks += (int64_t)B * p.W;
-        off += p.ws_floats;
-    }
-    for (int l = n_layers; l < kGramColsLayers; ++l) a.layer[l] = a.layer[0];
-    if (blocks >= (int64_t(1) << 31)) return hipErrorInvalidValue;
-    const hipError_t e = nb == 1 ? launch_cols_nb<1>(a, (unsigned)blocks, dt, st) : launch_cols_nb<2>(a, (unsigned)blocks, dt, st);
+    unsigned finish = 0;
+    const hipError_t e = launch_cols(layers, sums, n_layers, B, ws, max_floats, st, dt, a, finish);
     if (e != hipSuccess) return e;
-    const float C = co ? co->C : 0.f;
-    float* clip = co ? co->clip : nullptr;
-    if (nb == 1) k_gram_cols_finish<1><<<B, kFinishThreads, 0, st>>>(a, accumulate ? 1 : 0, sqnorm, C, clip);
-    else         k_gram_cols_finish<2><<<B, kFinishThreads, 0, st>>>(a, accumulate ? 1 : 0, sqnorm, C, clip);
+    k_gram_cols_sums<<<finish, kThreads, 0, st>>>(a);
     return hipGetLastError();
 }
 
 hipError_t launch_gram_cols(const GramColsPlan& p, const void* A, const void* G, int B, int T, int d_in, int d_out,
                             bool accumulate, float* sqnorm, float* ws, hipStream_t st, int dt, const ClipOut* co) {
     if (!p.use) return hipErrorInvalidValue;
-    GramLayerDesc y{A, G, T, d_in, d_out, nullptr, nullptr};
-    return launch_gram_cols_layers(&y, 1, B, accumulate, sqnorm, ws, st, dt, co);
+    const GramLayerDesc y{A, G, T, d_in, d_out, nullptr, nullptr};
+    GramColsArgs a;
+    unsigned finish = 0;
+    const hipError_t e = launch_cols(&y, nullptr, 1, B, ws, kAnySlices, st, dt, a, finish);
+    if (e != hipSuccess) return e;
+    const float C = co ? co->C : 0.f;
+    float* clip = co ? co->clip : nullptr;
+    if (p.nb == 1) k_gram_cols_finish<1><<<B, kFinishThreads, 0, st>>>(a, accumulate ? 1 : 0, sqnorm, C, clip);
+    else           k_gram_cols_finish<2><<<B, kFinishThreads, 0, st>>>(a, accumulate ? 1 : 0, sqnorm, C, clip);
+    return hipGetLastError();
 }
 
 }  // namespace dpk

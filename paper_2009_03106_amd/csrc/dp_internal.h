@@ -22,7 +22,7 @@ inline bool tiles_fit(int M, int N, int TM, int TN) {
 // defer: the several-layers call collects the partial sums of its layers that run one by one and folds them all in
 // one launch at the end (launch_finalize_queue) instead of one small launch per layer; a launcher that ends in
 // launch_finalize_partials then only records where its partial sums are.
-struct FinalizeQueue { static constexpr int kMax = 16; const float* partial[kMax]; int n[kMax]; int count = 0; };
+struct FinalizeQueue { static constexpr int kMax = 32; const float* partial[kMax]; int n[kMax]; int count = 0; };
 struct ClipOut { float C; float* clip; FinalizeQueue* defer = nullptr; };
 hipError_t launch_finalize_queue(const FinalizeQueue& q, int B, bool accumulate, float* sqnorm, hipStream_t st, const ClipOut* co);
 hipError_t launch_sqnorm_dense(const void* A, const void* G, int B, int d_in, int d_out, int dt,
@@ -273,11 +273,13 @@ struct GramLayerDesc { const void* A; const void* G; int T, d_in, d_out; float* 
 // dt: 0 float32, 1 bf16, 2 fp16 (the values of dp_dtype); use: whether this kernel takes the shape; ws_floats: its scratch
 struct GramColsPlan { bool use; int nb, W, per_wave; size_t ws_floats; };
 GramColsPlan plan_gram_cols(int B, int T, int d_in, int d_out, int dt);
-// several such layers (all with the same plan .nb) in one launch; ws: the sum of their ws_floats (A, G, T, d_in, d_out of
-// the descriptors are used)
+// several such layers in one launch (and one that adds the shares): sums[l] gets the layer's [B][gram_cols_sums(plan)] sums,
+// to be added by the caller; ws: max_floats, enough for one share per example and layer (A, G, T, d_in, d_out of the
+// descriptors are used)
 constexpr int kGramColsLayers = 16;
-hipError_t launch_gram_cols_layers(const GramLayerDesc* layers, int n_layers, int B, bool accumulate, float* sqnorm, float* ws,
-                                   hipStream_t st, int dt, const ClipOut* co = nullptr);
+int gram_cols_sums(const GramColsPlan& p);
+hipError_t launch_gram_cols_layers(const GramLayerDesc* layers, float* const* sums, int n_layers, int B, float* ws, size_t max_floats,
+                                   hipStream_t st, int dt);
 hipError_t launch_gram_cols(const GramColsPlan& p, const void* A, const void* G, int B, int T, int d_in, int d_out,
                             bool accumulate, float* sqnorm, float* ws, hipStream_t st, int dt, const ClipOut* co = nullptr);
 hipError_t launch_gram_bf16_dma_layers(const GramLayerDesc* layers, int n_layers, int B, bool accumulate, float* sqnorm,

@@ -293,19 +293,24 @@ __global__ void k_finalize_partials(const float* __restrict__ partial, int B, in
     if (clip) clip[i] = clip_factor_of(s, C);
 }
 
-// The partial sums of several layers, each [B][n_l]: one wave per example; lane j adds entries j, j + 64, ... of every
-// layer in the order of the queue, then the lanes' sums are added in the fixed order of wave_sum.
-__global__ __launch_bounds__(64) void k_finalize_queue(FinalizeQueue q, int accumulate, float* __restrict__ sqnorm, float C,
-                                                       float* __restrict__ clip) {
-    const int i = blockIdx.x, lane = threadIdx.x;
+// The partial sums of several layers, each [B][n_l]: one workgroup per example, whose threads take the entries of all layers
+// in one row (thread j entries j, j + 256, ... of the layers in the order of the queue), so that they are one memory round
+// trip (a wave that walked the layers one after the other took 8 us for 16 of them); their sums are added in the fixed
+// order of block_sum_256.
+__global__ __launch_bounds__(256) void k_finalize_queue(FinalizeQueue q, int accumulate, float* __restrict__ sqnorm, float C,
+                                                        float* __restrict__ clip) {
+    __shared__ float red[4];
+    const int i = blockIdx.x;
+    int total = 0;
+    for (int l = 0; l < q.count; ++l) total += q.n[l];
     float v = 0.f;
-#pragma unroll 4
-    for (int l = 0; l < q.count; ++l) {
-        const float* p = q.partial[l] + (size_t)i * q.n[l];
-        for (int j = lane; j < q.n[l]; j += 64) v += p[j];
+    for (int j = threadIdx.x; j < total; j += 256) {
+        int at = j, l = 0;
+        while (at >= q.n[l]) at -= q.n[l++];
+        v += q.partial[l][(size_t)i * q.n[l] + at];
     }
-    v = wave_sum(v);
-    if (lane == 0) {
+    v = block_sum_256(v, red);
+    if (threadIdx.x == 0) {
         const float s = accumulate ? sqnorm[i] + v : v;
         sqnorm[i] = s;
         if (clip) clip[i] = clip_factor_of(s, C);
@@ -314,7 +319,7 @@ __global__ __launch_bounds__(64) void k_finalize_queue(FinalizeQueue q, int accu
 
 hipError_t launch_finalize_queue(const FinalizeQueue& q, int B, bool accumulate, float* sqnorm, hipStream_t st, const ClipOut* co) {
     if (q.count < 1 || q.count > FinalizeQueue::kMax || B < 1) return hipErrorInvalidValue;
-    k_finalize_queue<<<(unsigned)B, 64, 0, st>>>(q, accumulate ? 1 : 0, sqnorm, co ? co->C : 0.f, co ? co->clip : nullptr);
+    k_finalize_queue<<<(unsigned)B, 256, 0, st>>>(q, accumulate ? 1 : 0, sqnorm, co ? co->C : 0.f, co ? co->clip : nullptr);
     return hipGetLastError();
 }
 

@@ -1,0 +1,73 @@
+"""Gram norms of layers of few positions and wide rows in a small batch: the columns of an example are split over
+workgroups, whose shares are added by a second launch."""
+import pytest
+import torch
+
+from paper_2009_03106_amd import dpclip as dp
+
+pytestmark = pytest.mark.gpu
+
+
+def _tensor(gen, B, T, d, dtype):
+    """B x T x d numbers in the middle of NaNs: nothing outside the matrix may count."""
+    pad = 1024
+    buf = torch.full((B * T * d + 2 * pad,), float("nan"), device="cuda", dtype=dtype)
+    x = buf[pad:pad + B * T * d].view(B, T, d)
+    x.copy_(torch.randn((B, T, d), device="cuda", generator=gen))
+    return x
+
+
+def _norm64(A, G):
+    return (A.double() @ A.double().transpose(1, 2).contiguous() * (G.double() @ G.double().transpose(1, 2).contiguous())).sum((1, 2))
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16, torch.float16])
+@pytest.mark.parametrize("B", [1, 20, 200])
+@pytest.mark.parametrize("shapes", [
+    [(16, 4608, 512)],                                                          # alone: the norms in the second launch
+    [(33, 1032, 264)],
+    [(2, 1024, 512), (7, 1048, 520), (31, 2304, 256), (32, 1152, 1032)],        # one 32-row block
+    [(64, 2304, 256), (33, 1160, 512), (8, 1024, 1024), (57, 3080, 72)],        # one and two in a launch
+    [(5 + 3 * l, 1024 + 8 * l, 512) for l in range(18)],                        # more than a launch takes
+])
+def test_norms_against_float64(dtype, B, shapes):
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    layers = [(_tensor(gen, B, T, a, dtype), _tensor(gen, B, T, b, dtype)) for T, a, b in shapes]
+    ref = sum(_norm64(A, G) for A, G in layers)
+    s = dp.layers_sqnorm(layers, path="gram")
+    # float32 sums over at most 4608 columns of products of random sign: sqrt(4608) 2^-24 of an entry, 1e-5 covers it
+    assert float(((s.double() - ref) / ref).abs().max()) < 1e-5
+    acc = torch.full((B,), 2.0, device="cuda")
+    dp.layers_sqnorm(layers, acc, path="gram", accumulate=True)
+    assert torch.allclose(acc.double(), ref + 2.0, rtol=1e-5, atol=0)
+
+
+@pytest.mark.parametrize("shapes", [[(17, 1023, 769)], [(64, 1025, 514), (16, 2047, 333), (3, 1021, 1022)]])
+def test_float32_rows_of_any_length(shapes):
+    gen = torch.Generator(device="cuda").manual_seed(8)
+    layers = [(_tensor(gen, 9, T, a, torch.float32), _tensor(gen, 9, T, b, torch.float32)) for T, a, b in shapes]
+    ref = sum(_norm64(A, G) for A, G in layers)
+    s = dp.layers_sqnorm(layers, path="gram")
+    assert float(((s.double() - ref) / ref).abs().max()) < 1e-5
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_clip_factors_beside_other_layers(dtype):
+    """Dense layers and layers of other norm kernels in the same step: the factors are those of the complete norms."""
+    gen = torch.Generator(device="cuda").manual_seed(9)
+    shapes = [(16, 1152, 512), (64, 1152, 256), (1, 512, 10), (256, 64, 64), (1024, 27, 64), (16, 2304, 512)]
+    layers = [(_tensor(gen, 12, T, a, dtype), _tensor(gen, 12, T, b, dtype)) for T, a, b in shapes]
+    ref = sum(_norm64(A, G) for A, G in layers)
+    for keep in (slice(0, 2), slice(0, 3), slice(0, 6), slice(1, 3), slice(0, 4)):
+        part = layers[keep]
+        want = sum(_norm64(A, G) for A, G in part)
+        C = float(want.median().sqrt())
+        sq, clip = torch.zeros(12, device="cuda"), torch.zeros(12, device="cuda")
+        grads = [torch.zeros((A.shape[-1], G.shape[-1]), device="cuda") for A, G in part]
+        squeezed = [(A.squeeze(1), G.squeeze(1)) if A.shape[1] == 1 else (A, G) for A, G in part]
+        arr, n, code = descs = dp.layer_descs(squeezed, grads)
+        need = max(dp.layers_workspace_bytes(arr, n, code), dp.layers_clipped_workspace_bytes(arr, n, code))
+        dp.layers_step(descs, C, sq, clip, torch.empty(need, dtype=torch.uint8, device="cuda"))
+        assert torch.allclose(sq.double(), want, rtol=1e-5, atol=0)
+        assert torch.allclose(clip.double(), (C / want.sqrt()).clamp(max=1.0), rtol=1e-5, atol=0)
+    assert torch.allclose(dp.layers_sqnorm([(A.squeeze(1), G.squeeze(1)) if A.shape[1] == 1 else (A, G) for A, G in layers]).double(), ref, rtol=1e-5, atol=0)
