@@ -338,28 +338,74 @@ __device__ __forceinline__ void tn_dma_tile(const DmaArgs& a, const int L) {
 
     wait_stage(min(n_stages - 1, NST - 1));
     __builtin_amdgcn_s_barrier();
+    // the first stage of the next example: the factor that rescales the running tile
+    auto next_example = [&]() -> float {
+        sub = 0;
+        ++ex;
+        const float c_next = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, vclip), ex - ex0));
+        const float ratio = c_cur / c_next;
+        // a zero factor, or one far below the largest so far, after a non-zero one: leave this example out
+        skip = __builtin_isinf(ratio) || c_next < c_ref * 0x1p-40f;
+        const float by = skip || c_next == c_cur ? 1.0f : ratio;
+        if (!skip) { c_cur = c_next; c_ref = fmaxf(c_ref, c_next); }
+        return by;
+    };
+    auto rescale = [&](float by) {
+#pragma unroll
+        for (int i = 0; i < FM; ++i)
+#pragma unroll
+            for (int j = 0; j < FN; ++j)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[i][j][r] *= by;
+    };
+    if constexpr (GEO::WAVES == 8) {
+        // Two waves per SIMD in opposite phases: while one multiplies a stage the other reads its fragments of one, so that
+        // the matrix unit does not wait for the LDS port.  (With all 8 waves in one phase a stage took 1620 cycles, 1024 of
+        // them MFMAs; 64 examples of 512 x (768, 2304), (768, 768), (768, 3072), (3072, 768): step 755 -> 731 us.)  Every phase ends at a barrier; waves 4 .. 7 start one phase
+        // later.  A stage's buffer is free once both halves have read it, one phase after the first: the copies of stage
+        // st - 1 + NST are requested while stage st is read, behind the reads.
+        const bool late = __builtin_amdgcn_readfirstlane(wave >> 2) != 0;
+        bf16x8 f[KS][NF];
+        int buf = 0, before = NST - 1;              // of stage st, and of the one before
+        if (late) __builtin_amdgcn_s_barrier();
+        for (int st = 0; st < n_stages; ++st) {
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) read_kstep(f[ks], (uint32_t)buf * STAGE_BYTES, ks);
+            __builtin_amdgcn_sched_barrier(0);
+            if (st > 0 && st - 1 + NST < n_stages) issue(before);
+            before = buf;
+            buf = buf + 1 == NST ? 0 : buf + 1;
+            float by = 1.0f;
+            bool scale = false;
+            if (MODE == 0 && sub == spe) {
+                by = next_example();
+                scale = __builtin_amdgcn_readfirstlane((int)(by != 1.0f)) != 0;
+            }
+            ++sub;
+            // stage st + 1 must have landed: the copies outstanding are those of the NST - 2 stages behind it, or fewer
+            if (st + NST <= n_stages) wait_vmcnt<(NST - 2) * LPS>(); else wait_vmcnt<0>();
+            __builtin_amdgcn_s_waitcnt(0xC07F);                                          // lgkmcnt(0): the fragments
+            __builtin_amdgcn_s_barrier();
+            __builtin_amdgcn_sched_barrier(0);
+            __builtin_amdgcn_s_setprio(1);
+            if (MODE == 0 && scale) rescale(by);
+            if (MODE != 0 || !skip) {
+#pragma unroll
+                for (int ks = 0; ks < KS; ++ks) mfma_kstep(f[ks]);
+            }
+            __builtin_amdgcn_s_setprio(0);
+            __builtin_amdgcn_sched_barrier(0);
+            if (!(late && st + 1 == n_stages)) __builtin_amdgcn_s_barrier();
+        }
+    } else {
     bf16x8 f[2][NF];                                // fragments of the current / next k step
     read_kstep(f[0], 0u, 0);
 
     for (int st = 0; st < n_stages; ++st) {
         const uint32_t sb = (uint32_t)(st % NST) * STAGE_BYTES;
         if (MODE == 0 && sub == spe) {
-            // first stage of the next example: rescale the running tile
-            sub = 0;
-            ++ex;
-            const float c_next = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, vclip), ex - ex0));
-            const float ratio = c_cur / c_next;
-            // a zero factor, or one far below the largest so far, after a non-zero one: leave this example out
-            skip = __builtin_isinf(ratio) || c_next < c_ref * 0x1p-40f;
-            if (c_next != c_cur && !skip) {
-#pragma unroll
-                for (int i = 0; i < FM; ++i)
-#pragma unroll
-                    for (int j = 0; j < FN; ++j)
-#pragma unroll
-                        for (int r = 0; r < 16; ++r) acc[i][j][r] *= ratio;
-            }
-            if (!skip) { c_cur = c_next; c_ref = fmaxf(c_ref, c_next); }
+            const float by = next_example();
+            if (by != 1.0f) rescale(by);
         }
         ++sub;
 #pragma unroll
@@ -380,6 +426,7 @@ __device__ __forceinline__ void tn_dma_tile(const DmaArgs& a, const int L) {
             if (MODE != 0 || !skip) mfma_kstep(f[ks & 1]);
             __builtin_amdgcn_sched_barrier(0);
         }
+    }
     }
 
     const int lrow = lane & 31, lhalf = lane >> 5;
@@ -413,6 +460,17 @@ __device__ __forceinline__ void tn_dma_tile(const DmaArgs& a, const int L) {
     }
     // the tile holds (1 / c_cur) * sum: finish with the last example's factor
     float* out = a.out + (size_t)z * a.slice;
+    if (m0 + GEO::TM <= a.M && n0 + GEO::TN <= a.N && !a.accumulate) {
+        // a whole tile: nothing to ask between the stores
+        float* p = out + (size_t)(m0 + wm * FM * 32 + 4 * lhalf) * a.N + n0 + wn * FN * 32 + lrow;
+#pragma unroll
+        for (int i = 0; i < FM; ++i)
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+#pragma unroll
+                for (int j = 0; j < FN; ++j) p[(size_t)(i * 32 + 8 * (r >> 2) + (r & 3)) * a.N + j * 32] = acc[i][j][r] * c_cur;
+        return;
+    }
 #pragma unroll
     for (int i = 0; i < FM; ++i)
 #pragma unroll
