@@ -13,6 +13,7 @@
 // One stage is one k step of the MFMA.  Which k a byte position of the operand registers stands for does not matter
 // as long as the A and the G fragment agree; both are read with the same row pattern (lanes 0-31: rows 0-31 of the
 // stage, lanes 32-63: rows 32-63, 8 rows per read).
+#include <algorithm>
 #include "dp_common.h"
 #include "dp_internal.h"
 #include <type_traits>
@@ -224,23 +225,16 @@ __device__ __forceinline__ void tn_f8_tile(const Dma8Args& a, const int L) {
 
     // rows 8 x .. 8 x + 7 of this lane half's 32 rows come with read x; the swizzle of a row depends on r % 8 only,
     // so the four reads differ by whole rows
-    auto read_stage = [&](v8i32 (&f)[NF], uint32_t sb) {
+    auto read_fragment = [&](uint32_t sb, int x) -> v8i32 {
         LDS_PTR(unsigned char) b = (LDS_PTR(unsigned char))lds + sb;
+        const int rb = x < FM ? RBA : RBG;
+        v2i32 q[4];
 #pragma unroll
-        for (int x = 0; x < NF; ++x) {
-            const int rb = x < FM ? RBA : RBG;
-            v2i32 q[4];
-#pragma unroll
-            for (int y = 0; y < 4; ++y) q[y] = __builtin_amdgcn_ds_read_tr8_b64_v2i32((LDS_PTR(v2i32))(b + rd[x] + y * 8 * rb));
-            f[x] = v8i32{q[0][0], q[0][1], q[1][0], q[1][1], q[2][0], q[2][1], q[3][0], q[3][1]};
-        }
+        for (int y = 0; y < 4; ++y) q[y] = __builtin_amdgcn_ds_read_tr8_b64_v2i32((LDS_PTR(v2i32))(b + rd[x] + y * 8 * rb));
+        return v8i32{q[0][0], q[0][1], q[1][0], q[1][1], q[2][0], q[2][1], q[3][0], q[3][1]};
     };
-    auto mfma_stage = [&](const v8i32 (&f)[NF]) {
-#pragma unroll
-        for (int i = 0; i < FM; ++i)
-#pragma unroll
-            for (int j = 0; j < FN; ++j)
-                acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(f[i], f[FM + j], acc[i][j], FA, FG, 0, 0, 0, 0);
+    auto mfma = [&](const v8i32 (&f)[NF], int t) {
+        acc[t / FN][t % FN] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(f[t / FN], f[FM + t % FN], acc[t / FN][t % FN], FA, FG, 0, 0, 0, 0);
     };
     // stage s (relative) landed once at most `ahead` later stages' copies are outstanding
     auto wait_stage = [&](int ahead) {
@@ -252,50 +246,103 @@ __device__ __forceinline__ void tn_f8_tile(const Dma8Args& a, const int L) {
 
     wait_stage(min(n_stages - 1, NST - 1));
     __builtin_amdgcn_s_barrier();
-    v8i32 f[2][NF];                                 // fragments of the current / next stage
-    read_stage(f[0], 0u);
-
-    // One stage: its fragments were requested while the stage before it was multiplied.  The barrier that makes
-    // stage st + 1 visible sits in front of the MFMAs of stage st, so that the reads of stage st + 1 are in flight
-    // under them; behind it the buffer of stage st (all reads retired) takes the copies of stage st + NST.
-    auto step = [&](int st, auto cur_tag) {
-        constexpr int CUR = decltype(cur_tag)::value;
-        if (MODE == 0 && sub == spe) {
-            // first stage of the next example: rescale the running tile
-            sub = 0;
-            ++ex;
-            const float c_next = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, vclip), ex - ex0));
-            const float ratio = c_cur / c_next;
-            // a zero factor, or one below 2^-40 of the largest so far (the tile in that unit would leave the float32
-            // range), after a non-zero one cannot become the tile's unit: the example's MFMAs are skipped and the unit
-            // stays, i.e. it counts with factor 0
-            skip = __builtin_isinf(ratio) || c_next < c_ref * 0x1p-40f;
-            if (c_next != c_cur && !skip) {
-#pragma unroll
-                for (int i = 0; i < FM; ++i)
-#pragma unroll
-                    for (int j = 0; j < FN; ++j)
-#pragma unroll
-                        for (int r = 0; r < 16; ++r) acc[i][j][r] *= ratio;
-            }
-            if (!skip) { c_cur = c_next; c_ref = fmaxf(c_ref, c_next); }
-        }
-        ++sub;
-        __builtin_amdgcn_s_waitcnt(0xC07F);                                              // lgkmcnt(0): this stage's fragments
-        if (st + 1 < n_stages) {
-            // stage st + 1 must have landed (later stages may stay in flight), for every wave; every wave has
-            // also retired its reads of stage st, so that buffer can take stage st + NST
-            wait_stage(min(n_stages - 2 - st, NST - 2));
-            __builtin_amdgcn_s_barrier();
-            if (st + NST < n_stages) issue(st % NST);
-            read_stage(f[CUR ^ 1], (uint32_t)((st + 1) % NST) * STAGE_BYTES);
-        }
-        if (MODE != 0 || !skip) mfma_stage(f[CUR]);
-        __builtin_amdgcn_sched_barrier(0);
+    // the first stage of the next example: the factor that rescales the running tile
+    auto next_example = [&]() -> float {
+        sub = 0;
+        ++ex;
+        const float c_next = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, vclip), ex - ex0));
+        const float ratio = c_cur / c_next;
+        // a zero factor, or one below 2^-40 of the largest so far (the tile in that unit would leave the float32 range),
+        // after a non-zero one cannot become the tile's unit: the example's MFMAs are skipped and the unit stays, i.e. it
+        // counts with factor 0
+        skip = __builtin_isinf(ratio) || c_next < c_ref * 0x1p-40f;
+        const float by = skip || c_next == c_cur ? 1.0f : ratio;
+        if (!skip) { c_cur = c_next; c_ref = fmaxf(c_ref, c_next); }
+        return by;
     };
-    for (int st = 0; st < n_stages; st += 2) {
-        step(st, std::integral_constant<int, 0>{});
-        if (st + 1 < n_stages) step(st + 1, std::integral_constant<int, 1>{});
+    auto rescale = [&](float by, int i, int j) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[i][j][r] *= by;
+    };
+    if constexpr (GEO::WAVES == 8) {
+        // Two waves per SIMD in opposite phases: while one multiplies a stage the other reads its fragments of one, so that
+        // the matrix unit never waits for the LDS port.  (With all 8 waves in one phase a stage took 1730 cycles, 1024 of them
+        // MFMAs; the four layers of 64 examples of 512 positions: step 409 -> 393 us.)  Every phase ends at a barrier; waves 4 .. 7 start one phase later.  A stage's buffer is free once both
+        // halves have read it, one phase after the first: the copies of stage st - 1 + NST are requested while stage st is
+        // read, behind the reads.
+        const bool late = __builtin_amdgcn_readfirstlane(wave >> 2) != 0;
+        v8i32 f[NF];
+        int buf = 0, before = NST - 1;              // of stage st, and of the one before
+        if (late) __builtin_amdgcn_s_barrier();
+        for (int st = 0; st < n_stages; ++st) {
+#pragma unroll
+            for (int x = 0; x < NF; ++x) f[x] = read_fragment((uint32_t)buf * STAGE_BYTES, x);
+            __builtin_amdgcn_sched_barrier(0);
+            if (st > 0 && st - 1 + NST < n_stages) issue(before);
+            before = buf;
+            buf = buf + 1 == NST ? 0 : buf + 1;
+            float by = 1.0f;
+            bool scale = false;
+            if (MODE == 0 && sub == spe) {
+                by = next_example();
+                scale = __builtin_amdgcn_readfirstlane((int)(by != 1.0f)) != 0;
+            }
+            ++sub;
+            // stage st + 1 must have landed: the copies outstanding are those of the NST - 2 stages behind it, or fewer
+            if (st + NST <= n_stages) wait_vmcnt8<(NST - 2) * LPS>(); else wait_vmcnt8<0>();
+            __builtin_amdgcn_s_waitcnt(0xC07F);                                          // lgkmcnt(0): the fragments
+            __builtin_amdgcn_s_barrier();
+            __builtin_amdgcn_sched_barrier(0);
+            __builtin_amdgcn_s_setprio(1);
+            if (MODE == 0 && scale) {
+#pragma unroll
+                for (int t = 0; t < FM * FN; ++t) rescale(by, t / FN, t % FN);
+            }
+            if (MODE != 0 || !skip) {
+#pragma unroll
+                for (int t = 0; t < FM * FN; ++t) mfma(f, t);
+            }
+            __builtin_amdgcn_s_setprio(0);
+            __builtin_amdgcn_sched_barrier(0);
+            if (!(late && st + 1 == n_stages)) __builtin_amdgcn_s_barrier();
+        }
+    } else {
+        v8i32 f[2][NF];                             // fragments of the current / next stage
+#pragma unroll
+        for (int x = 0; x < NF; ++x) f[0][x] = read_fragment(0u, x);
+        // One stage: its fragments were requested while the stage before it was multiplied.  The barrier that makes
+        // stage st + 1 visible sits in front of the MFMAs of stage st, so that the reads of stage st + 1 are in flight
+        // under them; behind it the buffer of stage st (all reads retired) takes the copies of stage st + NST.
+        auto step = [&](int st, auto cur_tag) {
+            constexpr int CUR = decltype(cur_tag)::value;
+            if (MODE == 0 && sub == spe) {
+                const float by = next_example();
+                if (by != 1.0f) {
+#pragma unroll
+                    for (int t = 0; t < FM * FN; ++t) rescale(by, t / FN, t % FN);
+                }
+            }
+            ++sub;
+            __builtin_amdgcn_s_waitcnt(0xC07F);                                          // lgkmcnt(0): this stage's fragments
+            if (st + 1 < n_stages) {
+                // stage st + 1 must have landed (later stages may stay in flight), for every wave; every wave has
+                // also retired its reads of stage st, so that buffer can take stage st + NST
+                wait_stage(min(n_stages - 2 - st, NST - 2));
+                __builtin_amdgcn_s_barrier();
+                if (st + NST < n_stages) issue(st % NST);
+#pragma unroll
+                for (int x = 0; x < NF; ++x) f[CUR ^ 1][x] = read_fragment((uint32_t)((st + 1) % NST) * STAGE_BYTES, x);
+            }
+            if (MODE != 0 || !skip) {
+#pragma unroll
+                for (int t = 0; t < FM * FN; ++t) mfma(f[CUR], t);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        for (int st = 0; st < n_stages; st += 2) {
+            step(st, std::integral_constant<int, 0>{});
+            if (st + 1 < n_stages) step(st + 1, std::integral_constant<int, 1>{});
+        }
     }
 
     const int lrow = lane & 31, lhalf = lane >> 5;
@@ -329,6 +376,17 @@ __device__ __forceinline__ void tn_f8_tile(const Dma8Args& a, const int L) {
     }
     // the tile holds (1 / c_cur) * sum: finish with the last example's factor
     float* out = a.out + (size_t)z * a.slice;
+    if (m0 + GEO::TM <= a.M && n0 + GEO::TN <= a.N && !a.accumulate) {
+        // a whole tile: nothing to ask between the stores
+        float* p = out + (size_t)(m0 + wm * FM * 32 + 4 * lhalf) * a.N + n0 + wn * FN * 32 + lrow;
+#pragma unroll
+        for (int i = 0; i < FM; ++i)
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+#pragma unroll
+                for (int j = 0; j < FN; ++j) p[(size_t)(i * 32 + 8 * (r >> 2) + (r & 3)) * a.N + j * 32] = acc[i][j][r] * c_cur;
+        return;
+    }
 #pragma unroll
     for (int i = 0; i < FM; ++i)
 #pragma unroll
@@ -361,17 +419,81 @@ struct Joint8Layer {
     const unsigned char* A; const unsigned char* G; const float* clip;
     float* slices;       // the layer's K slices; the gradient itself where one slice is the whole sum (then `accumulate` applies)
     int T, M, N, tiles_m, tiles_n, splits, stages_total, stages_per_split, first_item, accumulate;
+    int first_pack, pack;       // two lengths: the first workgroup of the layer's last slices, and how many of them a workgroup takes
 };
 struct Joint8Args {
     Joint8Layer layer[kJointLayers];
-    int n_layers, n_items, per_xcd, B;
+    int n_layers, n_items, n_groups, per_xcd, B;      // n_items: workgroups with one item; n_groups: all
 };
+
+// One launch of at most 256 workgroups, each of about the same number of stages: a layer's K range is cut into slices of one
+// length L and a shorter rest, a workgroup takes one slice of L stages or the rests of several tiles one after the other.
+// Few partial tiles to store and to fold, one start-up per compute unit: 108 tiles of 512 stages take 2 slices of 221
+// stages and a rest of 70, three rests to a workgroup, 252 workgroups, where equal slices take 7 of 74, three rounds.
+// (64 examples of 512 x (768, 2304), (768, 768), (768, 3072), (3072, 768): step 393 -> 346 us.)
+// (The 16-bit sums keep the shorter slices: their error grows with the square root of the slice, 4.4e-7 of the result at
+// 147 stages, 6.7e-7 at 341; that of the 8-bit sums is the instruction's own, 1.06e-5 in both cases.)
+struct TwoLengths { bool use; int sps[kJointLayers], splits[kJointLayers], longs[kJointLayers], pack[kJointLayers]; int items, groups; };
+TwoLengths plan_two_lengths(const JointShape* sh, int n_layers, int B, const JointPlan& equal) {
+    constexpr int64_t kItem = 16;                            // what an item costs besides its stages, in stages
+    // cost of the equal slices and of these, in stages: the rounds and the fold (4 MB in about one)
+    size_t floats_equal = 0;
+    int longest = 0;
+    for (int l = 0; l < n_layers; ++l) {
+        floats_equal += (size_t)equal.splits[l] * (size_t)splitk_slice_elems((int64_t)sh[l].M * sh[l].N);
+        longest = longest > equal.sps[l] ? longest : equal.sps[l];
+    }
+    int64_t best_cost = (((equal.items + 255) / 256) * (longest + kItem) + (int64_t)(floats_equal >> 20)) * 31 / 32;
+    TwoLengths best{};
+    int64_t stages_max = 1;
+    for (int l = 0; l < n_layers; ++l) {
+        const int64_t stages = (int64_t)B * (sh[l].T / DK8);
+        stages_max = stages_max > stages ? stages_max : stages;
+    }
+    for (int n = 1; n <= 8; ++n)
+        for (int pk = 1; pk <= 8; ++pk) {
+            // n slices of L and a rest r of which pk fill a workgroup: n L + r = stages_max, pk (r + kItem) = L + kItem
+            const int64_t L = (pk * (stages_max + kItem) - kItem + (int64_t)n * pk) / ((int64_t)n * pk + 1);
+            if (L < 16) continue;
+            TwoLengths p{};
+            int64_t items = 0, packs = 0, most = 0;
+            size_t floats = 0;
+            for (int l = 0; l < n_layers; ++l) {
+                const int64_t spe = sh[l].T / DK8, stages = (int64_t)B * spe, tiles = (int64_t)equal.tiles_m[l] * equal.tiles_n[l];
+                const int64_t len = L < 63 * spe ? L : 63 * spe;            // at most 64 examples in a slice
+                int64_t longs = stages / len, rest = stages - longs * len, sps = len;
+                if (longs == 0 || rest < 8) {                              // no rest worth an item: equal slices
+                    longs = longs == 0 ? 1 : longs;
+                    sps = (stages + longs - 1) / longs;
+                    if (sps > 63 * spe) { ++longs; sps = (stages + longs - 1) / longs; }
+                    longs = (stages + sps - 1) / sps;
+                    rest = 0;
+                }
+                p.sps[l] = (int)sps; p.longs[l] = (int)longs; p.splits[l] = (int)longs + (rest > 0 ? 1 : 0);
+                p.pack[l] = rest > 0 ? (int)std::max<int64_t>(1, (L + kItem) / (rest + kItem)) : 0;
+                items += tiles * longs;
+                most = std::max(most, sps + kItem);
+                if (rest > 0) {
+                    packs += (tiles + p.pack[l] - 1) / p.pack[l];
+                    most = std::max(most, (int64_t)p.pack[l] * (rest + kItem));
+                }
+                floats += (size_t)p.splits[l] * (size_t)splitk_slice_elems((int64_t)sh[l].M * sh[l].N);
+            }
+            if (floats > floats_equal) continue;                           // (the scratch is the equal slices')
+            const int64_t cost = ((items + packs + 255) / 256) * most + (int64_t)(floats >> 20);
+            if (cost < best_cost) { best_cost = cost; best = p; best.use = true; best.items = (int)items; best.groups = (int)(items + packs); }
+        }
+    return best;
+}
+
 template <int FA, int FG>
 __global__ __launch_bounds__(Geo8L::THREADS, Geo8L::OCC) void k_tn_f8_dma_joint(Joint8Args j) {
     const int L = (blockIdx.x & 7) * j.per_xcd + (blockIdx.x >> 3);
-    if (L >= j.n_items) return;
+    if (L >= j.n_groups) return;
+    const bool rests = L >= j.n_items;
     int l = 0;
-    while (l + 1 < j.n_layers && L >= j.layer[l + 1].first_item) ++l;
+    if (rests) while (l + 1 < j.n_layers && L >= j.layer[l + 1].first_pack) ++l;
+    else       while (l + 1 < j.n_layers && L >= j.layer[l + 1].first_item) ++l;
     const Joint8Layer& y = j.layer[l];
     Dma8Args a;
     a.A = y.A; a.G = y.G; a.clip = y.clip;
@@ -380,7 +502,14 @@ __global__ __launch_bounds__(Geo8L::THREADS, Geo8L::OCC) void k_tn_f8_dma_joint(
     a.tiles_m = y.tiles_m; a.tiles_n = y.tiles_n; a.splits = y.splits;
     a.stages_total = y.stages_total; a.stages_per_split = y.stages_per_split;
     a.per_xcd = 0; a.accumulate = y.accumulate; a.zero = nullptr;
-    tn_f8_tile<Geo8L, 0, false, FA, FG>(a, L - y.first_item);
+    // a layer's last slices are the last of its items
+    const int tiles = y.tiles_m * y.tiles_n;
+    const int first = rests ? (y.splits - 1) * tiles + (L - y.first_pack) * y.pack : L - y.first_item;
+    const int end = rests ? min(first + y.pack, y.splits * tiles) : first + 1;
+    for (int item = first; item < end; ++item) {
+        if (item > first) __syncthreads();               // every wave is done with the stages of the item before
+        tn_f8_tile<Geo8L, 0, false, FA, FG>(a, item);
+    }
 }
 
 // 0: not for this kernel; 1: Geo8L; 2: Geo8T
@@ -504,27 +633,33 @@ size_t joint8_workspace_floats(const JointShape* sh, int n_layers, int B, size_t
 hipError_t launch_clipped_f8_dma_joint(const JointShape* sh, const JointOperands* op, int n_layers, int B, bool accumulate,
                                        float stddev, uint64_t seed, float* ws, hipStream_t st, int fmt, size_t max_floats) {
     if (n_layers < 1 || n_layers > kJointLayers) return hipErrorInvalidValue;
-    const JointPlan p = plan_joint(sh, n_layers, B, DK8, Geo8L::TM, 256, max_floats);
-    if (p.items >= (int64_t(1) << 28)) return hipErrorInvalidValue;
+    const JointPlan equal = plan_joint(sh, n_layers, B, DK8, Geo8L::TM, 256, max_floats);
+    if (equal.items >= (int64_t(1) << 28)) return hipErrorInvalidValue;
+    const TwoLengths two = plan_two_lengths(sh, n_layers, B, equal);
+    const int* splits = two.use ? two.splits : equal.splits;
     Joint8Args j;
     float* slices = ws;
-    int64_t first = 0;
+    int64_t first = 0, packs = two.items;
     for (int l = 0; l < n_layers; ++l) {
         Joint8Layer& y = j.layer[l];
         y.A = reinterpret_cast<const unsigned char*>(op[l].A); y.G = reinterpret_cast<const unsigned char*>(op[l].G); y.clip = op[l].clip;
         // one slice and no noise to add: the launch writes the gradient itself, nothing to fold
-        const bool whole = p.splits[l] == 1 && stddev == 0.0f;
+        const bool whole = splits[l] == 1 && stddev == 0.0f;
         y.slices = whole ? op[l].grad : slices;
         y.accumulate = whole && accumulate ? 1 : 0;
         y.T = sh[l].T; y.M = sh[l].M; y.N = sh[l].N;
-        y.tiles_m = p.tiles_m[l]; y.tiles_n = p.tiles_n[l]; y.splits = p.splits[l];
-        y.stages_total = (int)((int64_t)B * (sh[l].T / DK8)); y.stages_per_split = p.sps[l];
+        y.tiles_m = equal.tiles_m[l]; y.tiles_n = equal.tiles_n[l]; y.splits = splits[l];
+        y.stages_total = (int)((int64_t)B * (sh[l].T / DK8)); y.stages_per_split = two.use ? two.sps[l] : equal.sps[l];
+        const int64_t tiles = (int64_t)y.tiles_m * y.tiles_n;
         y.first_item = (int)first;
-        first += (int64_t)p.tiles_m[l] * p.tiles_n[l] * p.splits[l];
-        slices += (size_t)p.splits[l] * (size_t)splitk_slice_elems((int64_t)sh[l].M * sh[l].N);
+        first += tiles * (two.use ? two.longs[l] : splits[l]);
+        y.pack = two.use ? two.pack[l] : 0;
+        y.first_pack = (int)packs;
+        if (y.pack > 0) packs += (tiles + y.pack - 1) / y.pack;
+        slices += (size_t)splits[l] * (size_t)splitk_slice_elems((int64_t)sh[l].M * sh[l].N);
     }
     for (int l = n_layers; l < kJointLayers; ++l) j.layer[l] = j.layer[0];
-    j.n_layers = n_layers; j.n_items = (int)p.items; j.per_xcd = ceil_div(p.items, 8);
+    j.n_layers = n_layers; j.n_items = (int)first; j.n_groups = two.use ? two.groups : (int)first; j.per_xcd = ceil_div(j.n_groups, 8);
     j.B = B;
     const unsigned grid = 8u * (unsigned)j.per_xcd;
     if (fmt == 2)      k_tn_f8_dma_joint<0, 0><<<grid, Geo8L::THREADS, 0, st>>>(j);
@@ -539,7 +674,7 @@ hipError_t launch_clipped_f8_dma_joint(const JointShape* sh, const JointOperands
     for (int l = 0; l < n_layers; ++l) {
         if (j.layer[l].slices == op[l].grad) continue;                 // written by the launch itself
         f.ws[nf] = j.layer[l].slices; f.grad[nf] = op[l].grad; f.n[nf] = (int64_t)sh[l].M * sh[l].N;
-        f.splits[nf] = p.splits[l]; f.noise_offset[nf] = op[l].noise_offset;
+        f.splits[nf] = splits[l]; f.noise_offset[nf] = op[l].noise_offset;
         ++nf;
     }
     if (nf == 0) return hipSuccess;
