@@ -377,12 +377,233 @@ __global__ __launch_bounds__(kThreads, GNST * GSTAGE <= 65536 ? 2 : 1) void k_gr
     if (tid == 0) a.partial[(size_t)ly.first + (size_t)ex * ly.npairs + slot] = diag ? s : 2.0f * s;
 }
 
+// The same sums in larger pieces, for launches that fill the chip with them: one workgroup of 8 waves per example and
+//   * diagonal block of 256 rows: of its 4 x 4 blocks of 64 x 64 the six above the diagonal go to waves 0 .. 5, the four on
+//     it, of which three quarters are formed (the rest is their mirror image), in pairs to waves 6 and 7;
+//   * 256 x 128 piece above them: 64 x 64 a wave.
+// What bounds these kernels is the way from L2 to LDS (12.5 TB/s in the kernel above: 64 examples of 512 positions copied
+// 3.2 GB in 0.25 ms).  An example of 512 rows is copied 2.5 times over here and 4 times there.
+constexpr int WROWS = 256, WCOLS = 128;                       // rows of the row side, and of the column side above the diagonal
+constexpr int WNST = 3;                                       // stages resident in LDS: one workgroup per compute unit
+constexpr int WSTAGE = (WROWS + WCOLS) * ROWB;
+constexpr int kWideThreads = 512;
+// pieces of an example: a diagonal block per 256 rows, and behind it the 128-row column pieces to its right
+__host__ __device__ inline int gram_wide_pieces(int T) {
+    const int nb = (T + WROWS - 1) / WROWS, nc = (T + WCOLS - 1) / WCOLS;
+    int n = 0;
+    for (int b = 0; b < nb; ++b) n += 1 + (nc > 2 * (b + 1) ? nc - 2 * (b + 1) : 0);
+    return n;
+}
+
+// One wave's part of a piece.  ON: two 64 x 64 blocks on the diagonal (rows r0 .., r1 ..), else the block (r0 .., r1 ..) above
+// it; DIAG: a diagonal piece, whose column side is its row side.  idle: the wave has no rows inside the example.
+template <int FMT, bool ON, bool DIAG>
+__device__ __forceinline__ float gram_wide_wave(const GramDmaLayer& ly, int ex, int row0, int col0, int r0, int r1, bool idle, unsigned char* lds) {
+    constexpr bool F16 = FMT == 1, F8 = fmt_is8(FMT);
+    constexpr int ES = F8 ? 1 : 2, GKE = ROWB / ES;
+    constexpr int UNITS = ON ? 6 : 4;                    // 32 x 32 tiles of the wave
+    constexpr int CPS = DIAG ? 4 : 6;                    // copies per stage and wave
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int sa = ly.d_in / GKE, n_stages = sa + ly.d_out / GKE;
+
+    // ---- copies: wave w moves rows 32 w .. + 31 of the row side and 16 w .. + 15 of the column side, 8 an instruction
+    const int lrow8 = lane / CPR, cp = lane % CPR;
+    uint32_t off[2][CPS];                                // [0] = A phase, [1] = G phase
+#pragma unroll
+    for (int u = 0; u < CPS; ++u) {
+        const int r = u < 4 ? wave * 32 + u * RPI + lrow8 : wave * 16 + (u - 4) * RPI + lrow8;   // row inside the side
+        const uint32_t c16 = (uint32_t)((cp ^ gram_swz(r)) << 4);
+        const uint32_t t = (uint32_t)min((u < 4 ? row0 : col0) + r, ly.T - 1);
+        off[0][u] = t * (uint32_t)ly.d_in * ES + c16;
+        off[1][u] = t * (uint32_t)ly.d_out * ES + c16;
+    }
+    const unsigned char* baseA = ly.A + (size_t)ex * ly.T * ly.d_in * ES;
+    const unsigned char* baseG = ly.G + (size_t)ex * ly.T * ly.d_out * ES;
+    const uint32_t lds_base = (uint32_t)(uintptr_t)(LDS_PTR(unsigned char))lds;
+    const uint32_t to_rows = __builtin_amdgcn_readfirstlane(lds_base + wave * 32 * ROWB);
+    const uint32_t to_cols = __builtin_amdgcn_readfirstlane(lds_base + WROWS * ROWB + wave * 16 * ROWB);
+    auto issue_phase = [&](const unsigned char* sbase, const uint32_t (&o)[CPS], int buf) {
+#pragma unroll
+        for (int u = 0; u < CPS; ++u) {
+            const uint32_t to = (u < 4 ? to_rows + u * 1024 : to_cols + (u - 4) * 1024) + buf * WSTAGE;
+            asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2" :: "s"(to), "v"(o[u]), "s"(sbase) : "memory", "m0");
+        }
+    };
+    auto issue = [&](int st, int buf) {
+        if (st < sa) issue_phase(baseA + st * ROWB, off[0], buf);
+        else issue_phase(baseG + (st - sa) * ROWB, off[1], buf);
+    };
+
+    // ---- fragments 0, 1: rows r0 .. + 63; 2, 3: rows r1 .. + 63 (of the column side above the diagonal)
+    const int lrow = lane & 31, lhalf = lane >> 5;
+    int rd[4];
+#pragma unroll
+    for (int x = 0; x < 4; ++x) {
+        const int r = (x < 2 ? r0 : r1) + (x & 1) * 32 + lrow;
+        rd[x] = (x >= 2 && !DIAG ? WROWS * ROWB : 0) + r * ROWB + ((lhalf ^ gram_swz(r)) << 4);
+    }
+    f32x16 accP[UNITS], accQ[UNITS];
+#pragma unroll
+    for (int t = 0; t < UNITS; ++t)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) { accP[t][r] = 0.f; accQ[t][r] = 0.f; }
+    // the fragments of tile t: above the diagonal (0, 2) (0, 3) (1, 2) (1, 3); on it (1, 0) (0, 0) (1, 1) and the same of 2, 3
+    auto left = [](int t) { return ON ? (t < 3 ? (t == 1 ? 0 : 1) : (t == 4 ? 2 : 3)) : t >> 1; };
+    auto right = [](int t) { return ON ? (t < 3 ? (t == 2 ? 1 : 0) : (t == 5 ? 3 : 2)) : 2 + (t & 1); };
+
+    int buf = 0;                                         // of the current stage
+    // at the end of stage st: stage st + 1 is there for every wave, every wave is done reading stage st
+    auto meet = [&](int st) {
+        if (st + 2 < n_stages) wait_vm<CPS>(); else wait_vm<0>();
+        __builtin_amdgcn_s_barrier();
+        if (st + WNST < n_stages) issue(st + WNST, buf);
+        buf = buf + 1 == WNST ? 0 : buf + 1;
+    };
+    bf16x8 f[2][4];
+    auto read_kstep = [&](bf16x8 (&g)[4], int ks) {
+        if (idle) return;
+#pragma unroll
+        for (int x = 0; x < 4; ++x) g[x] = *reinterpret_cast<const bf16x8*>(lds + buf * WSTAGE + (rd[x] ^ (ks << 5)));
+    };
+    auto stage = [&](int st, f32x16 (&acc)[UNITS]) {
+#pragma unroll
+        for (int ks = 0; ks < GK / 16; ++ks) {
+            __builtin_amdgcn_s_waitcnt(0xC07F);          // lgkmcnt(0): this k step's fragments (requested a k step ago)
+            if (ks + 1 < GK / 16) read_kstep(f[(ks + 1) & 1], ks + 1);
+            else if (st + 1 < n_stages) { meet(st); read_kstep(f[0], 0); }
+            if (!idle) {
+#pragma unroll
+                for (int t = 0; t < UNITS; ++t) acc[t] = In16<F16>::mfma(f[ks & 1][left(t)], f[ks & 1][right(t)], acc[t]);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    v8i32 f8[ON ? 1 : 2][4];
+    auto read_k8 = [&](v8i32 (&g)[4], int K) {
+        if (idle) return;
+#pragma unroll
+        for (int x = 0; x < 4; ++x) {
+            const uint4 lo = *reinterpret_cast<const uint4*>(lds + buf * WSTAGE + (rd[x] ^ ((2 * K) << 5)));
+            const uint4 hi = *reinterpret_cast<const uint4*>(lds + buf * WSTAGE + (rd[x] ^ ((2 * K + 1) << 5)));
+            g[x] = v8i32{(int)lo.x, (int)lo.y, (int)lo.z, (int)lo.w, (int)hi.x, (int)hi.y, (int)hi.z, (int)hi.w};
+        }
+    };
+    auto stage8 = [&](int st, f32x16 (&acc)[UNITS], auto tag) {
+        constexpr int F = decltype(tag)::value;
+#pragma unroll
+        for (int K = 0; K < 2; ++K) {
+            if (ON) read_k8(f8[0], K);                   // (192 registers of sums leave room for one set of fragments)
+            __builtin_amdgcn_s_waitcnt(0xC07F);
+            if (K == 0) { if (!ON) read_k8(f8[ON ? 0 : 1], 1); }
+            else if (st + 1 < n_stages) { meet(st); if (!ON) read_k8(f8[0], 0); }
+            if (!idle) {
+#pragma unroll
+                for (int t = 0; t < UNITS; ++t) acc[t] = mfma8<F>(f8[ON ? 0 : K][left(t)], f8[ON ? 0 : K][right(t)], acc[t]);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+#pragma unroll
+    for (int p = 0; p < WNST; ++p)
+        if (p < n_stages) issue(p, p);
+    if (n_stages >= WNST) wait_vm<(WNST - 1) * CPS>(); else wait_vm<0>();
+    __builtin_amdgcn_s_barrier();
+    if constexpr (F8) {
+        if (!ON) read_k8(f8[0], 0);
+        for (int st = 0; st < sa; ++st) stage8(st, accP, std::integral_constant<int, fmt8_of_A(FMT)>{});
+        for (int st = sa; st < n_stages; ++st) stage8(st, accQ, std::integral_constant<int, fmt8_of_G(FMT)>{});
+    } else {
+        read_kstep(f[0], 0);
+        for (int st = 0; st < sa; ++st) stage(st, accP);
+        for (int st = sa; st < n_stages; ++st) stage(st, accQ);
+    }
+    // the sum of the products, tiles off the diagonal twice; rows and columns beyond T are masked (they hold clamped rows)
+    float s = 0.f;
+#pragma unroll
+    for (int t = 0; t < UNITS; ++t) {
+        const int l = left(t), r = right(t);
+        const int col = (DIAG ? row0 : col0) + (r < 2 ? r0 : r1) + (r & 1) * 32 + lrow;
+        const int row1 = row0 + (l < 2 ? r0 : r1) + (l & 1) * 32 + 4 * lhalf;
+        float v = 0.f;
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+            const int row = row1 + 8 * (k >> 2) + (k & 3);
+            v += (row < ly.T && col < ly.T) ? accP[t][k] * accQ[t][k] : 0.f;
+        }
+        s += ON && l == r ? v : 2.0f * v;
+    }
+    return idle ? 0.f : s;
+}
+
+template <int FMT>
+__global__ __launch_bounds__(kWideThreads, 2) void k_gram_wide(GramDmaArgs a) {
+    __shared__ __attribute__((aligned(1024))) unsigned char lds[WNST * WSTAGE];
+    __shared__ float red[8];
+    // (items as in k_gram_bf16_dma: every XCD takes a contiguous eighth of every layer's list)
+    const int xcd = blockIdx.x & 7;
+    int q = blockIdx.x >> 3;
+    int li = 0;
+    while (li < a.n_layers && q >= a.layer[li].per_xcd) { q -= a.layer[li].per_xcd; ++li; }
+    if (li >= a.n_layers) return;
+    const GramDmaLayer ly = a.layer[li];
+    const int L = xcd * ly.per_xcd + q;
+    if (L >= a.B * ly.npairs) return;
+    const int ex = L / ly.npairs, slot = L - ex * ly.npairs;
+    const int nc = (ly.T + WCOLS - 1) / WCOLS;
+    int b = 0, c = slot;                                 // row block, and 0 for its diagonal piece or 1 + the column piece
+    for (;; ++b) {
+        const int n = 1 + max(0, nc - 2 * (b + 1));
+        if (c < n) break;
+        c -= n;
+    }
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int row0 = b * WROWS;
+    float s;
+    if (c > 0) {
+        const int col0 = (2 * (b + 1) + c - 1) * WCOLS, r0 = (wave >> 1) * 64, r1 = (wave & 1) * 64;
+        s = gram_wide_wave<FMT, false, false>(ly, ex, row0, col0, r0, r1, col0 + r1 >= ly.T, lds);
+    } else if (wave < 6) {                               // (0,1) (0,2) (0,3) (1,2) (1,3) (2,3)
+        const int r0 = wave < 3 ? 0 : wave < 5 ? 64 : 128, r1 = wave < 3 ? 64 * (wave + 1) : wave < 5 ? 64 * (wave - 1) : 192;
+        s = gram_wide_wave<FMT, false, true>(ly, ex, row0, 0, r0, r1, row0 + r1 >= ly.T, lds);
+    } else {
+        const int r0 = wave == 6 ? 0 : 64, r1 = r0 + 128;
+        s = gram_wide_wave<FMT, true, true>(ly, ex, row0, 0, r0, r1, row0 + r0 >= ly.T, lds);
+    }
+    s = wave_sum(s);
+    if ((threadIdx.x & 63) == 0) red[wave] = s;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        float v = 0.f;
+#pragma unroll
+        for (int w = 0; w < 8; ++w) v += red[w];
+        a.partial[(size_t)ly.first + (size_t)ex * ly.npairs + slot] = v;
+    }
+}
+
 }  // namespace
 
 bool gram_dma_ok(int T, int d_in, int d_out, int fmt) {
     const int64_t dmax = d_in > d_out ? d_in : d_out;
     const int es = fmt_is8(fmt) ? 1 : 2, gke = ROWB / es;
     return T > 64 && (d_in % gke) == 0 && (d_out % gke) == 0 && (int64_t)T * dmax * es < (int64_t(1) << 31);   // 32-bit lane offsets
+}
+
+// Whether a launch takes the larger pieces: no column sums wanted, and 10 % less by two estimates fitted to 240 measured shapes
+// (T = 130 .. 1024, 4 to 128 examples, 256 to 3072 columns; in microseconds for 768 + 3072 columns of 16 bits).  The larger
+// pieces go over the chip 256 at a time, 66 us a round and 45 to 70 for a last one that is not full; the pairs 512 at a
+// time with a tail that the next ones fill.  64 examples of 512 positions: 70 and 95 us, 128: 148 and 175; 64 of 768
+// positions, whose pieces fill 2.25 rounds, 183 and 169.
+static bool gram_wide(const GramLayerDesc* layers, int n_layers, int B) {
+    int64_t items = 0, pairs = 0;
+    for (int l = 0; l < n_layers; ++l) {
+        if (layers[l].upart) return false;
+        items += (int64_t)B * gram_wide_pieces(layers[l].T);
+        pairs += (int64_t)B * plan_gram_bf16(layers[l].T, layers[l].d_in, layers[l].d_out).npairs;
+    }
+    const int64_t last = items % 256;
+    const double wide = 66.0 * (double)(items / 256) + (last > 0 ? 45.0 + 25.0 * (double)last / 256.0 : 0.0);
+    const double small = pairs <= 256 ? 37.0 : pairs <= 512 ? 53.0 : 14.0 + 0.118 * (double)pairs;
+    return wide < 0.9 * small;
 }
 
 // Several layers in one launch (at most kGramBatch, every one passing gram_dma_ok); partial gets the layers' item
@@ -396,8 +617,10 @@ hipError_t launch_gram_bf16_dma_layers(const GramLayerDesc* layers, int n_layers
     fin.n_layers = n_layers;
     int64_t first = 0, queue = 0;
     bool any_bias = false;
+    const bool wide = gram_wide(layers, n_layers, B);
     for (int l = 0; l < n_layers; ++l) {
-        const GramPlan p = plan_gram_bf16(layers[l].T, layers[l].d_in, layers[l].d_out);
+        GramPlan p = plan_gram_bf16(layers[l].T, layers[l].d_in, layers[l].d_out);
+        if (wide) p.npairs = gram_wide_pieces(layers[l].T);   // (fewer: the scratch is the pairs')
         GramDmaLayer& y = a.layer[l];
         y.A = static_cast<const unsigned char*>(layers[l].A); y.G = static_cast<const unsigned char*>(layers[l].G);
         y.T = layers[l].T; y.d_in = layers[l].d_in; y.d_out = layers[l].d_out;
@@ -416,7 +639,13 @@ hipError_t launch_gram_bf16_dma_layers(const GramLayerDesc* layers, int n_layers
     if (queue * 8 >= (int64_t(1) << 31)) return hipErrorInvalidValue;
     a.per_xcd = (int)queue;
     const unsigned grid = 8u * (unsigned)a.per_xcd;
-    if (any_bias) {
+    if (wide) {
+        if (fmt == 0)      k_gram_wide<0><<<grid, kWideThreads, 0, st>>>(a);
+        else if (fmt == 1) k_gram_wide<1><<<grid, kWideThreads, 0, st>>>(a);
+        else if (fmt == 2) k_gram_wide<2><<<grid, kWideThreads, 0, st>>>(a);
+        else if (fmt == 3) k_gram_wide<3><<<grid, kWideThreads, 0, st>>>(a);
+        else               k_gram_wide<4><<<grid, kWideThreads, 0, st>>>(a);
+    } else if (any_bias) {
         if (fmt == 0) k_gram_bf16_dma<0, true><<<grid, kThreads, 0, st>>>(a);
         else if (fmt == 1) k_gram_bf16_dma<1, true><<<grid, kThreads, 0, st>>>(a);
         else return hipErrorInvalidValue;                     // 8-bit types: the caller takes the bias rows in a pass of their own

@@ -1,0 +1,42 @@
+"""Gram norms in pieces of 256 rows: launches that fill the chip with them, ragged last rows, layers of several lengths."""
+import pytest
+import torch
+
+from paper_2009_03106_amd import dpclip as dp
+
+pytestmark = pytest.mark.gpu
+
+
+def _norm64(A, G):
+    a, g = A.double(), G.double()
+    return ((a @ a.transpose(1, 2).contiguous()) * (g @ g.transpose(1, 2).contiguous())).sum((1, 2))
+
+
+# float32 sums of exact products: 1e-5 covers 1024 columns; the 8-bit instruction drops 2^-16 of the largest of 64 products
+@pytest.mark.parametrize("types,step,tol", [((torch.bfloat16,) * 2, 64, 1e-5), ((torch.float16,) * 2, 64, 1e-5),
+                                            ((torch.float8_e4m3fn, torch.float8_e5m2), 128, 2e-4), ((torch.float8_e5m2,) * 2, 128, 2e-4)])
+@pytest.mark.parametrize("B,shapes", [
+    (64, [(512, 1, 1)]),                                     # one stage of each operand, one round
+    (64, [(449, 1, 2)]), (64, [(385, 3, 1)]),                # the last block has 65 or 1 rows of its second half
+    (16, [(1000, 2, 3)]), (17, [(961, 1, 4)]), (256, [(256, 2, 2)]), (250, [(129, 1, 1)]),
+    (32, [(512, 4, 1), (500, 1, 1), (256, 2, 3), (130, 1, 2)]),
+])
+def test_norms_against_float64(types, step, tol, B, shapes):
+    gen = torch.Generator(device="cuda").manual_seed(B)
+    layers = []
+    for T, a, b in shapes:
+        pair = []
+        for d, t in ((a * step, types[0]), (b * step, types[1])):
+            buf = torch.full((B * T * d + 2048,), float("nan"), device="cuda").to(t)       # nothing around the matrix may count
+            x = buf[1024:1024 + B * T * d].view(B, T, d)
+            x.copy_(torch.randn((B, T, d), device="cuda", generator=gen).to(t))
+            pair.append(x)
+        layers.append(tuple(pair))
+    ref = sum(_norm64(A, G) for A, G in layers)
+    s = dp.layers_sqnorm(layers, path="gram")
+    assert float(((s.double() - ref) / ref).abs().max()) < tol
+    C = float(ref.median().sqrt())
+    clip = torch.zeros(B, device="cuda")
+    s2 = dp.layers_sqnorm(layers, torch.full((B,), 3.0, device="cuda"), path="gram", accumulate=True, C=C, clip=clip)
+    assert float(((s2.double() - ref - 3.0) / ref).abs().max()) < tol
+    assert torch.allclose(clip.double(), (C / (ref + 3.0).sqrt()).clamp(max=1.0), rtol=tol, atol=0)
