@@ -844,8 +844,9 @@ dp_status dp_layers_sqnorm_clip(const dp_layer_desc* layers, int64_t n_layers, i
     }
     const ClipOut clip_out{C, clip};
     // Two or more layers outside the dense and the Gram launches: their partial sums are folded by one launch at the end
-    // (FinalizeQueue) instead of a launch of a few microseconds behind every layer.
-    const bool defer_on = n_single + n_cols >= 2 && !is8(dtype);
+    // (FinalizeQueue) instead of a launch of a few microseconds behind every layer.  (Column-split Gram layers beside at most one
+    // other are added up by their own second launch: as many launches, or one less.)
+    const bool defer_on = n_single >= 2 && !is8(dtype);
     FinalizeQueue queue;
     size_t ws_off = 0;
     auto flush_queue = [&](bool with_clip) -> hipError_t {
@@ -855,21 +856,20 @@ dp_status dp_layers_sqnorm_clip(const dp_layer_desc* layers, int64_t n_layers, i
         return e;
     };
     // layers of few positions and wide rows in a small batch: shared column-split Gram launches, first of all.  Their sums
-    // join the queue; one such layer alone finishes its own norms (and the clip factors when nothing else follows).
+    // join the queue, or without one are added up behind them (with the clip factors when nothing else follows).
     const bool clip_with_cols = clip && !defer_on && !any_gram && !any_bias_pass && last_single < 0 && n_dense == 0 && n_cols > 0;
     if (n_cols > 0) {
         GramLayerDesc group[kGramColsLayers];
         int ng = 0;
+        int64_t cols_done = 0;
         size_t least = 0;                                    // what the group's sums and one share per example and layer take
         auto flush_cols = [&]() -> hipError_t {
             if (ng == 0) return hipSuccess;
+            cols_done += ng;
             if (!defer_on) {
-                const GramLayerDesc& y = group[0];
-                const GramColsPlan p = plan_gram_cols((int)B, y.T, y.d_in, y.d_out, (int)dtype);
-                ng = 0;
-                const hipError_t e = launch_gram_cols(p, y.A, y.G, (int)B, y.T, y.d_in, y.d_out, acc != 0, sqnorm, static_cast<float*>(workspace),
-                                                      stream, (int)dtype, clip_with_cols ? &clip_out : nullptr);
-                acc = 1; launched = true;
+                const hipError_t e = launch_gram_cols_norms(group, ng, (int)B, acc != 0, sqnorm, static_cast<float*>(workspace), n_cols == 1 ? kAnySlices : need / sizeof(float),
+                                                            stream, (int)dtype, clip_with_cols && cols_done == n_cols ? &clip_out : nullptr);
+                ng = 0; least = 0; acc = 1; launched = true;
                 return e;
             }
             if (queue.count + ng > FinalizeQueue::kMax) { const hipError_t e = flush_queue(false); if (e != hipSuccess) return e; }

@@ -298,31 +298,40 @@ __global__ __launch_bounds__(kThreads) void k_gram_cols_sums(GramColsArgs j) {
     if (threadIdx.x == 0) a.sums[item] = (nt == 3 && t == 1) ? 2.0f * s : s;
 }
 
-// One layer: sqnorm[ex] (+)= the same sums, added up; one workgroup of 1024 threads per example
+// The same added up, sqnorm[ex] (+)=, where no other layer's sums are to be added: one launch less.  One workgroup of 1024
+// threads per example, an entry of every tile a thread.  (A tile per quarter of the threads, 16 bytes at a time, took twice as
+// long: two layers of 62 positions, 15 and 4 shares, 11 and 21 us.)
 constexpr int kFinishThreads = 1024;
-template <int NB>
-__global__ __launch_bounds__(kFinishThreads) void k_gram_cols_finish(GramColsArgs j, int accumulate,
-                                                                       float* __restrict__ sqnorm, float C, float* __restrict__ clip) {
-    constexpr int NT = NB * (NB + 1) / 2;
+template <int NT>
+__device__ __forceinline__ float gram_cols_dot(const float* base, int W) {
     constexpr int HALF = NT * 16 * 64;
-    constexpr int PER = HALF / kFinishThreads;       // entries per thread: 1 or 3 (one of each tile)
-    __shared__ float red[kFinishThreads / 64];
-    const int ex = blockIdx.x, W = j.layer[0].W;
-    const float* base = j.part + j.layer[0].part_off + (size_t)ex * W * 2 * HALF + threadIdx.x;
-    float p[PER], q[PER];
+    float p[NT], q[NT];
 #pragma unroll
-    for (int i = 0; i < PER; ++i) { p[i] = 0.f; q[i] = 0.f; }
+    for (int i = 0; i < NT; ++i) { p[i] = 0.f; q[i] = 0.f; }
 #pragma unroll 4
     for (int w = 0; w < W; ++w) {
 #pragma unroll
-        for (int i = 0; i < PER; ++i) {
+        for (int i = 0; i < NT; ++i) {
             p[i] += base[(size_t)w * 2 * HALF + i * kFinishThreads];
             q[i] += base[(size_t)w * 2 * HALF + HALF + i * kFinishThreads];
         }
     }
     float s = 0.f;
 #pragma unroll
-    for (int i = 0; i < PER; ++i) s += (NB == 2 && i == 1) ? 2.0f * (p[i] * q[i]) : p[i] * q[i];
+    for (int i = 0; i < NT; ++i) s += (NT == 3 && i == 1) ? 2.0f * (p[i] * q[i]) : p[i] * q[i];
+    return s;
+}
+__global__ __launch_bounds__(kFinishThreads) void k_gram_cols_finish(GramColsArgs j, int accumulate, float* __restrict__ sqnorm, float C,
+                                                                       float* __restrict__ clip) {
+    __shared__ float red[kFinishThreads / 64];
+    const int ex = blockIdx.x;
+    float s = 0.f;
+    for (int li = 0; li < j.n_layers; ++li) {
+        const GramColsLayer& a = j.layer[li];
+        const float* base = j.part + a.part_off + threadIdx.x;
+        if (a.nb == 1) s += gram_cols_dot<1>(base + (size_t)ex * a.W * 2 * 1024, a.W);
+        else           s += gram_cols_dot<3>(base + (size_t)ex * a.W * 2 * 3072, a.W);
+    }
     s = wave_sum(s);
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
     __syncthreads();
@@ -376,7 +385,12 @@ void plan_cols_shared(const GramLayerDesc* layers, int n_layers, int B, int dt, 
         longest = longest > p[l].nb * ceil_div(steps[l], 4) ? longest : p[l].nb * ceil_div(steps[l], 4);
     }
     if (max_floats == kAnySlices) return;
+    // (float32 rows of a length that is no multiple of 4 come 4 bytes at a time, a memory round trip for 8 steps: those layers
+    // keep their own short waves.  49 examples of 17 positions, 656 -> 1673 and 1673 -> 656 among four layers: 19 us, 30 us
+    // with long ones)
+    bool short_waves = true;
     auto take = [&](int l, int length, int& W) {              // whole stages per wave, so that the copies move whole lines
+        if (short_waves && dt == 0 && ((layers[l].d_in | layers[l].d_out) & 3) != 0) { W = p[l].W; return p[l].per_wave; }
         const int least = length / p[l].nb > kColsSteps ? length / p[l].nb : kColsSteps;
         const int w = ceil_div(steps[l], 4 * least);
         const int per_wave = (ceil_div(steps[l], 4 * w) + kStageSteps - 1) / kStageSteps * kStageSteps;
@@ -401,6 +415,7 @@ void plan_cols_shared(const GramLayerDesc* layers, int n_layers, int B, int dt, 
         const int64_t cost = ((blocks + 511) / 512) * (most + kOverhead);
         if (best_cost < 0 || cost < best_cost) { best_cost = cost; best = len; }
     }
+    short_waves = best_cost >= 0;                             // (no room for theirs)
     for (int l = 0; l < n_layers; ++l) {
         const size_t share = p[l].ws_floats / (size_t)p[l].W;
         p[l].per_wave = take(l, best, p[l].W);
@@ -455,19 +470,21 @@ hipError_t launch_gram_cols_layers(const GramLayerDesc* layers, float* const* su
     return hipGetLastError();
 }
 
+hipError_t launch_gram_cols_norms(const GramLayerDesc* layers, int n_layers, int B, bool accumulate, float* sqnorm, float* ws, size_t max_floats,
+                                  hipStream_t st, int dt, const ClipOut* co) {
+    GramColsArgs a;
+    unsigned finish = 0;
+    const hipError_t e = launch_cols(layers, nullptr, n_layers, B, ws, max_floats, st, dt, a, finish);
+    if (e != hipSuccess) return e;
+    k_gram_cols_finish<<<B, kFinishThreads, 0, st>>>(a, accumulate ? 1 : 0, sqnorm, co ? co->C : 0.f, co ? co->clip : nullptr);
+    return hipGetLastError();
+}
+
 hipError_t launch_gram_cols(const GramColsPlan& p, const void* A, const void* G, int B, int T, int d_in, int d_out,
                             bool accumulate, float* sqnorm, float* ws, hipStream_t st, int dt, const ClipOut* co) {
     if (!p.use) return hipErrorInvalidValue;
     const GramLayerDesc y{A, G, T, d_in, d_out, nullptr, nullptr};
-    GramColsArgs a;
-    unsigned finish = 0;
-    const hipError_t e = launch_cols(&y, nullptr, 1, B, ws, kAnySlices, st, dt, a, finish);
-    if (e != hipSuccess) return e;
-    const float C = co ? co->C : 0.f;
-    float* clip = co ? co->clip : nullptr;
-    if (p.nb == 1) k_gram_cols_finish<1><<<B, kFinishThreads, 0, st>>>(a, accumulate ? 1 : 0, sqnorm, C, clip);
-    else           k_gram_cols_finish<2><<<B, kFinishThreads, 0, st>>>(a, accumulate ? 1 : 0, sqnorm, C, clip);
-    return hipGetLastError();
+    return launch_gram_cols_norms(&y, 1, B, accumulate, sqnorm, ws, kAnySlices, st, dt, co);
 }
 
 }  // namespace dpk

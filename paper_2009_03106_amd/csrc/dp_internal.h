@@ -280,6 +280,9 @@ constexpr int kGramColsLayers = 16;
 int gram_cols_sums(const GramColsPlan& p);
 hipError_t launch_gram_cols_layers(const GramLayerDesc* layers, float* const* sums, int n_layers, int B, float* ws, size_t max_floats,
                                    hipStream_t st, int dt);
+// the same with the layers' sums added to sqnorm (and the clip factors written) by the second launch
+hipError_t launch_gram_cols_norms(const GramLayerDesc* layers, int n_layers, int B, bool accumulate, float* sqnorm, float* ws, size_t max_floats,
+                                  hipStream_t st, int dt, const ClipOut* co);
 hipError_t launch_gram_cols(const GramColsPlan& p, const void* A, const void* G, int B, int T, int d_in, int d_out,
                             bool accumulate, float* sqnorm, float* ws, hipStream_t st, int dt, const ClipOut* co = nullptr);
 hipError_t launch_gram_bf16_dma_layers(const GramLayerDesc* layers, int n_layers, int B, bool accumulate, float* sqnorm,

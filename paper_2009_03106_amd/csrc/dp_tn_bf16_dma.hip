@@ -358,7 +358,8 @@ __device__ __forceinline__ void tn_dma_tile(const DmaArgs& a, const int L) {
 #pragma unroll
                 for (int r = 0; r < 16; ++r) acc[i][j][r] *= by;
     };
-    if constexpr (GEO::WAVES == 8) {
+    // (not for images, whose copies' addresses take longer than a phase: 111 examples of 16 x 16 x 256 lost 6 %)
+    if constexpr (GEO::WAVES == 8 && !CONV) {
         // Two waves per SIMD in opposite phases: while one multiplies a stage the other reads its fragments of one, so that
         // the matrix unit does not wait for the LDS port.  (With all 8 waves in one phase a stage took 1620 cycles, 1024 of
         // them MFMAs; 64 examples of 512 x (768, 2304), (768, 768), (768, 3072), (3072, 768): step 755 -> 731 us.)  Every phase ends at a barrier; waves 4 .. 7 start one phase
