@@ -52,51 +52,45 @@ struct F32SplitArgs {
 
 // The wave's sums once more with the float32 instruction, in the order of k: for sums of 2^80 and more, infinities and
 // NaN (see dp_split.h).  Straight from memory and slow.
-template <int MODE, class GEO>
-__device__ __forceinline__ void tn_f32_exact(const F32SplitArgs& a, int k_begin, int k_end, int mw, int nw, f32x16 (&acc)[GEO::MI][GEO::NI]) {
+template <int MODE, int MI, int NI>
+__device__ __forceinline__ void tn_f32_exact(const F32SplitArgs& a, int k_begin, int k_end, int mw, int nw, f32x16 (&acc)[MI][NI]) {
     const int lrow = threadIdx.x & 31, lhalf = (threadIdx.x & 63) >> 5;
 #pragma unroll
-    for (int i = 0; i < GEO::MI; ++i)
+    for (int i = 0; i < MI; ++i)
 #pragma unroll
-        for (int j = 0; j < GEO::NI; ++j)
+        for (int j = 0; j < NI; ++j)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
     for (int k = k_begin; k < k_end; k += 2) {
         const bool in = k + lhalf < k_end;                   // an odd last row: the other half of the lanes gives zeros
         const int row = in ? k + lhalf : k_end - 1;
         const float c = MODE == 0 ? a.clip[row / a.T] : 1.0f;
-        float fa[GEO::MI], fg[GEO::NI];
+        float fa[MI], fg[NI];
 #pragma unroll
-        for (int i = 0; i < GEO::MI; ++i) {
+        for (int i = 0; i < MI; ++i) {
             const float x = a.A[(size_t)row * a.M + min(mw + i * 32 + lrow, a.M - 1)] * c;
             fa[i] = in ? x : 0.f;
         }
 #pragma unroll
-        for (int j = 0; j < GEO::NI; ++j) {
+        for (int j = 0; j < NI; ++j) {
             const float x = a.G[(size_t)row * a.N + min(nw + j * 32 + lrow, a.N - 1)];
             fg[j] = in ? x : 0.f;
         }
 #pragma unroll
-        for (int i = 0; i < GEO::MI; ++i)
+        for (int i = 0; i < MI; ++i)
 #pragma unroll
-            for (int j = 0; j < GEO::NI; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[i], fg[j], acc[i][j], 0, 0, 0);
+            for (int j = 0; j < NI; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[i], fg[j], acc[i][j], 0, 0, 0);
     }
 }
 
 // MODE 0: clipped sum over K slice z = rows [z kchunk, (z + 1) kchunk).  MODE 1: direct squared norm of example z.
-// item L of the launch: (slice, tile), slice-major
-template <int MODE, class GEO>
-__device__ __forceinline__ void tn_f32_split_tile(const F32SplitArgs& a, const int L, u32x4* lds) {
-    constexpr int MI = GEO::MI, NI = GEO::NI, TM = GEO::TM, TN = GEO::TN, SU = GEO::STAGE_UNITS, PA = GEO::PA, PG = GEO::PG;
+// One wave's part of tile (m0, n0) of slice z: MI blocks of 32 rows from row m0 + mofs on (the tile's rows are those of its waves)
+template <int MODE, class GEO, int MI>
+__device__ __forceinline__ void tn_f32_split_wave(const F32SplitArgs& a, const int z, const int tile, const int m0, const int n0, const int mofs, u32x4* lds) {
+    constexpr int NI = GEO::NI, TM = GEO::TM, TN = GEO::TN, SU = GEO::STAGE_UNITS, PA = GEO::PA, PG = GEO::PG;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int tiles = a.tiles_m * a.tiles_n;
-    if (L >= (int64_t)tiles * a.splits) return;
-    const int z = L / tiles, tile = L - z * tiles;
-    int tm, tn;                                          // consecutive items walk the short side of the tile grid first
-    if (a.tiles_m < a.tiles_n) { tn = tile / a.tiles_m; tm = tile - tn * a.tiles_m; }
-    else { tm = tile / a.tiles_n; tn = tile - tm * a.tiles_n; }
-    const int m0 = tm * TM, n0 = tn * TN;
     int k_begin, k_end;
     if (MODE == 0) { k_begin = z * a.kchunk; k_end = min(a.K, k_begin + a.kchunk); }
     else { k_begin = z * a.T; k_end = k_begin + a.T; }
@@ -176,9 +170,9 @@ __device__ __forceinline__ void tn_f32_split_tile(const F32SplitArgs& a, const i
     };
 
     // ---- LDS -> MFMA operands: lane (lrow, lhalf) takes column lrow of a 32-wide block and rows 8 lhalf .. 8 lhalf + 7
-    const int wm = wave / GEO::WN, wn = wave % GEO::WN;
+    const int wn = wave % GEO::WN;
     const int lrow = lane & 31, lhalf = lane >> 5;
-    const uint32_t rdA = (uint32_t)(lhalf * TM + wm * MI * 32 + lrow);
+    const uint32_t rdA = (uint32_t)(lhalf * TM + mofs + lrow);
     const uint32_t rdG = (uint32_t)(6 * TM + lhalf * TN + wn * NI * 32 + lrow);
 
     f32x16 acc[MI][NI];
@@ -200,13 +194,13 @@ __device__ __forceinline__ void tn_f32_split_tile(const F32SplitArgs& a, const i
     // Past the end of the slice the copies bring zeros, which nobody reads: the loop has no branches.  One 32 x 32 tile
     // of the wave after the other: its six MFMAs, in their shadow a share of the next stage's split and the addition
     // of the tile before.  (With the split in front of all MFMAs the two add up: the waves of a workgroup are in step.)
-    constexpr int TILES = MI * NI, STEPS = (PA + PG) / TILES;
-    static_assert(TILES * STEPS == PA + PG, "");
+    constexpr int TILES = MI * NI;                       // the PA + PG steps of the split are dealt to them in turn
+    constexpr int STEPS = (PA + PG) / TILES;
     f32x16 pend = {};                                    // the sums of the tile before, not yet added
     // The 4-wave geometries keep their sums in two levels, blocks of 8 stages and their sum (four layers 576 -> 64, 32768
     // rows: 1.16e-7 of the result off, 1.85e-7 without; 128 x 128 then takes 250 registers and not 180, two workgroups
     // per compute unit in both cases).
-    constexpr bool TWO = MODE == 0 && MI * NI <= 4;
+    constexpr bool TWO = MODE == 0 && GEO::MI * GEO::NI <= 4;
     f32x16 total[TWO ? MI : 1][TWO ? NI : 1];
     if constexpr (TWO) {
 #pragma unroll
@@ -234,7 +228,7 @@ __device__ __forceinline__ void tn_f32_split_tile(const F32SplitArgs& a, const i
             acc[before / NI][before % NI] += pend * (MODE == 0 && t == 0 ? -sign : sign);
             pend = split_mfma(fa[i & 1], fg[j]);
 #pragma unroll
-            for (int q = 0; q < STEPS; ++q) split_step(t * STEPS + q, buf ^ 1);
+            for (int q = t * (PA + PG) / TILES; q < (t + 1) * (PA + PG) / TILES; ++q) split_step(q, buf ^ 1);
 #pragma unroll
             for (int q = 0; q < 6; ++q) {
                 __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
@@ -262,7 +256,7 @@ __device__ __forceinline__ void tn_f32_split_tile(const F32SplitArgs& a, const i
             for (int j = 0; j < NI; ++j) acc[i][j] += total[i][j];
     }
 
-    const int mw = m0 + wm * MI * 32, nw = n0 + wn * NI * 32;
+    const int mw = m0 + mofs, nw = n0 + wn * NI * 32;
     SplitCheck check;
 #pragma unroll
     for (int i = 0; i < MI; ++i)
@@ -270,7 +264,7 @@ __device__ __forceinline__ void tn_f32_split_tile(const F32SplitArgs& a, const i
         for (int j = 0; j < NI; ++j)
 #pragma unroll
             for (int r = 0; r < 16; ++r) check.add(acc[i][j][r]);
-    if (__any(check.suspect())) tn_f32_exact<MODE, GEO>(a, k_begin, k_end, mw, nw, acc);
+    if (__any(check.suspect())) tn_f32_exact<MODE, MI, NI>(a, k_begin, k_end, mw, nw, acc);
 
     if (MODE == 1) {
         float sq = 0.f;
@@ -314,6 +308,31 @@ __device__ __forceinline__ void tn_f32_split_tile(const F32SplitArgs& a, const i
                 }
             }
         }
+}
+
+// item L of the launch: (slice, tile), slice-major
+template <int MODE, class GEO>
+__device__ __forceinline__ void tn_f32_split_tile(const F32SplitArgs& a, const int L, u32x4* lds) {
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int tiles = a.tiles_m * a.tiles_n;
+    if (L >= (int64_t)tiles * a.splits) return;
+    const int z = L / tiles, tile = L - z * tiles;
+    int tm, tn;                                          // consecutive items walk the short side of the tile grid first
+    if (a.tiles_m < a.tiles_n) { tn = tile / a.tiles_m; tm = tile - tn * a.tiles_m; }
+    else { tm = tile / a.tiles_n; tn = tile - tm * a.tiles_n; }
+    const int n0 = tn * GEO::TN, wm = wave / GEO::WN;
+    if constexpr (GEO::MI == 4) {
+        // the blocks of 32 rows are dealt evenly to the tiles, a tile's to its two rows of waves: 784 rows are 25 blocks in tiles
+        // of 6 and 7, where four whole tiles would form 32 (65536 rows of 784 x 512: 31 % of the products for nothing)
+        // (f32_split_geo takes these tiles where at most a quarter is padding, so every tile has 6 to 8 blocks)
+        const int blocks = (a.M + 31) / 32;
+        const int b0 = (int)((int64_t)tm * blocks / a.tiles_m), b1 = (int)((int64_t)(tm + 1) * blocks / a.tiles_m);
+        const int upper = (b1 - b0 + 1) / 2, own = wm == 0 ? upper : b1 - b0 - upper, m0 = b0 * 32, mofs = wm == 0 ? 0 : upper * 32;
+        if (own == 4)      tn_f32_split_wave<MODE, GEO, 4>(a, z, tile, m0, n0, mofs, lds);
+        else               tn_f32_split_wave<MODE, GEO, 3>(a, z, tile, m0, n0, mofs, lds);
+    } else {
+        tn_f32_split_wave<MODE, GEO, GEO::MI>(a, z, tile, tm * GEO::TM, n0, wm * GEO::MI * 32, lds);
+    }
 }
 
 template <int MODE, class GEO>
