@@ -97,6 +97,7 @@ struct TnPlan {
     int epu;                // segmented: examples per K slice
     bool big;               // 16-bit clipped sum only: 256 x 256 tiles, one workgroup per compute unit
     bool zero_head = false; // the kernel needs a line of zeros: the first kZeroHeadFloats floats of the workspace are set aside for it
+    bool skinny = false;    // float32 clipped sum: the kernel of one operand of at most 32 columns
     bool dma;               // copy-pipeline kernel (direct-to-LDS copies; float32: the split kernel); tile_m x tile_n names its geometry
 };
 constexpr int kZeroHeadFloats = 64;   // 256 bytes

@@ -468,8 +468,9 @@ __global__ __launch_bounds__(256) void k_splitk_reduce(const float* __restrict__
 // in ascending order, and the 8 partial sums are added in the order g = 0 .. 7.  The order is fixed, so the
 // result is reproducible; it differs from the one-thread order only by rounding.
 template <bool NOISE>
-__global__ __launch_bounds__(256) void k_splitk_reduce_wide(const float* __restrict__ ws, int64_t n4, int64_t slice, int splits,
+__global__ __launch_bounds__(256) void k_splitk_reduce_wide(const float* __restrict__ ws, int64_t n, int64_t slice, int splits,
                                                             int accumulate, float* __restrict__ grad, NoiseArgs nz) {
+    const int64_t n4 = (n + 3) >> 2;                     // slices are whole groups of 4, also where n is not
     __shared__ float4 part[8][32];
     const int g = threadIdx.x >> 5, cl = threadIdx.x & 31;
     const int64_t c = (int64_t)blockIdx.x * 32 + cl;
@@ -496,6 +497,11 @@ __global__ __launch_bounds__(256) void k_splitk_reduce_wide(const float* __restr
     if (g == 0 && c < n4) {
 #pragma unroll
         for (int k = 1; k < 8; ++k) { const float4 v = part[k][cl]; acc.x += v.x; acc.y += v.y; acc.z += v.z; acc.w += v.w; }
+        if (4 * c + 4 > n) {                                 // the last entries
+            const float v[4] = {acc.x, acc.y, acc.z, acc.w};
+            for (int64_t k = 0; 4 * c + k < n; ++k) grad[4 * c + k] = accumulate ? grad[4 * c + k] + v[k] : v[k];
+            return;
+        }
         float4* o = reinterpret_cast<float4*>(grad) + c;
         if (accumulate) { const float4 q = *o; acc.x += q.x; acc.y += q.y; acc.z += q.z; acc.w += q.w; }
         if (NOISE) add_noise4(acc, (nz.offset >> 2) + (uint64_t)c, nz);
@@ -514,10 +520,10 @@ hipError_t launch_splitk_reduce(const float* ws, int64_t n, int splits, bool acc
     const bool nz = noise != nullptr && noise->stddev != 0.0f;
     if (nz && !splitk_noise_ok(n, noise->offset)) return hipErrorInvalidValue;
     const NoiseArgs na = nz ? *noise : NoiseArgs{0.f, 0u, 0u, 0u};
-    if (splits >= 16 && splitk_reduce_is_wide(n)) {
-        const unsigned grid = (unsigned)((n4 + 31) / 32);
-        if (nz) k_splitk_reduce_wide<true><<<grid, 256, 0, st>>>(ws, n4, splitk_slice_elems(n), splits, accumulate ? 1 : 0, grad, na);
-        else    k_splitk_reduce_wide<false><<<grid, 256, 0, st>>>(ws, n4, splitk_slice_elems(n), splits, accumulate ? 1 : 0, grad, na);
+    if (splits >= 16 && splitk_reduce_is_wide((n + 3) & ~(int64_t)3)) {
+        const unsigned grid = (unsigned)(((n + 3) / 4 + 31) / 32);
+        if (nz) k_splitk_reduce_wide<true><<<grid, 256, 0, st>>>(ws, n, splitk_slice_elems(n), splits, accumulate ? 1 : 0, grad, na);
+        else    k_splitk_reduce_wide<false><<<grid, 256, 0, st>>>(ws, n, splitk_slice_elems(n), splits, accumulate ? 1 : 0, grad, na);
         return hipGetLastError();
     }
     int64_t blocks = (n4 + 255) / 256;

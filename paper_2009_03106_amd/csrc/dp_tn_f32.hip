@@ -310,6 +310,119 @@ __global__ __launch_bounds__(kThreads) void k_tn_f32_short_layers(TnShortLayers 
     tn_f32_short_dispatch(a, (int)blockIdx.x - t.first_tile[li], sA, sG, part);
 }
 
+// Clipped sum of many rows with one narrow operand, at most 32 columns: a classifier head, the 27 patch columns of a first
+// convolution.  It is bound by reading the wide operand, so nothing goes through LDS on the way: 32 consecutive columns of
+// two rows are an operand of the 32 x 32 x 2 instruction as a wave's 4-byte loads bring them, the narrow one is loaded and
+// scaled once for WT blocks of the wide one, and a wave has the loads of 2 U rows in flight.  A workgroup of 8 waves takes
+// WT x 32 wide columns and a slice of the rows, a wave an eighth of it; their sums meet in LDS, three steps.  (64 x 64 tiles
+// were mostly padding, 8 stages one after the other: 65536 rows of 256 x 10 took 36 us, the fold among them, now 24; with
+// 256 columns a workgroup 31, their sums take longer to meet, with 32 rows in flight a wave 25.)
+// SWAP: the narrow operand is A.
+constexpr int kSkinnyThreads = 512;
+constexpr int kSkinnyPairs = 8;                     // U
+template <int WT, bool SWAP>
+__global__ __launch_bounds__(kSkinnyThreads, 2) void k_tn_f32_skinny(TnArgsF a) {
+    constexpr int U = kSkinnyPairs;
+    __shared__ float part[4][WT * 32][33];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int col = lane & 31, half = lane >> 5;
+    const float* wide = SWAP ? a.G : a.A;
+    const float* narrow = SWAP ? a.A : a.G;
+    const int dw = SWAP ? a.N : a.M, dn = SWAP ? a.M : a.N;
+    const int w0 = blockIdx.x * WT * 32, z = blockIdx.y;
+    const int per_wave = a.kchunk / 8;
+    const int k_begin = (int)min((int64_t)a.K, (int64_t)z * a.kchunk + (int64_t)wave * per_wave), k_end = (int)min((int64_t)a.K, (int64_t)k_begin + per_wave);
+    int cw[WT];                                          // columns outside the matrices feed sums that are never stored
+#pragma unroll
+    for (int t = 0; t < WT; ++t) cw[t] = min(w0 + t * 32 + col, dw - 1);
+    const int cn = min(col, dn - 1);
+    f32x16 acc[WT];
+#pragma unroll
+    for (int t = 0; t < WT; ++t)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[t][r] = 0.f;
+    for (int k0 = k_begin; k0 < k_end; k0 += 2 * U) {
+        const bool full = k0 + 2 * U <= k_end;           // uniform
+        const float* pw = wide + (size_t)k0 * dw;
+        const float* pn = narrow + (size_t)k0 * dn;
+        float w[U][WT], n[U], c[U];
+#pragma unroll
+        for (int j = 0; j < U; ++j) {
+            const int r = min(2 * j + half, k_end - 1 - k0);          // rows past the end read the last one
+#pragma unroll
+            for (int t = 0; t < WT; ++t) w[j][t] = pw[(uint32_t)(r * dw + cw[t])];
+            n[j] = pn[(uint32_t)(r * dn + cn)];
+            c[j] = a.T == 1 ? a.clip[k0 + r] : 0.f;
+        }
+        if (a.T != 1) {
+            const int ex = k0 / a.T;                     // uniform; one factor where the rows are of one example
+            const float one = a.clip[ex];
+            if ((min(k0 + 2 * U, k_end) - 1) / a.T == ex) {
+#pragma unroll
+                for (int j = 0; j < U; ++j) c[j] = one;
+            } else {
+#pragma unroll
+                for (int j = 0; j < U; ++j) c[j] = a.clip[(k0 + min(2 * j + half, k_end - 1 - k0)) / a.T];
+            }
+        }
+        if (!full) {                                     // ... and give zeros (both: an infinity times zero is NaN)
+#pragma unroll
+            for (int j = 0; j < U; ++j) {
+                const bool in = k0 + 2 * j + half < k_end;
+#pragma unroll
+                for (int t = 0; t < WT; ++t) w[j][t] = in ? w[j][t] : 0.f;
+                n[j] = in ? n[j] : 0.f;
+                c[j] = in ? c[j] : 0.f;
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < U; ++j) {
+            const float x = n[j] * c[j];
+#pragma unroll
+            for (int t = 0; t < WT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(w[j][t], x, acc[t], 0, 0, 0);
+        }
+    }
+    auto put = [&](float (*to)[33]) {
+#pragma unroll
+        for (int t = 0; t < WT; ++t)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) to[t * 32 + 8 * (r >> 2) + 4 * half + (r & 3)][col] = acc[t][r];
+    };
+    auto add = [&](float (*from)[33]) {
+#pragma unroll
+        for (int t = 0; t < WT; ++t)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[t][r] += from[t * 32 + 8 * (r >> 2) + 4 * half + (r & 3)][col];
+    };
+#pragma unroll
+    for (int n = 4; n >= 1; n >>= 1) {
+        if (wave >= n && wave < 2 * n) put(part[wave - n]);
+        __syncthreads();
+        if (wave < n) add(part[wave]);
+        __syncthreads();
+    }
+    if (wave == 0) put(part[0]);
+    __syncthreads();
+    const int rows = min(WT * 32, dw - w0);
+    float* out = a.out + (size_t)z * a.slice;
+    for (int e = tid; e < rows * dn; e += kSkinnyThreads) {
+        const int i = SWAP ? e % rows : e / dn, k = SWAP ? e / rows : e - i * dn;       // wide and narrow column
+        float* p = out + (SWAP ? (size_t)k * dw + w0 + i : (size_t)(w0 + i) * dn + k);
+        const float v = part[0][i][k];
+        *p = a.accumulate ? *p + v : v;
+    }
+}
+
+// blocks of 32 wide columns per workgroup
+inline int skinny_blocks(int dw) {
+    const int groups = ceil_div(dw, 128);
+    return ceil_div(ceil_div(dw, 32), groups) <= 2 ? 2 : 4;
+}
+template <bool SWAP> void launch_skinny(int blocks, dim3 grid, const TnArgsF& a, hipStream_t st) {
+    if (blocks == 2)      k_tn_f32_skinny<2, SWAP><<<grid, kSkinnyThreads, 0, st>>>(a);
+    else                  k_tn_f32_skinny<4, SWAP><<<grid, kSkinnyThreads, 0, st>>>(a);
+}
+
 template <int MODE, int FBK> void launch_f32_k(bool veca, bool vecg, dim3 grid, const TnArgsF& a, hipStream_t st) {
     if (veca) { if (vecg) k_tn_f32<MODE, FBK, true, true><<<grid, kThreads, 0, st>>>(a); else k_tn_f32<MODE, FBK, true, false><<<grid, kThreads, 0, st>>>(a); }
     else      { if (vecg) k_tn_f32<MODE, FBK, false, true><<<grid, kThreads, 0, st>>>(a); else k_tn_f32<MODE, FBK, false, false><<<grid, kThreads, 0, st>>>(a); }
@@ -350,6 +463,17 @@ ClippedF32Route clipped_f32_route(int64_t K, int M, int N) {
     else if (aligned && M <= f32_split_tile_m(geo) && N <= f32_split_tile_n(geo)) split = false;
     else split = products >= 3.7e8;
     return ClippedF32Route{false, split ? geo : F32_NONE};
+}
+
+// A sum that the kernel of one narrow operand takes (of those that are neither short nor the split kernel's).  The line, in
+// us (64 x 64 tiles / this kernel): one group of columns 64 x 10 from 4096 rows 12.5 / 12.7, 27 x 64 from 32768 13.9 / 11.3;
+// rows of odd length, which the tiles load word by word, 139 x 2 from 4096 16.9 / 13.0; else by the wide operand's entries:
+// 256 x 10 from 16384 rows 13.5 / 13.9, from 65536 36.2 / 24.4; 512 x 20 from 8192 12.2 / 14.2, from 10963 17.6 / 15.7;
+// 1024 x 10 from 4096 13.2 / 13.6, from 10963 26.9 / 20.4; 784 x 32 from 10963 21.9 / 21.1, from 65536 93 / 61.
+static bool skinny_ok(int64_t K, int M, int N) {
+    const int64_t dw = std::max(M, N);
+    if (std::min(M, N) > 32 || dw > (1 << 20) || K < 4096 || K >= (int64_t(1) << 31) - 4096) return false;
+    return dw <= 128 || (dw & 3) != 0 || K * dw >= 4500000;
 }
 
 TnPlan plan_clipped_f32(int B, int T, int M, int N) {
@@ -393,6 +517,19 @@ TnPlan plan_clipped_f32(int B, int T, int M, int N) {
             sp = (stages + sps - 2) / (sps - 1);             // the next count whose slices are shorter
         }
         const int64_t kchunk = (int64_t)((stages + best - 1) / best) * dk;
+        p.kchunk = (int)kchunk;
+        p.splits = (int)((K + kchunk - 1) / kchunk);
+        return p;
+    }
+    if (skinny_ok(K, M, N)) {
+        // one workgroup per compute unit: slices of at least 2 U rows a wave
+        const int dw = std::max(M, N), blocks = skinny_blocks(dw), least = 8 * 2 * kSkinnyPairs;
+        p.skinny = true;
+        p.tile_m = M >= N ? blocks * 32 : 32; p.tile_n = M >= N ? 32 : blocks * 32;
+        p.tiles_m = ceil_div(M, p.tile_m); p.tiles_n = ceil_div(N, p.tile_n);
+        const int64_t groups = (int64_t)p.tiles_m * p.tiles_n;
+        const int64_t want = groups >= 256 ? 1 : 256 / groups;
+        const int64_t kchunk = ceil_div(ceil_div(K, want), least) * (int64_t)least;
         p.kchunk = (int)kchunk;
         p.splits = (int)((K + kchunk - 1) / kchunk);
         return p;
@@ -511,6 +648,15 @@ hipError_t launch_clipped_f32(const TnPlan& p, const float* A, const float* G, c
     else { a.out = ws; a.slice = splitk_slice_elems(n); a.accumulate = 0; }
     if (p.dma) {
         hipError_t e = launch_tn_f32_split(0, p, A, G, clip, B, T, M, N, a.out, a.slice, a.accumulate != 0, st);
+        if (e != hipSuccess || p.splits == 1) return e;
+        return launch_splitk_reduce(ws, n, p.splits, accumulate, grad, st, noise);
+    }
+    if (p.skinny) {
+        const bool swap = M < N;
+        dim3 grid((unsigned)(p.tiles_m * p.tiles_n), (unsigned)p.splits);
+        if (swap) launch_skinny<true>(p.tile_n / 32, grid, a, st);
+        else      launch_skinny<false>(p.tile_m / 32, grid, a, st);
+        const hipError_t e = hipGetLastError();
         if (e != hipSuccess || p.splits == 1) return e;
         return launch_splitk_reduce(ws, n, p.splits, accumulate, grad, st, noise);
     }
