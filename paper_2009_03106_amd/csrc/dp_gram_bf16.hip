@@ -263,6 +263,9 @@ GramPlan plan_gram_bf16(int T, int d_in, int d_out) {
 hipError_t launch_gram_bf16_layers(const JointShape* sh, const JointOperands* op, float* const* partial, int n_layers, int B,
                                    hipStream_t st, bool f16) {
     if (n_layers < 1 || n_layers > kJointLayers) return hipErrorInvalidValue;
+    bool copied = true;                                  // by the copy pipeline
+    for (int l = 0; l < n_layers; ++l) copied = copied && gram_dma_ragged_ok(sh[l].T, sh[l].M, sh[l].N) && partial[l] >= partial[0];
+    if (copied) return launch_gram_dma_ragged(sh, op, partial, n_layers, B, st, f16);
     GramLayers g;
     int64_t first = 0;
     for (int l = 0; l < n_layers; ++l) {
@@ -287,6 +290,12 @@ hipError_t launch_gram_bf16_layers(const JointShape* sh, const JointOperands* op
 hipError_t launch_gram_bf16(const GramPlan& p, const uint16_t* A, const uint16_t* G, int B, int T, int d_in, int d_out,
                             bool accumulate, float* sqnorm, float* partial, hipStream_t st, bool f16, const ClipOut* co) {
     if (gram_dma_ok(T, d_in, d_out)) return launch_gram_bf16_dma(p, A, G, B, T, d_in, d_out, accumulate, sqnorm, partial, st, f16, co);
+    if (p.npairs > 1 && gram_dma_ragged_ok(T, d_in, d_out)) {
+        const JointShape sh{T, d_in, d_out};
+        const JointOperands op{A, G, nullptr, nullptr, 0};
+        const hipError_t e = launch_gram_dma_ragged(&sh, &op, &partial, 1, B, st, f16);
+        return e != hipSuccess ? e : launch_finalize_partials(partial, B, p.npairs, accumulate, sqnorm, st, co);
+    }
     GramArgs a;
     a.A = A; a.G = G; a.partial = partial;
     a.T = T; a.d_in = d_in; a.d_out = d_out;

@@ -85,7 +85,10 @@ template <int F8> __device__ __forceinline__ f32x16 mfma8(v8i32 x, v8i32 y, f32x
 // the transposing LDS load -- on the matrix unit, 4 extra MFMAs next to the 16 of the stage; the four partial sums
 // meet in LDS and wave 0 writes the stage's 64 sums to upart.  The pass over G that a separate bias kernel needs
 // is saved.
-template <int FMT, bool BIAS>
+// RAGW (16-bit types): widths are multiples of 8, not of the 64 columns of a stage.  In an operand's last stage the 16-byte
+// pieces past the end of a row are copied from the stage's first piece instead, and count as zero: the fragments are masked
+// behind their reads.
+template <int FMT, bool BIAS, bool RAGW = false>
 __global__ __launch_bounds__(kThreads, GNST * GSTAGE <= 65536 ? 2 : 1) void k_gram_bf16_dma(GramDmaArgs a) {
     constexpr bool F16 = FMT == 1, F8 = fmt_is8(FMT);
     constexpr int ES = F8 ? 1 : 2;                       // bytes per element
@@ -116,7 +119,10 @@ __global__ __launch_bounds__(kThreads, GNST * GSTAGE <= 65536 ? 2 : 1) void k_gr
     const int ss = tt + pair;
     const bool diag = (tt == ss);
 
-    const int sa = ly.d_in / GKE, sg = ly.d_out / GKE;    // stages of the A phase and of the G phase
+    static_assert(!(RAGW && (F8 || BIAS)), "");
+    const int sa = RAGW ? (ly.d_in + GKE - 1) / GKE : ly.d_in / GKE;      // stages of the A phase and of the G phase
+    const int sg = RAGW ? (ly.d_out + GKE - 1) / GKE : ly.d_out / GKE;
+    const int rem_a = ly.d_in * ES - (sa - 1) * ROWB, rem_g = ly.d_out * ES - (sg - 1) * ROWB;   // RAGW: bytes of a row's last stage
     const int n_stages = sa + sg;
 
     // ---- copies: wave w moves rows 32w .. 32w+31 of the t-tile and of the s-tile, 4 instructions each
@@ -124,11 +130,12 @@ __global__ __launch_bounds__(kThreads, GNST * GSTAGE <= 65536 ? 2 : 1) void k_gr
     const int lrow8 = lane / CPR, cp = lane % CPR;
     // per-lane byte offsets inside the example (tile rows clamped to valid rows), fixed for the whole kernel:
     // [0] = A phase, [1] = G phase
-    uint32_t off_t[2][IPT], off_s[2][IPT];
+    uint32_t off_t[2][IPT], off_s[2][IPT], piece[RAGW ? IPT : 1];
 #pragma unroll
     for (int u = 0; u < IPT; ++u) {
         const int r = wave * 32 + u * RPI + lrow8;                     // row inside the tile
         const uint32_t c16 = (uint32_t)((cp ^ gram_swz(r)) << 4);      // source chunk for this LDS slot
+        if (RAGW) piece[u] = c16;
         const uint32_t rt = (uint32_t)min(tt * GT + r, ly.T - 1), rs = (uint32_t)min(ss * GT + r, ly.T - 1);
         off_t[0][u] = rt * (uint32_t)ly.d_in * ES + c16;  off_s[0][u] = rs * (uint32_t)ly.d_in * ES + c16;
         off_t[1][u] = rt * (uint32_t)ly.d_out * ES + c16; off_s[1][u] = rs * (uint32_t)ly.d_out * ES + c16;
@@ -151,6 +158,19 @@ __global__ __launch_bounds__(kThreads, GNST * GSTAGE <= 65536 ? 2 : 1) void k_gr
         }
     };
     auto issue = [&](int st, int buf) {
+        if (RAGW && (st == sa - 1 ? rem_a < ROWB : st == n_stages - 1 && rem_g < ROWB)) {
+            const int ph = st < sa ? 0 : 1;
+            const uint32_t rem = (uint32_t)(ph ? rem_g : rem_a);
+            uint32_t ot[IPT], os[IPT];
+#pragma unroll
+            for (int u = 0; u < IPT; ++u) {
+                const uint32_t back = piece[RAGW ? u : 0] < rem ? 0u : piece[RAGW ? u : 0];
+                ot[u] = (ph ? off_t[1][u] : off_t[0][u]) - back;
+                os[u] = (ph ? off_s[1][u] : off_s[0][u]) - back;
+            }
+            issue_phase(ph ? baseG + (st - sa) * ROWB : baseA + st * ROWB, ot, os, buf);
+            return;
+        }
         if (st < sa) issue_phase(baseA + st * ROWB, off_t[0], off_s[0], buf);
         else issue_phase(baseG + (st - sa) * ROWB, off_t[1], off_s[1], buf);
     };
@@ -276,6 +296,15 @@ __global__ __launch_bounds__(kThreads, GNST * GSTAGE <= 65536 ? 2 : 1) void k_gr
                 __builtin_amdgcn_s_barrier();                // ... for every wave, and every wave is done reading stage st
                 if (st + GNST < n_stages) issue(st + GNST, st % GNST);
                 read_kstep(f[0], (st + 1) % GNST, 0);
+            }
+            if (RAGW && (st == sa - 1 ? rem_a < ROWB : st == n_stages - 1 && rem_g < ROWB)) {
+                const bool in = (2 * ks + lhalf) * 16 < (st == sa - 1 ? rem_a : rem_g);
+#pragma unroll
+                for (int x = 0; x < 4; ++x) {
+                    uint4 w = __builtin_bit_cast(uint4, f[ks & 1][x]);
+                    w = make_uint4(in ? w.x : 0u, in ? w.y : 0u, in ? w.z : 0u, in ? w.w : 0u);
+                    f[ks & 1][x] = __builtin_bit_cast(bf16x8, w);
+                }
             }
             mfma_kstep(f[ks & 1], acc);
             if (BIAS && do_bias && st >= sa) {
@@ -698,6 +727,41 @@ hipError_t launch_gram_bf16_dma_layers(const GramLayerDesc* layers, int n_layers
         accumulate = true;
     }
     return launch_finalize_layers(partial, fin, B, accumulate, sqnorm, st, C, clip);
+}
+
+// 16-bit layers of any widths that are multiples of 8, T > 64
+bool gram_dma_ragged_ok(int T, int d_in, int d_out) {
+    const int64_t dmax = d_in > d_out ? d_in : d_out;
+    return T > 64 && ((d_in | d_out) & 7) == 0 && (int64_t)T * dmax * 2 < (int64_t(1) << 31);       // 32-bit lane offsets
+}
+
+// Every layer passing gram_dma_ragged_ok; partial[l]: the layer's [B][npairs] sums, one array behind the other, to be added
+// by the caller.  (Three layers of 32 examples x 250 positions, 200 -> 600, 200 -> 512 and 512 -> 200: 21 us on the kernel for
+// any shape, which loads a stage into registers while it multiplies the one before.)
+hipError_t launch_gram_dma_ragged(const JointShape* sh, const JointOperands* op, float* const* partial, int n_layers, int B, hipStream_t st, bool f16) {
+    if (n_layers < 1 || n_layers > kGramBatch) return hipErrorInvalidValue;
+    GramDmaArgs a;
+    a.n_layers = n_layers; a.partial = partial[0]; a.B = B;
+    int64_t queue = 0;
+    for (int l = 0; l < n_layers; ++l) {
+        const GramPlan p = plan_gram_bf16(sh[l].T, sh[l].M, sh[l].N);
+        const int64_t items = (int64_t)B * p.npairs, first = partial[l] - partial[0];
+        if (first < 0 || first + items >= (int64_t(1) << 31)) return hipErrorInvalidValue;
+        GramDmaLayer& y = a.layer[l];
+        y.A = reinterpret_cast<const unsigned char*>(op[l].A); y.G = reinterpret_cast<const unsigned char*>(op[l].G);
+        y.T = sh[l].T; y.d_in = sh[l].M; y.d_out = sh[l].N;
+        y.nt = p.nt; y.npairs = p.npairs;
+        y.first = (int)first; y.per_xcd = (int)((items + 7) / 8);
+        y.upart = nullptr;
+        queue += y.per_xcd;
+    }
+    for (int l = n_layers; l < kGramBatch; ++l) a.layer[l] = GramDmaLayer{nullptr, nullptr, 0, 0, 0, 0, 0, 0, 0, nullptr};
+    if (queue * 8 >= (int64_t(1) << 31)) return hipErrorInvalidValue;
+    a.per_xcd = (int)queue;
+    const unsigned grid = 8u * (unsigned)queue;
+    if (f16) k_gram_bf16_dma<1, false, true><<<grid, kThreads, 0, st>>>(a);
+    else     k_gram_bf16_dma<0, false, true><<<grid, kThreads, 0, st>>>(a);
+    return hipGetLastError();
 }
 
 hipError_t launch_gram_bf16_dma(const GramPlan& p, const void* A, const void* G, int B, int T, int d_in, int d_out,

@@ -290,6 +290,8 @@ hipError_t launch_gram_bf16_dma_layers(const GramLayerDesc* layers, int n_layers
                                        float* partial, hipStream_t st, int fmt, float C = 0.f, float* clip = nullptr);
 hipError_t launch_gram_bf16_dma(const GramPlan& p, const void* A, const void* G, int B, int T, int d_in, int d_out,
                                 bool accumulate, float* sqnorm, float* partial, hipStream_t st, int fmt, const ClipOut* co = nullptr);
+bool gram_dma_ragged_ok(int T, int d_in, int d_out);
+hipError_t launch_gram_dma_ragged(const JointShape* sh, const JointOperands* op, float* const* partial, int n_layers, int B, hipStream_t st, bool f16);
 // float32 inputs (dp_gram_f32.hip)
 GramPlan plan_gram_f32(int B, int T);
 int gram_f32_sums(int T);              // the most sums per example that the plan of any batch has (scratch is sized by it)
