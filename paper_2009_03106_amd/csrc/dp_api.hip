@@ -317,7 +317,7 @@ int dp_clipped_grad_rounds_inputs(int64_t B, int64_t T, int64_t d_in, int64_t d_
     if (is8(dtype) && dma8_clipped_ok((int)T, (int)d_in, (int)d_out)) return 0;
     // 16-bit inputs, and 8-bit ones widened to fp16: the copy-pipeline and the example-by-example kernels scale in float32
     const TnPlan p = plan_clipped_bf16((int)B, (int)T, (int)d_in, (int)d_out);
-    return (p.dma || (!p.big && p.segmented)) ? 0 : 1;
+    return (p.dma || p.skinny || (!p.big && p.segmented)) ? 0 : 1;
 }
 
 dp_status dp_layer_sqnorm(const void* A, const void* G, int64_t B, int64_t T, int64_t d_in, int64_t d_out,

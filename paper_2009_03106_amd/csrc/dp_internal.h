@@ -97,7 +97,7 @@ struct TnPlan {
     int epu;                // segmented: examples per K slice
     bool big;               // 16-bit clipped sum only: 256 x 256 tiles, one workgroup per compute unit
     bool zero_head = false; // the kernel needs a line of zeros: the first kZeroHeadFloats floats of the workspace are set aside for it
-    bool skinny = false;    // float32 clipped sum: the kernel of one operand of at most 32 columns
+    bool skinny = false;    // clipped sum: the kernel of one operand of at most 32 columns
     bool dma;               // copy-pipeline kernel (direct-to-LDS copies; float32: the split kernel); tile_m x tile_n names its geometry
 };
 constexpr int kZeroHeadFloats = 64;   // 256 bytes
@@ -108,6 +108,11 @@ void plan_direct_chunks(TnPlan& p, int B, int T, int M, int N, int esize, int st
 hipError_t launch_direct_chunks_finish(const float* shares, int64_t slice, int S, int n, int B, float* sums, hipStream_t st);
 TnPlan plan_clipped_bf16(int B, int T, int M, int N);
 TnPlan plan_clipped_f32(int B, int T, int M, int N);
+// clipped sums of many rows with one operand of at most 32 columns (dp_tn_f32.hip): whether the kernel takes it, and its plan;
+// dt: 0 float32, 1 bf16, 2 fp16
+bool plan_skinny(TnPlan& p, int64_t K, int M, int N);
+hipError_t launch_clipped_skinny(const TnPlan& p, const void* A, const void* G, const float* clip, int B, int T, int M, int N, bool accumulate,
+                                 float* grad, float* ws, hipStream_t st, int dt, const NoiseArgs* noise);
 constexpr int kShortK = 512;            // the float32 short-contraction kernel takes up to this many rows
 int clipped_f32_split_geo(int64_t K, int M, int N);
 // how that plan takes a sum of K rows: the short-contraction kernel, else the split kernel with this geometry, or

@@ -632,6 +632,15 @@ constexpr int kSegMinT = 32;      // below this an LDS stage would be mostly pad
 TnPlan plan_clipped_bf16(int B, int T, int M, int N) {
     if (dma_clipped_ok(B, T, M, N)) return plan_clipped_bf16_dma(B, T, M, N, true);
     TnPlan p;
+    // One operand of at most 32 columns, 32 examples of 1024 positions, this file's kernels / that one (us): one group of 128
+    // columns 27 x 64 19.1 / 11.4, 75 x 16 19.3 / 13.9; more of them only in the place of the example-by-example kernel, and
+    // beyond 256 columns only of rows that are not whole 16-byte pieces: 144 x 32 22.5 / 16.9, 147 x 32 48.9 / 16.6, 1024 x 10
+    // 39.5 / 34.5 but 784 x 32 27.4 / 36.2, 2000 x 10 50.6 / 59.3; 65536 single rows of 512 x 20 27.3 / 36.0.
+    {
+        const int64_t dw = M > N ? M : N;
+        const bool by_example = T >= kSegMinT && (int64_t)B * ceil_div(M, BM) * ceil_div(N, BN) >= 64;
+        if ((dw <= 128 || (by_example && (dw <= 256 || (((M | N) & 7) != 0 && dw <= 1024)))) && plan_skinny(p, (int64_t)B * T, M, N)) return p;
+    }
     p.dma = false;
     p.tile_m = BM; p.tile_n = BN;
     p.tiles_m = ceil_div(M, BM); p.tiles_n = ceil_div(N, BN);
@@ -725,6 +734,7 @@ hipError_t launch_clipped_bf16(const TnPlan& p, const uint16_t* A, const uint16_
     const int64_t n = (int64_t)M * N;
     const int tiles = p.tiles_m * p.tiles_n;
     if (p.dma) return launch_clipped_bf16_dma(p, A, G, clip, B, T, M, N, accumulate, grad, ws, st, nullptr, nullptr, f16, noise);
+    if (p.skinny) return launch_clipped_skinny(p, A, G, clip, B, T, M, N, accumulate, grad, ws, st, f16 ? 2 : 1, noise);
     if (p.big) {
         BigArgs a;
         a.A = A; a.G = G; a.clip = clip;

@@ -317,17 +317,25 @@ __global__ __launch_bounds__(kThreads) void k_tn_f32_short_layers(TnShortLayers 
 // WT x 32 wide columns and a slice of the rows, a wave an eighth of it; their sums meet in LDS, three steps.  (64 x 64 tiles
 // were mostly padding, 8 stages one after the other: 65536 rows of 256 x 10 took 36 us, the fold among them, now 24; with
 // 256 columns a workgroup 31, their sums take longer to meet, with 32 rows in flight a wave 25.)
-// SWAP: the narrow operand is A.
+// SWAP: the narrow operand is A.  DT: 0 = float32, 1 = bf16, 2 = fp16; 16-bit inputs are widened as they come, so their products
+// with the factors are exact to float32 too.
 constexpr int kSkinnyThreads = 512;
 constexpr int kSkinnyPairs = 8;                     // U
-template <int WT, bool SWAP>
+template <int DT> struct SkinnyElem { typedef uint16_t type; };
+template <> struct SkinnyElem<0> { typedef float type; };
+template <int WT, bool SWAP, int DT>
 __global__ __launch_bounds__(kSkinnyThreads, 2) void k_tn_f32_skinny(TnArgsF a) {
+    typedef typename SkinnyElem<DT>::type Elem;
+    auto widen = [](Elem x) -> float {
+        if constexpr (DT == 0) return x;
+        else return In16<DT == 2>::lo((uint32_t)x);
+    };
     constexpr int U = kSkinnyPairs;
     __shared__ float part[4][WT * 32][33];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int col = lane & 31, half = lane >> 5;
-    const float* wide = SWAP ? a.G : a.A;
-    const float* narrow = SWAP ? a.A : a.G;
+    const Elem* wide = reinterpret_cast<const Elem*>(SWAP ? a.G : a.A);
+    const Elem* narrow = reinterpret_cast<const Elem*>(SWAP ? a.A : a.G);
     const int dw = SWAP ? a.N : a.M, dn = SWAP ? a.M : a.N;
     const int w0 = blockIdx.x * WT * 32, z = blockIdx.y;
     const int per_wave = a.kchunk / 8;
@@ -343,9 +351,10 @@ __global__ __launch_bounds__(kSkinnyThreads, 2) void k_tn_f32_skinny(TnArgsF a) 
         for (int r = 0; r < 16; ++r) acc[t][r] = 0.f;
     for (int k0 = k_begin; k0 < k_end; k0 += 2 * U) {
         const bool full = k0 + 2 * U <= k_end;           // uniform
-        const float* pw = wide + (size_t)k0 * dw;
-        const float* pn = narrow + (size_t)k0 * dn;
-        float w[U][WT], n[U], c[U];
+        const Elem* pw = wide + (size_t)k0 * dw;
+        const Elem* pn = narrow + (size_t)k0 * dn;
+        Elem w[U][WT], n[U];
+        float c[U];
 #pragma unroll
         for (int j = 0; j < U; ++j) {
             const int r = min(2 * j + half, k_end - 1 - k0);          // rows past the end read the last one
@@ -370,16 +379,16 @@ __global__ __launch_bounds__(kSkinnyThreads, 2) void k_tn_f32_skinny(TnArgsF a) 
             for (int j = 0; j < U; ++j) {
                 const bool in = k0 + 2 * j + half < k_end;
 #pragma unroll
-                for (int t = 0; t < WT; ++t) w[j][t] = in ? w[j][t] : 0.f;
-                n[j] = in ? n[j] : 0.f;
+                for (int t = 0; t < WT; ++t) w[j][t] = in ? w[j][t] : (Elem)0;
+                n[j] = in ? n[j] : (Elem)0;
                 c[j] = in ? c[j] : 0.f;
             }
         }
 #pragma unroll
         for (int j = 0; j < U; ++j) {
-            const float x = n[j] * c[j];
+            const float x = widen(n[j]) * c[j];
 #pragma unroll
-            for (int t = 0; t < WT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(w[j][t], x, acc[t], 0, 0, 0);
+            for (int t = 0; t < WT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(widen(w[j][t]), x, acc[t], 0, 0, 0);
         }
     }
     auto put = [&](float (*to)[33]) {
@@ -418,9 +427,14 @@ inline int skinny_blocks(int dw) {
     const int groups = ceil_div(dw, 128);
     return ceil_div(ceil_div(dw, 32), groups) <= 2 ? 2 : 4;
 }
-template <bool SWAP> void launch_skinny(int blocks, dim3 grid, const TnArgsF& a, hipStream_t st) {
-    if (blocks == 2)      k_tn_f32_skinny<2, SWAP><<<grid, kSkinnyThreads, 0, st>>>(a);
-    else                  k_tn_f32_skinny<4, SWAP><<<grid, kSkinnyThreads, 0, st>>>(a);
+template <bool SWAP, int DT> void launch_skinny_dt(int blocks, dim3 grid, const TnArgsF& a, hipStream_t st) {
+    if (blocks == 2) k_tn_f32_skinny<2, SWAP, DT><<<grid, kSkinnyThreads, 0, st>>>(a);
+    else             k_tn_f32_skinny<4, SWAP, DT><<<grid, kSkinnyThreads, 0, st>>>(a);
+}
+template <bool SWAP> void launch_skinny(int blocks, dim3 grid, const TnArgsF& a, int dt, hipStream_t st) {
+    if (dt == 0)      launch_skinny_dt<SWAP, 0>(blocks, grid, a, st);
+    else if (dt == 1) launch_skinny_dt<SWAP, 1>(blocks, grid, a, st);
+    else              launch_skinny_dt<SWAP, 2>(blocks, grid, a, st);
 }
 
 template <int MODE, int FBK> void launch_f32_k(bool veca, bool vecg, dim3 grid, const TnArgsF& a, hipStream_t st) {
@@ -470,10 +484,39 @@ ClippedF32Route clipped_f32_route(int64_t K, int M, int N) {
 // rows of odd length, which the tiles load word by word, 139 x 2 from 4096 16.9 / 13.0; else by the wide operand's entries:
 // 256 x 10 from 16384 rows 13.5 / 13.9, from 65536 36.2 / 24.4; 512 x 20 from 8192 12.2 / 14.2, from 10963 17.6 / 15.7;
 // 1024 x 10 from 4096 13.2 / 13.6, from 10963 26.9 / 20.4; 784 x 32 from 10963 21.9 / 21.1, from 65536 93 / 61.
-static bool skinny_ok(int64_t K, int M, int N) {
-    const int64_t dw = std::max(M, N);
+bool plan_skinny(TnPlan& p, int64_t K, int M, int N) {
+    const int dw = std::max(M, N);
     if (std::min(M, N) > 32 || dw > (1 << 20) || K < 4096 || K >= (int64_t(1) << 31) - 4096) return false;
-    return dw <= 128 || (dw & 3) != 0 || K * dw >= 4500000;
+    if (dw > 128 && (dw & 3) == 0 && K * dw < 4500000) return false;
+    // one workgroup per compute unit: slices of at least 2 U rows a wave
+    const int blocks = skinny_blocks(dw), least = 8 * 2 * kSkinnyPairs;
+    p.skinny = true;
+    p.segmented = false; p.epu = 0; p.big = false; p.dma = false; p.zero_head = false;
+    p.tile_m = M >= N ? blocks * 32 : 32; p.tile_n = M >= N ? 32 : blocks * 32;
+    p.tiles_m = ceil_div(M, p.tile_m); p.tiles_n = ceil_div(N, p.tile_n);
+    const int64_t groups = (int64_t)p.tiles_m * p.tiles_n;
+    const int64_t want = groups >= 256 ? 1 : 256 / groups;
+    const int64_t kchunk = ceil_div(ceil_div(K, want), least) * (int64_t)least;
+    p.kchunk = (int)kchunk;
+    p.splits = (int)((K + kchunk - 1) / kchunk);
+    return true;
+}
+
+hipError_t launch_clipped_skinny(const TnPlan& p, const void* A, const void* G, const float* clip, int B, int T, int M, int N, bool accumulate,
+                                 float* grad, float* ws, hipStream_t st, int dt, const NoiseArgs* noise) {
+    TnArgsF a;
+    a.A = static_cast<const float*>(A); a.G = static_cast<const float*>(G); a.clip = clip;
+    a.K = B * T; a.T = T; a.M = M; a.N = N;
+    a.tiles_m = p.tiles_m; a.tiles_n = p.tiles_n; a.kchunk = p.kchunk;
+    const int64_t n = (int64_t)M * N;
+    if (p.splits == 1) { a.out = grad; a.slice = 0; a.accumulate = accumulate ? 1 : 0; }
+    else { a.out = ws; a.slice = splitk_slice_elems(n); a.accumulate = 0; }
+    dim3 grid((unsigned)(p.tiles_m * p.tiles_n), (unsigned)p.splits);
+    if (M < N) launch_skinny<true>(p.tile_n / 32, grid, a, dt, st);
+    else       launch_skinny<false>(p.tile_m / 32, grid, a, dt, st);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess || p.splits == 1) return e;
+    return launch_splitk_reduce(ws, n, p.splits, accumulate, grad, st, noise);
 }
 
 TnPlan plan_clipped_f32(int B, int T, int M, int N) {
@@ -521,19 +564,7 @@ TnPlan plan_clipped_f32(int B, int T, int M, int N) {
         p.splits = (int)((K + kchunk - 1) / kchunk);
         return p;
     }
-    if (skinny_ok(K, M, N)) {
-        // one workgroup per compute unit: slices of at least 2 U rows a wave
-        const int dw = std::max(M, N), blocks = skinny_blocks(dw), least = 8 * 2 * kSkinnyPairs;
-        p.skinny = true;
-        p.tile_m = M >= N ? blocks * 32 : 32; p.tile_n = M >= N ? 32 : blocks * 32;
-        p.tiles_m = ceil_div(M, p.tile_m); p.tiles_n = ceil_div(N, p.tile_n);
-        const int64_t groups = (int64_t)p.tiles_m * p.tiles_n;
-        const int64_t want = groups >= 256 ? 1 : 256 / groups;
-        const int64_t kchunk = ceil_div(ceil_div(K, want), least) * (int64_t)least;
-        p.kchunk = (int)kchunk;
-        p.splits = (int)((K + kchunk - 1) / kchunk);
-        return p;
-    }
+    if (plan_skinny(p, K, M, N)) return p;
     p.tile_m = FBM; p.tile_n = FBN;
     p.tiles_m = ceil_div(M, FBM); p.tiles_n = ceil_div(N, FBN);
     const int64_t tiles = (int64_t)p.tiles_m * p.tiles_n;
@@ -651,15 +682,7 @@ hipError_t launch_clipped_f32(const TnPlan& p, const float* A, const float* G, c
         if (e != hipSuccess || p.splits == 1) return e;
         return launch_splitk_reduce(ws, n, p.splits, accumulate, grad, st, noise);
     }
-    if (p.skinny) {
-        const bool swap = M < N;
-        dim3 grid((unsigned)(p.tiles_m * p.tiles_n), (unsigned)p.splits);
-        if (swap) launch_skinny<true>(p.tile_n / 32, grid, a, st);
-        else      launch_skinny<false>(p.tile_m / 32, grid, a, st);
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess || p.splits == 1) return e;
-        return launch_splitk_reduce(ws, n, p.splits, accumulate, grad, st, noise);
-    }
+    if (p.skinny) return launch_clipped_skinny(p, A, G, clip, B, T, M, N, accumulate, grad, ws, st, 0, noise);
     if (p.tile_m == STM) {
         a.out = grad; a.slice = 0; a.accumulate = accumulate ? 1 : 0;
         const unsigned tiles = (unsigned)(p.tiles_m * p.tiles_n);

@@ -1,4 +1,4 @@
-"""float32 clipped sums of many rows with one operand of at most 32 columns."""
+"""Clipped sums of many rows with one operand of at most 32 columns."""
 import pytest
 import torch
 
@@ -12,12 +12,13 @@ pytestmark = pytest.mark.gpu
     (9001, 1, 2, 500), (20, 1024, 27, 64), (3, 4100, 31, 33), (30, 197, 33, 31), (1, 9999, 75, 16), (513, 8, 3, 131),
 ])
 @pytest.mark.parametrize("accumulate,noise", [(False, 0.0), (True, 0.0), (False, 0.5)])
-def test_sums_against_float64(B, T, a, b, accumulate, noise):
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16, torch.float16])
+def test_sums_against_float64(B, T, a, b, accumulate, noise, dtype):
     gen = torch.Generator(device="cuda").manual_seed(B + T)
     lead = (B,) if T == 1 else (B, T)
 
     def tensor(d):                                           # in the middle of NaNs: nothing around the matrix may count
-        buf = torch.full((B * T * d + 2048,), float("nan"), device="cuda")
+        buf = torch.full((B * T * d + 2048,), float("nan"), device="cuda", dtype=dtype)
         x = buf[1024:1024 + B * T * d].view(*lead, d)
         x.copy_(torch.randn((*lead, d), device="cuda", generator=gen))
         return x
@@ -37,8 +38,11 @@ def test_sums_against_float64(B, T, a, b, accumulate, noise):
         z = torch.zeros_like(grad)
         dp.add_noise(z, noise, 5, 0)
         ref = ref + z
-    # sums of random sign in blocks of at most 512 rows: below 1e-6 of the result
-    assert float((grad.double() - ref).norm() / ref.norm()) < 1e-6
+    # sums of random sign in blocks of at most 512 rows: below 1e-6 of the result; the kernels of the other 16-bit shapes may
+    # round the rows once more after the factor (2^-9 and 2^-12 of a term)
+    rounds = dp.load_library().dp_clipped_grad_rounds_inputs(B, T, a, b, dp.layer_descs([(A, G)])[2]) != 0
+    assert not (rounds and max(a, b) <= 128)
+    assert float((grad.double() - ref).norm() / ref.norm()) < (4e-3 if rounds else 1e-6)
 
 
 def test_infinite_rows_stay_in_their_columns():
