@@ -523,8 +523,7 @@ dp_status dp_bias_sqnorm(const void* G, int64_t B, int64_t T, int64_t d_out, dp_
     if (!G || !aligned16(G)) return DP_ERR_INVALID_ARG;
     // element type of G for the row kernels: the 8-bit pair types store G as e5m2 unless both are e4m3
     const int gdt = is8(dtype) ? (g_is_e5m2(dtype) ? 4 : 3) : (int)dtype;
-    hipError_t e = launch_bias_rows(G, nullptr, (int)B, (int)T, (int)d_out, gdt, bias_rows, nullptr, stream);
-    if (e == hipSuccess) e = launch_rows_sqnorm(bias_rows, (int)B, (int)d_out, accumulate != 0, sqnorm, stream);
+    const hipError_t e = launch_bias_rows(G, nullptr, (int)B, (int)T, (int)d_out, gdt, bias_rows, nullptr, accumulate != 0, sqnorm, stream);
     return e == hipSuccess ? DP_OK : DP_ERR_HIP;
 }
 
@@ -550,8 +549,7 @@ dp_status dp_layernorm_sqnorm(const void* G, const void* Hbar, int64_t B, int64_
     if (!G || !Hbar || !aligned16(G) || !aligned16(Hbar)) return DP_ERR_INVALID_ARG;
     // 8-bit types: Hbar is an activation (stored like A), G a backpropagated gradient
     const int gdt = dtype == DP_F8_E4M3 ? 3 : dtype == DP_F8_E5M2 ? 4 : dtype == DP_F8_E4M3_E5M2 ? 5 : (int)dtype;
-    hipError_t e = launch_bias_rows(G, Hbar, (int)B, (int)T, (int)d, gdt, gamma_rows, beta_rows, stream);
-    if (e == hipSuccess) e = launch_rows_sqnorm(gamma_rows, (int)B, (int)d, accumulate != 0, sqnorm, stream, beta_rows);
+    const hipError_t e = launch_bias_rows(G, Hbar, (int)B, (int)T, (int)d, gdt, gamma_rows, beta_rows, accumulate != 0, sqnorm, stream);
     return e == hipSuccess ? DP_OK : DP_ERR_HIP;
 }
 

@@ -4,6 +4,7 @@
 // LayerNorm scale / shift, sum_t G_i[t, :] (*) Hbar_i[t, :] and sum_t G_i[t, :] (Section 5.5,
 // Algorithm 5); their squared norms; and the clipped sum  sum_i nu_i u_i.
 // All of it is bandwidth-bound; every sum runs in a fixed order (no atomics).
+#include <algorithm>
 #include "dp_common.h"
 #include "dp_internal.h"
 #include "dp_noise.h"
@@ -28,7 +29,7 @@ template <int DT> __device__ __forceinline__ float f8_byte(uint32_t word, int wh
 }
 template <int DT, bool PROD, int DTH = DT>
 __device__ __forceinline__ void bias_rows_block(const void* __restrict__ G, const void* __restrict__ Hb, int T, int D, int ctl,
-                                                float* __restrict__ u, float* __restrict__ u2, int bx, int ex) {
+                                                float* __restrict__ u, float* __restrict__ u2, int bx, int ex, float* sqnorm = nullptr, int accumulate = 0) {
     constexpr int ES = ElemBytes<DT>::value;          // bytes per element
     static_assert(ElemBytes<DTH>::value == ES, "G and Hb of one width");
     constexpr int VEC = 16 / ES;
@@ -116,37 +117,63 @@ __device__ __forceinline__ void bias_rows_block(const void* __restrict__ G, cons
             for (int v = 0; v < VEC; ++v) o2[v] = acc2[v];
         }
     }
+    if (sqnorm && tid < kWave) {                       // the workgroup has the whole rows (ct <= 64 threads of the first wave)
+        float s = 0.f;
+        if (rgid == 0 && col0 < D) {
+#pragma unroll
+            for (int v = 0; v < VEC; ++v) s += PROD ? acc[v] * acc[v] + acc2[v] * acc2[v] : acc[v] * acc[v];
+        }
+        s = wave_sum(s);
+        if (tid == 0) sqnorm[ex] = accumulate ? sqnorm[ex] + s : s;
+    }
 }
 
 template <int DT, bool PROD, int DTH = DT>
 __global__ __launch_bounds__(kThreads) void k_bias_rows(const void* __restrict__ G, const void* __restrict__ Hb, int T, int D, int ctl,
-                                                        float* __restrict__ u, float* __restrict__ u2) {
-    bias_rows_block<DT, PROD, DTH>(G, Hb, T, D, ctl, u, u2, blockIdx.x, blockIdx.y);
+                                                        float* __restrict__ u, float* __restrict__ u2, float* __restrict__ sqnorm, int accumulate) {
+    bias_rows_block<DT, PROD, DTH>(G, Hb, T, D, ctl, u, u2, blockIdx.x, blockIdx.y, sqnorm, accumulate);
 }
 
-// Any D: one thread per column, rows in ascending order.
+// Any D: 32 columns a workgroup, its 8 row groups add rows g, g + 8, ... in ascending order, four loads in flight, and the
+// groups' sums are added in their order.  (One thread per column, a load after the other: 15 examples of 447 x 940 took 120 us.)
 template <int DT> __device__ __forceinline__ float load_elem(const void* p, size_t k) {
     if (DT >= 3) return f8_byte<DT>(static_cast<const unsigned char*>(p)[k], 0);
     if (DT != 0) return In16<DT == 2>::lo(static_cast<const uint16_t*>(p)[k]);
     return static_cast<const float*>(p)[k];
 }
+constexpr int kScalarColumns = 32;
 template <int DT, bool PROD, int DTH = DT>
 __device__ __forceinline__ void bias_rows_scalar_block(const void* __restrict__ G, const void* __restrict__ Hb, int T, int D,
                                                        float* __restrict__ u, float* __restrict__ u2, int bx, int ex) {
-    const int q = bx * kThreads + threadIdx.x;
-    if (q >= D) return;
+    constexpr int RG = kThreads / kScalarColumns;
+    __shared__ float part[PROD ? 2 : 1][RG][kScalarColumns];
+    const int cl = threadIdx.x & (kScalarColumns - 1), g = threadIdx.x / kScalarColumns;
+    const int q = bx * kScalarColumns + cl;
     float acc = 0.f, acc2 = 0.f;
-    const size_t base = (size_t)ex * T * D + q;
-    for (int t = 0; t < T; ++t) {
-        const size_t k = base + (size_t)t * D;
-        const float g = load_elem<DT>(G, k);
-        if (PROD) {
-            const float h = load_elem<DTH>(Hb, k);
-            acc += g * h; acc2 += g;
-        } else {
-            acc += g;
+    if (q < D) {
+        const size_t base = (size_t)ex * T * D + q;
+        auto add = [&](float x, float h) {
+            if (PROD) { acc += x * h; acc2 += x; } else acc += x;
+        };
+        int t = g;
+        for (; t + 3 * RG < T; t += 4 * RG) {
+            float x[4], h[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                x[k] = load_elem<DT>(G, base + (size_t)(t + k * RG) * D);
+                h[k] = PROD ? load_elem<DTH>(Hb, base + (size_t)(t + k * RG) * D) : 0.f;
+            }
+#pragma unroll
+            for (int k = 0; k < 4; ++k) add(x[k], h[k]);
         }
+        for (; t < T; t += RG) add(load_elem<DT>(G, base + (size_t)t * D), PROD ? load_elem<DTH>(Hb, base + (size_t)t * D) : 0.f);
     }
+    part[0][g][cl] = acc;
+    if (PROD) part[1][g][cl] = acc2;
+    __syncthreads();
+    if (g != 0 || q >= D) return;
+#pragma unroll
+    for (int r = 1; r < RG; ++r) { acc += part[0][r][cl]; if (PROD) acc2 += part[1][r][cl]; }
     u[(size_t)ex * D + q] = acc;
     if (PROD) u2[(size_t)ex * D + q] = acc2;
 }
@@ -187,7 +214,15 @@ __device__ __forceinline__ float row_sq(const float* __restrict__ p, int D, int 
         }
         for (; q < n4; q += kWave) { const float4 a = p4[q]; acc += a.x * a.x + a.y * a.y + a.z * a.z + a.w * a.w; }
     } else {
-        for (int q = lane; q < D; q += kWave) { const float v = p[q]; acc += v * v; }
+        int q = lane;
+        for (; q + 7 * kWave < D; q += 8 * kWave) {      // eight loads in flight, added in order
+            float v[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) v[k] = p[q + k * kWave];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) acc += v[k] * v[k];
+        }
+        for (; q < D; q += kWave) { const float v = p[q]; acc += v * v; }
     }
     return wave_sum(acc);
 }
@@ -205,19 +240,21 @@ __global__ __launch_bounds__(kThreads) void k_rows_sqnorm(const float* __restric
     }
 }
 
-// the same for several layers' rows, added in the order given: the bits of one launch per layer
+// the same for several layers' rows, added in the order given: the bits of one launch per layer.  A workgroup per example, its
+// waves take the layers in turn (one wave for all of them: 14 us for five layers of 656 to 1968 columns)
 struct RowsLayers { const float* u[kBiasLayers]; int D[kBiasLayers]; int n_layers; };
-__global__ __launch_bounds__(kThreads) void k_rows_sqnorm_layers(RowsLayers a, int B, int accumulate, float* __restrict__ sqnorm) {
-    const int lane = threadIdx.x & (kWave - 1);
-    const int ex = blockIdx.x * (kThreads / kWave) + (threadIdx.x >> 6);
-    if (ex >= B) return;
-    float s = 0.f;
-    if (accumulate) s = sqnorm[ex];
-    for (int l = 0; l < a.n_layers; ++l) {
+__global__ __launch_bounds__(kThreads) void k_rows_sqnorm_layers(RowsLayers a, int accumulate, float* __restrict__ sqnorm) {
+    __shared__ float sums[kBiasLayers];
+    const int lane = threadIdx.x & (kWave - 1), ex = blockIdx.x;
+    for (int l = threadIdx.x >> 6; l < a.n_layers; l += kThreads / kWave) {
         const float v = row_sq(a.u[l] + (size_t)ex * a.D[l], a.D[l], lane);
-        s = l == 0 && !accumulate ? v : s + v;
+        if (lane == 0) sums[l] = v;
     }
-    if (lane == 0) sqnorm[ex] = s;
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    float s = accumulate ? sqnorm[ex] + sums[0] : sums[0];
+    for (int l = 1; l < a.n_layers; ++l) s += sums[l];
+    sqnorm[ex] = s;
 }
 
 // grad_b[q] (+)= sum_i nu_i u[i, q].  A workgroup owns 32 columns; its NG row groups add examples g, g + NG, ... in
@@ -283,17 +320,21 @@ int column_threads_log2(int nvec, int B) {
     while (ctl > 4 && (int64_t)((nvec + (1 << ctl) - 1) >> ctl) * B < 1024) --ctl;
     return ctl;
 }
-template <int DT, int DTH = DT> void launch_bias_rows_dt(const void* G, const void* Hb, int B, int T, int D, float* u, float* u2, hipStream_t st) {
+// whether a workgroup of k_bias_rows has an example's whole rows
+bool bias_rows_whole(int B, int D, int vec) {
+    return D % vec == 0 && (D / vec) <= (1 << column_threads_log2(D / vec, B));
+}
+template <int DT, int DTH = DT> void launch_bias_rows_dt(const void* G, const void* Hb, int B, int T, int D, float* u, float* u2, float* sqnorm, int accumulate, hipStream_t st) {
     constexpr int vec = 16 / ElemBytes<DT>::value;
     const bool prod = Hb != nullptr;
     if (D % vec == 0) {
         const int nvec = D / vec;
         const int ctl = column_threads_log2(nvec, B);
         const dim3 grid((unsigned)((nvec + (1 << ctl) - 1) >> ctl), (unsigned)B);
-        if (prod) k_bias_rows<DT, true, DTH><<<grid, kThreads, 0, st>>>(G, Hb, T, D, ctl, u, u2);
-        else      k_bias_rows<DT, false><<<grid, kThreads, 0, st>>>(G, Hb, T, D, ctl, u, u2);
+        if (prod) k_bias_rows<DT, true, DTH><<<grid, kThreads, 0, st>>>(G, Hb, T, D, ctl, u, u2, sqnorm, accumulate);
+        else      k_bias_rows<DT, false><<<grid, kThreads, 0, st>>>(G, Hb, T, D, ctl, u, u2, sqnorm, accumulate);
     } else {
-        const dim3 grid((unsigned)((D + kThreads - 1) / kThreads), (unsigned)B);
+        const dim3 grid((unsigned)((D + kScalarColumns - 1) / kScalarColumns), (unsigned)B);
         if (prod) k_bias_rows_scalar<DT, true, DTH><<<grid, kThreads, 0, st>>>(G, Hb, T, D, u, u2);
         else      k_bias_rows_scalar<DT, false><<<grid, kThreads, 0, st>>>(G, Hb, T, D, u, u2);
     }
@@ -301,25 +342,31 @@ template <int DT, int DTH = DT> void launch_bias_rows_dt(const void* G, const vo
 
 }  // namespace
 
-// Hb == nullptr: u = column sums of G.  Otherwise u = column sums of G (*) Hb and u2 = column sums of G.
+// Hb == nullptr: u = column sums of G.  Otherwise u = column sums of G (*) Hb and u2 = column sums of G.  s_i (+)= the rows' sums of
+// squares, by the same launch where a workgroup has whole rows.
 // dt: type of G and Hb as above; 5: G e5m2 with Hb e4m3.
-hipError_t launch_bias_rows(const void* G, const void* Hb, int B, int T, int D, int dt, float* u, float* u2, hipStream_t st) {
-    // the examples are the grid's y dimension (at most 65535): larger batches go in several launches
+hipError_t launch_bias_rows(const void* G, const void* Hb, int B, int T, int D, int dt, float* u, float* u2, bool accumulate, float* sqnorm, hipStream_t st) {
+    // the examples are the grid's y dimension (at most 65535), a launch has at most 2^24 workgroups: larger batches go in
+    // several launches
+    const int most = std::min(65535, ((1 << 24) - 1) / ceil_div(D, kScalarColumns));
     const size_t es = dt == 0 ? 4 : (dt >= 3 ? 1 : 2);
-    for (int b0 = 0; b0 < B; b0 += 65535) {
-        const int nb = (B - b0 < 65535) ? (B - b0) : 65535;
+    for (int b0 = 0; b0 < B; b0 += most) {
+        const int nb = std::min(B - b0, most);
         const size_t in_off = (size_t)b0 * T * D * es, out_off = (size_t)b0 * D;
         const void* g = static_cast<const unsigned char*>(G) + in_off;
         const void* h = Hb ? static_cast<const unsigned char*>(Hb) + in_off : nullptr;
         float* pu = u + out_off;
         float* pu2 = u2 ? u2 + out_off : nullptr;
-        if (dt == 5)      launch_bias_rows_dt<4, 3>(g, h, nb, T, D, pu, pu2, st);
-        else if (dt == 4) launch_bias_rows_dt<4>(g, h, nb, T, D, pu, pu2, st);
-        else if (dt == 3) launch_bias_rows_dt<3>(g, h, nb, T, D, pu, pu2, st);
-        else if (dt == 2) launch_bias_rows_dt<2>(g, h, nb, T, D, pu, pu2, st);
-        else if (dt == 1) launch_bias_rows_dt<1>(g, h, nb, T, D, pu, pu2, st);
-        else              launch_bias_rows_dt<0>(g, h, nb, T, D, pu, pu2, st);
-        const hipError_t e = hipGetLastError();
+        // (with rows in several pieces the norms take a launch of their own)
+        float* sq = bias_rows_whole(nb, D, (int)(16 / es)) ? sqnorm + b0 : nullptr;
+        if (dt == 5)      launch_bias_rows_dt<4, 3>(g, h, nb, T, D, pu, pu2, sq, accumulate ? 1 : 0, st);
+        else if (dt == 4) launch_bias_rows_dt<4>(g, h, nb, T, D, pu, pu2, sq, accumulate ? 1 : 0, st);
+        else if (dt == 3) launch_bias_rows_dt<3>(g, h, nb, T, D, pu, pu2, sq, accumulate ? 1 : 0, st);
+        else if (dt == 2) launch_bias_rows_dt<2>(g, h, nb, T, D, pu, pu2, sq, accumulate ? 1 : 0, st);
+        else if (dt == 1) launch_bias_rows_dt<1>(g, h, nb, T, D, pu, pu2, sq, accumulate ? 1 : 0, st);
+        else              launch_bias_rows_dt<0>(g, h, nb, T, D, pu, pu2, sq, accumulate ? 1 : 0, st);
+        hipError_t e = hipGetLastError();
+        if (e == hipSuccess && !sq) e = launch_rows_sqnorm(pu, nb, D, accumulate, sqnorm + b0, st, pu2);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
@@ -388,7 +435,7 @@ hipError_t launch_bias_sqnorm_layers(const BiasLayerDesc* layers, int n_layers, 
         const bool wide = y.D % vec == 0;
         a.G[l] = y.G; a.u[l] = y.u; a.T[l] = y.T; a.D[l] = y.D;
         a.ctl[l] = wide ? column_threads_log2(y.D / vec, B) : -1;
-        a.chunks[l] = wide ? (y.D / vec + (1 << a.ctl[l]) - 1) >> a.ctl[l] : ceil_div(y.D, kThreads);
+        a.chunks[l] = wide ? (y.D / vec + (1 << a.ctl[l]) - 1) >> a.ctl[l] : ceil_div(y.D, kScalarColumns);
         a.first_block[l] = (int)blocks;
         if (l < n_layers) blocks += (int64_t)a.chunks[l] * B;
         if (blocks >= (int64_t(1) << 24)) return hipErrorInvalidValue;
@@ -400,8 +447,7 @@ hipError_t launch_bias_sqnorm_layers(const BiasLayerDesc* layers, int n_layers, 
     else              k_bias_rows_layers<2><<<(unsigned)blocks, kThreads, 0, st>>>(a);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const int per_block = kThreads / kWave;
-    k_rows_sqnorm_layers<<<(unsigned)((B + per_block - 1) / per_block), kThreads, 0, st>>>(r, B, accumulate ? 1 : 0, sqnorm);
+    k_rows_sqnorm_layers<<<(unsigned)B, kThreads, 0, st>>>(r, accumulate ? 1 : 0, sqnorm);
     return hipGetLastError();
 }
 

@@ -71,7 +71,7 @@ const void* device_zero_line(hipStream_t st);
 hipError_t launch_widen_f8(const void* src, uint16_t* dst, int64_t n, bool e5m2, hipStream_t st);
 hipError_t launch_add_noise(float* grad, int64_t n, float stddev, uint64_t seed, uint64_t offset, hipStream_t st);
 // ---- bias parameters (dp_bias.hip)
-hipError_t launch_bias_rows(const void* G, const void* Hb, int B, int T, int D, int dt, float* u, float* u2, hipStream_t st);
+hipError_t launch_bias_rows(const void* G, const void* Hb, int B, int T, int D, int dt, float* u, float* u2, bool accumulate, float* sqnorm, hipStream_t st);
 // u[i, :] = sum over nt row tiles of upart[i, tt, :];  s_i (+)= ||u[i, :]||^2
 hipError_t launch_bias_fold(const float* upart, int B, int nt, int D, bool accumulate, float* u, float* sqnorm, hipStream_t st);
 // s_i (+)= ||u[i, :]||^2, then + ||u2[i, :]||^2 where u2 is given
