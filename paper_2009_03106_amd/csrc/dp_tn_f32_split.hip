@@ -84,13 +84,39 @@ __device__ __forceinline__ void tn_f32_exact(const F32SplitArgs& a, int k_begin,
 }
 
 // MODE 0: clipped sum over K slice z = rows [z kchunk, (z + 1) kchunk).  MODE 1: direct squared norm of example z.
-// One wave's part of tile (m0, n0) of slice z: MI blocks of 32 rows from row m0 + mofs on (the tile's rows are those of its waves)
+// The rows of a wave.  256 x 256 tiles: the blocks of 32 rows are dealt evenly to the tiles, a tile's to its two rows of waves:
+// 784 rows are 25 blocks in tiles of 6 and 7, where four whole tiles would form 32 (65536 rows of 784 x 512: 31 % of the
+// products for nothing).  (f32_split_geo takes these tiles where at most a quarter is padding, so every tile has 6 to 8.)
+struct WaveRows { int m0, first, blocks; };            // first row of the tile, of the wave inside it, the wave's blocks
+template <class GEO> __device__ __forceinline__ WaveRows wave_rows(const F32SplitArgs& a, int tm, int wm) {
+    if constexpr (GEO::MI == 4) {
+        const int blocks = (a.M + 31) / 32;
+        const int b0 = (int)((int64_t)tm * blocks / a.tiles_m), b1 = (int)((int64_t)(tm + 1) * blocks / a.tiles_m);
+        const int upper = (b1 - b0 + 1) / 2;
+        return {b0 * 32, wm == 0 ? 0 : upper * 32, wm == 0 ? upper : b1 - b0 - upper};
+    } else {
+        return {tm * GEO::TM, wm * GEO::MI * 32, GEO::MI};
+    }
+}
+// tile of item L's (slice, tile)
+__device__ __forceinline__ void tile_of(const F32SplitArgs& a, int tile, int& tm, int& tn) {
+    if (a.tiles_m < a.tiles_n) { tn = tile / a.tiles_m; tm = tile - tn * a.tiles_m; }       // the short side of the tile grid first
+    else { tm = tile / a.tiles_n; tn = tile - tm * a.tiles_n; }
+}
+
+// One wave's part of item L of the launch, (slice, tile), slice-major: MI blocks of 32 rows
 template <int MODE, class GEO, int MI>
-__device__ __forceinline__ void tn_f32_split_wave(const F32SplitArgs& a, const int z, const int tile, const int m0, const int n0, const int mofs, u32x4* lds) {
+__device__ __forceinline__ void tn_f32_split_wave(const F32SplitArgs& a, const int L, u32x4* lds) {
     constexpr int NI = GEO::NI, TM = GEO::TM, TN = GEO::TN, SU = GEO::STAGE_UNITS, PA = GEO::PA, PG = GEO::PG;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int tiles = a.tiles_m * a.tiles_n;
+    if (L >= (int64_t)tiles * a.splits) return;
+    const int z = L / tiles, tile = L - z * tiles;
+    int tm, tn;
+    tile_of(a, tile, tm, tn);
+    const WaveRows rows = wave_rows<GEO>(a, tm, wave / GEO::WN);
+    const int m0 = rows.m0, n0 = tn * TN, mofs = rows.first;
     int k_begin, k_end;
     if (MODE == 0) { k_begin = z * a.kchunk; k_end = min(a.K, k_begin + a.kchunk); }
     else { k_begin = z * a.T; k_end = k_begin + a.T; }
@@ -117,11 +143,11 @@ __device__ __forceinline__ void tn_f32_split_wave(const F32SplitArgs& a, const i
     uint32_t at_a = 0, at_g = 0;
     auto fetch = [&](bool of_a, int q) {                 // rows 2 q and 2 q + 1 of one operand of the next stage, in order of q
         const int next_row = of_a ? next_a : next_g;
-        const int rows = __builtin_amdgcn_readfirstlane(max(0, min(of_a ? 2 * PA : 2 * PG, k_end - next_row)));
+        const int nrows = __builtin_amdgcn_readfirstlane(max(0, min(of_a ? 2 * PA : 2 * PG, k_end - next_row)));
         if (of_a) {
             if (q == 0) at_a = offA;
             asm volatile("" : "+v"(at_a));               // 16 offsets kept from stage to stage would not fit the registers
-            const auto buf = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.A + (size_t)next_row * a.M), (short)0, (int)(rows * rowA), 0x00020000);
+            const auto buf = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.A + (size_t)next_row * a.M), (short)0, (int)(nrows * rowA), 0x00020000);
             ra[2 * q] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(buf, at_a, 0, 0)); at_a += rowA;
             ra[2 * q + 1] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(buf, at_a, 0, 0)); at_a += rowA;
             if (q < PA - 1) return;
@@ -136,7 +162,7 @@ __device__ __forceinline__ void tn_f32_split_wave(const F32SplitArgs& a, const i
         }
         if (q == 0) at_g = offG;
         asm volatile("" : "+v"(at_g));
-        const auto buf = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.G + (size_t)next_row * a.N), (short)0, (int)(rows * rowG), 0x00020000);
+        const auto buf = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.G + (size_t)next_row * a.N), (short)0, (int)(nrows * rowG), 0x00020000);
         rg[2 * q] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(buf, at_g, 0, 0)); at_g += rowG;
         rg[2 * q + 1] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(buf, at_g, 0, 0)); at_g += rowG;
         if (q == PG - 1) next_g += DKF;
@@ -228,7 +254,10 @@ __device__ __forceinline__ void tn_f32_split_wave(const F32SplitArgs& a, const i
             acc[before / NI][before % NI] += pend * (MODE == 0 && t == 0 ? -sign : sign);
             pend = split_mfma(fa[i & 1], fg[j]);
 #pragma unroll
-            for (int q = t * (PA + PG) / TILES; q < (t + 1) * (PA + PG) / TILES; ++q) split_step(q, buf ^ 1);
+            for (int q = 0; q < (PA + PG + TILES - 1) / TILES; ++q) {
+                const int k = t * (PA + PG) / TILES + q;
+                if (k < (t + 1) * (PA + PG) / TILES) split_step(k, buf ^ 1);
+            }
 #pragma unroll
             for (int q = 0; q < 6; ++q) {
                 __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
@@ -310,28 +339,18 @@ __device__ __forceinline__ void tn_f32_split_wave(const F32SplitArgs& a, const i
         }
 }
 
-// item L of the launch: (slice, tile), slice-major
 template <int MODE, class GEO>
 __device__ __forceinline__ void tn_f32_split_tile(const F32SplitArgs& a, const int L, u32x4* lds) {
-    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    const int tiles = a.tiles_m * a.tiles_n;
-    if (L >= (int64_t)tiles * a.splits) return;
-    const int z = L / tiles, tile = L - z * tiles;
-    int tm, tn;                                          // consecutive items walk the short side of the tile grid first
-    if (a.tiles_m < a.tiles_n) { tn = tile / a.tiles_m; tm = tile - tn * a.tiles_m; }
-    else { tm = tile / a.tiles_n; tn = tile - tm * a.tiles_n; }
-    const int n0 = tn * GEO::TN, wm = wave / GEO::WN;
     if constexpr (GEO::MI == 4) {
-        // the blocks of 32 rows are dealt evenly to the tiles, a tile's to its two rows of waves: 784 rows are 25 blocks in tiles
-        // of 6 and 7, where four whole tiles would form 32 (65536 rows of 784 x 512: 31 % of the products for nothing)
-        // (f32_split_geo takes these tiles where at most a quarter is padding, so every tile has 6 to 8 blocks)
-        const int blocks = (a.M + 31) / 32;
-        const int b0 = (int)((int64_t)tm * blocks / a.tiles_m), b1 = (int)((int64_t)(tm + 1) * blocks / a.tiles_m);
-        const int upper = (b1 - b0 + 1) / 2, own = wm == 0 ? upper : b1 - b0 - upper, m0 = b0 * 32, mofs = wm == 0 ? 0 : upper * 32;
-        if (own == 4)      tn_f32_split_wave<MODE, GEO, 4>(a, z, tile, m0, n0, mofs, lds);
-        else               tn_f32_split_wave<MODE, GEO, 3>(a, z, tile, m0, n0, mofs, lds);
+        const int tiles = a.tiles_m * a.tiles_n;
+        int tm, tn;
+        tile_of(a, L % tiles, tm, tn);
+        if (wave_rows<GEO>(a, tm, __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6) / GEO::WN).blocks == 4)
+            tn_f32_split_wave<MODE, GEO, 4>(a, L, lds);
+        else
+            tn_f32_split_wave<MODE, GEO, 3>(a, L, lds);
     } else {
-        tn_f32_split_wave<MODE, GEO, GEO::MI>(a, z, tile, tm * GEO::TM, n0, wm * GEO::MI * 32, lds);
+        tn_f32_split_wave<MODE, GEO, GEO::MI>(a, L, lds);
     }
 }
 
