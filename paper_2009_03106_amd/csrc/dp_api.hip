@@ -885,18 +885,31 @@ dp_status dp_layers_sqnorm_clip(const dp_layer_desc* layers, int64_t n_layers, i
             ng = 0; least = 0;
             return e;
         };
-        for (int64_t l = 0; l < n_layers; ++l) {
+        // float32 rows that are no whole 16-byte pieces (kinds 1 and 2) run in a launch of their own, with the other layers of
+        // the same number of 32-row blocks: one launch that fills the chip (two layers of 10 examples, 36 positions of 959 ->
+        // 855 and 62 of 2500 -> 1620: 26 us, apart 37)
+        bool odd[3] = {false, false, false};
+        for (int64_t l = 0; dtype == DP_F32 && l < n_layers; ++l) {
             const dp_layer_desc& y = layers[l];
-            if (!gram_cols_layer(B, y.T, y.d_in, y.d_out, dtype, path)) continue;
-            // (a layer alone fits: its own plan has at least two shares per example, 4 KB and more each)
-            const GramColsPlan p = plan_gram_cols((int)B, (int)y.T, (int)y.d_in, (int)y.d_out, (int)dtype);
-            const size_t own = round16((size_t)B * gram_cols_sums(p) * sizeof(float)) + p.ws_floats / (size_t)p.W * sizeof(float);
-            if (ng > 0 && least + own > need && flush_cols() != hipSuccess) return DP_ERR_HIP;
-            least += own;
-            group[ng++] = GramLayerDesc{y.A, y.G, (int)y.T, (int)y.d_in, (int)y.d_out, nullptr, nullptr};
-            if (ng == kGramColsLayers && flush_cols() != hipSuccess) return DP_ERR_HIP;
+            if (gram_cols_layer(B, y.T, y.d_in, y.d_out, dtype, path)) odd[gram_cols_kind((int)y.T, (int)y.d_in, (int)y.d_out, (int)dtype)] = true;
         }
-        if (flush_cols() != hipSuccess) return DP_ERR_HIP;
+        for (int kind = 0; kind <= (dtype == DP_F32 ? 2 : 0); ++kind) {
+            for (int64_t l = 0; l < n_layers; ++l) {
+                const dp_layer_desc& y = layers[l];
+                if (!gram_cols_layer(B, y.T, y.d_in, y.d_out, dtype, path)) continue;
+                const int blocks32 = y.T <= 32 ? 1 : 2;
+                if ((odd[blocks32] ? blocks32 : 0) != kind) continue;
+                // (a layer alone fits: its own plan has at least two shares per example, 4 KB and more each; those of kinds 1 and 2
+                // fit with all their shares, except for the place that the sums in front of them take)
+                const GramColsPlan p = plan_gram_cols((int)B, (int)y.T, (int)y.d_in, (int)y.d_out, (int)dtype);
+                const size_t own = round16((size_t)B * gram_cols_sums(p) * sizeof(float)) + p.ws_floats / (size_t)p.W * sizeof(float);
+                if (ng > 0 && least + own > need && flush_cols() != hipSuccess) return DP_ERR_HIP;
+                least += own;
+                group[ng++] = GramLayerDesc{y.A, y.G, (int)y.T, (int)y.d_in, (int)y.d_out, nullptr, nullptr};
+                if (ng == kGramColsLayers && flush_cols() != hipSuccess) return DP_ERR_HIP;
+            }
+            if (flush_cols() != hipSuccess) return DP_ERR_HIP;
+        }
     }
     const bool clip_with_single = clip && !any_gram && !any_bias_pass && (last_single >= 0 || defer_on);
     const bool clip_with_dense = clip && !any_gram && !any_bias_pass && last_single < 0 && !defer_on && n_dense > 0;

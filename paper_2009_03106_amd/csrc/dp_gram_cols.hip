@@ -19,6 +19,7 @@
 // its own row, an instruction touches 32 lines for 32 bytes each, and the launches moved 1.9 TB/s: 32 examples of 64
 // positions into 2304 x 256, three layers, and 1152 x 256 took 19.4 us.  Eight layers of an 18-layer image model, 56 MB,
 // take 14 us in one launch (4 TB/s) and 5 us for the sums; in two launches by registers, with a walk through the shares, 60 us.)
+#include <algorithm>
 #include "dp_common.h"
 #include "dp_internal.h"
 
@@ -159,10 +160,11 @@ __device__ __forceinline__ void gram_cols_run(const unsigned char* __restrict__ 
     }
 }
 
-// float32 rows whose length is not a multiple of 4 start at any 4-byte address: four clamped 4-byte loads a piece
-template <int NB>
-__device__ __forceinline__ void gram_cols_run_odd(const float* __restrict__ X, int T, int D, int kb, int ke, int lane,
-                                                  f32x16 (&acc)[NB * (NB + 1) / 2]) {
+// float32 rows straight to registers, a lane's pieces of 8 steps in flight together.  VEC: rows of whole 16-byte pieces; else
+// rows start at any 4-byte address, and a piece is four clamped 4-byte loads.
+template <int NB, bool VEC>
+__device__ __forceinline__ void gram_cols_run_loads(const float* __restrict__ X, int T, int D, int kb, int ke, int lane,
+                                                    f32x16 (&acc)[NB * (NB + 1) / 2]) {
     const int row = lane & 31, half = lane >> 5;
     const float* p[NB];
     bool in[NB];
@@ -182,9 +184,14 @@ __device__ __forceinline__ void gram_cols_run_odd(const float* __restrict__ X, i
 #pragma unroll
             for (int b = 0; b < NB; ++b) {
                 const bool keep = ok && in[b];
-                const float x = p[b][c], y = p[b][min(c + 1, D - 1)], z = p[b][min(c + 2, D - 1)], w = p[b][min(c + 3, D - 1)];
-                f[u][b] = make_uint4(keep ? __float_as_uint(x) : 0u, (keep && c + 1 < D) ? __float_as_uint(y) : 0u,
-                                     (keep && c + 2 < D) ? __float_as_uint(z) : 0u, (keep && c + 3 < D) ? __float_as_uint(w) : 0u);
+                if (VEC) {
+                    const uint4 v = *reinterpret_cast<const uint4*>(p[b] + c);
+                    f[u][b] = make_uint4(keep ? v.x : 0u, keep ? v.y : 0u, keep ? v.z : 0u, keep ? v.w : 0u);
+                } else {
+                    const float x = p[b][c], y = p[b][min(c + 1, D - 1)], z = p[b][min(c + 2, D - 1)], w = p[b][min(c + 3, D - 1)];
+                    f[u][b] = make_uint4(keep ? __float_as_uint(x) : 0u, (keep && c + 1 < D) ? __float_as_uint(y) : 0u,
+                                         (keep && c + 2 < D) ? __float_as_uint(z) : 0u, (keep && c + 3 < D) ? __float_as_uint(w) : 0u);
+                }
             }
         }
 #pragma unroll
@@ -195,22 +202,11 @@ __device__ __forceinline__ void gram_cols_run_odd(const float* __restrict__ X, i
     }
 }
 
-// X_i of whichever type: DT 0 = float32, 1 = bf16, 2 = fp16 (the values of dp_dtype)
-template <int NB, int DT>
-__device__ __forceinline__ void gram_cols_side(const void* X, size_t ex, int T, int D, int kb, int ke, int lane, unsigned char* lds,
-                                               f32x16 (&acc)[NB * (NB + 1) / 2]) {
-    constexpr int ES = DT == 0 ? 4 : 2;
-    if constexpr (DT == 0) {
-        if ((D & 3) != 0) { gram_cols_run_odd<NB>(static_cast<const float*>(X) + ex * T * D, T, D, kb, ke, lane, acc); return; }
-    }
-    gram_cols_run<NB, DT>(static_cast<const unsigned char*>(X) + ex * T * D * ES, T, D * ES, kb, ke, lane, lds, acc);
-}
-
-template <int NB, int DT>
-__device__ __forceinline__ void gram_cols_block(const GramColsLayer& a, int item, float* part, unsigned char* lds) {
+// One workgroup's share.  run(X of the example, its columns, first step, end, sums): adds a range of steps of A or G.
+template <int NB, typename Run>
+__device__ __forceinline__ void gram_cols_block(const GramColsLayer& a, int item, float* part, unsigned char* lds, Run run) {
     constexpr int NT = NB * (NB + 1) / 2;            // tiles of the upper triangle
     constexpr int SHARE = 2 * NT * 4 * 64;           // 16-byte units of one wave's share (both products)
-    static_assert(2 * SHARE * 16 <= 4 * kWaveLds, "the waves' shares meet where their stages were");
     const int ex = item / a.W, w = item - ex * a.W;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 
@@ -224,10 +220,8 @@ __device__ __forceinline__ void gram_cols_block(const GramColsLayer& a, int item
 
     const int k0 = (w * 4 + wave) * a.per_wave;
     const int k1 = min(k0 + a.per_wave, a.steps);
-    if (k0 < a.steps_a)
-        gram_cols_side<NB, DT>(a.A, (size_t)ex, a.T, a.d_in, k0, min(k1, a.steps_a), lane, lds + wave * kWaveLds, acc[0]);
-    if (k1 > a.steps_a)
-        gram_cols_side<NB, DT>(a.G, (size_t)ex, a.T, a.d_out, max(k0, a.steps_a) - a.steps_a, k1 - a.steps_a, lane, lds + wave * kWaveLds, acc[1]);
+    if (k0 < a.steps_a) run(a.A, (size_t)ex, a.d_in, k0, min(k1, a.steps_a), acc[0]);
+    if (k1 > a.steps_a) run(a.G, (size_t)ex, a.d_out, max(k0, a.steps_a) - a.steps_a, k1 - a.steps_a, acc[1]);
 
     // waves 2, 3 -> LDS; waves 0, 1 add them; wave 1 -> LDS; wave 0 adds it and stores the workgroup's share
     auto put = [&](float4* slot) {
@@ -264,14 +258,43 @@ __device__ __forceinline__ void gram_cols_block(const GramColsLayer& a, int item
     }
 }
 
+template <int NB, int DT>
+__device__ __forceinline__ void gram_cols_copied(const GramColsLayer& a, const GramColsArgs& j, unsigned char* lds) {
+    static_assert(2 * NB * (NB + 1) * 4096 <= 4 * kWaveLds, "the waves' shares meet where their stages were");
+    constexpr int ES = DT == 0 ? 4 : 2;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    gram_cols_block<NB>(a, blockIdx.x - a.first_block, j.part, lds,
+        [&](const void* X, size_t ex, int D, int kb, int ke, f32x16 (&acc)[NB * (NB + 1) / 2]) {
+            gram_cols_run<NB, DT>(static_cast<const unsigned char*>(X) + ex * a.T * D * ES, a.T, D * ES, kb, ke, lane, lds + wave * kWaveLds, acc);
+        });
+}
+
+// rows of whole 16-byte pieces
 template <int DT>
 __global__ __launch_bounds__(kThreads, 2) void k_gram_cols(GramColsArgs j) {
     __shared__ __attribute__((aligned(1024))) unsigned char lds[4 * kWaveLds];
     int li = 0;
     while (li + 1 < j.n_layers && blockIdx.x >= j.layer[li + 1].first_block) ++li;
     const GramColsLayer& a = j.layer[li];
-    if (a.nb == 1) gram_cols_block<1, DT>(a, blockIdx.x - a.first_block, j.part, lds);
-    else           gram_cols_block<2, DT>(a, blockIdx.x - a.first_block, j.part, lds);
+    if (a.nb == 1) gram_cols_copied<1, DT>(a, j, lds);
+    else           gram_cols_copied<2, DT>(a, j, lds);
+}
+
+// float32 rows of any length, through registers
+template <int NB>
+__global__ __launch_bounds__(kThreads, 2) void k_gram_cols_loads(GramColsArgs j) {
+    __shared__ __attribute__((aligned(1024))) unsigned char lds[NB == 1 ? 16384 : 3 * 16384];
+    int li = 0;
+    while (li + 1 < j.n_layers && blockIdx.x >= j.layer[li + 1].first_block) ++li;
+    const GramColsLayer& a = j.layer[li];
+    const int lane = threadIdx.x & 63;
+    gram_cols_block<NB>(a, blockIdx.x - a.first_block, j.part, lds,
+        [&](const void* X, size_t ex, int D, int kb, int ke, f32x16 (&acc)[NB * (NB + 1) / 2]) {
+            const float* x = static_cast<const float*>(X) + ex * a.T * D;
+            // (the choice sits outside the loops: a branch around every load would make each wait for the one before)
+            if ((D & 3) == 0) gram_cols_run_loads<NB, true>(x, a.T, D, kb, ke, lane, acc);
+            else              gram_cols_run_loads<NB, false>(x, a.T, D, kb, ke, lane, acc);
+        });
 }
 
 // Several layers: sums[ex][t] of a layer = the sum over the entries of triangle tile t of (sum_w P_w) * (sum_w Q_w), the
@@ -370,27 +393,37 @@ GramColsPlan plan_gram_cols(int B, int T, int d_in, int d_out, int dt) {
 
 int gram_cols_sums(const GramColsPlan& p) { return p.nb == 1 ? 1 : 3; }
 
+int gram_cols_kind(int T, int d_in, int d_out, int dt) {
+    return dt != 0 || ((d_in | d_out) & 3) == 0 ? 0 : T <= 32 ? 1 : 2;
+}
+
 namespace {
+// the kind of a launch: that of the layers that have one
+int cols_launch_kind(const GramLayerDesc* layers, int n_layers, int dt) {
+    int kind = 0;
+    for (int l = 0; l < n_layers; ++l) kind = std::max(kind, gram_cols_kind(layers[l].T, layers[l].d_in, layers[l].d_out, dt));
+    return kind;
+}
+
 // The layers of a shared launch fill the chip together, so each takes fewer workgroups than it would alone, all of about one
 // length: few shares to store and to add, and waves that stream (a wave of kColsSteps waits once for all it loads).  The
 // length, counted in steps of 32 rows, that makes  rounds of 512 workgroups x (length + what a workgroup costs besides)
-// least, of those whose shares take at most max_floats (at the longest, one workgroup per example, they do).
+// least, of those whose shares take at most max_floats (at the longest, one workgroup per example, they do).  A layer alone,
+// and those that are loaded 4 bytes at a time, a memory round trip for 8 steps, keep their own plans where those fit (49
+// examples of 17 positions, 656 -> 1673 and 1673 -> 656 among four layers: 19 us, 30 us with long waves).
 void plan_cols_shared(const GramLayerDesc* layers, int n_layers, int B, int dt, size_t max_floats, GramColsPlan* p) {
     constexpr int kOverhead = 24;
     const int step = dt == 0 ? 8 : 16;
     int steps[kGramColsLayers], longest = kColsSteps;
+    size_t own = 0;
     for (int l = 0; l < n_layers; ++l) {
         p[l] = plan_gram_cols(B, layers[l].T, layers[l].d_in, layers[l].d_out, dt);
         steps[l] = ceil_div(layers[l].d_in, step) + ceil_div(layers[l].d_out, step);
         longest = longest > p[l].nb * ceil_div(steps[l], 4) ? longest : p[l].nb * ceil_div(steps[l], 4);
+        own += p[l].ws_floats;
     }
-    if (max_floats == kAnySlices) return;
-    // (float32 rows of a length that is no multiple of 4 come 4 bytes at a time, a memory round trip for 8 steps: those layers
-    // keep their own short waves.  49 examples of 17 positions, 656 -> 1673 and 1673 -> 656 among four layers: 19 us, 30 us
-    // with long ones)
-    bool short_waves = true;
+    if ((n_layers == 1 || cols_launch_kind(layers, n_layers, dt) != 0) && own <= max_floats) return;
     auto take = [&](int l, int length, int& W) {              // whole stages per wave, so that the copies move whole lines
-        if (short_waves && dt == 0 && ((layers[l].d_in | layers[l].d_out) & 3) != 0) { W = p[l].W; return p[l].per_wave; }
         const int least = length / p[l].nb > kColsSteps ? length / p[l].nb : kColsSteps;
         const int w = ceil_div(steps[l], 4 * least);
         const int per_wave = (ceil_div(steps[l], 4 * w) + kStageSteps - 1) / kStageSteps * kStageSteps;
@@ -414,8 +447,8 @@ void plan_cols_shared(const GramLayerDesc* layers, int n_layers, int B, int dt, 
         if (floats > max_floats) continue;
         const int64_t cost = ((blocks + 511) / 512) * (most + kOverhead);
         if (best_cost < 0 || cost < best_cost) { best_cost = cost; best = len; }
+        if (blocks <= 512) break;                             // one round: longer waves only take longer
     }
-    short_waves = best_cost >= 0;                             // (no room for theirs)
     for (int l = 0; l < n_layers; ++l) {
         const size_t share = p[l].ws_floats / (size_t)p[l].W;
         p[l].per_wave = take(l, best, p[l].W);
@@ -423,13 +456,13 @@ void plan_cols_shared(const GramLayerDesc* layers, int n_layers, int B, int dt, 
     }
 }
 
-// fills the launch's arguments and makes the first launch; sums: nullptr, or each layer's own array; max_floats: kAnySlices for
-// the layers' own plans
+// fills the launch's arguments and makes the first launch; sums: nullptr, or each layer's own array
 hipError_t launch_cols(const GramLayerDesc* layers, float* const* sums, int n_layers, int B, float* ws, size_t max_floats, hipStream_t st, int dt, GramColsArgs& a,
                        unsigned& finish_blocks) {
     if (n_layers < 1 || n_layers > kGramColsLayers || dt < 0 || dt > 2) return hipErrorInvalidValue;
     a.part = ws; a.n_layers = n_layers;
     const int step = dt == 0 ? 8 : 16;
+    const int kind = cols_launch_kind(layers, n_layers, dt);
     int64_t blocks = 0, finish = 0;
     size_t off = 0;
     GramColsPlan plans[kGramColsLayers];
@@ -437,7 +470,7 @@ hipError_t launch_cols(const GramLayerDesc* layers, float* const* sums, int n_la
     for (int l = 0; l < n_layers; ++l) {
         const GramLayerDesc& y = layers[l];
         const GramColsPlan& p = plans[l];
-        if (!p.use) return hipErrorInvalidValue;
+        if (!p.use || (kind != 0 && p.nb != kind)) return hipErrorInvalidValue;
         GramColsLayer& g = a.layer[l];
         g.A = y.A; g.G = y.G;
         g.sums = sums ? sums[l] : nullptr;
@@ -451,11 +484,16 @@ hipError_t launch_cols(const GramLayerDesc* layers, float* const* sums, int n_la
         off += p.ws_floats;
     }
     for (int l = n_layers; l < kGramColsLayers; ++l) a.layer[l] = a.layer[0];
-    if (blocks >= (int64_t(1) << 24) || finish >= (int64_t(1) << 24)) return hipErrorInvalidValue;   // (B < 2^8 where W >= 2)
+    if (blocks >= (int64_t(1) << 24) || finish >= (int64_t(1) << 24)) return hipErrorInvalidValue;   // (W >= 2 only where B < 2^9)
     finish_blocks = (unsigned)finish;
-    if (dt == 0)      k_gram_cols<0><<<(unsigned)blocks, kThreads, 0, st>>>(a);
-    else if (dt == 1) k_gram_cols<1><<<(unsigned)blocks, kThreads, 0, st>>>(a);
-    else              k_gram_cols<2><<<(unsigned)blocks, kThreads, 0, st>>>(a);
+    // Rows that are no whole 16-byte pieces are loaded to registers: what hides their many short loads is the number of
+    // workgroups (with the copied layers in one launch, two per compute unit, two layers of 64 examples lost half: 20 positions,
+    // 662 -> 600, and 41, 367 -> 3519, 49 and 104 us).
+    if (kind == 1)      k_gram_cols_loads<1><<<(unsigned)blocks, kThreads, 0, st>>>(a);
+    else if (kind == 2) k_gram_cols_loads<2><<<(unsigned)blocks, kThreads, 0, st>>>(a);
+    else if (dt == 0)   k_gram_cols<0><<<(unsigned)blocks, kThreads, 0, st>>>(a);
+    else if (dt == 1)   k_gram_cols<1><<<(unsigned)blocks, kThreads, 0, st>>>(a);
+    else                k_gram_cols<2><<<(unsigned)blocks, kThreads, 0, st>>>(a);
     return hipGetLastError();
 }
 }  // namespace

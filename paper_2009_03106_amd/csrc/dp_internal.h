@@ -281,9 +281,11 @@ struct GramColsPlan { bool use; int nb, W, per_wave; size_t ws_floats; };
 GramColsPlan plan_gram_cols(int B, int T, int d_in, int d_out, int dt);
 // several such layers in one launch (and one that adds the shares): sums[l] gets the layer's [B][gram_cols_sums(plan)] sums,
 // to be added by the caller; ws: max_floats, enough for one share per example and layer (A, G, T, d_in, d_out of the
-// descriptors are used)
+// descriptors are used).  Where a layer's kind is not 0, all have its number of 32-row blocks.
 constexpr int kGramColsLayers = 16;
 int gram_cols_sums(const GramColsPlan& p);
+// 0: rows of whole 16-byte pieces; float32 rows of other lengths: their 32-row blocks, 1 (T <= 32) or 2
+int gram_cols_kind(int T, int d_in, int d_out, int dt);
 hipError_t launch_gram_cols_layers(const GramLayerDesc* layers, float* const* sums, int n_layers, int B, float* ws, size_t max_floats,
                                    hipStream_t st, int dt);
 // the same with the layers' sums added to sqnorm (and the clip factors written) by the second launch
