@@ -4,9 +4,8 @@
 // convolutions of an image model (4 x 4 or 8 x 8 positions, 2304 -> 256 or 4608 -> 512 unfolded columns, 20 to 32
 // examples).  One workgroup per example walks thousands of columns alone there and leaves most of the chip idle, so
 // here the COLUMNS are split: every wave takes a range of the columns of A and G (one after the other), forms its
-// share of A_i A_i^T and of G_i G_i^T straight from registers, the four waves of a workgroup add their shares
-// through LDS, and a second kernel adds the workgroups' shares of an example in a fixed order, multiplies the two
-// T x T products entry by entry and sums.
+// share of A_i A_i^T and of G_i G_i^T, the four waves of a workgroup add their shares through LDS, and a second kernel
+// adds the workgroups' shares of an example in a fixed order, multiplies the two T x T products entry by entry and sums.
 //
 // Both operands of a Gram product are rows of the same matrix, so a 16-byte piece of a row serves the left and the right
 // side of the MFMA alike.  16-bit inputs: the piece (8 consecutive columns of one row) is one operand of the 32 x 32 x 16
@@ -29,7 +28,8 @@ namespace {
 
 constexpr int kColsSteps = 8;        // 32-byte steps of a row that a wave takes at least, in flight together
 constexpr int kStageSteps = 4;       // steps of one copied stage: 128 bytes of every row
-constexpr int kWaveLds = 16384;      // bytes of a wave's stages: 2 of 64 rows or 4 of 32 rows
+constexpr int kWaveLds = 16384;      // bytes of a wave's stages in a launch of several layers: 2 of 64 rows or 4 of 32 rows
+constexpr int kStages1 = 4, kStages2 = 2;      // stages in flight at most, rows of one and of two 32-row blocks
 #define LDS_PTR(T) __attribute__((address_space(3))) T*
 
 struct GramColsLayer {
@@ -47,11 +47,13 @@ struct GramColsLayer {
     unsigned first_finish;      // first workgroup of k_gram_cols_sums
 };
 // Several layers in one launch: a layer alone is a few hundred workgroups that each make one memory round trip, so the
-// launches of a model's layers mostly wait.
-struct GramColsArgs {
-    GramColsLayer layer[kGramColsLayers];
+// launches of a model's layers mostly wait.  CAP: the most layers (a layer alone does not pay for the arguments of 16).
+template <int CAP> struct GramColsArgs {
+    GramColsLayer layer[CAP];
     float* part;         // per layer [B][W][2][NT][4][64][4]: the workgroups' shares of the two products, in accumulator layout
     int n_layers;
+    int wave_lds;        // bytes of a wave's stages
+    int stages;          // of layers with one 32-row block: how many of them
 };
 
 // at most n of the wave's copies may still be in flight
@@ -65,7 +67,7 @@ __device__ __forceinline__ void wait_copies(int n) {
 }
 
 // acc[tile] += X[rows of block b0] . X[rows of block b1]^T for one step, a 16-byte piece per lane and block; tiles in the
-// order (0,0), (0,1), (1,1) for two 32-row blocks
+// order (0,0), (0,1), (1,1) for two 32-row blocks.
 template <int NB, int DT>
 __device__ __forceinline__ void gram_cols_mfma(const uint4 (&f)[NB], f32x16 (&acc)[NB * (NB + 1) / 2]) {
     if constexpr (DT == 0) {
@@ -92,13 +94,12 @@ __device__ __forceinline__ void gram_cols_mfma(const uint4 (&f)[NB], f32x16 (&ac
     }
 }
 
-// The steps [kb, ke) of X (an example's T rows of `row_bytes` bytes, a multiple of 16), copied through the wave's 16 KB of
-// LDS at `lds`.  Rows >= T and pieces past the end of a row count as zero: they are copied from valid addresses, or not
-// at all, and zeroed when they are read.
+// The steps [kb, ke) of X (an example's T rows of `row_bytes` bytes, a multiple of 16), copied through `nst` stages of LDS at
+// `lds`.  Rows >= T and pieces past the end of a row count as zero: they are copied from valid addresses, or not at all, and
+// zeroed when they are read.
 template <int NB, int DT>
 __device__ __forceinline__ void gram_cols_run(const unsigned char* __restrict__ X, int T, int row_bytes, int kb, int ke, int lane,
-                                              unsigned char* lds, f32x16 (&acc)[NB * (NB + 1) / 2]) {
-    constexpr int STAGE = NB * 32 * 128, NST = kWaveLds / STAGE;
+                                              unsigned char* lds, int nst, f32x16 (&acc)[NB * (NB + 1) / 2]) {
     constexpr int COPIES = NB * 4;                       // copy instructions of a whole stage, 8 rows each
     const int n_stages = (ke - kb + kStageSteps - 1) / kStageSteps;
     const int copies = min(COPIES, (T + 7) / 8);         // those with rows inside the example
@@ -118,7 +119,7 @@ __device__ __forceinline__ void gram_cols_run(const unsigned char* __restrict__ 
         for (int i = 0; i < COPIES; ++i) {
             if (i < copies) {
                 const uint64_t from = (uint64_t)(uintptr_t)(src[i] + (at[i] < limit ? at[i] : 0));
-                asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off" :: "s"(base + buf * STAGE + i * 1024), "v"(from) : "memory", "m0");
+                asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off" :: "s"(base + (buf * copies + i) * 1024), "v"(from) : "memory", "m0");
             }
             at[i] += 128;
         }
@@ -128,23 +129,24 @@ __device__ __forceinline__ void gram_cols_run(const unsigned char* __restrict__ 
     uint32_t rd[NB];
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
-        const int r = b * 32 + row;
-        in[b] = r < T;
+        const int r = min(b * 32 + row, T - 1);
+        in[b] = b * 32 + row < T;
         rd[b] = (uint32_t)(r * 128 + ((half ^ ((r >> 1) & 7)) << 4));
     }
-#pragma unroll
-    for (int p = 0; p < NST; ++p)
+    for (int p = 0; p < nst; ++p)
         if (p < n_stages) issue(p);
+    int buf = 0;
     for (int st = 0; st < n_stages; ++st) {
-        wait_copies(min(n_stages - 1 - st, NST - 1) * copies);
-        const unsigned char* sb = lds + (st % NST) * STAGE;
+        wait_copies(min(n_stages - 1 - st, nst - 1) * copies);
+        const unsigned char* sb = lds + buf * copies * 1024;
         uint4 f[kStageSteps][NB];
 #pragma unroll
         for (int u = 0; u < kStageSteps; ++u)
 #pragma unroll
             for (int b = 0; b < NB; ++b) f[u][b] = *reinterpret_cast<const uint4*>(sb + (rd[b] ^ (u << 5)));
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");          // read: the buffer takes a later stage
-        if (st + NST < n_stages) issue(st % NST);
+        if (st + nst < n_stages) issue(buf);
+        buf = buf + 1 == nst ? 0 : buf + 1;
         const int k = kb + st * kStageSteps;
 #pragma unroll
         for (int u = 0; u < kStageSteps; ++u) {
@@ -258,32 +260,39 @@ __device__ __forceinline__ void gram_cols_block(const GramColsLayer& a, int item
     }
 }
 
-template <int NB, int DT>
-__device__ __forceinline__ void gram_cols_copied(const GramColsLayer& a, const GramColsArgs& j, unsigned char* lds) {
-    static_assert(2 * NB * (NB + 1) * 4096 <= 4 * kWaveLds, "the waves' shares meet where their stages were");
+template <int NB, int DT, int CAP>
+__device__ __forceinline__ void gram_cols_copied(const GramColsLayer& a, const GramColsArgs<CAP>& j, unsigned char* lds) {
     constexpr int ES = DT == 0 ? 4 : 2;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     gram_cols_block<NB>(a, blockIdx.x - a.first_block, j.part, lds,
         [&](const void* X, size_t ex, int D, int kb, int ke, f32x16 (&acc)[NB * (NB + 1) / 2]) {
-            gram_cols_run<NB, DT>(static_cast<const unsigned char*>(X) + ex * a.T * D * ES, a.T, D * ES, kb, ke, lane, lds + wave * kWaveLds, acc);
+            gram_cols_run<NB, DT>(static_cast<const unsigned char*>(X) + ex * a.T * D * ES, a.T, D * ES, kb, ke, lane,
+                                       lds + wave * j.wave_lds, NB == 1 ? j.stages : kStages2, acc);
         });
 }
 
-// rows of whole 16-byte pieces
-template <int DT>
-__global__ __launch_bounds__(kThreads, 2) void k_gram_cols(GramColsArgs j) {
-    __shared__ __attribute__((aligned(1024))) unsigned char lds[4 * kWaveLds];
+// Rows of whole 16-byte pieces.  NB: the launch's largest number of 32-row blocks.  A layer alone may have more workgroups than
+// two per compute unit: for three of them 168 registers (and no more LDS than the rows that there are).  (With the registers
+// and the 64 KB of the kernel for several layers it lost 10 to 20 %: 60 examples of 8 positions, 5312 -> 2048, 10.9 and 13.5
+// us, 174 of 20 positions, 1456 -> 528, 10.5 and 12.7.)
+template <int NB, int DT, int CAP>
+__global__ __launch_bounds__(kThreads, CAP == 1 ? 3 : 2) void k_gram_cols(GramColsArgs<CAP> j) {
+    extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
     int li = 0;
     while (li + 1 < j.n_layers && blockIdx.x >= j.layer[li + 1].first_block) ++li;
     const GramColsLayer& a = j.layer[li];
-    if (a.nb == 1) gram_cols_copied<1, DT>(a, j, lds);
-    else           gram_cols_copied<2, DT>(a, j, lds);
+    if constexpr (CAP == 1) {
+        gram_cols_copied<NB, DT>(a, j, lds);
+    } else {
+        if (NB == 1 || a.nb == 1) gram_cols_copied<1, DT>(a, j, lds);
+        else                      gram_cols_copied<NB, DT>(a, j, lds);
+    }
 }
 
 // float32 rows of any length, through registers
-template <int NB>
-__global__ __launch_bounds__(kThreads, 2) void k_gram_cols_loads(GramColsArgs j) {
-    __shared__ __attribute__((aligned(1024))) unsigned char lds[NB == 1 ? 16384 : 3 * 16384];
+template <int NB, int CAP>
+__global__ __launch_bounds__(kThreads, 2) void k_gram_cols_loads(GramColsArgs<CAP> j) {
+    extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
     int li = 0;
     while (li + 1 < j.n_layers && blockIdx.x >= j.layer[li + 1].first_block) ++li;
     const GramColsLayer& a = j.layer[li];
@@ -301,7 +310,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_gram_cols_loads(GramColsArgs j)
 // tile (0,1) counted twice (it stands for its mirror image too), the shares added in the order of the workgroups.  One
 // workgroup per (example, tile).  (A workgroup per example that walked all layers' shares read them at 20 GB/s each: 13 and
 // 19 us for 32 examples of four layers.)
-__global__ __launch_bounds__(kThreads) void k_gram_cols_sums(GramColsArgs j) {
+__global__ __launch_bounds__(kThreads) void k_gram_cols_sums(GramColsArgs<kGramColsLayers> j) {
     __shared__ float red[4];
     int li = 0;
     while (li + 1 < j.n_layers && blockIdx.x >= j.layer[li + 1].first_finish) ++li;
@@ -344,7 +353,8 @@ __device__ __forceinline__ float gram_cols_dot(const float* base, int W) {
     for (int i = 0; i < NT; ++i) s += (NT == 3 && i == 1) ? 2.0f * (p[i] * q[i]) : p[i] * q[i];
     return s;
 }
-__global__ __launch_bounds__(kFinishThreads) void k_gram_cols_finish(GramColsArgs j, int accumulate, float* __restrict__ sqnorm, float C,
+template <int CAP>
+__global__ __launch_bounds__(kFinishThreads) void k_gram_cols_finish(GramColsArgs<CAP> j, int accumulate, float* __restrict__ sqnorm, float C,
                                                                        float* __restrict__ clip) {
     __shared__ float red[kFinishThreads / 64];
     const int ex = blockIdx.x;
@@ -456,16 +466,24 @@ void plan_cols_shared(const GramLayerDesc* layers, int n_layers, int B, int dt, 
     }
 }
 
+template <int NB, int CAP> void launch_cols_copied(unsigned blocks, size_t lds, hipStream_t st, int dt, const GramColsArgs<CAP>& a) {
+    if (dt == 0)      k_gram_cols<NB, 0, CAP><<<blocks, kThreads, lds, st>>>(a);
+    else if (dt == 1) k_gram_cols<NB, 1, CAP><<<blocks, kThreads, lds, st>>>(a);
+    else              k_gram_cols<NB, 2, CAP><<<blocks, kThreads, lds, st>>>(a);
+}
+
 // fills the launch's arguments and makes the first launch; sums: nullptr, or each layer's own array
-hipError_t launch_cols(const GramLayerDesc* layers, float* const* sums, int n_layers, int B, float* ws, size_t max_floats, hipStream_t st, int dt, GramColsArgs& a,
-                       unsigned& finish_blocks) {
-    if (n_layers < 1 || n_layers > kGramColsLayers || dt < 0 || dt > 2) return hipErrorInvalidValue;
+template <int CAP>
+hipError_t launch_cols(const GramLayerDesc* layers, float* const* sums, int n_layers, int B, float* ws, size_t max_floats, hipStream_t st, int dt,
+                       GramColsArgs<CAP>& a, unsigned& finish_blocks) {
+    if (n_layers < 1 || n_layers > CAP || dt < 0 || dt > 2) return hipErrorInvalidValue;
     a.part = ws; a.n_layers = n_layers;
     const int step = dt == 0 ? 8 : 16;
     const int kind = cols_launch_kind(layers, n_layers, dt);
     int64_t blocks = 0, finish = 0;
     size_t off = 0;
-    GramColsPlan plans[kGramColsLayers];
+    int nb = 1;
+    GramColsPlan plans[CAP];
     plan_cols_shared(layers, n_layers, B, dt, max_floats, plans);
     for (int l = 0; l < n_layers; ++l) {
         const GramLayerDesc& y = layers[l];
@@ -482,27 +500,53 @@ hipError_t launch_cols(const GramLayerDesc* layers, float* const* sums, int n_la
         blocks += (int64_t)B * p.W;
         finish += (int64_t)B * gram_cols_sums(p);
         off += p.ws_floats;
+        nb = nb > p.nb ? nb : p.nb;
     }
-    for (int l = n_layers; l < kGramColsLayers; ++l) a.layer[l] = a.layer[0];
+    for (int l = n_layers; l < CAP; ++l) a.layer[l] = a.layer[0];
     if (blocks >= (int64_t(1) << 24) || finish >= (int64_t(1) << 24)) return hipErrorInvalidValue;   // (W >= 2 only where B < 2^9)
     finish_blocks = (unsigned)finish;
+    // where a workgroup's shares meet: two waves' sums of both products, the tiles of one 32-row block or of two
+    const int meet = nb == 1 ? 16384 : 3 * 16384;
     // Rows that are no whole 16-byte pieces are loaded to registers: what hides their many short loads is the number of
     // workgroups (with the copied layers in one launch, two per compute unit, two layers of 64 examples lost half: 20 positions,
-    // 662 -> 600, and 41, 367 -> 3519, 49 and 104 us).
-    if (kind == 1)      k_gram_cols_loads<1><<<(unsigned)blocks, kThreads, 0, st>>>(a);
-    else if (kind == 2) k_gram_cols_loads<2><<<(unsigned)blocks, kThreads, 0, st>>>(a);
-    else if (dt == 0)   k_gram_cols<0><<<(unsigned)blocks, kThreads, 0, st>>>(a);
-    else if (dt == 1)   k_gram_cols<1><<<(unsigned)blocks, kThreads, 0, st>>>(a);
-    else                k_gram_cols<2><<<(unsigned)blocks, kThreads, 0, st>>>(a);
+    // 662 -> 600, and 41, 367 -> 3519, 49 and 104 us).  So is a float32 layer alone where three workgroups of 48 KB fill the
+    // chip and two of 64 KB would leave a second round (174 examples of 64 positions, 1456 -> 528: 41 and 46 us; 16 bits, half
+    // the products, gain from whole lines there too).
+    if (kind != 0 || (CAP == 1 && dt == 0 && layers[0].T > 48 && blocks > 512 && blocks <= 768)) {
+        if (nb == 1) k_gram_cols_loads<1, CAP><<<(unsigned)blocks, kThreads, (size_t)meet, st>>>(a);
+        else         k_gram_cols_loads<2, CAP><<<(unsigned)blocks, kThreads, (size_t)meet, st>>>(a);
+        return hipGetLastError();
+    }
+    a.stages = kStages1; a.wave_lds = kWaveLds;
+    if constexpr (CAP == 1) {
+        // fewer stages in flight where a compute unit has more than two workgroups
+        const int stage = ceil_div(layers[0].T, 8) * 1024, per_cu = (int)((blocks + 255) / 256);
+        while (a.stages > 2 && std::max(meet, 4 * a.stages * stage) * per_cu > 160 * 1024) --a.stages;
+        a.wave_lds = (nb == 1 ? a.stages : kStages2) * stage;
+    }
+    const size_t lds = (size_t)std::max(meet, 4 * a.wave_lds);
+    if constexpr (CAP == 1) { if (nb == 1) { launch_cols_copied<1, CAP>((unsigned)blocks, lds, st, dt, a); return hipGetLastError(); } }
+    launch_cols_copied<2, CAP>((unsigned)blocks, lds, st, dt, a);
+    return hipGetLastError();
+}
+
+template <int CAP>
+hipError_t launch_cols_norms(const GramLayerDesc* layers, int n_layers, int B, bool accumulate, float* sqnorm, float* ws, size_t max_floats, hipStream_t st,
+                             int dt, const ClipOut* co) {
+    GramColsArgs<CAP> a;
+    unsigned finish = 0;
+    const hipError_t e = launch_cols<CAP>(layers, nullptr, n_layers, B, ws, max_floats, st, dt, a, finish);
+    if (e != hipSuccess) return e;
+    k_gram_cols_finish<CAP><<<B, kFinishThreads, 0, st>>>(a, accumulate ? 1 : 0, sqnorm, co ? co->C : 0.f, co ? co->clip : nullptr);
     return hipGetLastError();
 }
 }  // namespace
 
 hipError_t launch_gram_cols_layers(const GramLayerDesc* layers, float* const* sums, int n_layers, int B, float* ws, size_t max_floats,
                                    hipStream_t st, int dt) {
-    GramColsArgs a;
+    GramColsArgs<kGramColsLayers> a;
     unsigned finish = 0;
-    const hipError_t e = launch_cols(layers, sums, n_layers, B, ws, max_floats, st, dt, a, finish);
+    const hipError_t e = launch_cols<kGramColsLayers>(layers, sums, n_layers, B, ws, max_floats, st, dt, a, finish);
     if (e != hipSuccess) return e;
     k_gram_cols_sums<<<finish, kThreads, 0, st>>>(a);
     return hipGetLastError();
@@ -510,12 +554,8 @@ hipError_t launch_gram_cols_layers(const GramLayerDesc* layers, float* const* su
 
 hipError_t launch_gram_cols_norms(const GramLayerDesc* layers, int n_layers, int B, bool accumulate, float* sqnorm, float* ws, size_t max_floats,
                                   hipStream_t st, int dt, const ClipOut* co) {
-    GramColsArgs a;
-    unsigned finish = 0;
-    const hipError_t e = launch_cols(layers, nullptr, n_layers, B, ws, max_floats, st, dt, a, finish);
-    if (e != hipSuccess) return e;
-    k_gram_cols_finish<<<B, kFinishThreads, 0, st>>>(a, accumulate ? 1 : 0, sqnorm, co ? co->C : 0.f, co ? co->clip : nullptr);
-    return hipGetLastError();
+    if (n_layers == 1) return launch_cols_norms<1>(layers, 1, B, accumulate, sqnorm, ws, max_floats, st, dt, co);
+    return launch_cols_norms<kGramColsLayers>(layers, n_layers, B, accumulate, sqnorm, ws, max_floats, st, dt, co);
 }
 
 hipError_t launch_gram_cols(const GramColsPlan& p, const void* A, const void* G, int B, int T, int d_in, int d_out,

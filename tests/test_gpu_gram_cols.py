@@ -122,3 +122,16 @@ def test_float32_rows_of_any_length_beside_others(B, shapes, others):
     # float32 sums over at most 4586 columns of products of random sign
     assert float(((s.double() - ref) / ref).abs().max()) < 1e-5
     assert bool((ws[need:] == 7).all())                     # nothing behind the scratch that was asked for
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16, torch.float16])
+@pytest.mark.parametrize("B,T,a,b", [
+    (60, 8, 5312, 2048), (100, 20, 1456, 528), (300, 32, 712, 504), (500, 25, 712, 504), (511, 31, 712, 504),      # one 32-row block: two to four workgroups
+    (300, 40, 1456, 528), (192, 48, 1216, 440), (174, 64, 1456, 528), (130, 49, 712, 504), (256, 64, 1456, 528)])  # two: two or three, copied or loaded
+def test_layers_alone_with_many_workgroups(dtype, B, T, a, b):
+    gen = torch.Generator(device="cuda").manual_seed(B)
+    A, G = _tensor(gen, B, T, a, dtype), _tensor(gen, B, T, b, dtype)
+    ref = _norm64(A, G)
+    s = dp.layer_sqnorm(A, G, path="gram")
+    # float32 sums over at most 5312 columns of products of random sign
+    assert float(((s.double() - ref) / ref).abs().max()) < 1e-5
