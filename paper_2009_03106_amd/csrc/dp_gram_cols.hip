@@ -67,39 +67,43 @@ __device__ __forceinline__ void wait_copies(int n) {
 }
 
 // acc[tile] += X[rows of block b0] . X[rows of block b1]^T for one step, a 16-byte piece per lane and block; tiles in the
-// order (0,0), (0,1), (1,1) for two 32-row blocks.
-template <int NB, int DT>
+// order (0,0), (0,1), (1,1) for two 32-row blocks.  FIRST: acc starts from zero.
+template <int NB, int DT, bool FIRST = false>
 __device__ __forceinline__ void gram_cols_mfma(const uint4 (&f)[NB], f32x16 (&acc)[NB * (NB + 1) / 2]) {
+    constexpr f32x16 zero = {};
     if constexpr (DT == 0) {
         const float a0[4] = {__uint_as_float(f[0].x), __uint_as_float(f[0].y), __uint_as_float(f[0].z), __uint_as_float(f[0].w)};
 #pragma unroll
-        for (int e = 0; e < 4; ++e) acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0[e], a0[e], acc[0], 0, 0, 0);
+        for (int e = 0; e < 4; ++e) acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0[e], a0[e], FIRST && e == 0 ? zero : acc[0], 0, 0, 0);
         if constexpr (NB == 2) {
             const float a1[4] = {__uint_as_float(f[1].x), __uint_as_float(f[1].y), __uint_as_float(f[1].z), __uint_as_float(f[1].w)};
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0[e], a1[e], acc[1], 0, 0, 0);
-                acc[2] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1[e], a1[e], acc[2], 0, 0, 0);
+                acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0[e], a1[e], FIRST && e == 0 ? zero : acc[1], 0, 0, 0);
+                acc[2] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1[e], a1[e], FIRST && e == 0 ? zero : acc[2], 0, 0, 0);
             }
         }
     } else {
         constexpr bool F16 = DT == 2;
         const bf16x8 f0 = __builtin_bit_cast(bf16x8, f[0]);
-        acc[0] = In16<F16>::mfma(f0, f0, acc[0]);
+        acc[0] = In16<F16>::mfma(f0, f0, FIRST ? zero : acc[0]);
         if constexpr (NB == 2) {
             const bf16x8 f1 = __builtin_bit_cast(bf16x8, f[1]);
-            acc[1] = In16<F16>::mfma(f0, f1, acc[1]);
-            acc[2] = In16<F16>::mfma(f1, f1, acc[2]);
+            acc[1] = In16<F16>::mfma(f0, f1, FIRST ? zero : acc[1]);
+            acc[2] = In16<F16>::mfma(f1, f1, FIRST ? zero : acc[2]);
         }
     }
 }
 
 // The steps [kb, ke) of X (an example's T rows of `row_bytes` bytes, a multiple of 16), copied through `nst` stages of LDS at
 // `lds`.  Rows >= T and pieces past the end of a row count as zero: they are copied from valid addresses, or not at all, and
-// zeroed when they are read.
-template <int NB, int DT>
+// zeroed when they are read.  TWO: the instruction's own sums are of at most kColsSteps steps, and are added up outside it:
+// over waves as long as a shared launch has them its roundings go to one side (bf16, three layers of 16 positions, 4608 -> 512,
+// and three of 64, 2304 -> 256: norms 7.8e-8 off in the mean, 1.1e-7 rms; so 6e-9 and 4.5e-8, for 4 % of the time).
+template <int NB, int DT, bool TWO>
 __device__ __forceinline__ void gram_cols_run(const unsigned char* __restrict__ X, int T, int row_bytes, int kb, int ke, int lane,
-                                              unsigned char* lds, int nst, f32x16 (&acc)[NB * (NB + 1) / 2]) {
+                                              unsigned char* lds, int nst, f32x16 (&total)[NB * (NB + 1) / 2]) {
+    constexpr int NT = NB * (NB + 1) / 2;
     constexpr int COPIES = NB * 4;                       // copy instructions of a whole stage, 8 rows each
     const int n_stages = (ke - kb + kStageSteps - 1) / kStageSteps;
     const int copies = min(COPIES, (T + 7) / 8);         // those with rows inside the example
@@ -133,6 +137,7 @@ __device__ __forceinline__ void gram_cols_run(const unsigned char* __restrict__ 
         in[b] = b * 32 + row < T;
         rd[b] = (uint32_t)(r * 128 + ((half ^ ((r >> 1) & 7)) << 4));
     }
+    f32x16 chain[TWO ? NT : 1];
     for (int p = 0; p < nst; ++p)
         if (p < n_stages) issue(p);
     int buf = 0;
@@ -157,7 +162,16 @@ __device__ __forceinline__ void gram_cols_run(const unsigned char* __restrict__ 
                 const bool keep = in[b] && (k + u) * 32 + half * 16 < row_bytes;
                 g[b] = make_uint4(keep ? f[u][b].x : 0u, keep ? f[u][b].y : 0u, keep ? f[u][b].z : 0u, keep ? f[u][b].w : 0u);
             }
-            gram_cols_mfma<NB, DT>(g, acc);
+            if constexpr (!TWO)            gram_cols_mfma<NB, DT>(g, total);
+            else if (u == 0 && !(st & 1))  gram_cols_mfma<NB, DT, true>(g, chain);
+            else                           gram_cols_mfma<NB, DT>(g, chain);
+        }
+        if constexpr (TWO) {
+            static_assert(kColsSteps == 2 * kStageSteps, "");
+            if ((st & 1) || st + 1 == n_stages) {
+#pragma unroll
+                for (int t = 0; t < NT; ++t) total[t] += chain[t];
+            }
         }
     }
 }
@@ -260,13 +274,13 @@ __device__ __forceinline__ void gram_cols_block(const GramColsLayer& a, int item
     }
 }
 
-template <int NB, int DT, int CAP>
+template <int NB, int DT, bool TWO, int CAP>
 __device__ __forceinline__ void gram_cols_copied(const GramColsLayer& a, const GramColsArgs<CAP>& j, unsigned char* lds) {
     constexpr int ES = DT == 0 ? 4 : 2;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     gram_cols_block<NB>(a, blockIdx.x - a.first_block, j.part, lds,
         [&](const void* X, size_t ex, int D, int kb, int ke, f32x16 (&acc)[NB * (NB + 1) / 2]) {
-            gram_cols_run<NB, DT>(static_cast<const unsigned char*>(X) + ex * a.T * D * ES, a.T, D * ES, kb, ke, lane,
+            gram_cols_run<NB, DT, TWO>(static_cast<const unsigned char*>(X) + ex * a.T * D * ES, a.T, D * ES, kb, ke, lane,
                                        lds + wave * j.wave_lds, NB == 1 ? j.stages : kStages2, acc);
         });
 }
@@ -282,10 +296,10 @@ __global__ __launch_bounds__(kThreads, CAP == 1 ? 3 : 2) void k_gram_cols(GramCo
     while (li + 1 < j.n_layers && blockIdx.x >= j.layer[li + 1].first_block) ++li;
     const GramColsLayer& a = j.layer[li];
     if constexpr (CAP == 1) {
-        gram_cols_copied<NB, DT>(a, j, lds);
+        gram_cols_copied<NB, DT, false>(a, j, lds);
     } else {
-        if (NB == 1 || a.nb == 1) gram_cols_copied<1, DT>(a, j, lds);
-        else                      gram_cols_copied<NB, DT>(a, j, lds);
+        if (NB == 1 || a.nb == 1) gram_cols_copied<1, DT, true>(a, j, lds);
+        else                      gram_cols_copied<NB, DT, true>(a, j, lds);
     }
 }
 
@@ -368,10 +382,10 @@ __global__ __launch_bounds__(kFinishThreads) void k_gram_cols_finish(GramColsArg
     s = wave_sum(s);
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
     __syncthreads();
+    if (threadIdx.x >= 64) return;
+    // (in a tree: one after the other these additions were most of a norm's error)
+    const float v = wave_sum(threadIdx.x < kFinishThreads / 64 ? red[threadIdx.x] : 0.f);
     if (threadIdx.x == 0) {
-        float v = 0.f;
-#pragma unroll
-        for (int i = 0; i < kFinishThreads / 64; ++i) v += red[i];
         const float t = accumulate ? sqnorm[ex] + v : v;
         sqnorm[ex] = t;
         if (clip) clip[ex] = clip_factor_of(t, C);
