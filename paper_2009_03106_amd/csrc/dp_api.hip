@@ -110,6 +110,37 @@ size_t clipped_ws_bytes(int64_t B, int64_t T, int64_t d_in, int64_t d_out, dp_dt
     return head + (size_t)p.splits * (size_t)splitk_slice_elems(d_in * d_out) * sizeof(float);
 }
 
+// A launch holds fewer than 2^32 threads, and drops the workgroups beyond without an error.  The norm kernels have up to 1024
+// threads a workgroup and one or more workgroups per example and sum, so a call of more than this many sums for a layer
+// goes in equal pieces of examples.
+constexpr int64_t kNormSums = (int64_t(1) << 22) - 16;
+// sums per example that a layer's norm kernel writes
+int64_t norm_sums(int64_t B, int64_t T, int64_t d_in, int64_t d_out, dp_dtype dtype, dp_path path) {
+    if (T <= 1 || d_in == 0 || d_out == 0) return 1;
+    const dp_dtype dt = is8(dtype) && !f8_fast_sqnorm(dtype, path, T, d_in, d_out) ? DP_F16 : dtype;      // (as it is widened)
+    if (resolve_path(path, dt, T, d_in, d_out) == DP_PATH_GRAM)
+        return dt == DP_F32 ? gram_f32_sums((int)T) : plan_gram_bf16((int)T, (int)d_in, (int)d_out).npairs;
+    const TnPlan p = is8(dt)  ? plan_direct_f8_dma((int)B, (int)T, (int)d_in, (int)d_out)
+                   : is16(dt) ? plan_direct_bf16((int)B, (int)T, (int)d_in, (int)d_out)
+                              : plan_direct_f32((int)B, (int)T, (int)d_in, (int)d_out);
+    return (int64_t)p.tiles_m * p.tiles_n;
+}
+// examples of a piece for such a layer, a multiple of 16 (every piece starts on a 16-byte boundary); B where one call holds them
+int64_t piece_examples(int64_t B, int64_t T, int64_t d_in, int64_t d_out, dp_dtype dtype, dp_path path) {
+    // (more sums than any kernel's tiles make, without a look at its plan)
+    const double pairs = (double)(T / 32 + 1) * (double)(T / 32 + 1), tiles = (double)(d_in / 32 + 1) * (double)(d_out / 32 + 1);
+    if ((double)B * (T <= 1 ? 1.0 : std::max(pairs, tiles)) <= (double)kNormSums) return B;
+    const int64_t sums = norm_sums(B, T, d_in, d_out, dtype, path);
+    const int64_t pieces = (B * sums + kNormSums - 1) / kNormSums;
+    return pieces <= 1 ? B : std::min(B, ((B + pieces - 1) / pieces + 15) & ~int64_t(15));
+}
+int64_t layers_piece_examples(const dp_layer_desc* layers, int64_t n_layers, int64_t B, dp_dtype dtype, dp_path path) {
+    int64_t piece = B;
+    for (int64_t l = 0; B > 0 && l < n_layers; ++l) piece = std::min(piece, piece_examples(B, layers[l].T, layers[l].d_in, layers[l].d_out, dtype, path));
+    return piece;
+}
+size_t elem_bytes(dp_dtype d) { return d == DP_F32 ? 4 : is16(d) ? 2 : 1; }
+
 // a layer that the batched Gram launch of dp_layers_sqnorm takes (everything else goes through dp_layer_sqnorm)
 bool gram_batchable(int64_t T, int64_t d_in, int64_t d_out, dp_dtype dtype, dp_path path) {
     if (T <= 1 || d_in == 0 || d_out == 0 || !(is16(dtype) || is8(dtype))) return false;
@@ -305,7 +336,11 @@ size_t dp_workspace_bytes(dp_op op, int64_t B, int64_t T, int64_t d_in, int64_t 
     if (op == DP_OP_SQNORM) {
         if (T == 1) return 0;
         const dp_path p = resolve_path(path, dtype, T, d_in, d_out);
-        return sqnorm_ws_bytes(B, T, d_in, d_out, dtype, p);
+        const int64_t piece = piece_examples(B, T, d_in, d_out, dtype, path);
+        size_t need = sqnorm_ws_bytes(B, T, d_in, d_out, dtype, p);
+        if (piece < B)
+            need = std::max({need, sqnorm_ws_bytes(piece, T, d_in, d_out, dtype, p), sqnorm_ws_bytes(B - (B - 1) / piece * piece, T, d_in, d_out, dtype, p)});
+        return need;
     }
     if (op == DP_OP_CLIPPED_GRAD) return clipped_ws_bytes(B, T, d_in, d_out, dtype);
     return 0;
@@ -374,7 +409,19 @@ dp_status layer_sqnorm_clip(const void* A, const void* G, int64_t B, int64_t T, 
         return layer_sqnorm_clip(w, w + na, B, T, d_in, d_out, DP_F16, path, accumulate, sqnorm, w + na + ng,
                                  workspace_bytes - na - ng, hip_stream, co);
     }
+    const int64_t piece = piece_examples(B, T, d_in, d_out, dtype, path);
+    auto in_pieces = [&]() -> dp_status {
+        for (int64_t b0 = 0; piece < B && b0 < B; b0 += piece) {
+            const ClipOut c{co ? co->C : 0.f, co && co->clip ? co->clip + b0 : nullptr};
+            const dp_status s1 = layer_sqnorm_clip(static_cast<const char*>(A) + (size_t)(b0 * T * d_in) * elem_bytes(dtype),
+                                                   static_cast<const char*>(G) + (size_t)(b0 * T * d_out) * elem_bytes(dtype), std::min(piece, B - b0), T, d_in, d_out,
+                                                   dtype, path, accumulate, sqnorm + b0, workspace, workspace_bytes, hip_stream, co ? &c : nullptr);
+            if (s1 != DP_OK) return s1;
+        }
+        return DP_OK;
+    };
     if (T == 1) {
+        if (piece < B) return in_pieces();
         e = launch_sqnorm_dense(A, G, (int)B, (int)d_in, (int)d_out, (int)dtype, accumulate != 0, sqnorm, stream, co);
         return e == hipSuccess ? DP_OK : DP_ERR_HIP;
     }
@@ -382,6 +429,8 @@ dp_status layer_sqnorm_clip(const void* A, const void* G, int64_t B, int64_t T, 
     const size_t need = sqnorm_ws_bytes(B, T, d_in, d_out, dtype, p);
     if (need >= (size_t(1) << 33)) return DP_ERR_UNSUPPORTED;           // > 2^31 partial sums
     if (!workspace || workspace_bytes < need || !aligned16(workspace)) return DP_ERR_WORKSPACE;
+    const dp_status sp = in_pieces();
+    if (sp != DP_OK || piece < B) return sp;
     float* partial = static_cast<float*>(workspace);
 
     if (is8(dtype)) {
@@ -751,6 +800,9 @@ dp_status layers_sqnorm_grouped(const dp_layer_desc* layers, int64_t n_layers, i
 
 // scratch: the layers that run one by one reuse one region, and so do the batched launches
 size_t layers_ws_bytes(const dp_layer_desc* layers, int64_t n_layers, int64_t B, dp_dtype dtype, dp_path path) {
+    const int64_t piece = layers_piece_examples(layers, n_layers, B, dtype, path);
+    if (piece < B)
+        return std::max(layers_ws_bytes(layers, n_layers, piece, dtype, path), layers_ws_bytes(layers, n_layers, B - (B - 1) / piece * piece, dtype, path));
     size_t single = 0, single_sum = 0, batch = 0, batch_max = 0;
     int in_batch = 0;
     for (int64_t l = 0; l < n_layers; ++l) {
@@ -814,6 +866,27 @@ dp_status dp_layers_sqnorm_clip(const dp_layer_desc* layers, int64_t n_layers, i
     if (st != DP_OK) return st;
     if (clip && !(C > 0.0f)) return DP_ERR_INVALID_ARG;
     if (B == 0) return DP_OK;
+    const int64_t piece = layers_piece_examples(layers, n_layers, B, dtype, path);
+    if (piece < B) {
+        const size_t need = layers_ws_bytes(layers, n_layers, B, dtype, path);
+        if (need > 0 && (!workspace || workspace_bytes < need || !aligned16(workspace))) return DP_ERR_WORKSPACE;
+        std::vector<dp_layer_desc> part((size_t)n_layers);
+        for (int64_t b0 = 0; b0 < B; b0 += piece) {
+            for (int64_t l = 0; l < n_layers; ++l) {
+                dp_layer_desc y = layers[l];
+                auto at = [&](const void* p, int64_t d) { return p ? static_cast<const char*>(p) + (size_t)(b0 * y.T * d) * elem_bytes(dtype) : nullptr; };
+                y.A = at(y.A, y.d_in); y.G = at(y.G, y.d_out);
+                if (y.bias_rows) y.bias_rows += b0 * y.d_out;
+                if (y.sqnorm) y.sqnorm += b0;
+                if (y.clip) y.clip += b0;
+                part[(size_t)l] = y;
+            }
+            const dp_status s1 = dp_layers_sqnorm_clip(part.data(), n_layers, std::min(piece, B - b0), dtype, path, accumulate, sqnorm ? sqnorm + b0 : nullptr, C,
+                                                       clip ? clip + b0 : nullptr, workspace, workspace_bytes, hip_stream);
+            if (s1 != DP_OK) return s1;
+        }
+        return DP_OK;
+    }
     for (int64_t l = 0; l < n_layers; ++l)
         if (layers[l].sqnorm)
             return layers_sqnorm_grouped(layers, n_layers, B, dtype, path, accumulate, sqnorm, C, clip, workspace, workspace_bytes, hip_stream);
@@ -1126,11 +1199,14 @@ dp_status dp_layers_sqnorm_clip(const dp_layer_desc* layers, int64_t n_layers, i
         nb = 0; acc = 1; launched = true;
         return e;
     };
+    int64_t batch_sums = 0;                                  // workgroups of the launch so far
     for (int64_t l = 0; l < n_layers; ++l) {
         const dp_layer_desc& y = layers[l];
         if (y.T == 0 || y.d_in == 0 || y.d_out == 0) continue;
         if (!gram_batchable(y.T, y.d_in, y.d_out, dtype, path)) continue;
-        if (nb == kGramBatch && flush(false) != hipSuccess) return DP_ERR_HIP;       // full, and another layer follows
+        const int64_t sums = B * plan_gram_bf16((int)y.T, (int)y.d_in, (int)y.d_out).npairs;
+        if ((nb == kGramBatch || (nb > 0 && batch_sums + sums > kJointItems)) && flush(false) != hipSuccess) return DP_ERR_HIP;   // full, and another layer follows
+        batch_sums = nb > 0 ? batch_sums + sums : sums;
         batch[nb++] = GramLayerDesc{y.A, y.G, (int)y.T, (int)y.d_in, (int)y.d_out, nullptr, is8(dtype) ? nullptr : y.bias_rows};
     }
     const bool clip_done = clip != nullptr && (nb > 0 || clip_with_single || clip_with_dense || clip_with_cols);
@@ -1239,11 +1315,14 @@ dp_status layers_sqnorm_grouped(const dp_layer_desc* layers, int64_t n_layers, i
         nb = 0;
         return e;
     };
+    int64_t batch_sums = 0;                                  // workgroups of the launch so far
     for (int64_t l = 0; l < n_layers; ++l) {
         const dp_layer_desc& y = layers[l];
         if (y.T == 0 || y.d_in == 0 || y.d_out == 0) continue;
         if (!gram_batchable(y.T, y.d_in, y.d_out, dtype, path)) continue;
-        if (nb == kGramBatch && flush() != hipSuccess) return DP_ERR_HIP;
+        const int64_t sums = B * plan_gram_bf16((int)y.T, (int)y.d_in, (int)y.d_out).npairs;
+        if ((nb == kGramBatch || (nb > 0 && batch_sums + sums > kJointItems)) && flush() != hipSuccess) return DP_ERR_HIP;
+        batch_sums = nb > 0 ? batch_sums + sums : sums;
         batch_group[nb] = group_of[l];
         batch[nb++] = GramLayerDesc{y.A, y.G, (int)y.T, (int)y.d_in, (int)y.d_out, nullptr, is8(dtype) ? nullptr : y.bias_rows};
     }

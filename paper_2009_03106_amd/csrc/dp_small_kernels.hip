@@ -318,7 +318,7 @@ __global__ __launch_bounds__(256) void k_finalize_queue(FinalizeQueue q, int acc
 }
 
 hipError_t launch_finalize_queue(const FinalizeQueue& q, int B, bool accumulate, float* sqnorm, hipStream_t st, const ClipOut* co) {
-    if (q.count < 1 || q.count > FinalizeQueue::kMax || B < 1) return hipErrorInvalidValue;
+    if (q.count < 1 || q.count > FinalizeQueue::kMax || B < 1 || B >= 1 << 24) return hipErrorInvalidValue;      // (a launch holds 2^32 threads)
     k_finalize_queue<<<(unsigned)B, 256, 0, st>>>(q, accumulate ? 1 : 0, sqnorm, co ? co->C : 0.f, co ? co->clip : nullptr);
     return hipGetLastError();
 }
