@@ -426,63 +426,79 @@ struct Joint8Args {
     int n_layers, n_items, n_groups, per_xcd, B;      // n_items: workgroups with one item; n_groups: all
 };
 
-// One launch of at most 256 workgroups, each of about the same number of stages: a layer's K range is cut into slices of one
+// Whole rounds of 256 workgroups, each of about the same number of stages: a layer's K range is cut into slices of one
 // length L and a shorter rest, a workgroup takes one slice of L stages or the rests of several tiles one after the other.
-// Few partial tiles to store and to fold, one start-up per compute unit: 108 tiles of 512 stages take 2 slices of 221
-// stages and a rest of 70, three rests to a workgroup, 252 workgroups, where equal slices take 7 of 74, three rounds.
+// Few partial tiles to store and to fold, few start-ups: 108 tiles of 512 stages take 2 slices of 224 stages and a rest
+// of 64, three rests to a workgroup, 252 workgroups, where equal slices take 7 of 74, three rounds.
 // (64 examples of 512 x (768, 2304), (768, 768), (768, 3072), (3072, 768): step 393 -> 346 us.)
 // (The 16-bit sums keep the shorter slices: their error grows with the square root of the slice, 4.4e-7 of the result at
 // 147 stages, 6.7e-7 at 341; that of the 8-bit sums is the instruction's own, 1.06e-5 in both cases.)
 struct TwoLengths { bool use; int sps[kJointLayers], splits[kJointLayers], longs[kJointLayers], pack[kJointLayers]; int items, groups; };
 TwoLengths plan_two_lengths(const JointShape* sh, int n_layers, int B, const JointPlan& equal) {
     constexpr int64_t kItem = 16;                            // what an item costs besides its stages, in stages
+    // layers of one T are cut alike: this loop is host time of every call
+    struct Same { int64_t spe, stages, tiles; size_t slice; int sps, longs, splits, pack; };
+    Same same[kJointLayers], at_best[kJointLayers];
+    int n_same = 0, of[kJointLayers], tiles[kJointLayers];
     // cost of the equal slices and of these, in stages: the rounds and the fold (4 MB in about one)
     size_t floats_equal = 0;
     int longest = 0;
+    int64_t stages_max = 1;
     for (int l = 0; l < n_layers; ++l) {
-        floats_equal += (size_t)equal.splits[l] * (size_t)splitk_slice_elems((int64_t)sh[l].M * sh[l].N);
-        longest = longest > equal.sps[l] ? longest : equal.sps[l];
+        const int64_t spe = sh[l].T / DK8;
+        int k = 0;
+        while (k < n_same && same[k].spe != spe) ++k;
+        if (k == n_same) same[n_same++] = Same{spe, (int64_t)B * spe, 0, 0, 0, 0, 0, 0};
+        const size_t slice = (size_t)splitk_slice_elems((int64_t)sh[l].M * sh[l].N);
+        of[l] = k;
+        tiles[l] = equal.tiles_m[l] * equal.tiles_n[l];
+        same[k].tiles += tiles[l]; same[k].slice += slice;
+        floats_equal += (size_t)equal.splits[l] * slice;
+        longest = std::max(longest, equal.sps[l]);
+        stages_max = std::max(stages_max, same[k].stages);
     }
     int64_t best_cost = (((equal.items + 255) / 256) * (longest + kItem) + (int64_t)(floats_equal >> 20)) * 31 / 32;
     TwoLengths best{};
-    int64_t stages_max = 1;
-    for (int l = 0; l < n_layers; ++l) {
-        const int64_t stages = (int64_t)B * (sh[l].T / DK8);
-        stages_max = stages_max > stages ? stages_max : stages;
-    }
     for (int n = 1; n <= 8; ++n)
         for (int pk = 1; pk <= 8; ++pk) {
             // n slices of L and a rest r of which pk fill a workgroup: n L + r = stages_max, pk (r + kItem) = L + kItem
             const int64_t L = (pk * (stages_max + kItem) - kItem + (int64_t)n * pk) / ((int64_t)n * pk + 1);
             if (L < 16) continue;
-            TwoLengths p{};
             int64_t items = 0, packs = 0, most = 0;
             size_t floats = 0;
-            for (int l = 0; l < n_layers; ++l) {
-                const int64_t spe = sh[l].T / DK8, stages = (int64_t)B * spe, tiles = (int64_t)equal.tiles_m[l] * equal.tiles_n[l];
-                const int64_t len = L < 63 * spe ? L : 63 * spe;            // at most 64 examples in a slice
-                int64_t longs = stages / len, rest = stages - longs * len, sps = len;
+            for (int k = 0; k < n_same; ++k) {
+                Same& y = same[k];
+                const int64_t len = L < 63 * y.spe ? L : 63 * y.spe;       // at most 64 examples in a slice
+                int64_t longs = y.stages / len, rest = y.stages - longs * len, sps = len;
                 if (longs == 0 || rest < 8) {                              // no rest worth an item: equal slices
                     longs = longs == 0 ? 1 : longs;
-                    sps = (stages + longs - 1) / longs;
-                    if (sps > 63 * spe) { ++longs; sps = (stages + longs - 1) / longs; }
-                    longs = (stages + sps - 1) / sps;
+                    sps = (y.stages + longs - 1) / longs;
+                    if (sps > 63 * y.spe) { ++longs; sps = (y.stages + longs - 1) / longs; }
+                    longs = (y.stages + sps - 1) / sps;
                     rest = 0;
                 }
-                p.sps[l] = (int)sps; p.longs[l] = (int)longs; p.splits[l] = (int)longs + (rest > 0 ? 1 : 0);
-                p.pack[l] = rest > 0 ? (int)std::max<int64_t>(1, (L + kItem) / (rest + kItem)) : 0;
-                items += tiles * longs;
-                most = std::max(most, sps + kItem);
-                if (rest > 0) {
-                    packs += (tiles + p.pack[l] - 1) / p.pack[l];
-                    most = std::max(most, (int64_t)p.pack[l] * (rest + kItem));
-                }
-                floats += (size_t)p.splits[l] * (size_t)splitk_slice_elems((int64_t)sh[l].M * sh[l].N);
+                y.sps = (int)sps; y.longs = (int)longs; y.splits = (int)longs + (rest > 0 ? 1 : 0);
+                y.pack = rest > 0 ? (int)std::max<int64_t>(1, (L + kItem) / (rest + kItem)) : 0;
+                items += y.tiles * longs;
+                floats += (size_t)y.splits * y.slice;
+                most = std::max({most, sps + kItem, (int64_t)y.pack * (rest + kItem)});
             }
             if (floats > floats_equal) continue;                           // (the scratch is the equal slices')
+            for (int l = 0; l < n_layers; ++l) {
+                const int pack = same[of[l]].pack;
+                if (pack > 0) packs += (tiles[l] + pack - 1) / pack;
+            }
             const int64_t cost = ((items + packs + 255) / 256) * most + (int64_t)(floats >> 20);
-            if (cost < best_cost) { best_cost = cost; best = p; best.use = true; best.items = (int)items; best.groups = (int)(items + packs); }
+            if (cost < best_cost) {
+                best_cost = cost;
+                best.use = true; best.items = (int)items; best.groups = (int)(items + packs);
+                std::copy(same, same + n_same, at_best);
+            }
         }
+    for (int l = 0; best.use && l < n_layers; ++l) {
+        const Same& y = at_best[of[l]];
+        best.sps[l] = y.sps; best.splits[l] = y.splits; best.longs[l] = y.longs; best.pack[l] = y.pack;
+    }
     return best;
 }
 
