@@ -1,7 +1,8 @@
 /*
  * dpclip_probes -- measurement probes that ship with libdpclip.so.
  *
- * They are not part of the method: each launches one small kernel that
+ * They are not part of the method: each but the two plan queries at the end
+ * launches one small kernel that
  * exercises a single unit of the MI355X the way the library's kernels use it,
  * so that a benchmark can quote the library's kernels against what this very
  * part sustains (next to the published peaks).  The caller times the launch
@@ -50,6 +51,18 @@ dp_status dp_probe_read(const void* src, size_t bytes, float* sink, void* hip_st
  *      chunk swizzle
  * *bytes receives the bytes that all lanes of the launch receive. */
 dp_status dp_probe_lds_read(int kind, int64_t iters, float* sink, double* bytes, void* hip_stream);
+
+/* Which form a several-layers call takes, by its shapes alone (host only; the
+ * layers' T, d_in, d_out and, for the first, bias_rows are read).  For tests of
+ * a form that only some shapes reach.
+ * dp_plan_gram_wide: 1 if the layers share one Gram launch of dp_layers_sqnorm
+ * and it takes pieces of 256 rows, 0 if it takes pairs of 128, -1 if they do
+ * not share one.
+ * dp_plan_sums_in_two_lengths: 8-bit layers that share one launch of
+ * dp_layers_clipped_grad: the workgroups of it that take several short slices
+ * one after the other (0: all slices are equal), -1 if they do not share one. */
+int dp_plan_gram_wide(const dp_layer_desc* layers, int64_t n_layers, int64_t B, dp_dtype dtype, dp_path path);
+int dp_plan_sums_in_two_lengths(const dp_layer_desc* layers, int64_t n_layers, int64_t B, dp_dtype dtype);
 
 #ifdef __cplusplus
 }

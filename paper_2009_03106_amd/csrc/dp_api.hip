@@ -2,6 +2,7 @@
 // choice, workspace carving and kernel launches.  No device allocation, no
 // synchronisation, no host reads of device memory.
 #include "../../include/dpclip.h"
+#include "../../include/dpclip_probes.h"
 #include "dp_internal.h"
 #include <algorithm>
 #include <mutex>
@@ -1551,6 +1552,30 @@ dp_status dp_layers_clipped_grad_noise(const dp_layer_desc* layers, int64_t n_la
         if (e != hipSuccess) return DP_ERR_HIP;
     }
     return DP_OK;
+}
+
+int dp_plan_gram_wide(const dp_layer_desc* layers, int64_t n_layers, int64_t B, dp_dtype dtype, dp_path path) {
+    if (check_layers(layers, n_layers, B, dtype, path, false, DP_OP_SQNORM) != DP_OK || B == 0 || n_layers < 1 || n_layers > kGramBatch) return -1;
+    if (layers_piece_examples(layers, n_layers, B, dtype, path) < B) return -1;
+    GramLayerDesc group[kGramBatch] = {};
+    for (int64_t l = 0; l < n_layers; ++l) {
+        const dp_layer_desc& y = layers[l];
+        if (!gram_batchable(y.T, y.d_in, y.d_out, dtype, path)) return -1;
+        if (y.bias_rows && !is8(dtype)) return 0;                  // column sums are wanted
+        group[l].T = (int)y.T; group[l].d_in = (int)y.d_in; group[l].d_out = (int)y.d_out;
+    }
+    return gram_wide(group, (int)n_layers, (int)B) ? 1 : 0;
+}
+
+int dp_plan_sums_in_two_lengths(const dp_layer_desc* layers, int64_t n_layers, int64_t B, dp_dtype dtype) {
+    if (check_layers(layers, n_layers, B, dtype, DP_PATH_DIRECT, false, DP_OP_CLIPPED_GRAD) != DP_OK || n_layers < 2 || n_layers > kJointLayers || !is8(dtype)) return -1;
+    JointShape sh[kJointLayers];
+    for (int64_t l = 0; l < n_layers; ++l) {
+        const dp_layer_desc& y = layers[l];
+        if (clipped_join_class(B, y.T, y.d_in, y.d_out, dtype) != 1) return -1;
+        sh[l] = JointShape{(int)y.T, (int)y.d_in, (int)y.d_out};
+    }
+    return joint8_rest_groups(sh, (int)n_layers, (int)B);
 }
 
 }  // extern "C"

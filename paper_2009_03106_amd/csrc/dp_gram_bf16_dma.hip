@@ -622,7 +622,7 @@ bool gram_dma_ok(int T, int d_in, int d_out, int fmt) {
 // pieces go over the chip 256 at a time, 66 us a round and 45 to 70 for a last one that is not full; the pairs 512 at a
 // time with a tail that the next ones fill.  64 examples of 512 positions: 70 and 95 us, 128: 148 and 175; 64 of 768
 // positions, whose pieces fill 2.25 rounds, 183 and 169.
-static bool gram_wide(const GramLayerDesc* layers, int n_layers, int B) {
+bool gram_wide(const GramLayerDesc* layers, int n_layers, int B) {
     int64_t items = 0, pairs = 0;
     for (int l = 0; l < n_layers; ++l) {
         if (layers[l].upart) return false;

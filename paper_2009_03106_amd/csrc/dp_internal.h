@@ -219,6 +219,7 @@ hipError_t launch_clipped_f32_split_joint(const JointShape* sh, const JointOpera
 // the same for 8-bit inputs (dp_tn_f8_dma.hip; 256 x 256 tiles, T a multiple of 64); A, G of JointOperands are byte pointers
 bool dma8_joint_ok(int T, int M, int N);
 size_t joint8_workspace_floats(const JointShape* sh, int n_layers, int B, size_t max_floats);
+int joint8_rest_groups(const JointShape* sh, int n_layers, int B);      // its workgroups that take several short slices (0: all slices are equal)
 hipError_t launch_clipped_f8_dma_joint(const JointShape* sh, const JointOperands* op, int n_layers, int B, bool accumulate,
                                        float stddev, uint64_t seed, float* ws, hipStream_t st, int fmt, size_t max_floats);
 // noise: stddev == 0 for none, else every layer's d_in * d_out and noise_offset are multiples of 4
@@ -293,6 +294,7 @@ hipError_t launch_gram_cols_norms(const GramLayerDesc* layers, int n_layers, int
                                   hipStream_t st, int dt, const ClipOut* co);
 hipError_t launch_gram_cols(const GramColsPlan& p, const void* A, const void* G, int B, int T, int d_in, int d_out,
                             bool accumulate, float* sqnorm, float* ws, hipStream_t st, int dt, const ClipOut* co = nullptr);
+bool gram_wide(const GramLayerDesc* layers, int n_layers, int B);      // whether that launch takes pieces of 256 rows
 hipError_t launch_gram_bf16_dma_layers(const GramLayerDesc* layers, int n_layers, int B, bool accumulate, float* sqnorm,
                                        float* partial, hipStream_t st, int fmt, float C = 0.f, float* clip = nullptr);
 hipError_t launch_gram_bf16_dma(const GramPlan& p, const void* A, const void* G, int B, int T, int d_in, int d_out,

@@ -646,6 +646,11 @@ size_t joint8_workspace_floats(const JointShape* sh, int n_layers, int B, size_t
     return slices;
 }
 
+int joint8_rest_groups(const JointShape* sh, int n_layers, int B) {
+    const TwoLengths two = plan_two_lengths(sh, n_layers, B, plan_joint(sh, n_layers, B, DK8, Geo8L::TM, 256, kAnySlices));
+    return two.use ? two.groups - two.items : 0;
+}
+
 hipError_t launch_clipped_f8_dma_joint(const JointShape* sh, const JointOperands* op, int n_layers, int B, bool accumulate,
                                        float stddev, uint64_t seed, float* ws, hipStream_t st, int fmt, size_t max_floats) {
     if (n_layers < 1 || n_layers > kJointLayers) return hipErrorInvalidValue;

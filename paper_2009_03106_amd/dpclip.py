@@ -27,8 +27,8 @@ EXPORTS = ("dp_layer_sqnorm", "dp_layer_sqnorm_static", "dp_layers_sqnorm", "dp_
            "dp_conv_sqnorm", "dp_conv_clipped_grad", "dp_conv_workspace_bytes", "dp_conv_rows_resident", "dp_add_noise", "dp_workspace_bytes", "dp_choose_path", "dp_status_string", "dp_philox_raw",
            "dp_clipped_grad_rounds_inputs")
 
-# the measurement probes of include/dpclip_probes.h
-PROBE_EXPORTS = ("dp_probe_mfma", "dp_probe_read", "dp_probe_lds_read")
+# the measurement probes and plan queries of include/dpclip_probes.h
+PROBE_EXPORTS = ("dp_probe_mfma", "dp_probe_read", "dp_probe_lds_read", "dp_plan_gram_wide", "dp_plan_sums_in_two_lengths")
 PROBE_SINK_FLOATS = 1024 * 256
 
 _lib = None
@@ -113,6 +113,10 @@ def load_library() -> ctypes.CDLL:
     lib.dp_probe_read.restype = ci
     lib.dp_probe_lds_read.argtypes = [ci, i64, vp, ctypes.POINTER(ctypes.c_double), vp]
     lib.dp_probe_lds_read.restype = ci
+    lib.dp_plan_gram_wide.argtypes = [ctypes.POINTER(LayerDesc), i64, i64, ci, ci]
+    lib.dp_plan_gram_wide.restype = ci
+    lib.dp_plan_sums_in_two_lengths.argtypes = [ctypes.POINTER(LayerDesc), i64, i64, ci]
+    lib.dp_plan_sums_in_two_lengths.restype = ci
     _lib = lib
     return lib
 

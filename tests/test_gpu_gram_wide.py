@@ -1,4 +1,5 @@
-"""Gram norms in pieces of 256 rows: launches that fill the chip with them, ragged last rows, layers of several lengths."""
+"""Gram norms in pieces of 256 rows: launches that fill the chip with them, ragged last rows, layers of several lengths (and some
+that do not fill it, on the pairs of 128)."""
 import pytest
 import torch
 
@@ -40,3 +41,43 @@ def test_norms_against_float64(types, step, tol, B, shapes):
     s2 = dp.layers_sqnorm(layers, torch.full((B,), 3.0, device="cuda"), path="gram", accumulate=True, C=C, clip=clip)
     assert float(((s2.double() - ref - 3.0) / ref).abs().max()) < tol
     assert torch.allclose(clip.double(), (C / (ref + 3.0).sqrt()).clamp(max=1.0), rtol=tol, atol=0)
+
+
+def _layers(gen, B, shapes, types, step):
+    layers = []
+    for T, a, b in shapes:
+        pair = []
+        for d, t in ((a * step, types[0]), (b * step, types[1])):
+            buf = torch.full((B * T * d + 2048,), float("nan"), device="cuda").to(t)       # nothing around the matrix may count
+            x = buf[1024:1024 + B * T * d].view(B, T, d)
+            x.copy_(torch.randn((B, T, d), device="cuda", generator=gen).to(t))
+            pair.append(x)
+        layers.append(tuple(pair))
+    return layers
+
+
+@pytest.mark.parametrize("types,step,tol", [((torch.bfloat16,) * 2, 64, 1e-5), ((torch.float16,) * 2, 64, 1e-5),
+                                            ((torch.float8_e4m3fn, torch.float8_e5m2), 128, 2e-4), ((torch.float8_e4m3fn,) * 2, 128, 2e-4)])
+@pytest.mark.parametrize("B,shapes", [
+    (25, [(512, 4, 1), (500, 1, 1), (256, 2, 3), (130, 1, 2)]),        # 4, 4, 1 and 1 pieces an example, one round
+    (50, [(512, 4, 1), (500, 1, 1), (256, 2, 3), (130, 1, 2)]),        # the second round is not full
+    (64, [(449, 1, 1), (385, 2, 1)]),                                  # both with a ragged second half
+    (9, [(1000, 1, 2), (641, 1, 1), (257, 2, 1)]),                     # 16, 9 and 3 pieces an example
+])
+def test_layers_of_several_lengths(types, step, tol, B, shapes):
+    gen = torch.Generator(device="cuda").manual_seed(B)
+    layers = _layers(gen, B, shapes, types, step)
+    descs = dp.layer_descs(layers)
+    assert dp.load_library().dp_plan_gram_wide(descs[0], len(layers), B, descs[2], dp.DP_PATH_GRAM) == 1
+    each = [_norm64(A, G) for A, G in layers]
+    need = dp.layers_workspace_bytes(descs[0], B, descs[2], "gram")
+    ws = torch.full((need + 4096,), 7, dtype=torch.uint8, device="cuda")
+    s = dp.layers_sqnorm(layers, torch.zeros(B, device="cuda"), path="gram", workspace=ws[:need], descs=descs)
+    assert float(((s.double() - sum(each)) / sum(each)).abs().max()) < tol
+    assert bool((ws[need:] == 7).all())                     # nothing behind the scratch that was asked for
+    # an array for every layer: each layer's own sums
+    own = [torch.zeros(B, device="cuda") for _ in layers]
+    descs = dp.layer_descs(layers, groups=[(x, None, 0.0) for x in own])
+    dp.layers_sqnorm(layers, torch.zeros(B, device="cuda"), path="gram", descs=descs)
+    for x, ref in zip(own, each):
+        assert float(((x.double() - ref) / ref).abs().max()) < tol

@@ -70,3 +70,36 @@ def test_several_layers(types, tol, B, T, shapes, noise, accumulate):
             ref += z
         at += a * b
         assert float((g.double() - ref).norm() / ref.norm()) < tol
+
+
+@pytest.mark.parametrize("types", [F8, (F8[0],) * 2])
+@pytest.mark.parametrize("B,layers_of", [
+    (8, [(384, 1792, 2304), (64, 1024, 2048), (64, 1536, 1792), (384, 2304, 1280)]),     # packs of two over 63 and 45 tiles, two layers without
+    (14, [(256, 1280, 2304), (64, 2048, 2048), (256, 2048, 2048)]),                      # a layer without rests between two with them
+    (64, [(512, 768, 2304), (512, 768, 768), (512, 768, 3072), (512, 3072, 768)]),       # packs of three
+    (14, [(256, 1264, 2304), (256, 2048, 2032), (64, 2048, 2048)]),                      # edge tiles
+])
+@pytest.mark.parametrize("noise,accumulate", [(0.0, False), (0.5, False), (0.0, True)])
+def test_slices_of_two_lengths(types, B, layers_of, noise, accumulate):
+    gen = torch.Generator(device="cuda").manual_seed(B)
+    layers = [_pair(gen, B, T, a, b, types) for T, a, b in layers_of]
+    clip = torch.rand(B, device="cuda", generator=gen) + 0.25
+    clip[0] = clip[B // 2] = clip[-1] = 0.0                 # the last examples lie in the rests
+    clip[-2] = 2e-14                                        # left out: below 2^-40 of the largest before it
+    counted = torch.where(clip < 1e-12, torch.zeros_like(clip), clip)
+    grads = [torch.ones((a, b), device="cuda") for _, a, b in layers_of]
+    descs = dp.layer_descs(layers, grads)
+    assert dp.load_library().dp_plan_sums_in_two_lengths(descs[0], len(layers), B, descs[2]) > 0
+    need = dp.layers_clipped_workspace_bytes(descs[0], B, descs[2])
+    ws = torch.full((need + 4096,), 7, dtype=torch.uint8, device="cuda")
+    dp.layers_clipped_grad(layers, clip, grads, workspace=ws[:need], descs=descs, noise_std=noise, seed=3, accumulate=accumulate)
+    assert bool((ws[need:] == 7).all())                     # nothing behind the scratch that was asked for
+    at = 0
+    for (A, G), g, (_, a, b) in zip(layers, grads, layers_of):
+        ref = _sum64(A, G, counted) + (1.0 if accumulate else 0.0)
+        if noise:
+            z = torch.zeros_like(g)
+            dp.add_noise(z, noise, 3, at)
+            ref += z
+        at += a * b
+        assert float((g.double() - ref).norm() / ref.norm()) < 6e-5
