@@ -509,7 +509,7 @@ __global__ __launch_bounds__(256) void k_splitk_reduce_wide(const float* __restr
     }
 }
 
-bool splitk_reduce_is_wide(int64_t n) { return ((n + 3) >> 2) <= (int64_t)256 * 1024; }
+bool splitk_reduce_is_wide(int64_t n) { return (n & 3) == 0 && (n >> 2) <= (int64_t)256 * 1024; }
 bool splitk_noise_ok(int64_t n, uint64_t offset) { return (n & 3) == 0 && (offset & 3) == 0; }
 
 // noise: nullptr or stddev == 0 for none; otherwise splitk_noise_ok(n, noise->offset) must hold
@@ -520,7 +520,7 @@ hipError_t launch_splitk_reduce(const float* ws, int64_t n, int splits, bool acc
     const bool nz = noise != nullptr && noise->stddev != 0.0f;
     if (nz && !splitk_noise_ok(n, noise->offset)) return hipErrorInvalidValue;
     const NoiseArgs na = nz ? *noise : NoiseArgs{0.f, 0u, 0u, 0u};
-    if (splits >= 16 && splitk_reduce_is_wide(n)) {
+    if (splits >= 16 && splitk_reduce_is_wide((n + 3) & ~(int64_t)3)) {
         const unsigned grid = (unsigned)(((n + 3) / 4 + 31) / 32);
         if (nz) k_splitk_reduce_wide<true><<<grid, 256, 0, st>>>(ws, n, splitk_slice_elems(n), splits, accumulate ? 1 : 0, grad, na);
         else    k_splitk_reduce_wide<false><<<grid, 256, 0, st>>>(ws, n, splitk_slice_elems(n), splits, accumulate ? 1 : 0, grad, na);

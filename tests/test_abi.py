@@ -384,13 +384,3 @@ def test_conv_geometry_queries_over_many_shapes(lib):
                         # narrow that a 32-position stage consumes more image rows than a round of copies brings
                         assert T >= 64 and (T < 512 or W + 2 * pad > 102 or W + 2 * pad - 2 < 8), geo
     assert n_rows > 500 and n_general > 100 and n_none > 100, (n_rows, n_general, n_none)
-
-
-@pytest.mark.parametrize("K", [2000, 20000, 60000])
-@pytest.mark.parametrize("M,N", [(256, 128), (512, 256), (704, 336)])
-def test_slices_of_sizes_that_are_no_whole_groups_of_four(lib, K, M, N):
-    """float32 sums: the launch that adds the slices takes any number of entries eight threads to one, and the plan counts on
-    it: a size just below has as many slices."""
-    def slices(m, n):
-        return dpclip.workspace_bytes(dpclip.DP_OP_CLIPPED_GRAD, K, 1, m, n, dpclip.DP_F32) // (4 * ((m * n + 3) // 4 * 4))
-    assert slices(M - 1, N - 1) == slices(M, N) > 1
