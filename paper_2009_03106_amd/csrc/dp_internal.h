@@ -59,7 +59,8 @@ struct FoldLayers {
     const float* ws[kJointLayers]; float* grad[kJointLayers]; int64_t n[kJointLayers], slice[kJointLayers];
     uint64_t noise_offset[kJointLayers]; int splits[kJointLayers]; unsigned first_block[kJointLayers]; int n_layers;
 };
-bool splitk_reduce_is_wide(int64_t n);   // launch_splitk_reduce takes 16 slices or more of n entries with eight threads per entry
+// launch_splitk_reduce takes 16 slices or more of n entries with eight threads per entry, n a multiple of 4 (other sizes as the next one)
+bool splitk_reduce_is_wide(int64_t n);
 // blocks: the slices of eight first, then those sums (float32 layers)
 hipError_t launch_splitk_reduce_layers(FoldLayers& f, bool accumulate, hipStream_t st, float stddev, uint64_t seed, bool blocks);
 hipError_t launch_fill_zero(float* p, int64_t n, hipStream_t st);

@@ -541,7 +541,9 @@ TnPlan plan_clipped_f32(int B, int T, int M, int N) {
         const int64_t tiles = (int64_t)p.tiles_m * p.tiles_n;
         // K slices: the (tile, slice) items run `slots` at a time; an item costs its stages plus about 16 stage times of
         // start-up and store, and the fold reads all slices, 4 MB in about a stage time, and walks them one after the
-        // other, 32 (k_splitk_reduce_wide) or 4 (k_splitk_reduce) in a stage time.  Take the slice count with the
+        // other, 32 (k_splitk_reduce_wide) or 4 (k_splitk_reduce) in a stage time.  (Sizes that are no multiple of 4 are counted
+        // at 4, though the wide fold takes them too: with 32 they would take up to twice the slices and scratch for 0.9 % of the
+        // time, 60 sizes between 0.92 and 1.5.)  Take the slice count with the
         // smallest rounds x (stages per slice + 16) + fold: a count that just spills into one more round (540 items)
         // costs a whole extra round, many short slices cost their overheads.
         const uint32_t stages = (uint32_t)((K + dk - 1) / dk);
