@@ -17,6 +17,7 @@
 //     at its stage barrier.
 // Rows t >= T of a ragged last tile are read from a clamped (valid) row and
 // masked out of the final product.
+#include <algorithm>
 #include "dp_common.h"
 #include "dp_internal.h"
 #include <type_traits>
@@ -617,22 +618,39 @@ bool gram_dma_ok(int T, int d_in, int d_out, int fmt) {
     return T > 64 && (d_in % gke) == 0 && (d_out % gke) == 0 && (int64_t)T * dmax * es < (int64_t(1) << 31);   // 32-bit lane offsets
 }
 
-// Whether a launch takes the larger pieces: no column sums wanted, and 10 % less by two estimates fitted to 240 measured shapes
-// (T = 130 .. 1024, 4 to 128 examples, 256 to 3072 columns; in microseconds for 768 + 3072 columns of 16 bits).  The larger
-// pieces go over the chip 256 at a time, 66 us a round and 45 to 70 for a last one that is not full; the pairs 512 at a
-// time with a tail that the next ones fill.  64 examples of 512 positions: 70 and 95 us, 128: 148 and 175; 64 of 768
-// positions, whose pieces fill 2.25 rounds, 183 and 169.
+// Whether a launch takes the larger pieces: no column sums wanted, and 11 % less by two estimates fitted to 265 measured shapes
+// of single layers (T = 130 .. 1024, 4 to 128 examples, 256 to 3072 columns, 16 and 8 bits; in microseconds for 768 + 3072
+// columns of 16 bits, of which only the ratio counts).  The larger pieces go over the chip 256 at a time, 66 us a round and 45
+// to 70 for a last one that is not full; the pairs 512 at a time with a tail that the next ones fill.  64 examples of 512
+// positions: 70 and 95 us (8 bits 38 and 46), 128: 148 and 175 (71 and 76); 64 of 768 positions, whose pieces fill 2.25 rounds,
+// 183 and 169.  Layers of several widths, heaviest first: a round of pieces is as long as its heaviest (51 examples of 256
+// positions, 768 -> 704, and 512, 320 -> 640: 37 us, the pairs 31.6).
 bool gram_wide(const GramLayerDesc* layers, int n_layers, int B) {
-    int64_t items = 0, pairs = 0;
+    if (n_layers < 1 || n_layers > kGramBatch) return false;
+    int order[kGramBatch];
     for (int l = 0; l < n_layers; ++l) {
         if (layers[l].upart) return false;
-        items += (int64_t)B * gram_wide_pieces(layers[l].T);
-        pairs += (int64_t)B * plan_gram_bf16(layers[l].T, layers[l].d_in, layers[l].d_out).npairs;
+        order[l] = l;
     }
-    const int64_t last = items % 256;
-    const double wide = 66.0 * (double)(items / 256) + (last > 0 ? 45.0 + 25.0 * (double)last / 256.0 : 0.0);
-    const double small = pairs <= 256 ? 37.0 : pairs <= 512 ? 53.0 : 14.0 + 0.118 * (double)pairs;
-    return wide < 0.9 * small;
+    auto columns = [&](int l) { return layers[l].d_in + layers[l].d_out; };
+    std::stable_sort(order, order + n_layers, [&](int p, int q) { return columns(p) > columns(q); });
+    int64_t pairs = 0, left = 0;                         // left: places in the round that is open
+    double wide = 0.0, weighted = 0.0, width = 1.0;      // width: of the layer that opened it, the heaviest layer's being 1
+    for (int k = 0; k < n_layers; ++k) {
+        const GramLayerDesc& y = layers[order[k]];
+        const double w = (double)columns(order[k]) / (double)columns(order[0]);
+        const int64_t n = (int64_t)B * plan_gram_bf16(y.T, y.d_in, y.d_out).npairs, over = (int64_t)B * gram_wide_pieces(y.T) - left;
+        pairs += n;
+        weighted += (double)n * w;
+        if (over <= 0) { left = -over; continue; }
+        const int64_t rounds = (over + 255) / 256;
+        wide += 66.0 * (double)rounds * w;
+        left = rounds * 256 - over;
+        width = w;
+    }
+    if (left > 0) wide += (45.0 + 25.0 * (double)(256 - left) / 256.0 - 66.0) * width;
+    const double small = pairs <= 256 ? 37.0 : pairs <= 512 ? 53.0 : 14.0 + 0.118 * weighted;
+    return wide < 0.89 * small;
 }
 
 // Several layers in one launch (at most kGramBatch, every one passing gram_dma_ok); partial gets the layers' item

@@ -59,10 +59,10 @@ def _layers(gen, B, shapes, types, step):
 @pytest.mark.parametrize("types,step,tol", [((torch.bfloat16,) * 2, 64, 1e-5), ((torch.float16,) * 2, 64, 1e-5),
                                             ((torch.float8_e4m3fn, torch.float8_e5m2), 128, 2e-4), ((torch.float8_e4m3fn,) * 2, 128, 2e-4)])
 @pytest.mark.parametrize("B,shapes", [
-    (25, [(512, 4, 1), (500, 1, 1), (256, 2, 3), (130, 1, 2)]),        # 4, 4, 1 and 1 pieces an example, one round
+    (25, [(512, 2, 2), (500, 2, 1), (256, 1, 3), (130, 1, 2)]),        # 4, 4, 1 and 1 pieces an example, one round
     (50, [(512, 4, 1), (500, 1, 1), (256, 2, 3), (130, 1, 2)]),        # the second round is not full
     (64, [(449, 1, 1), (385, 2, 1)]),                                  # both with a ragged second half
-    (9, [(1000, 1, 2), (641, 1, 1), (257, 2, 1)]),                     # 16, 9 and 3 pieces an example
+    (9, [(1000, 2, 2), (513, 2, 2), (385, 2, 2)]),                     # 16, 9 and 4 pieces an example
 ])
 def test_layers_of_several_lengths(types, step, tol, B, shapes):
     gen = torch.Generator(device="cuda").manual_seed(B)
