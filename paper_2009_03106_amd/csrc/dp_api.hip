@@ -902,7 +902,7 @@ dp_status dp_layers_sqnorm_clip(const dp_layer_desc* layers, int64_t n_layers, i
     // Which kernel completes the norms and can write the clip factors with them: the last shared Gram launch if
     // there is one; else, unless a bias pass follows, the last layer that runs on its own; else the last launch
     // of dense layers.  Otherwise (bias passes at the end, or nothing to launch) the clip kernel runs.
-    int64_t n_dense = 0, n_cols = 0, n_single = 0, last_single = -1;
+    int64_t n_dense = 0, n_cols = 0, n_single = 0, last_single = -1, n_queue = 0, n_gram16 = 0;
     bool any_gram = false, any_bias_pass = false;
     for (int64_t l = 0; l < n_layers; ++l) {
         const dp_layer_desc& y = layers[l];
@@ -912,13 +912,22 @@ dp_status dp_layers_sqnorm_clip(const dp_layer_desc* layers, int64_t n_layers, i
         if (y.T == 1 && !is8(dtype)) ++n_dense;
         else if (gram_batchable(y.T, y.d_in, y.d_out, dtype, path)) any_gram = true;
         else if (gram_cols_layer(B, y.T, y.d_in, y.d_out, dtype, path)) ++n_cols;
-        else { last_single = l; ++n_single; }
+        else {
+            last_single = l; ++n_single;
+            // (a 16-bit Gram norm of one sum an example is added by its own kernel, unless it shares a launch)
+            const bool own_sum = is16(dtype) && resolve_path(path, dtype, y.T, y.d_in, y.d_out) == DP_PATH_GRAM && plan_gram_bf16((int)y.T, (int)y.d_in, (int)y.d_out).npairs == 1;
+            if (gram16_joinable(B, y.T, y.d_in, y.d_out, dtype, path)) ++n_gram16;
+            if (!own_sum) ++n_queue;
+        }
     }
+    if (n_gram16 >= 2) n_queue += n_gram16;
     const ClipOut clip_out{C, clip};
     // Two or more layers outside the dense and the Gram launches: their partial sums are folded by one launch at the end
     // (FinalizeQueue) instead of a launch of a few microseconds behind every layer.  (Column-split Gram layers beside at most one
-    // other are added up by their own second launch: as many launches, or one less.)
+    // other, or beside layers whose kernels add their norms themselves, are added up by their own second launch: as many
+    // launches, or one less.)
     const bool defer_on = n_single >= 2 && !is8(dtype);
+    const bool defer_cols = defer_on && n_queue > 0;
     FinalizeQueue queue;
     size_t ws_off = 0;
     auto flush_queue = [&](bool with_clip) -> hipError_t {
@@ -938,7 +947,7 @@ dp_status dp_layers_sqnorm_clip(const dp_layer_desc* layers, int64_t n_layers, i
         auto flush_cols = [&]() -> hipError_t {
             if (ng == 0) return hipSuccess;
             cols_done += ng;
-            if (!defer_on) {
+            if (!defer_cols) {
                 const hipError_t e = launch_gram_cols_norms(group, ng, (int)B, acc != 0, sqnorm, static_cast<float*>(workspace), n_cols == 1 ? kAnySlices : need / sizeof(float),
                                                             stream, (int)dtype, clip_with_cols && cols_done == n_cols ? &clip_out : nullptr);
                 ng = 0; least = 0; acc = 1; launched = true;

@@ -151,3 +151,25 @@ def test_norms_of_several_layers_are_not_off_to_one_side(dtype, B, shapes):
         ref = sum(_norm64(A, G) for A, G in layers)
         errors.append((dp.layers_sqnorm(layers, path="gram").double() - ref) / ref)
     assert abs(float(torch.cat(errors).mean())) < 3e-8
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("others", [[(12, 64, 64)] * 2, [(100, 200, 72)], [(100, 200, 72)] * 2, [(12, 64, 64), (100, 200, 72), (300, 200, 72)], [(12, 64, 64)] * 2 + [(256, 64, 64)]])
+@pytest.mark.parametrize("biased", [False, True])
+def test_beside_layers_that_add_their_own_norms(dtype, others, biased):
+    """16-bit Gram norms of one sum an example are added by their own kernels, other layers' by the queue: complete norms and
+    their clip factors with both, and accumulated."""
+    gen = torch.Generator(device="cuda").manual_seed(13)
+    B = 10
+    layers = [(_tensor(gen, B, T, a, dtype), _tensor(gen, B, T, b, dtype)) for T, a, b in [(16, 1152, 512), (64, 1152, 256)] + others]
+    ref = sum(_norm64(A, G) for A, G in layers)
+    rows = [torch.zeros((B, G.shape[-1]), device="cuda") if biased and l % 2 else None for l, (_, G) in enumerate(layers)]
+    ref = ref + sum(G.double().sum(1).pow(2).sum(1) for (_, G), r in zip(layers, rows) if r is not None)
+    C = float(ref.median().sqrt())
+    descs = dp.layer_descs(layers, bias_rows=rows)
+    for start in (None, 5.0):
+        s, clip = torch.full((B,), start or float("nan"), device="cuda"), torch.zeros(B, device="cuda")
+        dp.layers_sqnorm(layers, s, path="gram", accumulate=start is not None, descs=descs, C=C, clip=clip)
+        want = ref + (start or 0.0)
+        assert torch.allclose(s.double(), want, rtol=1e-5, atol=0)
+        assert torch.allclose(clip.double(), (C / want.sqrt()).clamp(max=1.0), rtol=1e-5, atol=0)
