@@ -138,8 +138,9 @@ __device__ __forceinline__ void gram_cols_run(const unsigned char* __restrict__ 
         rd[b] = (uint32_t)(r * 128 + ((half ^ ((r >> 1) & 7)) << 4));
     }
     f32x16 chain[TWO ? NT : 1];
-    for (int p = 0; p < nst; ++p)
-        if (p < n_stages) issue(p);
+#pragma unroll
+    for (int p = 0; p < (NB == 1 ? kStages1 : kStages2); ++p)
+        if (p < nst && p < n_stages) issue(p);
     int buf = 0;
     for (int st = 0; st < n_stages; ++st) {
         wait_copies(min(n_stages - 1 - st, nst - 1) * copies);
@@ -169,8 +170,13 @@ __device__ __forceinline__ void gram_cols_run(const unsigned char* __restrict__ 
         if constexpr (TWO) {
             static_assert(kColsSteps == 2 * kStageSteps, "");
             if ((st & 1) || st + 1 == n_stages) {
+                if (st <= 1) {                                       // (total is zero: nothing to wait for)
 #pragma unroll
-                for (int t = 0; t < NT; ++t) total[t] += chain[t];
+                    for (int t = 0; t < NT; ++t) total[t] = chain[t];
+                } else {
+#pragma unroll
+                    for (int t = 0; t < NT; ++t) total[t] += chain[t];
+                }
             }
         }
     }
@@ -496,7 +502,7 @@ hipError_t launch_cols(const GramLayerDesc* layers, float* const* sums, int n_la
     const int kind = cols_launch_kind(layers, n_layers, dt);
     int64_t blocks = 0, finish = 0;
     size_t off = 0;
-    int nb = 1;
+    int nb = 1, rows = 0;
     GramColsPlan plans[CAP];
     plan_cols_shared(layers, n_layers, B, dt, max_floats, plans);
     for (int l = 0; l < n_layers; ++l) {
@@ -514,7 +520,7 @@ hipError_t launch_cols(const GramLayerDesc* layers, float* const* sums, int n_la
         blocks += (int64_t)B * p.W;
         finish += (int64_t)B * gram_cols_sums(p);
         off += p.ws_floats;
-        nb = nb > p.nb ? nb : p.nb;
+        nb = std::max(nb, p.nb); rows = std::max(rows, y.T);
     }
     for (int l = n_layers; l < CAP; ++l) a.layer[l] = a.layer[0];
     if (blocks >= (int64_t(1) << 24) || finish >= (int64_t(1) << 24)) return hipErrorInvalidValue;   // (W >= 2 only where B < 2^9)
@@ -532,15 +538,15 @@ hipError_t launch_cols(const GramLayerDesc* layers, float* const* sums, int n_la
         return hipGetLastError();
     }
     a.stages = kStages1; a.wave_lds = kWaveLds;
-    if constexpr (CAP == 1) {
-        // fewer stages in flight where a compute unit has more than two workgroups
-        const int stage = ceil_div(layers[0].T, 8) * 1024, per_cu = (int)((blocks + 255) / 256);
+    if (CAP == 1 || nb == 1) {
+        // no more LDS than the rows that there are, and fewer stages in flight where a compute unit has more than two workgroups
+        const int stage = ceil_div(rows, 8) * 1024, per_cu = (int)((blocks + 255) / 256);
         while (a.stages > 2 && std::max(meet, 4 * a.stages * stage) * per_cu > 160 * 1024) --a.stages;
         a.wave_lds = (nb == 1 ? a.stages : kStages2) * stage;
     }
     const size_t lds = (size_t)std::max(meet, 4 * a.wave_lds);
-    if constexpr (CAP == 1) { if (nb == 1) { launch_cols_copied<1, CAP>((unsigned)blocks, lds, st, dt, a); return hipGetLastError(); } }
-    launch_cols_copied<2, CAP>((unsigned)blocks, lds, st, dt, a);
+    if (nb == 1) launch_cols_copied<1, CAP>((unsigned)blocks, lds, st, dt, a);
+    else         launch_cols_copied<2, CAP>((unsigned)blocks, lds, st, dt, a);
     return hipGetLastError();
 }
 
