@@ -140,8 +140,9 @@ dp_status dp_layer_sqnorm_static(const void* A, const void* G,
  * multiples of 128 for 8-bit inputs) with T > 64 share kernel launches, up to 16 layers each: the workgroups of one
  * layer then fill the idle tail of another's, which a per-layer launch leaves
  * empty.  Dense layers (T == 1) share launches too, 16 each, and so do 16-bit
- * Gram layers of at most 64 positions with wide rows in a batch of fewer than
- * 512 (their columns are split over workgroups), and 16-bit layers on the
+ * and float32 Gram layers of at most 64 positions with wide rows in a batch of
+ * fewer than 512 (their columns are split over workgroups; 16-bit rows of whole
+ * 16-byte pieces, float32 rows of any length), and 16-bit layers on the
  * direct path with T >= 64 and widths that are multiples of 8, unless they
  * are large enough to do better alone.  Every other layer runs the
  * kernels dp_layer_sqnorm runs for it; where there are two or more of them,

@@ -2,9 +2,8 @@
  * dpclip_probes -- measurement probes that ship with libdpclip.so.
  *
  * They are not part of the method: each but the two plan queries at the end
- * launches one small kernel that
- * exercises a single unit of the MI355X the way the library's kernels use it,
- * so that a benchmark can quote the library's kernels against what this very
+ * launches one small kernel that exercises a single unit of the MI355X the way
+ * the library's kernels use it, so that a benchmark can quote the library's kernels against what this very
  * part sustains (next to the published peaks).  The caller times the launch
  * (HIP events on `hip_stream`); the amount of work of one launch is returned.
  * Conventions as in dpclip.h: device pointers, asynchronous on `hip_stream`,

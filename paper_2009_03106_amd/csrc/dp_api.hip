@@ -915,7 +915,8 @@ dp_status dp_layers_sqnorm_clip(const dp_layer_desc* layers, int64_t n_layers, i
         else {
             last_single = l; ++n_single;
             // (a 16-bit Gram norm of one sum an example is added by its own kernel, unless it shares a launch)
-            const bool own_sum = is16(dtype) && resolve_path(path, dtype, y.T, y.d_in, y.d_out) == DP_PATH_GRAM && plan_gram_bf16((int)y.T, (int)y.d_in, (int)y.d_out).npairs == 1;
+            const bool own_sum = is16(dtype) && resolve_path(path, dtype, y.T, y.d_in, y.d_out) == DP_PATH_GRAM &&
+                                 plan_gram_bf16((int)y.T, (int)y.d_in, (int)y.d_out).npairs == 1;
             if (gram16_joinable(B, y.T, y.d_in, y.d_out, dtype, path)) ++n_gram16;
             if (!own_sum) ++n_queue;
         }
@@ -938,7 +939,7 @@ dp_status dp_layers_sqnorm_clip(const dp_layer_desc* layers, int64_t n_layers, i
     };
     // layers of few positions and wide rows in a small batch: shared column-split Gram launches, first of all.  Their sums
     // join the queue, or without one are added up behind them (with the clip factors when nothing else follows).
-    const bool clip_with_cols = clip && !defer_on && !any_gram && !any_bias_pass && last_single < 0 && n_dense == 0 && n_cols > 0;
+    const bool clip_with_cols = clip && !any_gram && !any_bias_pass && last_single < 0 && n_dense == 0 && n_cols > 0;
     if (n_cols > 0) {
         GramLayerDesc group[kGramColsLayers];
         int ng = 0;
@@ -948,8 +949,8 @@ dp_status dp_layers_sqnorm_clip(const dp_layer_desc* layers, int64_t n_layers, i
             if (ng == 0) return hipSuccess;
             cols_done += ng;
             if (!defer_cols) {
-                const hipError_t e = launch_gram_cols_norms(group, ng, (int)B, acc != 0, sqnorm, static_cast<float*>(workspace), n_cols == 1 ? kAnySlices : need / sizeof(float),
-                                                            stream, (int)dtype, clip_with_cols && cols_done == n_cols ? &clip_out : nullptr);
+                const hipError_t e = launch_gram_cols_norms(group, ng, (int)B, acc != 0, sqnorm, static_cast<float*>(workspace),
+                                                            n_cols == 1 ? kAnySlices : need / sizeof(float), stream, (int)dtype, clip_with_cols && cols_done == n_cols ? &clip_out : nullptr);
                 ng = 0; least = 0; acc = 1; launched = true;
                 return e;
             }
@@ -994,8 +995,8 @@ dp_status dp_layers_sqnorm_clip(const dp_layer_desc* layers, int64_t n_layers, i
             if (flush_cols() != hipSuccess) return DP_ERR_HIP;
         }
     }
-    const bool clip_with_single = clip && !any_gram && !any_bias_pass && (last_single >= 0 || defer_on);
-    const bool clip_with_dense = clip && !any_gram && !any_bias_pass && last_single < 0 && !defer_on && n_dense > 0;
+    const bool clip_with_single = clip && !any_gram && !any_bias_pass && last_single >= 0;
+    const bool clip_with_dense = clip && !any_gram && !any_bias_pass && last_single < 0 && n_dense > 0;
     // dense layers (T = 1, closed form): up to kDenseBatch per launch, in the order given
     DenseLayers dense;
     dense.n_layers = 0;
@@ -1577,7 +1578,8 @@ int dp_plan_gram_wide(const dp_layer_desc* layers, int64_t n_layers, int64_t B, 
 }
 
 int dp_plan_sums_in_two_lengths(const dp_layer_desc* layers, int64_t n_layers, int64_t B, dp_dtype dtype) {
-    if (check_layers(layers, n_layers, B, dtype, DP_PATH_DIRECT, false, DP_OP_CLIPPED_GRAD) != DP_OK || n_layers < 2 || n_layers > kJointLayers || !is8(dtype)) return -1;
+    if (check_layers(layers, n_layers, B, dtype, DP_PATH_DIRECT, false, DP_OP_CLIPPED_GRAD) != DP_OK) return -1;
+    if (n_layers < 2 || n_layers > kJointLayers || !is8(dtype)) return -1;
     JointShape sh[kJointLayers];
     for (int64_t l = 0; l < n_layers; ++l) {
         const dp_layer_desc& y = layers[l];

@@ -183,7 +183,7 @@ __global__ __launch_bounds__(kThreads) void k_bias_rows_scalar(const void* __res
     bias_rows_scalar_block<DT, PROD, DTH>(G, Hb, T, D, u, u2, blockIdx.x, blockIdx.y);
 }
 
-// The bias rows of several layers in one launch, each with its own launch's split (ctl; < 0: one thread per column): a
+// The bias rows of several layers in one launch, each with its own launch's split (ctl; < 0: 32 columns a workgroup): a
 // layer of 32 examples is a few hundred workgroups of 5 to 6 us, five of them and their norms were ten launches.
 struct BiasRowsLayers { const void* G[kBiasLayers]; float* u[kBiasLayers]; int T[kBiasLayers], D[kBiasLayers], ctl[kBiasLayers],
                         chunks[kBiasLayers], first_block[kBiasLayers]; int n_layers; };
@@ -240,7 +240,8 @@ __global__ __launch_bounds__(kThreads) void k_rows_sqnorm(const float* __restric
     }
 }
 
-// the same for several layers' rows, added in the order given: the bits of one launch per layer.  A workgroup per example, its
+// the same for several layers' rows, added in the order given: the bits of one launch of k_rows_sqnorm per layer (a call for one
+// layer whose launch has whole rows adds their squares by pieces: equal to float32 rounding).  A workgroup per example, its
 // waves take the layers in turn (one wave for all of them: 14 us for five layers of 656 to 1968 columns)
 struct RowsLayers { const float* u[kBiasLayers]; int D[kBiasLayers]; int n_layers; };
 __global__ __launch_bounds__(kThreads) void k_rows_sqnorm_layers(RowsLayers a, int accumulate, float* __restrict__ sqnorm) {

@@ -17,6 +17,8 @@
 //     at its stage barrier.
 // Rows t >= T of a ragged last tile are read from a clamped (valid) row and
 // masked out of the final product.
+// Two forms beside it: 16-bit widths that are multiples of 8 (RAGW: the last stage of a row is masked), and launches that
+// fill the chip with larger pieces, 256 rows of an example to a workgroup of 8 waves (k_gram_wide; gram_wide says when).
 #include <algorithm>
 #include "dp_common.h"
 #include "dp_internal.h"

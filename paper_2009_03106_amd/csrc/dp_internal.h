@@ -78,8 +78,8 @@ hipError_t launch_bias_fold(const float* upart, int B, int nt, int D, bool accum
 // s_i (+)= ||u[i, :]||^2, then + ||u2[i, :]||^2 where u2 is given
 hipError_t launch_rows_sqnorm(const float* u, int B, int D, bool accumulate, float* sqnorm, hipStream_t st, const float* u2 = nullptr);
 hipError_t launch_clipped_bias(const float* u, const float* clip, int B, int D, bool accumulate, float* grad_b, hipStream_t st);
-// Several layers at once, the same values: u and the sums of squares of up to kBiasLayers layers (float32 and 16-bit inputs,
-// T, D >= 1, B <= 65535) in two launches, and their clipped sums with the noise in one.  hipErrorInvalidValue before any
+// Several layers at once: u (the bits of a launch per layer) and the sums of squares (to float32 rounding) of up to kBiasLayers
+// layers (float32 and 16-bit inputs, T, D >= 1, B <= 65535) in two launches, and their clipped sums with the noise in one.  hipErrorInvalidValue before any
 // launch where a launch would be too large.
 constexpr int kBiasLayers = 16;
 struct BiasLayerDesc { const void* G; int T, D; float* u; };

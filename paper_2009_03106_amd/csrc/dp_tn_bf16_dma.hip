@@ -362,9 +362,9 @@ __device__ __forceinline__ void tn_dma_tile(const DmaArgs& a, const int L) {
     if constexpr (GEO::WAVES == 8 && !CONV) {
         // Two waves per SIMD in opposite phases: while one multiplies a stage the other reads its fragments of one, so that
         // the matrix unit does not wait for the LDS port.  (With all 8 waves in one phase a stage took 1620 cycles, 1024 of
-        // them MFMAs; 64 examples of 512 x (768, 2304), (768, 768), (768, 3072), (3072, 768): step 755 -> 731 us.)  Every phase ends at a barrier; waves 4 .. 7 start one phase
-        // later.  A stage's buffer is free once both halves have read it, one phase after the first: the copies of stage
-        // st - 1 + NST are requested while stage st is read, behind the reads.
+        // them MFMAs; 64 examples of 512 x (768, 2304), (768, 768), (768, 3072), (3072, 768): step 755 -> 731 us.)  Every phase ends
+        // at a barrier; waves 4 .. 7 start one phase later.  A stage's buffer is free once both halves have read it, one phase
+        // after the first: the copies of stage st - 1 + NST are requested while stage st is read, behind the reads.
         const bool late = __builtin_amdgcn_readfirstlane(wave >> 2) != 0;
         bf16x8 f[KS][NF];
         int buf = 0, before = NST - 1;              // of stage st, and of the one before

@@ -267,9 +267,9 @@ __device__ __forceinline__ void tn_f8_tile(const Dma8Args& a, const int L) {
     if constexpr (GEO::WAVES == 8) {
         // Two waves per SIMD in opposite phases: while one multiplies a stage the other reads its fragments of one, so that
         // the matrix unit never waits for the LDS port.  (With all 8 waves in one phase a stage took 1730 cycles, 1024 of them
-        // MFMAs; the four layers of 64 examples of 512 positions: step 409 -> 393 us.)  Every phase ends at a barrier; waves 4 .. 7 start one phase later.  A stage's buffer is free once both
-        // halves have read it, one phase after the first: the copies of stage st - 1 + NST are requested while stage st is
-        // read, behind the reads.
+        // MFMAs; the four layers of 64 examples of 512 positions: step 409 -> 393 us.)  Every phase ends at a barrier; waves 4 .. 7
+        // start one phase later.  A stage's buffer is free once both halves have read it, one phase after the first: the
+        // copies of stage st - 1 + NST are requested while stage st is read, behind the reads.
         const bool late = __builtin_amdgcn_readfirstlane(wave >> 2) != 0;
         v8i32 f[NF];
         int buf = 0, before = NST - 1;              // of stage st, and of the one before

@@ -315,7 +315,8 @@ def test_layers_call_clip_factors_whatever_kernel_writes_them(dp, dtype, kinds):
 def test_per_layer_clipping_in_the_layers_calls(dp):
     """Per-layer clipping (threshold c / sqrt(m) for each of the m layers, Section 4) through the several-layers calls:
     every layer names its own norm and clip arrays, the Gram launch is still shared, and the clipped sums take each
-    layer's own factors.  Norms are bit for bit those of the per-layer entry point."""
+    layer's own factors.  At this batch the shared and the single launch form the same pieces: norms are bit for bit those
+    of the per-layer entry point (where only one of them takes 256-row pieces, they differ by float32 rounding)."""
     w, layers = wl.generate("transformer", B=5, straddle=True)
     dev = [(to_dev(A), to_dev(G)) for A, G in layers]
     m, B = len(dev), 5
