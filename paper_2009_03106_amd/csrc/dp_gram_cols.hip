@@ -17,7 +17,7 @@
 // into the wave's own 16 KB, from where a lane reads its row.  (Loaded straight to registers a lane needs the 16 bytes of
 // its own row, an instruction touches 32 lines for 32 bytes each, and the launches moved 1.9 TB/s: 32 examples of 64
 // positions into 2304 x 256, three layers, and 1152 x 256 took 19.4 us.  Eight layers of an 18-layer image model, 56 MB,
-// take 14 us in one launch (4 TB/s) and 5 us for the sums; in two launches by registers, with a walk through the shares, 60 us.)
+// take 15 us in one launch (3.8 TB/s) and 5 us for the sums; in two launches by registers, with a walk through the shares, 60 us.)
 #include <algorithm>
 #include "dp_common.h"
 #include "dp_internal.h"
