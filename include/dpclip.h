@@ -25,7 +25,9 @@
  *  - Errors come back as dp_status; on any error nothing is launched and the
  *    outputs are untouched.  Negative sizes, NULL required pointers, C <= 0,
  *    stddev < 0 or unknown enum values give DP_ERR_INVALID_ARG.  B*T must be
- *    below 2^31 and d_in, d_out below 2^24, else DP_ERR_UNSUPPORTED.
+ *    below 2^31 and d_in, d_out below 2^24, else DP_ERR_UNSUPPORTED (and so is
+ *    a norm of which 16 examples have more tile sums than a launch holds
+ *    workgroups: 2^24, e.g. 740 000 positions of one example on the Gram path).
  *  - A zero B, T, d_in or d_out is a valid empty problem: DP_OK, and with
  *    accumulate == 0 the output is zero-filled.
  *  - NaN / Inf inputs are not detected; they propagate into the outputs.

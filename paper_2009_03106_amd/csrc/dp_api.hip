@@ -115,8 +115,9 @@ size_t clipped_ws_bytes(int64_t B, int64_t T, int64_t d_in, int64_t d_out, dp_dt
 // threads a workgroup and one or more workgroups per example and sum, so a call of more than this many sums for a layer
 // goes in equal pieces of examples.
 constexpr int64_t kNormSums = (int64_t(1) << 22) - 16;
-// sums per example that a layer's norm kernel writes
-int64_t norm_sums(int64_t B, int64_t T, int64_t d_in, int64_t d_out, dp_dtype dtype, dp_path path) {
+// sums per example that a layer's norm kernel writes; most: how many one launch can write (a call in several has no limit)
+int64_t norm_sums(int64_t B, int64_t T, int64_t d_in, int64_t d_out, dp_dtype dtype, dp_path path, int64_t* most = nullptr) {
+    if (most) *most = (int64_t(1) << 24) - 128;
     if (T <= 1 || d_in == 0 || d_out == 0) return 1;
     const dp_dtype dt = is8(dtype) && !f8_fast_sqnorm(dtype, path, T, d_in, d_out) ? DP_F16 : dtype;      // (as it is widened)
     if (resolve_path(path, dt, T, d_in, d_out) == DP_PATH_GRAM)
@@ -124,16 +125,28 @@ int64_t norm_sums(int64_t B, int64_t T, int64_t d_in, int64_t d_out, dp_dtype dt
     const TnPlan p = is8(dt)  ? plan_direct_f8_dma((int)B, (int)T, (int)d_in, (int)d_out)
                    : is16(dt) ? plan_direct_bf16((int)B, (int)T, (int)d_in, (int)d_out)
                               : plan_direct_f32((int)B, (int)T, (int)d_in, (int)d_out);
+    if (most && !p.dma) *most = INT64_MAX;
+    else if (most && p.tile_m == 256 && p.tile_n == 256) *most = (int64_t(1) << 23) - 64;      // (8 waves)
     return (int64_t)p.tiles_m * p.tiles_n;
 }
-// examples of a piece for such a layer, a multiple of 16 (every piece starts on a 16-byte boundary); B where one call holds them
-int64_t piece_examples(int64_t B, int64_t T, int64_t d_in, int64_t d_out, dp_dtype dtype, dp_path path) {
-    // (more sums than any kernel's tiles make, without a look at its plan)
+// whether a call has at most kNormSums sums by more than any kernel's tiles make, without a look at its plan
+bool few_norm_sums(int64_t B, int64_t T, int64_t d_in, int64_t d_out) {
     const double pairs = (double)(T / 32 + 1) * (double)(T / 32 + 1), tiles = (double)(d_in / 32 + 1) * (double)(d_out / 32 + 1);
-    if ((double)B * (T <= 1 ? 1.0 : std::max(pairs, tiles)) <= (double)kNormSums) return B;
+    return (double)B * (T <= 1 ? 1.0 : std::max(pairs, tiles)) <= (double)kNormSums;
+}
+// examples of a piece for such a layer, a multiple of 16 (every piece starts on a 16-byte boundary); B where one call holds them all
+int64_t piece_examples(int64_t B, int64_t T, int64_t d_in, int64_t d_out, dp_dtype dtype, dp_path path) {
+    if (few_norm_sums(B, T, d_in, d_out)) return B;
     const int64_t sums = norm_sums(B, T, d_in, d_out, dtype, path);
     const int64_t pieces = (B * sums + kNormSums - 1) / kNormSums;
     return pieces <= 1 ? B : std::min(B, ((B + pieces - 1) / pieces + 15) & ~int64_t(15));
+}
+// a piece of 16 examples or fewer whose sums are still more than a launch holds: nothing that can be run
+bool norm_too_large(int64_t B, int64_t T, int64_t d_in, int64_t d_out, dp_dtype dtype, dp_path path) {
+    if (few_norm_sums(B, T, d_in, d_out)) return false;
+    int64_t most = 0;
+    const int64_t sums = norm_sums(B, T, d_in, d_out, dtype, path, &most);
+    return std::min<int64_t>(B, 16) * sums > most;
 }
 int64_t layers_piece_examples(const dp_layer_desc* layers, int64_t n_layers, int64_t B, dp_dtype dtype, dp_path path) {
     int64_t piece = B;
@@ -410,8 +423,14 @@ dp_status layer_sqnorm_clip(const void* A, const void* G, int64_t B, int64_t T, 
         return layer_sqnorm_clip(w, w + na, B, T, d_in, d_out, DP_F16, path, accumulate, sqnorm, w + na + ng,
                                  workspace_bytes - na - ng, hip_stream, co);
     }
+    if (norm_too_large(B, T, d_in, d_out, dtype, path)) return DP_ERR_UNSUPPORTED;
     const int64_t piece = piece_examples(B, T, d_in, d_out, dtype, path);
     auto in_pieces = [&]() -> dp_status {
+        if (piece < B && T > 1) {                          // (an error launches nothing)
+            const dp_path p = resolve_path(path, dtype, T, d_in, d_out);
+            if (workspace_bytes < std::max(sqnorm_ws_bytes(piece, T, d_in, d_out, dtype, p), sqnorm_ws_bytes(B - (B - 1) / piece * piece, T, d_in, d_out, dtype, p)))
+                return DP_ERR_WORKSPACE;
+        }
         for (int64_t b0 = 0; piece < B && b0 < B; b0 += piece) {
             const ClipOut c{co ? co->C : 0.f, co && co->clip ? co->clip + b0 : nullptr};
             const dp_status s1 = layer_sqnorm_clip(static_cast<const char*>(A) + (size_t)(b0 * T * d_in) * elem_bytes(dtype),
@@ -799,9 +818,10 @@ dp_status layers_sqnorm_grouped(const dp_layer_desc* layers, int64_t n_layers, i
                                 int accumulate, float* sqnorm, float C, float* clip, void* workspace, size_t workspace_bytes,
                                 void* hip_stream);
 
-// scratch: the layers that run one by one reuse one region, and so do the batched launches
-size_t layers_ws_bytes(const dp_layer_desc* layers, int64_t n_layers, int64_t B, dp_dtype dtype, dp_path path) {
-    const int64_t piece = layers_piece_examples(layers, n_layers, B, dtype, path);
+// scratch: the layers that run one by one reuse one region, and so do the batched launches.  whole: as if one call held
+// all examples.
+size_t layers_ws_bytes(const dp_layer_desc* layers, int64_t n_layers, int64_t B, dp_dtype dtype, dp_path path, bool whole = false) {
+    const int64_t piece = whole ? B : layers_piece_examples(layers, n_layers, B, dtype, path);
     if (piece < B)
         return std::max(layers_ws_bytes(layers, n_layers, piece, dtype, path), layers_ws_bytes(layers, n_layers, B - (B - 1) / piece * piece, dtype, path));
     size_t single = 0, single_sum = 0, batch = 0, batch_max = 0;
@@ -867,8 +887,11 @@ dp_status dp_layers_sqnorm_clip(const dp_layer_desc* layers, int64_t n_layers, i
     if (st != DP_OK) return st;
     if (clip && !(C > 0.0f)) return DP_ERR_INVALID_ARG;
     if (B == 0) return DP_OK;
+    for (int64_t l = 0; l < n_layers; ++l)
+        if (norm_too_large(B, layers[l].T, layers[l].d_in, layers[l].d_out, dtype, path)) return DP_ERR_UNSUPPORTED;
     const int64_t piece = layers_piece_examples(layers, n_layers, B, dtype, path);
     if (piece < B) {
+        if (layers_ws_bytes(layers, n_layers, B, dtype, path, true) >= (size_t(1) << 33)) return DP_ERR_UNSUPPORTED;      // (as below)
         const size_t need = layers_ws_bytes(layers, n_layers, B, dtype, path);
         if (need > 0 && (!workspace || workspace_bytes < need || !aligned16(workspace))) return DP_ERR_WORKSPACE;
         std::vector<dp_layer_desc> part((size_t)n_layers);

@@ -398,3 +398,14 @@ def test_gram_pieces_of_layers_of_several_widths(lib):
     assert wide(64, [(512, 768, 2304), (512, 768, 768), (512, 768, 3072), (512, 3072, 768)]) == 1
     assert wide(64, [(512, 768, 768)]) == 1 and wide(32, [(512, 768, 768)]) == 0 and wide(64, [(768, 768, 768)]) == 0
     assert wide(64, [(64, 768, 768)]) == -1 and wide(64, [(512, 760, 768)]) == -1        # not in that launch
+
+
+@pytest.mark.parametrize("dtype", [dpclip.DP_BF16, dpclip.DP_F32, dpclip.DP_F8_E4M3])
+@pytest.mark.parametrize("B,T,d,path", [(1, 1 << 20, 128, dpclip.DP_PATH_GRAM), (16, 1 << 19, 128, dpclip.DP_PATH_GRAM), (2, 256, 1 << 20, dpclip.DP_PATH_DIRECT)])
+def test_an_example_of_more_sums_than_a_launch_holds_is_refused(lib, dtype, B, T, d, path):
+    """A launch drops the workgroups beyond 2^32 threads without an error: examples that a smaller piece does not help are
+    refused before anything is launched (the pointers are never read)."""
+    st = lib.dp_layer_sqnorm(1 << 20, 1 << 20, B, T, d, d, dtype, path, 0, 1 << 20, 1 << 20, 1 << 45, None)
+    arr = (dpclip.LayerDesc * 1)(dpclip.LayerDesc(1 << 20, 1 << 20, T, d, d))
+    many = lib.dp_layers_sqnorm(arr, 1, B, dtype, path, 0, 1 << 20, 1 << 20, 1 << 45, None)
+    assert st == many == 2
