@@ -278,7 +278,7 @@ hipError_t launch_gram_bf16_layers(const JointShape* sh, const JointOperands* op
         a.sqnorm = nullptr; a.accumulate = 0; a.C = 0.f; a.clip = nullptr;
         g.n_items[l] = (int)n; g.first_item[l] = (int)first;
         first += (n + 7) / 8;
-        if (first >= (int64_t(1) << 28)) return hipErrorInvalidValue;
+        if (!launch_holds(8 * first, kThreads)) return hipErrorInvalidValue;
     }
     for (int l = n_layers; l < kJointLayers; ++l) { g.layer[l] = g.layer[0]; g.n_items[l] = 0; g.first_item[l] = (int)first; }
     g.n_layers = n_layers;

@@ -685,7 +685,7 @@ hipError_t launch_gram_bf16_dma_layers(const GramLayerDesc* layers, int n_layers
         queue += y.per_xcd;
     }
     for (int l = n_layers; l < kGramBatch; ++l) a.layer[l] = GramDmaLayer{nullptr, nullptr, 0, 0, 0, 0, 0, 0, 0, nullptr};
-    if (queue * 8 >= (int64_t(1) << 31)) return hipErrorInvalidValue;
+    if (!launch_holds(8 * queue, wide ? kWideThreads : kThreads)) return hipErrorInvalidValue;
     a.per_xcd = (int)queue;
     const unsigned grid = 8u * (unsigned)a.per_xcd;
     if (wide) {
@@ -776,7 +776,7 @@ hipError_t launch_gram_dma_ragged(const JointShape* sh, const JointOperands* op,
         queue += y.per_xcd;
     }
     for (int l = n_layers; l < kGramBatch; ++l) a.layer[l] = GramDmaLayer{nullptr, nullptr, 0, 0, 0, 0, 0, 0, 0, nullptr};
-    if (queue * 8 >= (int64_t(1) << 31)) return hipErrorInvalidValue;
+    if (!launch_holds(8 * queue, kThreads)) return hipErrorInvalidValue;
     a.per_xcd = (int)queue;
     const unsigned grid = 8u * (unsigned)queue;
     if (f16) k_gram_bf16_dma<1, false, true><<<grid, kThreads, 0, st>>>(a);

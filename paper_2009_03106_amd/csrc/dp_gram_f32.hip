@@ -381,7 +381,7 @@ hipError_t launch_gram_f32_layers(const JointShape* sh, const JointOperands* op,
         if (n >= (int64_t(1) << 31) - 8) return hipErrorInvalidValue;
         y.n_items = (int)n;
         first += (n + 7) / 8;
-        if (first >= (int64_t(1) << 28)) return hipErrorInvalidValue;
+        if (!launch_holds(8 * first, kThreads)) return hipErrorInvalidValue;
     }
     for (int l = n_layers; l < kJointLayers; ++l) g.layer[l] = g.layer[0];
     g.n_layers = n_layers;

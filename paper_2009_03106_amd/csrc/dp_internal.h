@@ -10,6 +10,8 @@ namespace dpk {
 
 inline int ceil_div(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
 // an M x N output tiles into TM x TN blocks with at most a quarter of the padded area wasted
+// A launch holds fewer than 2^32 threads; the workgroups beyond are dropped without an error.
+inline bool launch_holds(int64_t workgroups, int threads) { return workgroups * threads < (int64_t(1) << 32); }
 inline bool tiles_fit(int M, int N, int TM, int TN) {
     const int64_t padded = (int64_t)ceil_div(M, TM) * TM * ceil_div(N, TN) * TN;
     return padded * 4 <= (int64_t)M * N * 5;

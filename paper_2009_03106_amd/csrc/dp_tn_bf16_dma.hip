@@ -838,7 +838,7 @@ hipError_t launch_direct_bf16_dma_joint(const JointShape* sh, const JointOperand
         first += (int64_t)y.tiles_m * y.tiles_n * B;
         ragged = ragged || (sh[l].T % DK) != 0;
     }
-    if (first >= (int64_t(1) << 28)) return hipErrorInvalidValue;
+    if (!launch_holds(8 * first, GeoT::THREADS)) return hipErrorInvalidValue;
     for (int l = n_layers; l < kJointMax; ++l) j.layer[l] = j.layer[0];
     j.n_layers = n_layers; j.n_items = (int)first; j.per_xcd = ceil_div(first, 8);
     j.B = B;
@@ -890,7 +890,7 @@ hipError_t launch_direct_bf16_dma(const TnPlan& p, const uint16_t* A, const uint
     a.out = partial; a.slice = 0; a.accumulate = 0;
     const int tiles = a.tiles_m * a.tiles_n;
     const int64_t total = (int64_t)tiles * B;
-    if (total >= (int64_t(1) << 28)) return hipErrorInvalidValue;
+    if (!launch_holds((total + 7) / 8 * 8, p.tile_m == GeoL::TM && p.tile_n == GeoL::TN ? GeoL::THREADS : GeoT::THREADS)) return hipErrorInvalidValue;
     a.per_xcd = ceil_div(total, 8);
     const hipError_t e = launch_any<1>(geo_of_plan(p), a, am, f16, st);
     if (e != hipSuccess) return e;

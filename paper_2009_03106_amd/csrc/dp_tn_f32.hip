@@ -736,8 +736,8 @@ hipError_t launch_direct_f32(const TnPlan& p, const float* A, const float* G, in
     a.slice = 0; a.accumulate = 0;
     const int tiles = p.tiles_m * p.tiles_n;
     if (p.dma) {
-        // one launch of (example, tile) items; batches beyond the 32-bit item count go in pieces
-        const int64_t per = ((int64_t(1) << 30) / tiles);
+        // one launch of (example, tile) items; batches of more than a launch holds go in pieces
+        const int64_t per = std::max<int64_t>(1, (int64_t(1) << 22) / tiles);
         for (int64_t b0 = 0; b0 < B; b0 += per) {
             const int nb = (int)((B - b0 < per) ? (B - b0) : per);
             hipError_t e = launch_tn_f32_split(1, p, A + (size_t)b0 * T * M, G + (size_t)b0 * T * N, nullptr, nb, T, M, N,

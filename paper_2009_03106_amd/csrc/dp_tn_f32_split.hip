@@ -534,7 +534,7 @@ hipError_t launch_tn_f32_split(int mode, const TnPlan& p, const float* A, const 
     a.kchunk = mode == 0 ? p.kchunk : T;
     a.accumulate = accumulate ? 1 : 0;
     const int64_t items = (int64_t)p.tiles_m * p.tiles_n * a.splits;
-    if (items <= 0 || items >= (int64_t(1) << 31) - 8) return hipErrorInvalidValue;
+    if (items <= 0 || !launch_holds((items + 7) / 8 * 8, p.tile_m == GeoBig::TM && mode == 0 ? GeoBig::THREADS : GeoMid::THREADS)) return hipErrorInvalidValue;
     if (mode == 0 && (p.kchunk % DKF) != 0) return hipErrorInvalidValue;
     a.per_xcd = (int)((items + 7) / 8);
     const unsigned grid = 8u * (unsigned)a.per_xcd;
@@ -564,7 +564,7 @@ hipError_t launch_direct_f32_split_joint(const JointShape* sh, const JointOperan
         y.first_item = (int)first;
         first += ceil_div((int64_t)y.tiles_m * y.tiles_n * B, 8);
     }
-    if (first >= (int64_t(1) << 25)) return hipErrorInvalidValue;
+    if (!launch_holds(8 * first, GeoMid::THREADS)) return hipErrorInvalidValue;
     for (int l = n_layers; l < kJointLayers; ++l) j.layer[l] = j.layer[0];
     j.n_layers = n_layers; j.n_items = (int)first; j.per_xcd = 0;
     k_tn_f32_split_joint<1, false><<<8u * (unsigned)first, GeoMid::THREADS, 0, st>>>(j);

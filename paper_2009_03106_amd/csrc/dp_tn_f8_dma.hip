@@ -737,7 +737,7 @@ hipError_t launch_direct_f8_dma(const TnPlan& p, const void* A, const void* G, i
     a.out = partial; a.slice = 0; a.accumulate = 0;
     const int tiles = a.tiles_m * a.tiles_n;
     const int64_t total = (int64_t)tiles * B;
-    if (total >= (int64_t(1) << 28)) return hipErrorInvalidValue;
+    if (!launch_holds((total + 7) / 8 * 8, p.big ? Geo8L::THREADS : Geo8T::THREADS)) return hipErrorInvalidValue;
     a.per_xcd = ceil_div(total, 8);
     const hipError_t e = launch_any8<1>(p.big, a, p.zero_head, fmt, st);
     if (e != hipSuccess) return e;
